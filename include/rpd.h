@@ -109,14 +109,12 @@ typedef struct rpd_opts {
   int32_t precision;   /* RPD_FP32_FALLBACK or RPD_FP64 */
   int32_t clip_budget; /* max candidate sites per tet in the fast path: 0 = tuned or 28, else 4..28; tets
                           with more go to the large-capacity kernel */
-  int32_t block;       /* threads per workgroup of the FP32 clipping kernel: 0 = tuned or 128, 64, 128 or 256
-                          (the FP64 path always runs 64) */
+  int32_t block;       /* 0, 64, 128 or 256; no effect (the clipping kernels run one wavefront per workgroup) */
   uint32_t flags;      /* RPD_* flags above */
   void* stream;        /* hipStream_t to run on; NULL = the null stream */
-  int32_t slots;       /* vertex slots per piece polytope of the 64-thread FP32 clipping kernel: 0 = tuned or 16;
-                          16 (six workgroups per compute unit) or 12 (eight: two waves per SIMD, at the cost of
-                          more pieces redone with 64 slots and more blocks split); blocks of 128 or 256 threads
-                          and the FP64 path use 16. Every value gives the same elements */
+  int32_t slots;       /* vertex slots per piece polytope of the FP32 clipping kernel: 0 = tuned or 16; 16, or 12
+                          (less on-chip memory per wavefront, more pieces redone with 64 slots); blocks of 128 or
+                          256 threads and the FP64 path use 16. Every value gives the same elements */
 } rpd_opts;
 
 typedef struct rpd_stats {
@@ -135,7 +133,7 @@ typedef struct rpd_stats {
   int64_t n_defer_kmax;   /* tets deferred because more candidates than the clip budget remained */
   int64_t n_defer_clip;   /* pieces deferred by the fast path: a predicate undecided in FP64, or over 64 vertices */
   int64_t n_split;        /* workgroup blocks redone in smaller chunks because their site list overflowed */
-  int64_t n_items;        /* work items of the fast kernel (blocks, and parts of blocks that were heavy before) */
+  int64_t n_items;        /* work items of the candidate kernel (blocks, and parts of blocks that were heavy before) */
   int64_t n_big;          /* pieces over the fast path's 16 vertex slots, redone there with a 64-slot polytope */
 } rpd_stats;
 
@@ -277,10 +275,9 @@ rpd_status rpd_piece_terms(const rpd_result* r, int32_t shape, int32_t kind, int
 
 void rpd_free(rpd_result* r);
 
-/* Autotuner for the batched FP32 path: runs rpd_build on these inputs once per launch shape (block of 64, 128 or 256
- * threads x clip budget 8, 16 or 28 with 16 vertex slots, and 64 threads with 12 slots x budget 16 or 28), each
- * timed by HIP events over the clipping kernels, best of two after a warm-up, writes the fastest into *best (a copy
- * of *opts with block, clip_budget and slots set; the default 64 x 28 x 16 is kept unless another shape is more than
+/* Autotuner for the batched FP32 path: runs rpd_build on these inputs once per launch shape (clip budget 8, 16 or 28
+ * with 16 vertex slots, and 16 or 28 with 12 slots, all with block 64), each timed by HIP events over the clipping
+ * kernels, best of two after a warm-up, writes the fastest into *best (a copy of *opts with block, clip_budget and slots set; the default 64 x 28 x 16 is kept unless another shape is more than
  * 2% faster) and caches it for the process under the bucket (floor log2 of the mean sites per shape, floor log2 of
  * the mean tets per shape). Later rpd_build calls take the cached value of their bucket for each of block,
  * clip_budget and slots that is 0 (else 64, 28 and 16), and so does a session. Every launch shape gives the same

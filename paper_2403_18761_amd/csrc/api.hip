@@ -150,7 +150,7 @@ static void d2h(std::vector<T>& v, const void* src, size_t n, hipStream_t s) {
   if (n) hip_check(hipMemcpyAsync(v.data(), src, sizeof(T) * n, hipMemcpyDeviceToHost, s), "download");
 }
 
-// vertex slots per piece of the FP32 fast kernel: 12 only where asked for with 64 threads, else 16
+// vertex slots per piece of the FP32 piece kernel: 12 only where asked for with 64 threads, else 16
 static int fast_slots(const rpd_opts& o) {
   return (o.precision == RPD_FP32_FALLBACK && (o.block == 0 || o.block == 64) && o.slots == 12) ? 12 : 16;
 }
@@ -163,10 +163,11 @@ struct DeviceState {
   int nsh = 0, ns_cap = 0;
   long long nt_tot = 0;
   unsigned capF = 0, capE = 0, capQ = 0, capN = 0;
-  int def_cap = 0, piece_cap = 0, term_cap = 0, list_cap = 0, big_cap = 0;
+  int def_cap = 0, piece_cap = 0, term_cap = 0, pcap = 0, pool_cap = 0, big_cap = 0;
   DBuf site, status, cell_chi, cell_geo, cell_np, cell_b0;
   DBuf fkeys, face_chi, face_np, face_b0, ekeys, edge_chi, edge_np, edge_len, edge_b0, qkeys, rpv_cnt;
-  DBuf nodes, glist, gseg, clist, cseg, bigp, deferred, deferred2, dlist, pieces, terms, counters, tetU, slow, touch, removed;
+  DBuf pdesc, psite, pout, recs, chunk_recs;
+  DBuf nodes, glist, gseg, clist, cseg, bigp, deferred, deferred2, pieces, terms, counters, tetU, slow, touch, removed;
   int waves = 0;
 
   unsigned long long* cnt() const { return counters.as<unsigned long long>(); }
@@ -214,9 +215,21 @@ struct DeviceState {
     gseg.alloc(sizeof(int) * (size_t)capN / 256);  // the gluing list's segments
     deferred.alloc(16 * (size_t)def_cap);
     deferred2.alloc(16 * (size_t)(def_cap / 4 + 1024));
-    // candidate lists of deferred tets and pieces (a few per cent of the tets on the heaviest workloads)
-    list_cap = (int)std::min<size_t>((nt / 8 + 4096) * (size_t)scale, (1u << 25) - 1);
-    dlist.alloc(sizeof(int) * KRAW * (size_t)list_cap);
+    // Piece slots and records of one clipping pass. A tet has about 1 + 4 r^(1/3) candidates at r sites per tet
+    // (1.9 at 0.018, 4.9 at 0.33, 8.6 at 0.54 measured); an incremental pass clips the dirty tets twice. Memory past
+    // what a pass fills is never touched.
+    {
+      const double r = nt > 0 ? (double)ns / (double)nt : 0.0;
+      const double per = (4.0 + 12.0 * std::cbrt(r * r)) * scale;
+      const double n = std::min((double)nt * per + 16384.0 * scale, 1.0e9);
+      pcap = (int)((size_t)n / CHUNK) * CHUNK;
+      pool_cap = pcap / 2;
+      pdesc.alloc(sizeof(PieceDesc) * (size_t)pcap);
+      psite.alloc(sizeof(int) * (size_t)pcap);
+      pout.alloc(sizeof(PieceOut) * (size_t)pcap);
+      chunk_recs.alloc(sizeof(int) * (size_t)(pcap / CHUNK));
+      recs.alloc(sizeof(ElemRec) * ((size_t)(pcap / CHUNK) * REC_CHUNK + (size_t)pool_cap));
+    }
     // pieces over the fast kernel's vertex slots: about 1 in 10^4 on the benchmark shapes with 16 slots, up to 1 in
     // 10^2 with 12; an incremental session gets room for four times as many per pass as a build (its pool must
     // never run out)
@@ -296,8 +309,13 @@ struct DeviceState {
     a.deferred_cap = def_cap;
     a.deferred2 = deferred2.as<int4>();
     a.deferred2_cap = def_cap / 4 + 1024;
-    a.deferred_list = dlist.as<int>();
-    a.list_cap = list_cap;
+    a.pdesc = pdesc.as<PieceDesc>();
+    a.psite = psite.as<int>();
+    a.pout = pout.as<PieceOut>();
+    a.pcap = pcap;
+    a.recs = recs.as<ElemRec>();
+    a.chunk_recs = chunk_recs.as<int>();
+    a.pool_cap = pool_cap;
     a.big = bigp.as<unsigned char>();
     a.big_cap = big_cap;
     a.pieces = pieces.as<PieceRec>();
@@ -438,7 +456,7 @@ static bool collect(DeviceState& D, const std::vector<ShapeDesc>& hd, const Shap
   auto check_totals = [&]() {
     D.totals(hc, s, &hst);
     if (hst & ST_TABLE_FULL) return false;
-    if (hc[C_DEFER_ITEMS] > (unsigned long long)D.def_cap || hc[C_LISTS] > (unsigned long long)D.list_cap ||
+    if (hc[C_DEFER_ITEMS] > (unsigned long long)D.def_cap ||
         (D.piece_cap &&
          (hc[C_PIECES] > (unsigned long long)D.piece_cap || hc[C_TERMS] > (unsigned long long)D.term_cap)))
       return false;
@@ -886,13 +904,15 @@ static bool run_batch(const rpd_mesh* const* meshes, const rpd_sites* sites, int
   a.item_cost = dcost.as<unsigned>();
   Timing tm((o.flags & RPD_TIMING) != 0);
   tm.mark(0, s);
-  hip_check(launch_clip_fast(a, o.precision, o.block, fast_slots(o), s), "clip kernel");
+  hip_check(launch_candidates(a, s), "candidate kernel");
+  hip_check(launch_clip_pieces(a, o.precision, fast_slots(o), s), "clip kernel");
   tm.mark(1, s);
   if (!items.empty())  // read by the host after collect's synchronisation
     hip_check(hipMemcpyAsync(ticks_host.p, dcost.p, sizeof(unsigned) * items.size(), hipMemcpyDeviceToHost, s),
               "download");
   hip_check(launch_clip_slow(a, D.slow.as<unsigned char>(), D.waves, s), "deferred clip kernel");
   tm.mark(2, s);
+  hip_check(launch_emit(a, s), "emission");
   D.components(a, s);
   if (!collect(D, hd, dshapes_p, meshes, s, tm, outs, st)) return false;
   learn_costs(items, (const unsigned*)ticks_host.p, hd, meshes);
@@ -1073,9 +1093,7 @@ rpd_status rpd_autotune(const rpd_mesh* const* meshes, const rpd_sites* sites, i
   o.flags &= ~(uint32_t)RPD_KEEP_PIECES;
   // the default shape (64 threads, the full budget) is timed first; another shape replaces it only when it is
   // faster by more than 2%, so that shapes within the timing noise do not alternate from run to run
-  const int cand[11][3] = {{64, rpd::KMAX, 16}, {64, 8, 16},  {64, 16, 16},  {128, 8, 16},         {128, 16, 16},
-                           {128, rpd::KMAX, 16}, {256, 8, 16}, {256, 16, 16}, {256, rpd::KMAX, 16}, {64, rpd::KMAX, 12},
-                           {64, 16, 12}};
+  const int cand[5][3] = {{64, rpd::KMAX, 16}, {64, 8, 16}, {64, 16, 16}, {64, rpd::KMAX, 12}, {64, 16, 12}};
   double best_ms = INFINITY;
   int bb = 64, bk = rpd::KMAX, bs = 16;
   for (const auto& sh : cand) {
@@ -1295,11 +1313,11 @@ static void check_status(rpd_session* S) {
 
 // one full clipping pass over the items of a (all blocks, or the dirty ones with a device-side count)
 static void clip_pass(rpd_session* S, const ShapeArgs& a) {
-  hip_check(launch_fill_u64(S->D.cnt() + C_DEFER_ITEMS, 0, 1, S->stream), "fill");
-  hip_check(launch_fill_u64(S->D.cnt() + C_DEFER2, 0, 1, S->stream), "fill");
-  hip_check(launch_fill_u64(S->D.cnt() + C_LISTS, 0, 2, S->stream), "fill");  // C_LISTS and C_BIG
-  hip_check(launch_clip_fast(a, S->o.precision, S->o.block, fast_slots(S->o), S->stream), "clip kernel");
+  hip_check(launch_fill_u64(S->D.cnt() + C_PIECE_SLOTS, 0, PASS_CURSORS, S->stream), "fill");
+  hip_check(launch_candidates(a, S->stream), "candidate kernel");
+  hip_check(launch_clip_pieces(a, S->o.precision, fast_slots(S->o), S->stream), "clip kernel");
   hip_check(launch_clip_slow(a, S->D.slow.as<unsigned char>(), S->D.waves, S->stream), "deferred clip kernel");
+  hip_check(launch_emit(a, S->stream), "emission");
 }
 
 // Allocate at the given table scale, upload, compute the initial state. False if a table overflowed.

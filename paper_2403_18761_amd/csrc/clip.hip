@@ -1,12 +1,17 @@
 // Tet-Cell clipping (paper Sec. 5.2) with on-the-fly fractional Euler characteristic (Sec. 4.1.2) and the gluing
-// information for connected components (Sec. 4.1.1).
+// information for connected components (Sec. 4.1.1), in two kernels.
 //
-// Fast kernel: one workgroup owns TB spatially consecutive tets. It (1) selects the sites that can own any point of
-// the group's bounding box, (2) selects per tet the candidate sites that can own a point of the tet, sorted by power
-// distance at the tet centroid, (3) clips every (tet, candidate) piece by the bisectors of all other candidates, one
-// thread per piece with the polytope in LDS, and (4) emits the piece's volume, moments, chi numerators and gluing
-// bits. Pieces that do not fit (too many candidates or vertices) or whose predicates stay undecided in FP64 are
-// deferred to the large-capacity kernel, which recomputes them with FP64 constructions and exact predicates.
+// Candidate kernel: one wavefront owns up to TB spatially consecutive tets. It selects the sites that can own any
+// point of the group's bounding box, then per tet the candidate sites that can own a point of the tet, sorted by power
+// distance at the tet centroid, and hands every tet a run of piece slots, one per candidate.
+//
+// Piece kernel: 64 consecutive piece slots per wavefront, one lane per piece: the tet is clipped by the bisectors of
+// all other candidates with the polytope in LDS, and the piece's cell terms and element records (faces, edges, RPVs:
+// chi numerators, gluing bits, lengths) are written out. No hash table and no shared accumulator is touched here: the
+// emission kernel turns the records into sums.
+//
+// Tets with too many candidates and pieces whose predicates stay undecided in FP64 go to the large-capacity kernel,
+// which computes them with FP64 constructions and exact predicates.
 #include <hip/hip_runtime.h>
 
 #include <climits>
@@ -19,7 +24,7 @@
 namespace rpd {
 
 // ---------------------------------------------------------------------------------------------------------------
-// emission of one nonempty piece
+// the terms of one nonempty piece
 // ---------------------------------------------------------------------------------------------------------------
 template <typename Topo>
 __device__ inline int pos_of(typename Topo::W w, int p) {
@@ -34,52 +39,258 @@ __device__ inline long long wv_of(typename Topo::W w, const unsigned* nu, long l
   return w_vertex(Topo::plane(w, 0), Topo::plane(w, 1), Topo::plane(w, 2), nu, L);
 }
 
-// One element piece (element, tet) is emitted exactly once per shape: adding sets its gluing bits and count,
-// removing (the same piece recomputed from the state before an incremental update, sign -1) takes both back.
-// The two happen in one launch, in either order. Each records the piece's gluing bits in its own half of the
-// piece's tag pair; a scan after the launch flags the element for a new union-find only where the two differ (a
-// piece put back with the same gluing bits leaves the element's forest as it was).
-__device__ inline void node_emit(const ShapeArgs& a, int sign, unsigned long long key, int glue) {
-  int ns = node_insert(a.N, key, a.status);
-  if (ns < 0) return;
-  atomicAdd(&a.N.rec[ns].st, sign * (NODE_UNIT + glue));  // removal re-emits the same bits, so this is exact
-  if (a.touch_cell) a.removed[2 * (size_t)ns + (sign > 0)] = (unsigned short)(0x100 | glue);
-}
+// What the first pass over a piece's vertices leaves for emit_out.
+template <typename CL>
+struct EmitAcc {
+  typedef typename CL::Real T;
+  typedef typename CL::MaskT Mask;
+  long long sv, se;         // vertex and edge weights
+  T gx, gy, gz;             // vertex sums
+  int nv;
+  unsigned planes;          // planes present (Topo32: at most 32 of them)
+  int nface, nedge, nrpv;   // element records of the piece (elements whose smallest site is the piece's)
+  Mask edge[3], rpv;        // vertices k with such an edge at position f (k below its other end), or such an RPV
+  __device__ int records() const { return nface + nedge + nrpv; }
+};
 
-// a per-piece element term for sampled comparisons (RPD_KEEP_PIECES only)
-__device__ inline void keep_term(const ShapeArgs& a, int kind, int t, int i, int j, int k, int l, int glue,
-                                 long long num) {
-  if (!(a.flags & RPD_KEEP_PIECES)) return;
-  const unsigned long long idx = atomicAdd(&a.counters[C_TERMS], 1ull);
-  if (idx < (unsigned long long)a.term_cap) {
-    TermRec r;
-    r.kind = kind;
-    r.t = t;
-    r.i = i;
-    r.j = j;
-    r.k = k;
-    r.l = l;
-    r.glue = glue;
-    r.pad = 0;
-    r.num = num;
-    a.terms[idx] = r;
-  } else {
-    atomicOr(a.status, ST_TABLE_FULL);
+// vertex pass: vertex and edge weights, the first vertex of every face (kept in the clipper's table), the records
+template <typename CL>
+__device__ __forceinline__ void emit_scan(CL& c, const unsigned* nu, long long L, EmitAcc<CL>& e) {
+  typedef typename CL::TopoT Topo;
+  typedef typename Topo::W W;
+  const int i = c.env.site_i;  // batch-global site id
+  e.sv = e.se = 0;
+  e.gx = e.gy = e.gz = 0;
+  e.nv = e.nface = e.nedge = e.nrpv = 0;
+  e.planes = 0;
+  e.edge[0] = e.edge[1] = e.edge[2] = e.rpv = 0;
+  for (auto m = c.live; m; m &= m - 1) {
+    const int k = ctz_mask(m);
+    const W w = c.st.topo(k);
+    const auto v = c.st.get(k);
+    e.gx += v.x;
+    e.gy += v.y;
+    e.gz += v.z;
+    ++e.nv;
+    const int p0 = Topo::plane(w, 0), p1 = Topo::plane(w, 1), p2 = Topo::plane(w, 2);
+    e.sv += w_vertex(p0, p1, p2, nu, L);
+    bool above[3];  // the plane is a bisector against a higher site
+    for (int f = 0; f < 3; ++f) {
+      const int p = Topo::plane(w, f);
+      above[f] = p >= 4 && c.env.cand_id(p - 4) > i;
+      if (c.tab.get(p) == 0) {
+        c.tab.set(p, k + 1);
+        if (CL::FEW_PLANES) e.planes |= 1u << (p & 31);
+        e.nface += above[f] ? 1 : 0;
+      }
+    }
+    for (int f = 0; f < 3; ++f) {
+      if (k < Topo::nb(w, f)) {
+        const int f1 = f == 2 ? 0 : f + 1, f2 = f == 0 ? 2 : f - 1;
+        e.se += w_edge(Topo::plane(w, f1), Topo::plane(w, f2), nu, L);
+        if (above[f1] && above[f2]) {
+          ++e.nedge;
+          e.edge[f] |= CL::bit(k);
+        }
+      }
+    }
+    if (above[0] && above[1] && above[2]) {
+      ++e.nrpv;
+      e.rpv |= CL::bit(k);
+    }
   }
 }
 
-// Hands a tet's sorted candidates (list positions into the workgroup's site list) to the large-capacity kernel;
-// returns the item's list word (64 x list index + m), or 0 when the list buffer is full (the call is then redone
-// with larger buffers, so no item is ever processed without its list).
-__device__ inline int hand_over_list(const ShapeArgs& a, const unsigned char* cand, const int* sid, int m) {
-  const unsigned long long idx = atomicAdd(&a.counters[C_LISTS], 1ull);
-  if (idx >= (unsigned long long)a.list_cap) {
-    atomicOr(a.status, ST_TABLE_FULL);
-    return 0;
+// The piece's cell terms and its element records, written to slot p_slot and to records [base, base + e.records()).
+// Every loop takes one item of the lane's own list per trip (an edge, an RPV, a face vertex), so that lanes whose
+// pieces have different shapes stay together; a loop over plane numbers and one over the face's edges inside it kept
+// one lane in five busy.
+template <typename CL>
+__device__ __forceinline__ void emit_out(CL& c, const ShapeDesc& sd, int tl, EmitAcc<CL>& e, int p_slot, int base,
+                                         const ShapeArgs& a) {
+  typedef typename CL::Real T;
+  typedef typename CL::TopoT Topo;
+  typedef typename Topo::W W;
+  const int i = c.env.site_i;
+  const unsigned* nu = sd.nu + 14 * (size_t)tl;
+  const long long L = sd.L;
+  const int4 tn4 = reinterpret_cast<const int4*>(sd.tn)[tl];  // face neighbours (-1: boundary), one load
+  const unsigned interior = (tn4.x >= 0 ? 1u : 0u) | (tn4.y >= 0 ? 2u : 0u) | (tn4.z >= 0 ? 4u : 0u) |
+                            (tn4.w >= 0 ? 8u : 0u);  // bit f: face f is shared with another tet
+  auto put = [&](int r, int j, int k, int z, long long num, double len) {
+    ElemRec R;
+    R.j = j;
+    R.k = k;
+    R.z = z;
+    R.p = p_slot;
+    R.num = num;
+    R.len = len;
+    a.recs[r] = R;
+  };
+  auto inner = [&](int p) { return p < 4 ? (int)(interior & (1u << p)) : 0; };  // the gluing bit of an interior face
+  int re = base + e.nface;
+  while (e.edge[0] | e.edge[1] | e.edge[2]) {  // RPE pieces
+    const int k = ctz_mask(e.edge[0] | e.edge[1] | e.edge[2]);
+    const auto b = CL::bit(k);
+    const int f = (e.edge[0] & b) ? 0 : (e.edge[1] & b) ? 1 : 2;
+    if (f == 0) e.edge[0] &= ~b;
+    else if (f == 1) e.edge[1] &= ~b;
+    else e.edge[2] &= ~b;
+    const W wk = c.st.topo(k);
+    const int n = Topo::nb(wk, f);
+    const W wn = c.st.topo(n);
+    const auto C = c.st.get(k), N = c.st.get(n);
+    const int pa = Topo::plane(wk, f == 2 ? 0 : f + 1), pb = Topo::plane(wk, f == 0 ? 2 : f - 1);
+    const int ea = pos_of<Topo>(wn, pa), eb = pos_of<Topo>(wn, pb);
+    if (ea < 0 || eb < 0) atomicOr(a.status, ST_INTERNAL);
+    const int sa = c.env.cand_id(pa - 4), sb = c.env.cand_id(pb - 4);
+    const T lx = N.x - C.x, ly = N.y - C.y, lz = N.z - C.z;
+    const long long ev = wv_of<Topo>(wk, nu, L) + wv_of<Topo>(wn, nu, L) - L;
+    // the third planes at the two ends
+    const int g = inner(Topo::plane(wk, f)) | inner(Topo::plane(wn, (3 - ea - eb) & 3));
+    put(re++, min(sa, sb), max(sa, sb), (REC_EDGE << REC_SHIFT) | g, ev, (double)sqrt(lx * lx + ly * ly + lz * lz));
   }
-  int* dst = a.deferred_list + idx * (size_t)KRAW;
-  for (int c = 0; c < m; ++c) dst[c] = sid[cand[c]];
-  return (int)(idx * 64) + m;
+  int rq = base + e.nface + e.nedge;
+  for (auto m = e.rpv; m; m &= m - 1) {  // an RPV is recorded once, from its smallest site
+    const W w = c.st.topo(ctz_mask(m));
+    const int s0 = c.env.cand_id(Topo::plane(w, 0) - 4), s1 = c.env.cand_id(Topo::plane(w, 1) - 4),
+              s2 = c.env.cand_id(Topo::plane(w, 2) - 4);
+    const int lo = min(s0, min(s1, s2)), hi = max(s0, max(s1, s2)), mid = s0 + s1 + s2 - lo - hi;
+    put(rq++, lo, mid, (REC_RPV << REC_SHIFT) | hi, 1, 0.0);
+  }
+  const T inv_nv = T(1) / T(e.nv);
+  const T ax = e.gx * inv_nv, ay = e.gy * inv_nv, az = e.gz * inv_nv;
+
+  // ---- face cycles, by ascending plane (volume fans, face terms): one vertex per trip, the first of a face starts it
+  long long sf = 0;
+  int cell_glue = 0;
+  T vol = 0, mx = 0, my = 0, mz = 0;
+  int rf = base;
+  auto next_face = [&](int p) {  // the next plane with a face, or -1
+    if (CL::FEW_PLANES) {
+      if (!e.planes) return -1;
+      const int q = ctz_mask(e.planes);
+      e.planes &= e.planes - 1;
+      return q;
+    }
+    for (++p; p < c.np; ++p)
+      if (c.tab.get(p)) return p;
+    return -1;
+  };
+  int p = next_face(-1);
+  bool start = true, felem = false;
+  int r = 0, nxt = 0, acur = 0, sp = -1, steps = 0, fglue = 0;
+  long long fchi = 0;
+  T Rx = 0, Ry = 0, Rz = 0, Cx = 0, Cy = 0, Cz = 0;
+  while (p >= 0) {
+    if (start) {
+      nxt = c.tab.get(p) - 1;
+      c.tab.set(p, 0);
+    }
+    const W wn = c.st.topo(nxt);
+    const auto N = c.st.get(nxt);
+    const int epn = pos_of<Topo>(wn, p);
+    const int ea = start ? 0 : pos_of<Topo>(wn, acur);
+    if (ea < 0 || epn < 0 || steps > CL::SLOTS) {  // a broken polytope: the call fails
+      atomicOr(a.status, ST_INTERNAL);
+      start = true;
+      steps = 0;
+      if (felem && rf < base + e.nface) put(rf++, 0, 0, REC_NONE << REC_SHIFT, 0, 0.0);
+      felem = false;
+      p = next_face(p);
+      continue;
+    }
+    if (start) {
+      r = nxt;
+      sf += (p < 4) ? (long long)nu[10 + p] : L;
+      if (p < 4) cell_glue |= inner(p) ? 1 << p : 16 << p;  // glue across an interior face; boundary contact
+      sp = c.env.plane_site(p);
+      felem = p >= 4 && sp > i;
+      fchi = L;
+      fglue = 0;
+      steps = 0;
+      Rx = N.x;
+      Ry = N.y;
+      Rz = N.z;
+      if (felem) fchi += wv_of<Topo>(wn, nu, L);
+      acur = Topo::plane(wn, epn == 2 ? 0 : epn + 1);
+      nxt = Topo::nb(wn, epn == 0 ? 2 : epn - 1);
+      start = false;
+    } else {
+      const bool closed = nxt == r;
+      if (felem) {  // the edge to nxt lies on planes {p, acur}
+        fchi -= w_edge(p, acur, nu, L);
+        if (!closed) fchi += wv_of<Topo>(wn, nu, L);
+        fglue |= inner(acur);
+      }
+      if (closed) {
+        if (felem && rf < base + e.nface) put(rf++, sp, -1, (REC_FACE << REC_SHIFT) | fglue, fchi, 0.0);
+        felem = false;
+        start = true;
+        p = next_face(p);
+      } else {
+        if (steps > 0) {  // fan triangle (R, C, N) with the apex: a tet of the piece
+          T ux = Cx - Rx, uy = Cy - Ry, uz = Cz - Rz;
+          T vx = N.x - Rx, vy = N.y - Ry, vz = N.z - Rz;
+          T wx = ax - Rx, wy = ay - Ry, wz = az - Rz;
+          T det = ux * (vy * wz - vz * wy) - uy * (vx * wz - vz * wx) + uz * (vx * wy - vy * wx);
+          T tv = fabs(det) * T(1.0 / 6.0);
+          vol += tv;
+          mx += tv * (Rx + Cx + N.x + ax);
+          my += tv * (Ry + Cy + N.y + ay);
+          mz += tv * (Rz + Cz + N.z + az);
+        }
+        ++steps;
+        const int ec = 3 - ea - epn;
+        nxt = Topo::nb(wn, ea);  // leave the vertex along {p, its third plane}: the neighbour opposite acur
+        acur = Topo::plane(wn, ec & 3);
+      }
+    }
+    Cx = N.x;
+    Cy = N.y;
+    Cz = N.z;
+  }
+  // records counted but not written (a broken polytope): nothing may read stale ones
+  for (; rf < base + e.nface; ++rf) put(rf, 0, 0, REC_NONE << REC_SHIFT, 0, 0.0);
+  // moments were accumulated with 4x the centroid sum; shift to absolute coordinates
+  const float4 o = c.env.o;
+  PieceOut out;
+  out.vol = (double)vol;
+  out.mx = (double)mx * 0.25 + out.vol * o.x;
+  out.my = (double)my * 0.25 + out.vol * o.y;
+  out.mz = (double)mz * 0.25 + out.vol * o.z;
+  out.chi = e.sv - e.se + sf - L;
+  out.rec = base;
+  out.word = piece_word(e.nface, e.nedge, e.nrpv, cell_glue);
+  a.pout[p_slot] = out;
+}
+
+// Room for n records in the pool, from the calling lane: the first, or -1 when the pool is full.
+__device__ inline int pool_records(const ShapeArgs& a, int n) {
+  if (n == 0) return 0;
+  const unsigned long long q = atomicAdd(&a.counters[C_REC_POOL], (unsigned long long)n);
+  if (q + n > (unsigned long long)a.pool_cap) {
+    atomicOr(a.status, ST_TABLE_FULL);
+    return -1;
+  }
+  return (a.pcap / CHUNK) * REC_CHUNK + (int)q;
+}
+
+// A piece clipped outside its chunk's pass: terms to its slot, records to the pool.
+template <typename CL>
+__device__ __forceinline__ void emit_alone(CL& c, const ShapeDesc& sd, int tl, int p_slot, const ShapeArgs& a) {
+  EmitAcc<CL> e;
+  emit_scan(c, sd.nu + 14 * (size_t)tl, sd.L, e);
+  const int base = pool_records(a, e.records());
+  if (base >= 0) emit_out(c, sd, tl, e, p_slot, base, a);
+}
+
+// Hands piece slot p (or, with p = -1, every candidate of the tet) to the large-capacity kernel. first: the tet's
+// first piece slot, or -1 when its candidates are still to be found.
+__device__ inline void defer_item(const ShapeArgs& a, int shape, int t, int p, int first) {
+  const unsigned long long idx = atomicAdd(&a.counters[C_DEFER_ITEMS], 1ull);
+  if (idx < (unsigned long long)a.deferred_cap) a.deferred[idx] = make_int4(shape, t, p, first);
+  else atomicOr(a.status, ST_TABLE_FULL);
 }
 
 // The next chunk of a split item: the next tet while tets are taken one at a time (up to single_end), else the next
@@ -101,303 +312,66 @@ __device__ inline bool next_chunk(int& sub, int& sub_n, int& single_end, int ntb
   return true;
 }
 
-// The environment of the fast kernel's piece (tet t, candidate ci of the tet's candidate bytes) in its shared lists.
-__device__ inline void fast_env(TetEnv& env, const ShapeDesc& sd, int t, const float4* sites, const int* sid,
-                                const unsigned char* cand, int ci) {
-  env.tv = sd.tp + 4 * (size_t)t;
-  env.o = env.tv[0];
-  env.face64 = sd.tf + 4 * (size_t)t;
-  env.sites = sites;
-  env.sid = sid;
-  env.cidx8 = cand;
-  env.cidx32 = nullptr;
-  env.csite = nullptr;
-  env.ncs = 0;
-  env.ci = ci;
-  env.si = sites[cand[ci]];
-  env.site_i = sid[cand[ci]];
-}
-
-// Hands a piece (tet t of the shape, site) with its tet's candidates to the large-capacity kernel.
-__device__ inline void defer_piece(const ShapeArgs& a, int shape, int t, int site, const unsigned char* cand,
-                                   const int* sid, int m) {
-  stat_add(a, C_DEFER_CLIP, 1ull);
-  const int list = hand_over_list(a, cand, sid, m);
-  unsigned long long idx = atomicAdd(&a.counters[C_DEFER_ITEMS], 1ull);
-  if (idx < (unsigned long long)a.deferred_cap) a.deferred[idx] = make_int4(shape, t, site, list);
-  else atomicOr(a.status, ST_TABLE_FULL);
-}
-
-__device__ inline long long fixed56(double v) { return llrint(v * 72057594037927936.0); }  // 2^-56 units
-
-// Cell volumes and first moments are exact sums of 128-bit integers in units of 2^-80 (resolution 8e-25, range
-// 2^47), so that a nonempty piece far smaller than a grid cell still counts, every sum is independent of the order
-// of the additions, and a removal pass takes its contributions back exactly. An accumulator is a (low, high) pair
-// of 64-bit words; an addition adds the low word atomically and carries into the high word only when needed.
-struct Fix128 {
-  unsigned long long lo;
-  long long hi;
-};
-__device__ inline Fix128 fixed80(double v) {
-  const double D = rint(ldexp(v, 80));  // exact scaling, then the nearest integer
-  const double h = floor(ldexp(D, -64));
-  const double l = D - ldexp(h, 64);    // in [0, 2^64): the low bits of D, exact
-  return Fix128{(unsigned long long)l, (long long)h};
-}
-__device__ inline Fix128 signed128(Fix128 x, int sign) {
-  if (sign > 0) return x;
-  return Fix128{0ull - x.lo, -x.hi - (x.lo != 0ull ? 1 : 0)};
-}
-__device__ inline void acc128(unsigned long long* p, Fix128 v) {
-  const unsigned long long old = atomicAdd(p, v.lo);
-  const long long h = v.hi + (old + v.lo < old ? 1 : 0);  // carry out of the low word
-  if (h) atomicAdd(p + 1, (unsigned long long)h);
-}
-
-// Workgroup-local sums of the cell terms (chi numerator, piece count, fixed-point volume and moments) in n slots,
-// each holding one site of the workgroup's list; a piece whose site has no slot adds to the global arrays directly.
-struct CellSink {
-  long long* chi;  // [n] (LDS)
-  int* np;         // [n]
-  unsigned long long* geo_lo;  // [4 n] low words of the workgroup's 128-bit sums
-  int* geo_hi;                 // [4 n] their high words (a workgroup's sum stays below 2^84: 32 bits suffice)
-  int n;
-  int q;           // the slot of the piece's site, or -1 or >= n: none
-};
-
-template <typename T, typename Topo, typename Mask, int VCAP, bool EXACT, typename Tab>
-__device__ __forceinline__ void emit_piece(Clipper<T, Topo, Mask, VCAP, EXACT, Tab>& c, const ShapeDesc& sd, int tl, const ShapeArgs& a,
-                           const CellSink& sink) {
-  typedef typename Topo::W W;
-  const int i = c.env.site_i;  // batch-global site id
-  const unsigned* nu = sd.nu + 14 * (size_t)tl;
-  const long long L = sd.L;
-  const int4 tn4 = reinterpret_cast<const int4*>(sd.tn)[tl];  // face neighbours (-1: boundary), one load
-  const unsigned interior = (tn4.x >= 0 ? 1u : 0u) | (tn4.y >= 0 ? 2u : 0u) | (tn4.z >= 0 ? 4u : 0u) |
-                            (tn4.w >= 0 ? 8u : 0u);  // bit f: face f is shared with another tet
-  const int t = (int)(sd.tet_off + tl);  // batch-global tet id (node keys, piece records)
-  const int sign = sd.sign;
-  int* status = a.status;
-
-  // ---- vertex pass: vertex and edge weights, face references, apex, RPVs
-  long long sv = 0, se = 0;
-  T gx = 0, gy = 0, gz = 0;
-  int nv = 0;
-  for (Mask m = c.live; m; m &= m - 1) {
-    int k = ctz_mask(m);
-    W w = c.st.topo(k);
-    auto v = c.st.get(k);
-    gx += v.x;
-    gy += v.y;
-    gz += v.z;
-    ++nv;
-    int p0 = Topo::plane(w, 0), p1 = Topo::plane(w, 1), p2 = Topo::plane(w, 2);
-    sv += w_vertex(p0, p1, p2, nu, L);
-    for (int e = 0; e < 3; ++e) {
-      int nb = Topo::nb(w, e);
-      if (k < nb) se += w_edge(Topo::plane(w, (e + 1) % 3), Topo::plane(w, (e + 2) % 3), nu, L);
-      int p = Topo::plane(w, e);
-      if (c.tab.get(p) == 0) c.tab.set(p, k + 1);
-    }
-    if (p0 >= 4 && p1 >= 4 && p2 >= 4) {
-      int s0 = c.env.plane_site(p0), s1 = c.env.plane_site(p1), s2 = c.env.plane_site(p2);
-      if (s0 > i && s1 > i && s2 > i) {  // the RPV is recorded once, from its smallest site
-        int lo = min(s0, min(s1, s2)), hi = max(s0, max(s1, s2)), mid = s0 + s1 + s2 - lo - hi;
-        unsigned long long ekey = ((unsigned long long)i << 42) | ((unsigned long long)lo << 21) | (unsigned)mid;
-        int es = ht_insert(a.E, ekey, status);
-        if (es >= 0) {
-          int qs = ht_insert(a.Q, ((unsigned long long)es << 21) | (unsigned)hi, status);
-          if (qs >= 0) atomicAdd(&a.rpv_cnt[qs], sign);
-        }
-        stat_add(a, C_RPV, 1ull);
-        keep_term(a, 4, t, i, lo, mid, hi, 0, 1);
-      }
-    }
-  }
-  const T inv_nv = T(1) / T(nv);
-  const T ax = gx * inv_nv, ay = gy * inv_nv, az = gz * inv_nv;
-
-  // ---- face pass: face weights, cell gluing, face cycles (volume fans, RPF and RPE terms)
-  long long sf = 0;
-  int cell_glue = 0;
-  T vol = 0, mx = 0, my = 0, mz = 0;
-  for (int p = 0; p < c.np; ++p) {
-    int r = c.tab.get(p);
-    if (r == 0) continue;
-    c.tab.set(p, 0);
-    r -= 1;
-    sf += (p < 4) ? (long long)nu[10 + p] : L;
-    if (p < 4) cell_glue |= ((interior >> p) & 1u) ? 1 << p : 16 << p;  // glue across an interior face; boundary contact
-    const int sp = c.env.plane_site(p);
-    const bool felem = (p >= 4) && (sp > i);
-    long long fv = 0, fe = 0;
-    int fglue = 0;
-    W wr = c.st.topo(r);
-    auto R = c.st.get(r);
-    int ep = pos_of<Topo>(wr, p);
-    if (ep < 0) {
-      atomicOr(status, ST_INTERNAL);
-      continue;
-    }
-    int acur = Topo::plane(wr, (ep + 1) % 3);
-    int nxt = Topo::nb(wr, (ep + 2) % 3);
-    int cur = r;
-    W wcur = wr;
-    auto C = R;
-    if (felem) fv += wv_of<Topo>(wr, nu, L);
-    bool closed = false;
-    for (int step = 0; step <= VCAP; ++step) {
-      W wn = c.st.topo(nxt);
-      auto N = c.st.get(nxt);
-      int ea = pos_of<Topo>(wn, acur), epn = pos_of<Topo>(wn, p);
-      if (ea < 0 || epn < 0) break;
-      if (felem) {  // the edge cur -> nxt lies on planes {p, acur}
-        fe += w_edge(p, acur, nu, L);
-        if (acur < 4) {
-          if ((interior >> acur) & 1u) fglue |= 1 << acur;
-        } else if (acur > p) {
-          int sa = c.env.plane_site(acur);
-          if (sa > i) {  // RPE piece of {i, sp, sa}, counted from its smaller plane id
-            int e1 = pos_of<Topo>(wcur, p), e2 = pos_of<Topo>(wcur, acur);
-            int t1 = Topo::plane(wcur, 3 - e1 - e2);
-            int t2 = Topo::plane(wn, 3 - ea - epn);
-            long long ev = wv_of<Topo>(wcur, nu, L) + wv_of<Topo>(wn, nu, L) - L;
-            int j = min(sp, sa), k = max(sp, sa);
-            unsigned long long key = ((unsigned long long)i << 42) | ((unsigned long long)j << 21) | (unsigned)k;
-            int es = ht_insert(a.E, key, status);
-            if (es >= 0) {
-              atomicAdd((unsigned long long*)&a.edge_chi[es], (unsigned long long)(sign * ev));
-              atomicAdd(&a.edge_np[es], sign);
-              const T lx = N.x - C.x, ly = N.y - C.y, lz = N.z - C.z;
-              const double len = (double)sqrt(lx * lx + ly * ly + lz * lz);
-              atomicAdd((unsigned long long*)&a.edge_len[es], (unsigned long long)(sign * fixed56(len)));
-              int g = ((t1 < 4 && ((interior >> t1) & 1u)) ? (1 << t1) : 0) |
-                      ((t2 < 4 && ((interior >> t2) & 1u)) ? (1 << t2) : 0);
-              node_emit(a, sign, node_key(3, es, t), g);
-              keep_term(a, 3, t, i, j, k, -1, g, ev);
-            }
-          }
-        }
-      }
-      if (nxt == r) {
-        closed = true;
-        break;
-      }
-      if (felem) fv += wv_of<Topo>(wn, nu, L);
-      if (cur != r) {  // fan triangle (R, C, N) with the apex: a tet of the piece
-        T ux = C.x - R.x, uy = C.y - R.y, uz = C.z - R.z;
-        T vx = N.x - R.x, vy = N.y - R.y, vz = N.z - R.z;
-        T wx = ax - R.x, wy = ay - R.y, wz = az - R.z;
-        T det = ux * (vy * wz - vz * wy) - uy * (vx * wz - vz * wx) + uz * (vx * wy - vy * wx);
-        T tv = fabs(det) * T(1.0 / 6.0);
-        vol += tv;
-        mx += tv * (R.x + C.x + N.x + ax);
-        my += tv * (R.y + C.y + N.y + ay);
-        mz += tv * (R.z + C.z + N.z + az);
-      }
-      int ec = 3 - ea - epn;
-      int c3 = Topo::plane(wn, ec);
-      int nn = Topo::nb(wn, ea);  // leave nxt along {p, c3}: the neighbour opposite acur
-      cur = nxt;
-      wcur = wn;
-      C = N;
-      acur = c3;
-      nxt = nn;
-    }
-    if (!closed) {
-      atomicOr(status, ST_INTERNAL);
-      continue;
-    }
-    if (felem) {
-      long long fvl = fv - fe + L;
-      unsigned long long key = ((unsigned long long)i << 32) | (unsigned)sp;
-      int fs = ht_insert(a.F, key, status);
-      if (fs >= 0) {
-        atomicAdd((unsigned long long*)&a.face_chi[fs], (unsigned long long)(sign * fvl));
-        atomicAdd(&a.face_np[fs], sign);
-        node_emit(a, sign, node_key(2, fs, t), fglue);
-      }
-      keep_term(a, 2, t, i, sp, -1, -1, fglue, fvl);
-    }
-  }
-  // ---- cell contributions
-  long long chi = sv - se + sf - L;
-  node_emit(a, sign, node_key(1, i, t), cell_glue);
-  keep_term(a, 1, t, i, -1, -1, -1, cell_glue, chi);
-  // moments were accumulated with 4x the centroid sum; shift to absolute coordinates
-  const float4 o = c.env.o;
-  double dvol = (double)vol;
-  double dmx = (double)mx * 0.25 + dvol * o.x, dmy = (double)my * 0.25 + dvol * o.y,
-         dmz = (double)mz * 0.25 + dvol * o.z;
-  const Fix128 g[4] = {fixed80(dvol), fixed80(dmx), fixed80(dmy), fixed80(dmz)};
-  if (sink.q >= 0 && sink.q < sink.n) {  // workgroup-local sums, flushed once per workgroup pass
-    atomicAdd((unsigned long long*)&sink.chi[sink.q], (unsigned long long)chi);
-    atomicAdd(&sink.np[sink.q], 1);
-    for (int k = 0; k < 4; ++k) {
-      const unsigned long long old = atomicAdd(&sink.geo_lo[4 * sink.q + k], g[k].lo);
-      const long long h = g[k].hi + (old + g[k].lo < old ? 1 : 0);
-      if (h) atomicAdd(&sink.geo_hi[4 * sink.q + k], (int)h);
-    }
-  } else {
-    atomicAdd((unsigned long long*)&a.cell_chi[i], (unsigned long long)(sign * chi));
-    atomicAdd(&a.cell_np[i], sign);
-    for (int k = 0; k < 4; ++k)
-      acc128((unsigned long long*)&a.cell_geo[2 * (4 * (size_t)i + k)], signed128(g[k], sign));
-  }
-  if (a.flags & RPD_KEEP_PIECES) {
-    unsigned long long idx = atomicAdd(&a.counters[C_PIECES], 1ull);
-    if (idx < (unsigned long long)a.piece_cap) {
-      PieceRec pr;
-      pr.t = t;
-      pr.i = i;
-      pr.vol = (float)dvol;
-      pr.mx = (float)dmx;
-      pr.my = (float)dmy;
-      pr.mz = (float)dmz;
-      pr.chi = chi;
-      a.pieces[idx] = pr;
-    } else {
-      atomicOr(status, ST_TABLE_FULL);
-    }
-  }
-}
-
 // ---------------------------------------------------------------------------------------------------------------
 // clipping of one (tet, candidate) piece against the other candidates in order; returns CLIP_* for the piece
 // ---------------------------------------------------------------------------------------------------------------
-template <typename T, typename Topo, typename Mask, int VCAP, bool EXACT, typename Tab>
-__device__ __forceinline__ int clip_piece(Clipper<T, Topo, Mask, VCAP, EXACT, Tab>& cl, int m, int* status) {
+template <typename CL>
+__device__ __forceinline__ int clip_piece(CL& cl, int m) {
+  typedef typename CL::Real T;
   const TetEnv& env = cl.env;
   const float4 o = env.o;
   const double y1x = (double)env.tv[1].x - o.x, y1y = (double)env.tv[1].y - o.y, y1z = (double)env.tv[1].z - o.z;
   const double y2x = (double)env.tv[2].x - o.x, y2y = (double)env.tv[2].y - o.y, y2z = (double)env.tv[2].z - o.z;
   const double y3x = (double)env.tv[3].x - o.x, y3y = (double)env.tv[3].y - o.y, y3z = (double)env.tv[3].z - o.z;
-  cl.init_tet();
-  for (int c = 0; c < m; ++c) {
-    if (c == env.ci) continue;
-    float4 sj = env.cand_site(c);
-    Plane<double> P = bisector64(env.si, sj, o);
+  // CUT: the bisector against candidate c cuts the tet; SKIP: the tet lies in its kept half-space; else it lies outside
+  enum { SKIP, CUT, OUTSIDE };
+  auto classify = [&](int c, Plane<double>& P) {
+    const float4 sj = env.cand_site(c);
+    P = bisector64(env.si, sj, o);
     if (P.nx == 0.0 && P.ny == 0.0 && P.nz == 0.0) {  // concentric spheres: the larger one owns everything
-      if (P.d > 0) continue;
+      if (P.d > 0) return SKIP;
       // equal spheres: under the weight perturbation eps_i - eps_j the lower site id owns everything
-      if (P.d == 0 && env.site_i < env.cand_id(c)) continue;
-      return CLIP_EMPTY;
+      return P.d == 0 && env.site_i < env.cand_id(c) ? SKIP : OUTSIDE;
     }
     // the bisector's values at the tet vertices are exact in FP64
-    double h0 = P.d;
-    double h1 = fma(P.nx, y1x, fma(P.ny, y1y, fma(P.nz, y1z, P.d)));
-    double h2 = fma(P.nx, y2x, fma(P.ny, y2y, fma(P.nz, y2z, P.d)));
-    double h3 = fma(P.nx, y3x, fma(P.ny, y3y, fma(P.nz, y3z, P.d)));
-    if (h0 > 0 && h1 > 0 && h2 > 0 && h3 > 0) continue;  // the tet lies in H_ij: no cut
-    if (h0 < 0 && h1 < 0 && h2 < 0 && h3 < 0) return CLIP_EMPTY;
-    int r = cl.clip(4 + c, round_plane<T>(P));
+    const double h0 = P.d;
+    const double h1 = fma(P.nx, y1x, fma(P.ny, y1y, fma(P.nz, y1z, P.d)));
+    const double h2 = fma(P.nx, y2x, fma(P.ny, y2y, fma(P.nz, y2z, P.d)));
+    const double h3 = fma(P.nx, y3x, fma(P.ny, y3y, fma(P.nz, y3z, P.d)));
+    if (h0 > 0 && h1 > 0 && h2 > 0 && h3 > 0) return SKIP;
+    if (h0 < 0 && h1 < 0 && h2 < 0 && h3 < 0) return OUTSIDE;
+    return CUT;
+  };
+  cl.init_tet();
+  Plane<double> P;
+  if (CL::FEW_PLANES) {  // at most 28 candidates: find the cutting ones first, then every lane clips by its next one
+    unsigned cut = 0;
+    for (int c = 0; c < m; ++c) {
+      if (c == env.ci) continue;
+      const int k = classify(c, P);
+      if (k == OUTSIDE) return CLIP_EMPTY;
+      if (k == CUT) cut |= 1u << c;
+    }
+    for (; cut; cut &= cut - 1) {
+      const int c = ctz_mask(cut);
+      const int r = cl.clip(4 + c, round_plane<T>(bisector64(env.si, env.cand_site(c), o)));
+      if (r != CLIP_OK) return r;
+    }
+    return CLIP_OK;
+  }
+  for (int c = 0; c < m; ++c) {
+    if (c == env.ci) continue;
+    const int k = classify(c, P);
+    if (k == OUTSIDE) return CLIP_EMPTY;
+    if (k == SKIP) continue;
+    const int r = cl.clip(4 + c, round_plane<T>(P));
     if (r != CLIP_OK) return r;
   }
   return CLIP_OK;
 }
 
 // ---------------------------------------------------------------------------------------------------------------
-// fast kernel
+// candidate kernel
 // ---------------------------------------------------------------------------------------------------------------
 __device__ inline double wave_min(double v) {
   for (int off = 32; off > 0; off >>= 1) v = fmin(v, __shfl_xor(v, off));
@@ -422,9 +396,6 @@ __device__ __forceinline__ void g4(const float4* tv, const float4& s, double* g)
     g[v] = D - 2.0 * (((double)tv[v].x - o.x) * ax + ((double)tv[v].y - o.y) * ay + ((double)tv[v].z - o.z) * az);
 }
 
-// Remove candidates dominated on the whole tet by one of the first three candidates (exact test: g_j - g_i is
-// affine, so being larger at the four vertices means larger everywhere on the tet and j owns no point of it).
-// The list must be sorted (only_count: the list is unsorted and over budget; it is filtered but stays unsorted).
 // Drops the candidates that another candidate beats at all four tet vertices (g is affine, so then everywhere on the
 // tet: the site owns nothing there and its bisector constrains no piece; the values are exact in FP64). The list is
 // sorted by the power distance at the centroid, and a dominator has the smaller one, so rounds of three dominators
@@ -455,81 +426,23 @@ __device__ __forceinline__ int refine_candidates(const float4* tv, const float4*
   return m;
 }
 
-// Two LDS layouts of the fast kernel (64 threads). With 16 vertex slots per piece, 256 sites in the shared list, 40
-// raw candidates per tet and the cell sums of 32 sites, a workgroup takes about 27 KB and six fit a compute unit; with
-// 12 slots, 192 sites, 36 raw candidates and the sums of 16 sites it takes under 20 KB and eight fit (two waves per
-// SIMD). Pieces that outgrow their slots are redone inside the kernel with the 64-slot polytope, and a tet's path to
-// the large-capacity kernel depends on its own candidates only, so both layouts give the same elements; the 12-slot
-// one redoes more pieces and splits more blocks, and wins where occupancy, not the longest items, bounds the kernel.
-template <int SLOTS>
-struct FastCfg;
-template <>
-struct FastCfg<16> {
-  static constexpr int VCAP = 16, SL = 256, KR = 40, AGG64 = 32;
-  static constexpr bool USED_FIRST = false;
-};
-template <>
-struct FastCfg<12> {
-  static constexpr int VCAP = 12, SL = 192, KR = 36, AGG64 = 16;
-  static constexpr bool USED_FIRST = true;
-};
-
-template <typename T, int NT, int SLOTS>
-__global__ __launch_bounds__(NT) void k_clip_fast(ShapeArgs a) {
-  typedef FastCfg<SLOTS> FC;
-  constexpr int SLMAX = FC::SL, KRAW = FC::KR, VMAX = FC::VCAP;
-  static_assert(KRAW <= rpd::KRAW && SLMAX <= 256, "candidate bytes index the site list; hand-over lists hold rpd::KRAW");
-  static_assert(NT % TB == 0 && NT >= TB, "threads per block must be a multiple of the tets per block");
-  constexpr int TPT = NT / TB;  // threads per tet in the candidate phase
+// One wavefront per work item (a block, or a part of one). Latency-bound (site scans through the caches, FP64 values on
+// a few dozen sites per tet); 17.5 KB of LDS, so nine items fit a compute unit.
+__global__ __launch_bounds__(64) void k_candidates(ShapeArgs a) {
+  static_assert(SLMAX <= 256, "candidate bytes index the site list");
+  static_assert(TB * KRAW < 32768, "piece offsets are 16-bit");
   __shared__ float4 s_site[SLMAX];
   __shared__ int s_sid[SLMAX];
   __shared__ unsigned char s_cand[TB][KRAW];
-  // the candidates' sort keys are dead before the clipping phase starts: they share storage with the polytopes
-  typedef typename StoreOf<T, Topo32, VMAX>::type PolyStore;
-  constexpr size_t XYZ_BYTES = PolyStore::coord_bytes(NT);
-  constexpr size_t KEY_BYTES = sizeof(float) * TB * KRAW;
-  __shared__ __attribute__((aligned(16))) unsigned char s_share[XYZ_BYTES > KEY_BYTES ? XYZ_BYTES : KEY_BYTES];
-  float(*s_key)[KRAW] = reinterpret_cast<float(*)[KRAW]>(s_share);
-  __shared__ int s_m[TB];
-  static_assert(TB * KMAX < 32768, "piece offsets are 16-bit");
+  __shared__ float s_key[TB][KRAW];  // the candidates' sort keys
+  __shared__ int s_m[TB];            // candidates of each tet; -1: left to the large-capacity kernel without a list
   __shared__ short s_off[TB + 1];
   __shared__ short s_order[TB];
-  __shared__ float s_box[6];
-  __shared__ double s_red[NT / 64];
   __shared__ int s_nsl;
-  __shared__ unsigned long long s_cnt[4];
-  __shared__ unsigned s_topo[VMAX * NT];
-  __shared__ int s_over[NT];  // this round's pieces that ran out of vertex slots: tet << 16 | candidate
-  __shared__ int s_nover;
-  // per-site sums of the workgroup's cell terms (the first 128 sites of the list, or the first 32 with 64 threads,
-  // where the LDS budget for four workgroups per compute unit is tight); pieces of later sites add to the global
-  // accumulators directly
-  constexpr int AGG = NT == 64 ? FC::AGG64 : 128;
-  __shared__ long long s_acc_chi[AGG];
-  __shared__ int s_acc_np[AGG];
-  __shared__ unsigned long long s_acc_lo[4 * AGG];
-  __shared__ int s_acc_hi[4 * AGG];
-  // the sums' slot of each site of the list (255: none): with USED_FIRST, the sites that are candidates of a tet
-  // clipped here take the first AGG slots in list order, so that the few sums cover the sites that own the pieces;
-  // else slot q holds list position q (no map: its bytes would cost the 16-slot layout its sixth workgroup)
-  constexpr bool UF = FC::USED_FIRST;
-  __shared__ unsigned char s_agg[UF ? SLMAX : 1];
-  __shared__ unsigned char s_aggq[UF ? AGG : 1];  // the list position of each slot's site
-  __shared__ int s_nagg;
 
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wid = tid >> 6;
-  if (tid == 0) s_nover = 0;
-  for (int k = tid; k < AGG; k += NT) {
-    s_acc_chi[k] = 0;
-    s_acc_np[k] = 0;
-    for (int d = 0; d < 4; ++d) {
-      s_acc_lo[4 * k + d] = 0;
-      s_acc_hi[4 * k + d] = 0;
-    }
-  }
-  unsigned long long n_pairs = 0, n64 = 0, n_cand = 0;
+  const int tid = threadIdx.x, lane = tid;
   const int nitems = a.nitems_dev ? *a.nitems_dev : a.nitems;
+  unsigned long long n_cand = 0;
   // Work items are (shape, block or part of a block), ordered heaviest first. In a build the grid covers them, one
   // item per workgroup, and the hardware dispatcher hands them to compute units in that order as they free up,
   // which is the work queue. The passes of an incremental round read the item count on the device and launch a
@@ -566,13 +479,12 @@ __global__ __launch_bounds__(NT) void k_clip_fast(ShapeArgs a) {
     if (!next_chunk(sub, sub_n, single_end, ntb_all)) break;
     continue;
   }
-  int tpt = TPT;  // threads per tet in the candidate phase
-  while (tpt < 64 && 2 * tpt * ntb <= NT) tpt *= 2;
+  int tpt = 1;  // lanes per tet in the candidate phase
+  while (tpt < 64 && 2 * tpt * ntb <= 64) tpt *= 2;
 
-  // ---- 1. the tets' bounding box (tet vertices and face planes are read from HBM where they are needed, through
-  //        the caches: on chip, the LDS budget goes to the polytopes, so that more workgroups fit a compute unit)
+  // ---- 1. the tets' bounding box 
   float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-  if (tid < TB) {
+  {
     if (!single && tid < ntb && ((cmask >> tid) & 1ull)) {
       const float4* tp = sd.tp + 4 * (size_t)(t0 + tid);
       for (int v = 0; v < 4; ++v) {
@@ -585,15 +497,12 @@ __global__ __launch_bounds__(NT) void k_clip_fast(ShapeArgs a) {
         hi[2] = fmaxf(hi[2], p.z);
       }
     }
-    s_m[tid] = 0;
-    for (int k = 0; k < 3; ++k) {
-      float l = wave_minf(lo[k]), h = wave_maxf(hi[k]);
-      if (tid == 0) {
-        s_box[k] = l;
-        s_box[3 + k] = h;
-      }
-    }
   }
+  for (int k = 0; k < 3; ++k) {
+    lo[k] = wave_minf(lo[k]);
+    hi[k] = wave_maxf(hi[k]);
+  }
+  s_m[tid] = 0;
   if (tid == 0) s_nsl = 0;
   __syncthreads();
 
@@ -619,7 +528,7 @@ __global__ __launch_bounds__(NT) void k_clip_fast(ShapeArgs a) {
       dv[k] = INFINITY;
       dj[k] = 0x7fffffff;
     }
-    for (int j = tid; j < sd.ns; j += NT) {
+    for (int j = tid; j < sd.ns; j += 64) {
       const float4 s = ssite[j];
       const double ax_ = (double)s.x - o.x, ay_ = (double)s.y - o.y, az_ = (double)s.z - o.z;
       double gq[4];
@@ -643,25 +552,6 @@ __global__ __launch_bounds__(NT) void k_clip_fast(ShapeArgs a) {
           dj[k] = j2;
         }
       }
-    if constexpr (NT > 64) {  // across the waves, through the polytope area (unused until the pieces)
-      double* xv = reinterpret_cast<double*>(s_share);
-      int* xj = reinterpret_cast<int*>(s_share + sizeof(double) * 5 * (NT / 64));
-      if (lane == 0)
-        for (int k = 0; k < 5; ++k) {
-          xv[5 * wid + k] = dv[k];
-          xj[5 * wid + k] = dj[k];
-        }
-      __syncthreads();
-      for (int w = 0; w < NT / 64; ++w)
-        for (int k = 0; k < 5; ++k) {
-          const double x2 = xv[5 * w + k];
-          const int j2 = xj[5 * w + k];
-          if (x2 < dv[k] || (x2 == dv[k] && j2 < dj[k])) {
-            dv[k] = x2;
-            dj[k] = j2;
-          }
-        }
-    }
     const double U = dv[0];
     double gb[5][4];
     for (int k = 0; k < 5; ++k) {
@@ -670,7 +560,7 @@ __global__ __launch_bounds__(NT) void k_clip_fast(ShapeArgs a) {
       gb[k][0] = ax_ * ax_ + ay_ * ay_ + az_ * az_ - (double)s.w * s.w;
       for (int v = 0; v < 3; ++v) gb[k][v + 1] = gb[k][0] - 2.0 * (y[v][0] * ax_ + y[v][1] * ay_ + y[v][2] * az_);
     }
-    for (int j = tid; j < sd.ns; j += NT) {
+    for (int j = tid; j < sd.ns; j += 64) {
       const float4 s = ssite[j];
       const double ax_ = (double)s.x - o.x, ay_ = (double)s.y - o.y, az_ = (double)s.z - o.z;
       double g[4];
@@ -689,22 +579,18 @@ __global__ __launch_bounds__(NT) void k_clip_fast(ShapeArgs a) {
       }
     }
   } else {
-  const double bx = s_box[0], by = s_box[1], bz = s_box[2];
-  const double ex = (double)s_box[3] - bx, ey = (double)s_box[4] - by, ez = (double)s_box[5] - bz;
+  const double bx = lo[0], by = lo[1], bz = lo[2];
+  const double ex = (double)hi[0] - bx, ey = (double)hi[1] - by, ez = (double)hi[2] - bz;
   double umin = INFINITY;
-  for (int j = tid; j < sd.ns; j += NT) {
+  for (int j = tid; j < sd.ns; j += 64) {
     float4 s = ssite[j];
     double ax_ = (double)s.x - bx, ay_ = (double)s.y - by, az_ = (double)s.z - bz;
     double D = ax_ * ax_ + ay_ * ay_ + az_ * az_ - (double)s.w * s.w;
     double gmax = D + fmax(0.0, -2.0 * ex * ax_) + fmax(0.0, -2.0 * ey * ay_) + fmax(0.0, -2.0 * ez * az_);
     umin = fmin(umin, gmax);
   }
-  umin = wave_min(umin);
-  if (lane == 0) s_red[wid] = umin;
-  __syncthreads();
-  double UB = s_red[0];
-  for (int w = 1; w < NT / 64; ++w) UB = fmin(UB, s_red[w]);
-  for (int j = tid; j < sd.ns; j += NT) {
+  const double UB = wave_min(umin);
+  for (int j = tid; j < sd.ns; j += 64) {
     float4 s = ssite[j];
     double ax_ = (double)s.x - bx, ay_ = (double)s.y - by, az_ = (double)s.z - bz;
     double D = ax_ * ax_ + ay_ * ay_ + az_ * az_ - (double)s.w * s.w;
@@ -737,8 +623,6 @@ __global__ __launch_bounds__(NT) void k_clip_fast(ShapeArgs a) {
     }
   }
   const bool block_overflow = nsl > SLMAX || (a.flags & RPD_FORCE_SLOW_PATH);
-  if constexpr (UF)
-    for (int q = tid; q < min(nsl, SLMAX); q += NT) s_agg[q] = 0;
 
   // ---- 3. candidates of every tet: sites whose minimum over the tet is <= min_j max over the tet
   if (!block_overflow) {
@@ -825,8 +709,7 @@ __global__ __launch_bounds__(NT) void k_clip_fast(ShapeArgs a) {
     }
   }
   __syncthreads();
-  // sort each tet's candidates by (power distance at the centroid, site id), drop the dominated ones, and mark the
-  // tets that keep more than the budget
+  // sort each tet's candidates by (power distance at the centroid, site id) and drop the dominated ones
   if (tid < ntb && ((cmask >> tid) & 1ull)) {
     int m = s_m[tid];
     if (!block_overflow && m <= KRAW) {
@@ -845,117 +728,200 @@ __global__ __launch_bounds__(NT) void k_clip_fast(ShapeArgs a) {
       }
       m = refine_candidates(sd.tp + 4 * (size_t)(t0 + tid), s_site, s_cand[tid], s_key[tid], m);
     }
-    if (block_overflow || m > a.kmax) {
-      s_m[tid] = -1;
-      stat_add(a, block_overflow ? C_DEFER_BLOCK : C_DEFER_KMAX, 1ull);
-      // the sorted, refined candidates go with the tet when they fit the list (else the large-capacity kernel finds
-      // them among all sites); either way the choice depends on the tet's candidates only
-      const int list = (!block_overflow && m <= KRAW) ? hand_over_list(a, s_cand[tid], s_sid, m) : 0;
-      unsigned long long idx = atomicAdd(&a.counters[C_DEFER_ITEMS], 1ull);
-      if (idx < (unsigned long long)a.deferred_cap) a.deferred[idx] = make_int4(shape, t0 + tid, -1, list);
-      else atomicOr(a.status, ST_TABLE_FULL);
-    } else {
-      s_m[tid] = m;
-      if constexpr (UF)
-        for (int x = 0; x < m; ++x) s_agg[s_cand[tid][x]] = 1;
+    // a tet over the budget goes to the large-capacity kernel, with its sorted, refined candidates when they fit the
+    // list (else that kernel finds them among all sites); either way the choice depends on its own candidates only
+    if (block_overflow || m > a.kmax) stat_add(a, block_overflow ? C_DEFER_BLOCK : C_DEFER_KMAX, 1ull);
+    if (block_overflow || m > KRAW) {
+      m = -1;
+      defer_item(a, shape, t0 + tid, -1, -1);
     }
+    s_m[tid] = m;
   }
   __syncthreads();
   // pieces are laid out tet by tet with the tets ordered by candidate count, largest first: every piece of a tet
   // loops over the same planes, so a wavefront's lanes then have similar trip counts
-  if (tid < TB) {
+  {
     const int mt = tid < ntb ? max(s_m[tid], 0) : 0;
-    int rank = 0;
+    int rank = 0, off = 0;
     for (int u = 0; u < TB; ++u) {
-      const int mu = u < ntb ? max(s_m[u], 0) : 0;
-      rank += (mu > mt || (mu == mt && u < tid)) ? 1 : 0;
-    }
-    s_order[rank] = tid;
-  }
-  __syncthreads();
-  if (wid == 0) {
-    const int nl = min(nsl, SLMAX);
-    int nagg = nl;
-    if constexpr (UF) {
-      nagg = 0;
-      for (int c = 0; c < nl; c += 64) {
-        const int q = c + lane;
-        const bool used = q < nl && s_agg[q] != 0;
-        const unsigned long long mk = __ballot(used);
-        const int r = nagg + __popcll(mk & ((1ull << lane) - 1ull));
-        if (q < nl) s_agg[q] = (used && r < AGG) ? (unsigned char)r : (unsigned char)255;
-        if (used && r < AGG) s_aggq[r] = (unsigned char)q;
-        nagg += __popcll(mk);
+      const int mu = __shfl(mt, u);
+      if (mu > mt || (mu == mt && u < tid)) {
+        ++rank;
+        off += mu;
       }
     }
-    if (lane == 0) s_nagg = min(nagg, AGG);
-  }
-  if (tid == 0) {
-    int acc = 0;
-    for (int j = 0; j < TB; ++j) {
-      s_off[j] = acc;
-      const int lt = s_order[j];
-      if (lt < ntb && s_m[lt] > 0) acc += s_m[lt];
-    }
-    s_off[TB] = acc;
+    s_order[rank] = (short)tid;
+    s_off[rank] = (short)off;
+    if (rank == TB - 1) s_off[TB] = (short)(off + mt);
   }
   __syncthreads();
-
-  // ---- 4. one thread per (tet, candidate) piece
   const int npairs = s_off[TB];
-  n_cand += npairs;
-  for (int base = 0; base < npairs; base += NT) {  // rounds of NT pieces (the same count for every thread)
-    const int p = base + tid;
-    if (p < npairs) {
+  int base = 0;
+  if (lane == 0 && npairs) {
+    const unsigned long long q = atomicAdd(&a.counters[C_PIECE_SLOTS], (unsigned long long)npairs);
+    base = q + npairs <= (unsigned long long)a.pcap ? (int)q : -1;
+    if (base < 0) atomicOr(a.status, ST_TABLE_FULL);
+  }
+  base = __builtin_amdgcn_readfirstlane(base);
+  if (base >= 0) {
+    for (int p = tid; p < npairs; p += 64) {
       int lo_ = 0, hi_ = TB - 1;  // last position j with s_off[j] <= p
       while (lo_ < hi_) {
-        int mid = (lo_ + hi_ + 1) >> 1;
+        const int mid = (lo_ + hi_ + 1) >> 1;
         if (s_off[mid] <= p) lo_ = mid;
         else hi_ = mid - 1;
       }
-      const int lt = s_order[lo_];
-      const int ci = p - s_off[lo_];
-      const int m = s_m[lt];
-      Clipper<T, Topo32, unsigned, VMAX, false, RegTab> cl;
-      cl.st.bind(s_share, s_topo, tid, NT);
+      const int lt = s_order[lo_], first = s_off[lo_], m = s_m[lt];
+      a.psite[base + p] = s_sid[s_cand[lt][p - first]];
+      PieceDesc d;
+      d.t = t0 + lt;
+      d.shape = shape;
+      d.first = base + first;
+      d.m = m;
+      a.pdesc[base + p] = d;
+      if (m > a.kmax) {
+        if (p == first) defer_item(a, shape, t0 + lt, -1, base + first);
+      } else {
+        ++n_cand;
+      }
+    }
+  }
+  if (!split || !next_chunk(sub, sub_n, single_end, ntb_all)) break;
+  __syncthreads();  // the next chunk reuses every shared array
+  }
+  __syncthreads();  // the next item reuses every shared array
+  if (a.item_cost && tid == 0)  // the item's duration (every thread is past it), a scheduling hint for the next build
+    a.item_cost[item] = (unsigned)min(wall_clock64() - clock0, 0xffffffffull);
+  }
+  for (int off = 32; off > 0; off >>= 1) n_cand += __shfl_xor(n_cand, off);
+  if (lane == 0 && n_cand) stat_add(a, C_CAND, n_cand);
+}
+
+// ---------------------------------------------------------------------------------------------------------------
+// piece kernel
+// ---------------------------------------------------------------------------------------------------------------
+// Vertex slots per piece: 16 (19.7 KB of LDS a wavefront in FP32) or 12 (15.6 KB: more wavefronts fit a compute unit).
+// A piece that outgrows them is redone after its chunk with a 64-slot polytope; the arithmetic is the same.
+//
+// A piece's terms are plain stores, no value of which the kernel waits for: with the sums and the element pieces
+// entered into hash tables here, a chunk spent most of its time on the round trips of those dependent atomics.
+constexpr int WIN = CHUNK + 2 * KRAW;  // candidate slots of the tets that a chunk touches
+
+template <typename T, int SLOTS>
+__global__ __launch_bounds__(64) void k_clip_pieces(ShapeArgs a) {
+  typedef typename StoreOf<T, Topo32, SLOTS>::type PolyStore;
+  __shared__ __attribute__((aligned(16))) unsigned char s_poly[PolyStore::coord_bytes(64)];
+  __shared__ unsigned s_topo[SLOTS * 64];
+  __shared__ float4 s_csite[WIN];
+  __shared__ int s_csid[WIN];
+  __shared__ int s_over[CHUNK];  // this chunk's pieces that ran out of vertex slots
+  __shared__ int s_nover;
+  if (*a.status & ST_TABLE_FULL) return;  // some slots were never filled; the call is redone with larger buffers
+  const int lane = threadIdx.x;
+  const int np_all = (int)min(a.counters[C_PIECE_SLOTS], (unsigned long long)a.pcap);
+  const int nchunks = (np_all + CHUNK - 1) / CHUNK;
+  if (lane == 0) {
+    s_nover = 0;
+    if (blockIdx.x == 0) a.counters[C_CHUNKS] = (unsigned long long)nchunks;
+  }
+  long long n_pairs = 0;
+  unsigned long long n64 = 0;
+  for (int chunk = blockIdx.x; chunk < nchunks; chunk += gridDim.x) {
+    const int p = chunk * CHUNK + lane;
+    const int last = min(CHUNK, np_all - chunk * CHUNK) - 1;
+    PieceDesc d = a.pdesc[chunk * CHUNK + min(lane, last)];
+    const bool run = lane <= last && d.m <= a.kmax;
+    // the candidates of the chunk's tets are consecutive slots
+    const int w0 = __shfl(d.first, 0), w1 = min(__shfl(d.first + d.m, last), w0 + WIN);
+    __syncthreads();
+    for (int q = w0 + lane; q < w1; q += 64) {
+      const int s = a.psite[q];
+      s_csid[q - w0] = s;
+      s_csite[q - w0] = a.site[s];
+    }
+    __syncthreads();
+    const ShapeDesc& sd = a.shapes[d.shape];
+    const int co = d.first - w0;
+    auto bind = [&](TetEnv& env, int t, int c0, int ci) {
+      env.tv = sd.tp + 4 * (size_t)t;
+      env.o = env.tv[0];
+      env.face64 = sd.tf + 4 * (size_t)t;
+      env.sid = s_csid + c0;
+      env.csite = s_csite + c0;
+      env.site = nullptr;
+      env.ncs = INT_MAX;
+      env.ci = ci;
+      env.si = env.csite[ci];
+      env.site_i = env.sid[ci];
+    };
+    typedef Clipper<T, Topo32, unsigned, SLOTS, false, RegTab> CL;
+    CL cl;
+    EmitAcc<CL> e;
+    e.nface = e.nedge = e.nrpv = 0;
+    int r = CLIP_EMPTY;
+    if (run) {
+      cl.st.bind(s_poly, s_topo, lane, 64);
       cl.tab.clear(0);
       cl.a = nullptr;  // only the exact predicates use it (not compiled into this kernel)
       cl.flags = a.flags;
-      cl.np = 4 + m;
+      cl.np = 4 + d.m;
       cl.n64 = 0;
       cl.nex = 0;
-      fast_env(cl.env, sd, t0 + lt, s_site, s_sid, s_cand[lt], ci);
-      const int r = clip_piece(cl, m, a.status);
+      bind(cl.env, d.t, co, p - d.first);
+      r = clip_piece(cl, d.m);
       n64 += cl.n64;
       if (r == CLIP_OK) {
-        n_pairs += (unsigned long long)(long long)sd.sign;  // live pieces, in two's complement
-        const int slot = UF ? (int)s_agg[s_cand[lt][ci]] : (int)s_cand[lt][ci];
-        emit_piece(cl, sd, t0 + lt, a, CellSink{s_acc_chi, s_acc_np, s_acc_lo, s_acc_hi, AGG, slot});
-      } else if (r == CLIP_DEFER) {
-        defer_piece(a, shape, t0 + lt, cl.env.site_i, s_cand[lt], s_sid, m);
-      } else if (r == CLIP_FULL) {  // out of vertex slots: redone below, after this round
-        s_over[atomicAdd(&s_nover, 1)] = (lt << 16) | ci;
+        n_pairs += sd.sign;  // live pieces
+        emit_scan(cl, sd.nu + 14 * (size_t)d.t, sd.L, e);
+      } else {
+        a.pout[p].word = 0;
+        if (r == CLIP_DEFER) {
+          stat_add(a, C_DEFER_CLIP, 1ull);
+          defer_item(a, d.shape, d.t, p, d.first);
+        } else if (r == CLIP_FULL) {
+          s_over[atomicAdd(&s_nover, 1)] = lane;
+        }
       }
     }
-    // Pieces that ran out of vertex slots are redone here, one per thread, with a BIG_VCAP-slot polytope (they
-    // would otherwise wait for the deferred kernel, after this one). The round's small polytopes are dead by now,
-    // so the first records live in their LDS; more go to a global-memory pool (same arithmetic, same bits). Which
-    // path computes a piece must depend on the piece alone (an incremental update must take back exactly the bits
-    // it added), so a full pool is a table overflow (the call is redone with larger buffers), never a deferral.
+    // records: the lanes' runs one after the other, in the chunk's own range when they fit
+    const int n = e.records();
+    int incl = n;
+    for (int off = 1; off < 64; off <<= 1) {
+      const int y = __shfl_up(incl, off);
+      if (lane >= off) incl += y;
+    }
+    const int total = __shfl(incl, 63);
+    int base = chunk * REC_CHUNK;
+    if (total > REC_CHUNK) {
+      int q = 0;
+      if (lane == 0) q = pool_records(a, total);
+      base = __builtin_amdgcn_readfirstlane(q);
+    }
+    if (lane == 0) a.chunk_recs[chunk] = total > REC_CHUNK ? 0 : total;
+    if (run && r == CLIP_OK && base >= 0) emit_out(cl, sd, d.t, e, p, base + incl - n, a);
+    // Pieces that ran out of vertex slots are redone here, one per lane, with a BIG_VCAP-slot polytope. The chunk's
+    // small polytopes are dead by now, so the first records live in their LDS; more go to a global-memory pool (same
+    // arithmetic, same bits). Which path computes a piece must depend on the piece alone (an incremental update must
+    // take back exactly the bits it added), so a full pool is a table overflow (the call is redone with larger
+    // buffers), never a deferral.
     __syncthreads();
     const int nover = s_nover;
     if (nover) {
-      if (tid < nover) {
-        const int lt = s_over[tid] >> 16, ci = s_over[tid] & 0xffff, m = s_m[lt];
+      if (lane < nover) {
+        const int src = s_over[lane];
+        const int pb = chunk * CHUNK + src;
+        const PieceDesc db = a.pdesc[pb];
+        const ShapeDesc& sb = a.shapes[db.shape];
+        const int m = db.m;
         constexpr size_t CB = sizeof(typename Coord4<T>::type) * BIG_VCAP;
         constexpr size_t REC = (CB + 8 * BIG_VCAP + 64 + 15) / 16 * 16;
-        constexpr int NLDS = (int)(sizeof(s_share) / REC);
+        constexpr int NLDS = (int)(sizeof(s_poly) / REC);
         static_assert(CB + 8 * BIG_VCAP + 32 <= BIG_BYTES, "large-capacity polytope record");
         const unsigned long long slot = atomicAdd(&a.counters[C_BIG], 1ull);
-        if (tid >= NLDS && slot >= (unsigned long long)a.big_cap) {
+        if (lane >= NLDS && slot >= (unsigned long long)a.big_cap) {
           atomicOr(a.status, ST_TABLE_FULL);
         } else {
-          unsigned char* b = tid < NLDS ? s_share + (size_t)tid * REC : a.big + slot * BIG_BYTES;
+          unsigned char* b = lane < NLDS ? s_poly + (size_t)lane * REC : a.big + slot * BIG_BYTES;
           Clipper<T, Topo64, unsigned long long, BIG_VCAP, false, MemTab> cb;
           cb.st.c = reinterpret_cast<typename Coord4<T>::type*>(b);
           cb.st.w = reinterpret_cast<unsigned long long*>(b + CB);
@@ -968,56 +934,40 @@ __global__ __launch_bounds__(NT) void k_clip_fast(ShapeArgs a) {
           cb.np = 4 + m;
           cb.n64 = 0;
           cb.nex = 0;
-          fast_env(cb.env, sd, t0 + lt, s_site, s_sid, s_cand[lt], ci);
-          const int r = clip_piece(cb, m, a.status);
+          {
+            cb.env.tv = sb.tp + 4 * (size_t)db.t;
+            cb.env.o = cb.env.tv[0];
+            cb.env.face64 = sb.tf + 4 * (size_t)db.t;
+            cb.env.sid = s_csid + (db.first - w0);
+            cb.env.csite = s_csite + (db.first - w0);
+            cb.env.site = nullptr;
+            cb.env.ncs = INT_MAX;
+            cb.env.ci = pb - db.first;
+            cb.env.si = cb.env.csite[cb.env.ci];
+            cb.env.site_i = cb.env.sid[cb.env.ci];
+          }
+          const int rb = clip_piece(cb, m);
           n64 += cb.n64;
-          if (r == CLIP_OK) {
-            n_pairs += (unsigned long long)(long long)sd.sign;
-            const int slot = UF ? (int)s_agg[s_cand[lt][ci]] : (int)s_cand[lt][ci];
-            emit_piece(cb, sd, t0 + lt, a, CellSink{s_acc_chi, s_acc_np, s_acc_lo, s_acc_hi, AGG, slot});
-          } else if (r != CLIP_EMPTY) {  // a predicate undecided in FP64, or over BIG_VCAP vertices
-            defer_piece(a, shape, t0 + lt, cb.env.site_i, s_cand[lt], s_sid, m);
+          if (rb == CLIP_OK) {
+            n_pairs += sb.sign;
+            emit_alone(cb, sb, db.t, pb, a);
+          } else if (rb != CLIP_EMPTY) {  // a predicate undecided in FP64, or over BIG_VCAP vertices
+            stat_add(a, C_DEFER_CLIP, 1ull);
+            defer_item(a, db.shape, db.t, pb, db.first);
           }
         }
       }
       __syncthreads();
-      if (tid == 0) s_nover = 0;
-      __syncthreads();
+      if (lane == 0) s_nover = 0;
     }
   }
-  // flush the workgroup's cell sums of this pass (the site list changes with the next chunk)
-  __syncthreads();
-  for (int q = tid; q < s_nagg; q += NT) {  // q: the slot
-    const int np_q = s_acc_np[q];
-    if (np_q == 0) continue;
-    const int i = s_sid[UF ? (int)s_aggq[q] : q];
-    atomicAdd((unsigned long long*)&a.cell_chi[i], (unsigned long long)(sd.sign * s_acc_chi[q]));
-    atomicAdd(&a.cell_np[i], sd.sign * np_q);
-    for (int d = 0; d < 4; ++d) {
-      const Fix128 v{s_acc_lo[4 * q + d], (long long)s_acc_hi[4 * q + d]};
-      acc128((unsigned long long*)&a.cell_geo[8 * (size_t)i + 2 * d], signed128(v, sd.sign));
-      s_acc_lo[4 * q + d] = 0;
-      s_acc_hi[4 * q + d] = 0;
-    }
-    s_acc_chi[q] = 0;
-    s_acc_np[q] = 0;
+  for (int off = 32; off > 0; off >>= 1) {
+    n_pairs += __shfl_xor(n_pairs, off);
+    n64 += __shfl_xor(n64, off);
   }
-  if (!split || !next_chunk(sub, sub_n, single_end, ntb_all)) break;
-  __syncthreads();  // the next chunk reuses every shared array
-  }
-  __syncthreads();  // the next item reuses every shared array
-  if (a.item_cost && tid == 0)  // the item's duration (every thread is past it), a scheduling hint for the next build
-    a.item_cost[item] = (unsigned)min(wall_clock64() - clock0, 0xffffffffull);
-  }
-  if (tid < 4) s_cnt[tid] = 0;
-  __syncthreads();
-  atomicAdd(&s_cnt[0], n_pairs);
-  atomicAdd(&s_cnt[1], n64);
-  __syncthreads();
-  if (tid == 0 && n_cand) {
-    if (s_cnt[0]) stat_add(a, C_PAIRS, s_cnt[0]);
-    if (s_cnt[1]) stat_add(a, C_FP64, s_cnt[1]);
-    stat_add(a, C_CAND, n_cand);
+  if (lane == 0) {
+    if (n_pairs) stat_add(a, C_PAIRS, (unsigned long long)n_pairs);  // in two's complement
+    if (n64) stat_add(a, C_FP64, n64);
   }
 }
 
@@ -1077,6 +1027,7 @@ __global__ __launch_bounds__(64, LDS ? 1 : 2) void k_clip_slow(ShapeArgs a, unsi
   __shared__ float4 s_tv4[4];
   __shared__ double4 s_tf4[4];
   __shared__ float4 s_csite[SC];
+  if (*a.status & ST_TABLE_FULL) return;  // the call is redone with larger buffers
   const int n_main = (int)min(min(a.counters[C_DEFER_ITEMS], (unsigned long long)a.deferred_cap),
                               (unsigned long long)item_end);
   const int n_over = LDS ? 0 : (int)min(a.counters[C_DEFER2], (unsigned long long)a.deferred2_cap);
@@ -1102,7 +1053,8 @@ __global__ __launch_bounds__(64, LDS ? 1 : 2) void k_clip_slow(ShapeArgs a, unsi
     const int4 di = vi < main_count ? a.deferred[item_begin + vi] : a.deferred2[vi - main_count];
     const ShapeDesc sd = a.shapes[__builtin_amdgcn_readfirstlane(di.x)];
     const int t = di.y;
-    const int want = di.z;
+    const int want = di.z;  // piece slot, or -1: every candidate of the tet
+    int first = di.w;       // the tet's first piece slot, or -1: its candidates are found here
     const float4* ssite = a.site + sd.site_off;
     float4 tv[4];
     for (int v = 0; v < 4; ++v) tv[v] = sd.tp[4 * (size_t)t + v];
@@ -1119,18 +1071,20 @@ __global__ __launch_bounds__(64, LDS ? 1 : 2) void k_clip_slow(ShapeArgs a, unsi
     }
     const double ycx = (y[0][0] + y[1][0] + y[2][0]) * 0.25, ycy = (y[0][1] + y[1][1] + y[2][1]) * 0.25,
                  ycz = (y[0][2] + y[1][2] + y[2][2]) * 0.25;
-    // the fast kernel hands over the sorted candidates of the tets and pieces it defers when they fit its list (a
-    // function of the tet's candidates only); otherwise they are found here among all sites
-    const int m_list = di.w & 63;
+    // a tet's sorted candidates come with its piece slots when they fit the candidate kernel's list (a function of
+    // the tet's candidates only); otherwise they are found here among all sites
     int m = 0;
-    if (m_list > 0) {
-      const int* lst = a.deferred_list + (size_t)(di.w >> 6) * KRAW;
-      for (int x = lane; x < m_list; x += 64) {
-        const int sx = lst[x];
+    if (first >= 0) {
+      m = a.pdesc[first].m;
+      if (LDS && m > KC) {  // (a tet whose candidates this kernel's global variant found)
+        if (lane == 0) push_overflow(a, di);
+        continue;
+      }
+      for (int x = lane; x < m; x += 64) {
+        const int sx = a.psite[first + x];
         scand[x] = sx;
         if (x < SC) s_csite[x] = a.site[sx];
       }
-      m = m_list;
       __syncthreads();
     } else {
       // candidates among ALL sites of the shape (same exact test as the fast kernel)
@@ -1221,12 +1175,32 @@ __global__ __launch_bounds__(64, LDS ? 1 : 2) void k_clip_slow(ShapeArgs a, unsi
         skey[rank] = kx;
         if (rank < SC) s_csite[rank] = a.site[cand[x]];
       }
+      // piece slots for the tet's candidates
+      __syncthreads();
+      int q = -1;
+      if (lane == 0) {
+        const unsigned long long at = atomicAdd(&a.counters[C_PIECE_SLOTS], (unsigned long long)m);
+        if (at + m <= (unsigned long long)a.pcap) q = (int)at;
+        else atomicOr(a.status, ST_TABLE_FULL);
+      }
+      first = __builtin_amdgcn_readfirstlane(q);
+      if (first < 0) continue;
+      for (int x = lane; x < m; x += 64) {
+        PieceDesc d;
+        d.t = t;
+        d.shape = di.x;
+        d.first = first;
+        d.m = m;
+        a.pdesc[first + x] = d;
+        a.psite[first + x] = scand[x];
+        a.pout[first + x].word = 0;
+      }
     }
     if (lane < CL)
       for (int k = 0; k < 4 + m; ++k) tab[CL * k] = 0;  // the plane ids of this item start unpaired
     __syncthreads();
     for (int ci = lane; ci < m && lane < CL; ci += CL) {
-      if (want >= 0 && scand[ci] != want) continue;
+      if (want >= 0 && first + ci != want) continue;
       Clipper<double, Topo64, typename C::Mask, C::VCAP, true, MemTab> cl;
       cl.st.c = xyz;
       cl.st.w = topo;
@@ -1240,26 +1214,25 @@ __global__ __launch_bounds__(64, LDS ? 1 : 2) void k_clip_slow(ShapeArgs a, unsi
       cl.env.tv = s_tv4;
       cl.env.o = s_tv4[0];
       cl.env.face64 = s_tf4;
-      cl.env.sites = a.site;
-      cl.env.sid = nullptr;  // candidates hold batch-global site ids directly
-      cl.env.cidx8 = nullptr;
-      cl.env.cidx32 = scand;
+      cl.env.sid = scand;
       cl.env.csite = s_csite;
+      cl.env.site = a.site;
       cl.env.ncs = min(m, SC);
       cl.env.ci = ci;
       cl.env.si = a.site[scand[ci]];
       cl.env.site_i = scand[ci];
-      int r = clip_piece(cl, m, a.status);
+      a.pout[first + ci].word = 0;
+      int r = clip_piece(cl, m);
       n64 += cl.n64;
       nex += cl.nex;
       if (r == CLIP_FULL) {  // out of vertex slots: the global variant redoes the piece with the same candidates
-        if (LDS) push_overflow(a, make_int4(di.x, t, scand[ci], di.w));
+        if (LDS) push_overflow(a, make_int4(di.x, t, first + ci, first));
         else atomicOr(a.status, ST_SLOW_CAPACITY);
         continue;
       }
       if (r == CLIP_OK) {
         n_pairs += (unsigned long long)(long long)sd.sign;
-        emit_piece(cl, sd, t, a, CellSink{nullptr, nullptr, nullptr, nullptr, 0, -1});
+        emit_alone(cl, sd, t, first + ci, a);
       }
     }
     __syncthreads();  // the candidate list is rewritten by the next item
@@ -1279,19 +1252,26 @@ __global__ __launch_bounds__(64, LDS ? 1 : 2) void k_clip_slow(ShapeArgs a, unsi
 // ---------------------------------------------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------------------------------------------
-template <typename T, int NT, int SLOTS>
-static hipError_t launch_items(const ShapeArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL((k_clip_fast<T, NT, SLOTS>), dim3(a.nitems), dim3(NT), 0, s, a);
+// The piece count is known on the device only: a grid of several times the wavefronts that fit the chip takes the
+// chunks in grid-stride order (workgroups past the last chunk exit at once).
+template <typename T, int SLOTS>
+static hipError_t launch_pieces(const ShapeArgs& a, hipStream_t s) {
+  const int grid = std::max(1, std::min(a.pcap / CHUNK, 8192));
+  hipLaunchKernelGGL((k_clip_pieces<T, SLOTS>), dim3(grid), dim3(64), 0, s, a);
   return hipGetLastError();
 }
 
-hipError_t launch_clip_fast(const ShapeArgs& a, int precision, int block, int slots, hipStream_t s) {
+hipError_t launch_candidates(const ShapeArgs& a, hipStream_t s) {
   if (a.nitems == 0) return hipSuccess;
-  if (precision == RPD_FP64) return launch_items<double, 64, 16>(a, s);
-  if (block == 128) return launch_items<float, 128, 16>(a, s);
-  if (block == 256) return launch_items<float, 256, 16>(a, s);
-  if (slots == 12) return launch_items<float, 64, 12>(a, s);  // eight workgroups per compute unit
-  return launch_items<float, 64, 16>(a, s);  // 64 threads (also for block 0): six workgroups per compute unit
+  hipLaunchKernelGGL(k_candidates, dim3(a.nitems), dim3(64), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_clip_pieces(const ShapeArgs& a, int precision, int slots, hipStream_t s) {
+  if (a.nitems == 0) return hipSuccess;
+  if (precision == RPD_FP64) return launch_pieces<double, 16>(a, s);
+  if (slots == 12) return launch_pieces<float, 12>(a, s);
+  return launch_pieces<float, 16>(a, s);
 }
 
 size_t slow_scratch_bytes(int waves) { return (size_t)waves * SlowScratch::bytes; }

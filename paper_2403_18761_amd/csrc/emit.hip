@@ -1,0 +1,242 @@
+// Emission: the clipped pieces' cell terms and element records (rpd_common.h) turned into the sums of the cells, faces,
+// edges and RPVs, and into the element pieces that the components are found over.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "rpd_device.h"
+#include "rpd_launch.h"
+
+namespace rpd {
+
+// One element piece (element, tet) is emitted exactly once per shape: adding sets its gluing bits and count,
+// removing (the same piece recomputed from the state before an incremental update, sign -1) takes both back.
+// The two happen in one launch, in either order. Each records the piece's gluing bits in its own half of the
+// piece's tag pair; a scan after the launch flags the element for a new union-find only where the two differ (a
+// piece put back with the same gluing bits leaves the element's forest as it was).
+__device__ inline void node_emit(const ShapeArgs& a, int sign, unsigned long long key, int glue) {
+  int ns = node_insert(a.N, key, a.status);
+  if (ns < 0) return;
+  atomicAdd(&a.N.rec[ns].st, sign * (NODE_UNIT + glue));  // removal re-emits the same bits, so this is exact
+  if (a.touch_cell) a.removed[2 * (size_t)ns + (sign > 0)] = (unsigned short)(0x100 | glue);
+}
+
+// a per-piece element term for sampled comparisons (RPD_KEEP_PIECES only)
+__device__ inline void keep_term(const ShapeArgs& a, int kind, int t, int i, int j, int k, int l, int glue,
+                                 long long num) {
+  if (!(a.flags & RPD_KEEP_PIECES)) return;
+  const unsigned long long idx = atomicAdd(&a.counters[C_TERMS], 1ull);
+  if (idx < (unsigned long long)a.term_cap) {
+    TermRec r;
+    r.kind = kind;
+    r.t = t;
+    r.i = i;
+    r.j = j;
+    r.k = k;
+    r.l = l;
+    r.glue = glue;
+    r.pad = 0;
+    r.num = num;
+    a.terms[idx] = r;
+  } else {
+    atomicOr(a.status, ST_TABLE_FULL);
+  }
+}
+
+__device__ inline long long fixed56(double v) { return llrint(v * 72057594037927936.0); }  // 2^-56 units
+
+// Cell volumes and first moments are exact sums of 128-bit integers in units of 2^-80 (resolution 8e-25, range
+// 2^47), so that a nonempty piece far smaller than a grid cell still counts, every sum is independent of the order
+// of the additions, and a removal pass takes its contributions back exactly. An accumulator is a (low, high) pair
+// of 64-bit words; an addition adds the low word atomically and carries into the high word only when needed.
+struct Fix128 {
+  unsigned long long lo;
+  long long hi;
+};
+__device__ inline Fix128 fixed80(double v) {
+  const double D = rint(ldexp(v, 80));  // exact scaling, then the nearest integer
+  const double h = floor(ldexp(D, -64));
+  const double l = D - ldexp(h, 64);    // in [0, 2^64): the low bits of D, exact
+  return Fix128{(unsigned long long)l, (long long)h};
+}
+__device__ inline Fix128 signed128(Fix128 x, int sign) {
+  if (sign > 0) return x;
+  return Fix128{0ull - x.lo, -x.hi - (x.lo != 0ull ? 1 : 0)};
+}
+__device__ inline void acc128(unsigned long long* p, Fix128 v) {
+  const unsigned long long old = atomicAdd(p, v.lo);
+  const long long h = v.hi + (old + v.lo < old ? 1 : 0);  // carry out of the low word
+  if (h) atomicAdd(p + 1, (unsigned long long)h);
+}
+
+// Sums of a workgroup's cell terms, one slot per site (open addressing): consecutive piece slots belong to
+// neighbouring tets, so a few dozen sites own EMIT_PIECES of them and the global accumulators see one addition per
+// site and workgroup.
+constexpr int EMIT_NT = 256;
+constexpr int EMIT_PIECES = 1024;  // piece slots per workgroup and step
+constexpr int CELL_SLOTS = 256;
+struct CellSums {
+  int site[CELL_SLOTS];  // -1: free
+  int np[CELL_SLOTS];
+  long long chi[CELL_SLOTS];
+  unsigned long long lo[4 * CELL_SLOTS];
+  int hi[4 * CELL_SLOTS];  // a workgroup's sum stays below 2^84: 32 bits suffice
+};
+
+__device__ inline int cell_slot(CellSums& S, int site) {
+  unsigned s = ((unsigned)site * 2654435761u) >> 24;
+  for (int probe = 0; probe < 16; ++probe) {
+    const int old = atomicCAS(&S.site[s], -1, site);
+    if (old == -1 || old == site) return (int)s;
+    s = (s + 1) & (CELL_SLOTS - 1);
+  }
+  return -1;
+}
+
+__device__ __forceinline__ void emit_cells(const ShapeArgs& a) {
+  static_assert(CELL_SLOTS == 256 && EMIT_NT == CELL_SLOTS, "one slot per thread; the hash takes the top 8 bits");
+  __shared__ CellSums S;
+  const int tid = threadIdx.x;
+  const int np_all = (int)min(a.counters[C_PIECE_SLOTS], (unsigned long long)a.pcap);
+  unsigned long long nodes = 0;
+  for (int base = blockIdx.x * EMIT_PIECES; base < np_all; base += gridDim.x * EMIT_PIECES) {
+    S.site[tid] = -1;
+    S.np[tid] = 0;
+    S.chi[tid] = 0;
+    for (int d = 0; d < 4; ++d) {
+      S.lo[4 * tid + d] = 0;
+      S.hi[4 * tid + d] = 0;
+    }
+    __syncthreads();
+    for (int q = 0; q < EMIT_PIECES / EMIT_NT; ++q) {
+      const int p = base + q * EMIT_NT + tid;
+      if (p >= np_all) break;
+      const PieceOut o = a.pout[p];
+      if (!(o.word & 1u)) continue;
+      const PieceDesc d = a.pdesc[p];
+      const ShapeDesc& sd = a.shapes[d.shape];
+      const int i = a.psite[p], sign = sd.sign, glue = pw_glue(o.word);
+      const int t = (int)(sd.tet_off + d.t);
+      const double v[4] = {o.vol, o.mx, o.my, o.mz};
+      const int s = cell_slot(S, i);
+      if (s >= 0) {
+        atomicAdd(&S.np[s], sign);
+        atomicAdd((unsigned long long*)&S.chi[s], (unsigned long long)(sign * o.chi));
+        for (int k = 0; k < 4; ++k) {
+          const Fix128 g = signed128(fixed80(v[k]), sign);
+          const unsigned long long old = atomicAdd(&S.lo[4 * s + k], g.lo);
+          const long long h = g.hi + (old + g.lo < old ? 1 : 0);
+          if (h) atomicAdd(&S.hi[4 * s + k], (int)h);
+        }
+      } else {
+        atomicAdd(&a.cell_np[i], sign);
+        atomicAdd((unsigned long long*)&a.cell_chi[i], (unsigned long long)(sign * o.chi));
+        for (int k = 0; k < 4; ++k)
+          acc128((unsigned long long*)&a.cell_geo[8 * (size_t)i + 2 * k], signed128(fixed80(v[k]), sign));
+      }
+      node_emit(a, sign, node_key(1, i, t), glue);
+      keep_term(a, 1, t, i, -1, -1, -1, glue, o.chi);
+      if (a.flags & RPD_KEEP_PIECES) {
+        const unsigned long long idx = atomicAdd(&a.counters[C_PIECES], 1ull);
+        if (idx < (unsigned long long)a.piece_cap) {
+          PieceRec pr;
+          pr.t = t;
+          pr.i = i;
+          pr.vol = (float)o.vol;
+          pr.mx = (float)o.mx;
+          pr.my = (float)o.my;
+          pr.mz = (float)o.mz;
+          pr.chi = o.chi;
+          a.pieces[idx] = pr;
+        } else {
+          atomicOr(a.status, ST_TABLE_FULL);
+        }
+      }
+    }
+    __syncthreads();
+    const int i = S.site[tid];
+    if (i >= 0) {
+      if (S.np[tid]) atomicAdd(&a.cell_np[i], S.np[tid]);
+      if (S.chi[tid]) atomicAdd((unsigned long long*)&a.cell_chi[i], (unsigned long long)S.chi[tid]);
+      for (int d = 0; d < 4; ++d)
+        acc128((unsigned long long*)&a.cell_geo[8 * (size_t)i + 2 * d],
+               Fix128{S.lo[4 * tid + d], (long long)S.hi[4 * tid + d]});
+    }
+    __syncthreads();
+  }
+}
+
+// one element record
+__device__ __forceinline__ void emit_record(const ShapeArgs& a, int r, unsigned long long& rpvs) {
+  const ElemRec R = a.recs[r];
+  const int kind = R.z >> REC_SHIFT;
+  if (kind == REC_NONE) return;
+  const int low = R.z & ((1 << REC_SHIFT) - 1);
+  const int i = a.psite[R.p];
+  const PieceDesc d = a.pdesc[R.p];
+  const ShapeDesc& sd = a.shapes[d.shape];
+  const int sign = sd.sign;
+  const int t = (int)(sd.tet_off + d.t);  // batch-global tet id (node keys, piece records)
+  if (kind == REC_FACE) {
+    const int fs = ht_insert(a.F, ((unsigned long long)i << 32) | (unsigned)R.j, a.status);
+    if (fs >= 0) {
+      atomicAdd((unsigned long long*)&a.face_chi[fs], (unsigned long long)(sign * R.num));
+      atomicAdd(&a.face_np[fs], sign);
+      node_emit(a, sign, node_key(2, fs, t), low);
+    }
+    keep_term(a, 2, t, i, R.j, -1, -1, low, R.num);
+    return;
+  }
+  const int es = ht_insert(a.E, ((unsigned long long)i << 42) | ((unsigned long long)R.j << 21) | (unsigned)R.k, a.status);
+  if (kind == REC_EDGE) {
+    if (es >= 0) {
+      atomicAdd((unsigned long long*)&a.edge_chi[es], (unsigned long long)(sign * R.num));
+      atomicAdd(&a.edge_np[es], sign);
+      atomicAdd((unsigned long long*)&a.edge_len[es], (unsigned long long)(sign * fixed56(R.len)));
+      node_emit(a, sign, node_key(3, es, t), low);
+    }
+    keep_term(a, 3, t, i, R.j, R.k, -1, low, R.num);
+    return;
+  }
+  if (es >= 0) {
+    const int qs = ht_insert(a.Q, ((unsigned long long)es << 21) | (unsigned)low, a.status);
+    if (qs >= 0) atomicAdd(&a.rpv_cnt[qs], sign);
+  }
+  ++rpvs;
+  keep_term(a, 4, t, i, R.j, R.k, low, 0, 1);
+}
+
+// One launch for everything (blockIdx.y: cells, the chunks' records, the pool's records). Bound by the random accesses
+// of the table inserts, all of which are in flight at once over a grid that fills the chip.
+__global__ __launch_bounds__(EMIT_NT) void k_emit(ShapeArgs a) {
+  if (*a.status & ST_TABLE_FULL) return;  // some slots were never filled; the call is redone with larger buffers
+  if (blockIdx.y == 0) {
+    emit_cells(a);
+    return;
+  }
+  const int tid = threadIdx.x;
+  unsigned long long rpvs = 0;
+  if (blockIdx.y == 1) {
+    const int nchunks = (int)a.counters[C_CHUNKS];
+    const int per = EMIT_NT / 64;
+    for (int c = blockIdx.x * per + (tid >> 6); c < nchunks; c += gridDim.x * per) {
+      const int n = a.chunk_recs[c];
+      for (int q = tid & 63; q < n; q += 64) emit_record(a, c * REC_CHUNK + q, rpvs);
+    }
+  } else {
+    const int n = (int)min(a.counters[C_REC_POOL], (unsigned long long)a.pool_cap);
+    const int r0 = (a.pcap / CHUNK) * REC_CHUNK;
+    for (int q = blockIdx.x * EMIT_NT + tid; q < n; q += gridDim.x * EMIT_NT) emit_record(a, r0 + q, rpvs);
+  }
+  for (int off = 32; off > 0; off >>= 1) rpvs += __shfl_xor(rpvs, off);
+  if ((tid & 63) == 0 && rpvs) stat_add(a, C_RPV, rpvs);
+}
+
+// The counts are known on the device only: a grid of the workgroups that fit the chip, grid-stride.
+hipError_t launch_emit(const ShapeArgs& a, hipStream_t s) {
+  const int grid = std::max(1, std::min(a.pcap / (4 * CHUNK), 2048));
+  hipLaunchKernelGGL(k_emit, dim3(grid, 3), dim3(EMIT_NT), 0, s, a);
+  return hipGetLastError();
+}
+
+}  // namespace rpd

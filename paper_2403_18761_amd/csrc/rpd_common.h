@@ -10,7 +10,6 @@ namespace rpd {
 constexpr int TB = 64;       // tets per workgroup
 constexpr int KMAX = 28;     // candidate sites per tet kept for clipping (plane ids 4 + position must fit 5 bits)
 constexpr int KRAW = 40;     // candidate sites per tet before the dominance refinement
-constexpr int VMAX = 16;     // vertex slots of one piece (4-bit neighbour ids)
 constexpr int SLMAX = 256;   // sites in a workgroup's shared candidate list
 constexpr int SUB = 8;       // tets per chunk when a block's site list overflows
 // Work items are (shape + (tet mask << 16), block + (part << ITEM_PART_SHIFT)): part 0 is the whole block, part
@@ -23,7 +22,7 @@ constexpr int SPLIT_TETS = 16;       // = the width of the tet mask
 constexpr int SLOW_KMAX = 1020;  // candidate sites per tet
 constexpr int SLOW_VMAX = 64;    // vertex slots of one piece
 constexpr int SLOW_PMAX = 4 + SLOW_KMAX;
-// Fast-path pieces that outgrow VMAX vertex slots are redone in the same kernel with a global-memory polytope of
+// Fast-path pieces that outgrow their vertex slots are redone in the same kernel with a global-memory polytope of
 // BIG_VCAP slots (coordinates + bound in the kernel's precision, 64-bit topology words, a byte per plane for the
 // pairing table).
 constexpr int BIG_VCAP = 64;
@@ -38,20 +37,24 @@ constexpr int ST_INVALID = 16;       // invalid site value (off grid, out of ran
 
 // counters (ShapeArgs::counters)
 enum {
-  C_PAIRS = 0, C_CAND, C_FP64, C_EXACT, C_DEFER_ITEMS, C_GLUE, C_RPV, C_PIECES, C_NODES,
+  C_PAIRS = 0, C_CAND, C_FP64, C_EXACT, C_GLUE, C_RPV, C_PIECES, C_NODES,
   C_DEFER_BLOCK,  // tets deferred because their own candidates overflow the workgroup's site list
   C_DEFER_KMAX,   // tets deferred because they kept more than the candidate budget
-  C_DEFER_CLIP,   // pieces deferred because the polytope outgrew the vertex slots
+  C_DEFER_CLIP,   // pieces deferred because a predicate stayed undecided or the polytope outgrew 64 vertex slots
   C_SPLIT,        // workgroup blocks redone in chunks because their site list overflowed
-  C_DEFER2,       // items handed on by the LDS variant of the large-capacity kernel
   C_GLUE_BITS,    // gluing bits of the pieces whose components are (re)computed
   C_GLUE_PAIRS,   // glued pairs matched
   C_TERMS,        // per-piece element terms kept with RPD_KEEP_PIECES (cursor)
-  C_LISTS,        // candidate lists handed from the fast kernel to the large-capacity kernel (cursor)
-  C_BIG,          // pieces the fast kernel redid in a global-memory polytope after running out of slots (cursor;
-                  // follows C_LISTS: an incremental pass resets both together)
+  // the cursors of one clipping pass (an incremental pass resets the PASS_CURSORS of them together)
+  C_PIECE_SLOTS,  // piece slots handed out
+  C_CHUNKS,       // chunks of the piece kernel (the large-capacity kernel hands out slots after them)
+  C_REC_POOL,     // element records outside the chunks' own ranges
+  C_DEFER_ITEMS,  // items for the large-capacity kernel
+  C_DEFER2,       // items handed on by the LDS variant of the large-capacity kernel
+  C_BIG,          // pieces redone with a 64-slot polytope after running out of vertex slots
   NCOUNTERS
 };
+constexpr int PASS_CURSORS = NCOUNTERS - C_PIECE_SLOTS;
 // C_RPV counts RPV emissions; the RPV list itself is the set of keys of ShapeArgs::Q with a positive count
 
 // Statistics counters are spread over NSPREAD copies (picked by workgroup id) so that thousands of workgroups do
@@ -136,6 +139,48 @@ struct OutDesc {
   __device__ OutLayout layout() const { return out_layout(ns, nsh, n[0], n[1], n[2]); }
 };
 
+// A clipping pass works on pieces, one per (tet, candidate site): the candidate kernel hands every tet a run of
+// consecutive piece slots, one per candidate in sorted order. Each clipped piece leaves its cell terms (geometry, chi
+// numerator) in its slot and its face, edge and RPV terms as element records; the emission kernel turns both into sums.
+struct PieceDesc {
+  int t;      // tet, local to its shape
+  int shape;
+  int first;  // the tet's first piece slot: candidate c has slot first + c
+  int m;      // the tet's candidates (more than the clip budget: left to the large-capacity kernel)
+};
+struct PieceOut {
+  double vol, mx, my, mz;  // volume and first moment (absolute coordinates)
+  long long chi;           // fractional chi numerator of the cell term
+  int rec;                 // first of its element records: faces, then edges, then RPVs
+  unsigned word;           // piece_word()
+};
+// bit 0: the piece is nonempty; 7 bits each: faces, edges and RPVs among its records; 8 bits: gluing bits (interior
+// faces of the tet the piece touches) and, above them, boundary contact bits. A piece of at most 64 vertices has at
+// most 34 faces, 96 edges and 64 vertices.
+__host__ __device__ inline unsigned piece_word(int nface, int nedge, int nrpv, int glue) {
+  return 1u | ((unsigned)nface << 1) | ((unsigned)nedge << 8) | ((unsigned)nrpv << 15) | ((unsigned)glue << 22);
+}
+__host__ __device__ inline int pw_faces(unsigned w) { return (int)((w >> 1) & 127u); }
+__host__ __device__ inline int pw_edges(unsigned w) { return (int)((w >> 8) & 127u); }
+__host__ __device__ inline int pw_rpvs(unsigned w) { return (int)((w >> 15) & 127u); }
+__host__ __device__ inline int pw_glue(unsigned w) { return (int)((w >> 22) & 255u); }
+
+// The term of piece p (site i) in the element {i, j}, {i, j, k} or {i, j, k, l}, i smallest and j < k < l.
+struct ElemRec {
+  int j, k;       // k = -1: a face
+  int z;          // REC_* kind in the top bits; below: gluing bits (faces, edges) or l (RPVs)
+  int p;          // piece slot
+  long long num;  // fractional chi numerator (faces, edges)
+  double len;     // segment length (edges)
+};
+constexpr int REC_NONE = 0, REC_FACE = 1, REC_EDGE = 2, REC_RPV = 3, REC_SHIFT = 24;
+
+// Pieces are clipped 64 consecutive slots (a chunk) per wavefront. A chunk's records go to its own range of REC_CHUNK
+// records when they fit (no cursor shared between wavefronts), else, like those of every piece computed outside its
+// chunk's pass, to the pool behind the chunks' ranges.
+constexpr int CHUNK = 64;
+constexpr int REC_CHUNK = 128;
+
 // per-piece record kept with RPD_KEEP_PIECES
 struct PieceRec {
   int t;  // internal tet id
@@ -202,13 +247,17 @@ struct ShapeArgs {
   unsigned short* removed;  // [2 cap N] with touch flags: per element-piece slot, 0x100 | the gluing bits with which
                             // an incremental update took the piece out (even entry) and put it back (odd entry)
   double* tet_U;         // optional [total tets]: U_t of the candidate test, kept for the incremental update
-  int4* deferred;        // (shape, local tet, global site or -1 for every candidate, list) for the large-capacity
-                         // path; list = 64 x (index in deferred_list) + m when the fast kernel hands over the tet's
-                         // m sorted candidates, else 0 (the large-capacity kernel then finds them itself)
+  PieceDesc* pdesc;      // [pcap] the pass's pieces
+  int* psite;            // [pcap] their sites (batch-global)
+  PieceOut* pout;        // [pcap]
+  int pcap;              // a whole number of chunks
+  ElemRec* recs;         // [pcap / CHUNK ranges of REC_CHUNK, then the pool]
+  int* chunk_recs;       // [pcap / CHUNK] records in the chunk's own range
+  int pool_cap;          // records of the pool
+  int4* deferred;        // items of the large-capacity path: (shape, local tet, piece slot or -1 for all of the tet's
+                         // candidates, the tet's first piece slot or -1 when its candidates are yet to be found)
   int deferred_cap;
-  int* deferred_list;    // [list_cap][KRAW] batch-global site ids
-  int list_cap;
-  unsigned char* big;    // [big_cap][BIG_BYTES] global-memory polytopes of the fast kernel's overflowing pieces
+  unsigned char* big;    // [big_cap][BIG_BYTES] global-memory polytopes of pieces that ran out of vertex slots
   int big_cap;
   int4* deferred2;       // items the LDS variant of the large-capacity path hands to its global variant
   int deferred2_cap;
@@ -221,7 +270,7 @@ struct ShapeArgs {
   int* status;
   unsigned flags;        // RPD_FORCE_* / RPD_KEEP_PIECES as in rpd.h
   int kmax;              // fast-path candidate budget (<= KMAX)
-  unsigned* item_cost;   // optional [nitems]: wall-clock ticks each work item took in the fast kernel
+  unsigned* item_cost;   // optional [nitems]: wall-clock ticks each work item took in the candidate kernel
 };
 
 // shape of a batch-global id by binary search over the shapes' offsets

@@ -420,7 +420,7 @@ struct Store {
   static constexpr size_t coord_bytes(int nthreads) { return sizeof(typename Coord4<T>::type) * VCAP * nthreads; }
 };
 
-// The FP32 polytopes of the fast kernel in 16 bytes per vertex: x and y as a pair and z in separate [slot][lane]
+// The FP32 polytopes of the piece kernel in 16 bytes per vertex: x and y as a pair and z in separate [slot][lane]
 // planes, the topology word, and in its five free bits the vertex's error bound F rounded up to a power of two
 // between 2^-40 and 2^-10 (code 31: infinite, every test on the vertex goes to FP64). Rounding F up only makes the
 // FP32 filter more cautious, so every sign it certifies is still right.
@@ -472,6 +472,8 @@ struct StoreOf<float, Topo32, VCAP> {  // Topo32 leaves bits 27..31 free
 
 __device__ inline int ctz_mask(unsigned m) { return __builtin_ctz(m); }
 __device__ inline int ctz_mask(unsigned long long m) { return __builtin_ctzll(m); }
+__device__ inline int popc_mask(unsigned m) { return __builtin_popcount(m); }
+__device__ inline int popc_mask(unsigned long long m) { return __builtin_popcountll(m); }
 
 // ---------------------------------------------------------------------------------------------------------------
 // Environment of one tet: planes by id (0..3 faces, 4+c the bisector against candidate c), site ids, weights.
@@ -480,19 +482,16 @@ struct TetEnv {
   const float4* tv;      // 4 vertices (absolute)
   float4 o;              // vertex 0: the origin of the tet-local frame
   const double4* face64;  // the tet's 4 face planes in FP64 (normal exact, offset rounded once)
-  const float4* sites;   // candidate site data, indexed through cidx
-  const int* sid;        // site ids, indexed through cidx
-  const unsigned char* cidx8;  // candidate -> index into sites/sid (fast path)
-  const int* cidx32;     // candidate -> index (slow path)
-  const float4* csite;   // the first ncs candidates' sites by candidate position (slow path: on chip), or nullptr
+  const int* sid;        // candidate -> site id
+  const float4* csite;   // candidate -> site, the first ncs of them
+  const float4* site;    // site id -> site, for the candidates past ncs
   int ncs;
   int ci;                // candidate position of the piece's own site
   float4 si;             // own site
   int site_i;            // own site id
 
-  __device__ int cand_index(int c) const { return cidx8 ? (int)cidx8[c] : cidx32[c]; }
-  __device__ float4 cand_site(int c) const { return c < ncs ? csite[c] : sites[cand_index(c)]; }
-  __device__ int cand_id(int c) const { return sid ? sid[cand_index(c)] : cand_index(c); }
+  __device__ float4 cand_site(int c) const { return c < ncs ? csite[c] : site[sid[c]]; }
+  __device__ int cand_id(int c) const { return sid[c]; }
   __device__ int plane_site(int p) const { return p < 4 ? -1 : cand_id(p - 4); }
 
   __device__ Plane<double> plane64(int p) const {
@@ -511,7 +510,7 @@ struct TetEnv {
 };
 
 // FP32 planes are rounded from the FP64 ones on every use (face planes included: the FP64 face planes are read
-// through the caches, which keeps the per-workgroup LDS of the fast kernel to its polytopes)
+// through the caches, which keeps the LDS of the piece kernel to its polytopes)
 template <>
 __device__ inline Plane<float> TetEnv::planeT<float>(int p) const {
   return round_plane<float>(plane64(p));
@@ -525,19 +524,28 @@ __device__ inline Plane<double> TetEnv::planeT<double>(int p) const {
 // (faces f are opposite vertex f; local edges (0,1),(0,2),(0,3),(1,2),(1,3),(2,3) -> 0..5):
 // no face: tet interior (L); one face f: that face; two faces: the edge joining the two vertices neither face
 // excludes; three faces: their common vertex
-__device__ inline int pair_index(int a, int b) {  // a < b
-  return a == 0 ? b - 1 : (a == 1 ? b + 1 : 5);
+// The entry of a tet's 14 numerators that a face mask selects (14: L), one nibble per mask: vertices 0-3, then the
+// edges (0,1) (0,2) (0,3) (1,2) (1,3) (2,3), then the faces.
+constexpr unsigned weight_entry(unsigned fm) {
+  const int nf = (int)((fm & 1) + ((fm >> 1) & 1) + ((fm >> 2) & 1) + ((fm >> 3) & 1));
+  const int b[4] = {(int)(fm & 1), (int)((fm >> 1) & 1), (int)((fm >> 2) & 1), (int)((fm >> 3) & 1)};
+  if (nf == 1) return 10u + (b[0] ? 0u : b[1] ? 1u : b[2] ? 2u : 3u);
+  if (nf == 3) return !b[0] ? 0u : !b[1] ? 1u : !b[2] ? 2u : 3u;
+  if (nf == 2) {  // the edge of the two vertices neither face excludes
+    const int u = !b[0] ? 0 : !b[1] ? 1 : 2, v = !b[3] ? 3 : !b[2] ? 2 : 1;
+    return 4u + (unsigned)(u == 0 ? v - 1 : u == 1 ? v + 1 : 5);
+  }
+  return 14u;
+}
+constexpr unsigned long long weight_entries() {
+  unsigned long long t = 0;
+  for (unsigned fm = 0; fm < 16; ++fm) t |= (unsigned long long)weight_entry(fm) << (4 * fm);
+  return t;
 }
 __device__ inline long long w_mask(unsigned fm, const unsigned* nu, long long L) {
-  const int nf = __builtin_popcount(fm);
-  if (nf == 0) return L;
-  if (nf == 1) return nu[10 + __builtin_ctz(fm)];
-  const unsigned rest = ~fm & 15u;
-  if (nf == 2) {
-    int a = __builtin_ctz(rest), b = 31 - __builtin_clz(rest);
-    return nu[4 + pair_index(a, b)];
-  }
-  return nu[__builtin_ctz(rest)];
+  constexpr unsigned long long T = weight_entries();
+  const unsigned e = (unsigned)(T >> (4 * fm)) & 15u;
+  return e == 14u ? L : (long long)nu[e];
 }
 __device__ inline unsigned face_bit(int p) { return p < 4 ? (1u << p) : 0u; }
 __device__ inline long long w_vertex(int p0, int p1, int p2, const unsigned* nu, long long L) {
@@ -652,6 +660,11 @@ enum { CLIP_OK = 0, CLIP_EMPTY = 1, CLIP_DEFER = 2, CLIP_FULL = 3 };  // DEFER: 
 template <typename T, typename Topo, typename Mask, int VCAP, bool EXACT, typename Tab>
 struct Clipper {
   typedef typename Topo::W W;
+  typedef T Real;
+  typedef Topo TopoT;
+  typedef Mask MaskT;
+  static constexpr int SLOTS = VCAP;
+  static constexpr bool FEW_PLANES = sizeof(W) == 4;  // Topo32: plane ids below 32
   typename StoreOf<T, Topo, VCAP>::type st;
   Tab tab;  // per plane id: 0 or (slot + 1); all zero between operations
   Mask live;
@@ -730,35 +743,44 @@ struct Clipper {
       return CLIP_EMPTY;
     }
     const Mask full = (VCAP >= 8 * (int)sizeof(Mask)) ? ~(Mask)0 : ((bit(VCAP)) - 1);
-    Mask kept = live & ~out;
+    const Mask kept = live & ~out;
     Mask freem = ~kept & full;
-    Mask added = 0;
+    // the edges from a kept to a cut-off vertex, one mask per position e in the kept vertex's word: every lane then
+    // builds its next new vertex in the same trip of the loop below (the construction is the expensive part, and
+    // the lanes' crossings sit at different vertices)
+    Mask cross[3] = {0, 0, 0};
+    int ncross = 0;
     for (Mask m = kept; m; m &= m - 1) {
-      int k = ctz_mask(m);
-      W w = st.topo(k);
-      bool changed = false;
-      for (int e = 0; e < 3; ++e) {
-        int nb = Topo::nb(w, e);
-        if (!(out & bit(nb))) continue;
-        if (!freem) {  // out of vertex slots: clear the half-done pairing state and give the piece up
-          tab.clear(np);
-          return CLIP_FULL;
+      const int k = ctz_mask(m);
+      const W w = st.topo(k);
+      for (int e = 0; e < 3; ++e)
+        if (out & bit(Topo::nb(w, e))) {
+          cross[e] |= bit(k);
+          ++ncross;
         }
-        int s = ctz_mask(freem);
-        freem &= freem - 1;
-        int pa = Topo::plane(w, (e + 1) % 3), pb = Topo::plane(w, (e + 2) % 3);
-        T x, y, z, F;
-        make_vertex(env.planeT<T>(pa), env.planeT<T>(pb), P, x, y, z, F);
-        W nw = st.with_F(Topo::make(pa, pb, q, 0, 0, k), F);
-        st.put(s, x, y, z, F);
-        pair_up(pa, s, nw, 1);  // edge (pa, q) is opposite pb (position 1)
-        pair_up(pb, s, nw, 0);  // edge (pb, q) is opposite pa (position 0)
-        st.set_topo(s, nw);
-        w = Topo::set_nb(w, e, s);
-        changed = true;
-        added |= bit(s);
-      }
-      if (changed) st.set_topo(k, w);
+    }
+    if (ncross > popc_mask(freem)) return CLIP_FULL;  // out of vertex slots
+    Mask added = 0;
+    while (cross[0] | cross[1] | cross[2]) {  // by kept vertex, then position
+      const int k = ctz_mask(cross[0] | cross[1] | cross[2]);
+      const Mask b = bit(k);
+      const int e = (cross[0] & b) ? 0 : (cross[1] & b) ? 1 : 2;
+      if (e == 0) cross[0] &= ~b;
+      else if (e == 1) cross[1] &= ~b;
+      else cross[2] &= ~b;
+      const int s = ctz_mask(freem);
+      freem &= freem - 1;
+      const W w = st.topo(k);
+      const int pa = Topo::plane(w, e == 2 ? 0 : e + 1), pb = Topo::plane(w, e == 0 ? 2 : e - 1);
+      T x, y, z, F;
+      make_vertex(env.planeT<T>(pa), env.planeT<T>(pb), P, x, y, z, F);
+      W nw = st.with_F(Topo::make(pa, pb, q, 0, 0, k), F);
+      st.put(s, x, y, z, F);
+      pair_up(pa, s, nw, 1);  // edge (pa, q) is opposite pb (position 1)
+      pair_up(pb, s, nw, 0);  // edge (pb, q) is opposite pa (position 0)
+      st.set_topo(s, nw);
+      st.set_topo(k, Topo::set_nb(w, e, s));
+      added |= bit(s);
     }
     live = kept | added;
     return CLIP_OK;

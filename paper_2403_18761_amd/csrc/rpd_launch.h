@@ -8,10 +8,14 @@
 namespace rpd {
 
 // clip.hip
-hipError_t launch_clip_fast(const ShapeArgs& a, int precision, int block, int slots, hipStream_t s);
+hipError_t launch_candidates(const ShapeArgs& a, hipStream_t s);
+hipError_t launch_clip_pieces(const ShapeArgs& a, int precision, int slots, hipStream_t s);
 size_t slow_scratch_bytes(int waves);
 // the item count is read on the device from counters[C_DEFER_ITEMS] (no host synchronisation)
 hipError_t launch_clip_slow(const ShapeArgs& a, unsigned char* scratch, int waves, hipStream_t s);
+
+// emit.hip: the sums and element pieces of a pass's pieces
+hipError_t launch_emit(const ShapeArgs& a, hipStream_t s);
 
 // reduce.hip
 hipError_t launch_fill_u64(unsigned long long* p, unsigned long long v, size_t n, hipStream_t s);
