@@ -166,7 +166,7 @@ struct DeviceState {
   int def_cap = 0, piece_cap = 0, term_cap = 0, pcap = 0, pool_cap = 0, big_cap = 0;
   DBuf site, status, cell_chi, cell_geo, cell_np, cell_b0;
   DBuf fkeys, face_chi, face_np, face_b0, ekeys, edge_chi, edge_np, edge_len, edge_b0, qkeys, rpv_cnt;
-  DBuf pdesc, psite, pout, recs, chunk_recs;
+  DBuf pdesc, psite, pout, pref, recs, chunk_recs, tet_slots, pparent, rparent;
   DBuf nodes, glist, gseg, clist, cseg, bigp, deferred, deferred2, pieces, terms, counters, tetU, slow, touch, removed;
   int waves = 0;
 
@@ -186,10 +186,6 @@ struct DeviceState {
     capF = pow2_cap((32 * (size_t)ns + 1024) * scale);
     capE = pow2_cap((32 * (size_t)ns + 1024) * scale);
     capQ = pow2_cap((16 * (size_t)ns + 1024) * scale);
-    // element pieces: 12 slots per tet keeps the probe chains of the emission's inserts short; past 2^23 slots
-    // the table scans of the gluing pass cost more than that saves, so large meshes get 6
-    capN = pow2_cap((12 * (size_t)nt + 4096) * scale);
-    if (capN > (1u << 23)) capN = std::max(1u << 23, pow2_cap((6 * (size_t)nt + 4096) * scale));
     def_cap = (int)std::min<size_t>((4 * (size_t)nt + 4096) * scale, 1u << 30);
     piece_cap = keep_pieces ? (int)std::min<size_t>((8 * (size_t)nt + 1024) * scale, 1u << 30) : 0;
     term_cap = keep_pieces ? (int)std::min<size_t>((24 * (size_t)nt + 4096) * scale, 1u << 30) : 0;
@@ -210,9 +206,6 @@ struct DeviceState {
     edge_b0.alloc(4 * (size_t)capE);
     qkeys.alloc(8 * (size_t)capQ);
     rpv_cnt.alloc(4 * (size_t)capQ);
-    nodes.alloc(sizeof(NodeRec) * (size_t)capN);
-    glist.alloc(sizeof(int) * (size_t)capN);
-    gseg.alloc(sizeof(int) * (size_t)capN / 256);  // the gluing list's segments
     deferred.alloc(16 * (size_t)def_cap);
     deferred2.alloc(16 * (size_t)(def_cap / 4 + 1024));
     // Piece slots and records of one clipping pass. A tet has about 1 + 4 r^(1/3) candidates at r sites per tet
@@ -221,14 +214,21 @@ struct DeviceState {
     {
       const double r = nt > 0 ? (double)ns / (double)nt : 0.0;
       const double per = (4.0 + 12.0 * std::cbrt(r * r)) * scale;
-      const double n = std::min((double)nt * per + 16384.0 * scale, 1.0e9);
+      const double n = std::min((double)nt * per + 16384.0 * scale, 8.0e8);
       pcap = (int)((size_t)n / CHUNK) * CHUNK;
       pool_cap = pcap / 2;
       pdesc.alloc(sizeof(PieceDesc) * (size_t)pcap);
       psite.alloc(sizeof(int) * (size_t)pcap);
       pout.alloc(sizeof(PieceOut) * (size_t)pcap);
       chunk_recs.alloc(sizeof(int) * (size_t)(pcap / CHUNK));
-      recs.alloc(sizeof(ElemRec) * ((size_t)(pcap / CHUNK) * REC_CHUNK + (size_t)pool_cap));
+      const size_t nrec = (size_t)(pcap / CHUNK) * REC_CHUNK + (size_t)pool_cap;
+      recs.alloc(sizeof(ElemRec) * nrec);
+      pref.alloc(sizeof(PieceRef) * (size_t)pcap);
+      if (!keep_U) {
+        tet_slots.alloc(sizeof(int2) * (size_t)std::max<long long>(nt, 1));
+        pparent.alloc(sizeof(int) * (size_t)pcap);
+        rparent.alloc(sizeof(int) * nrec);
+      }
     }
     // pieces over the fast kernel's vertex slots: about 1 in 10^4 on the benchmark shapes with 16 slots, up to 1 in
     // 10^2 with 12; an incremental session gets room for four times as many per pass as a build (its pool must
@@ -240,6 +240,13 @@ struct DeviceState {
     terms.alloc(sizeof(TermRec) * (size_t)std::max(term_cap, 1));
     counters.alloc(8 * (NCOUNTERS + 8 + (size_t)NSPREAD * NCOUNTERS));
     if (keep_U) {  // incremental updates: U_t per tet, the touched-element flags, the removed-piece tags
+      // element pieces: 12 slots per tet keeps the probe chains of the emission's inserts short; past 2^23 slots
+      // the table scans of the gluing pass cost more than that saves, so large meshes get 6
+      capN = pow2_cap((12 * (size_t)nt + 4096) * scale);
+      if (capN > (1u << 23)) capN = std::max(1u << 23, pow2_cap((6 * (size_t)nt + 4096) * scale));
+      nodes.alloc(sizeof(NodeRec) * (size_t)capN);
+      glist.alloc(sizeof(int) * (size_t)capN);
+      gseg.alloc(sizeof(int) * (size_t)capN / 256);  // the gluing list's segments
       tetU.alloc(8 * (size_t)std::max<long long>(nt, 1));
       touch.alloc(touch_words() * 4);
       removed.alloc(4 * (size_t)capN);
@@ -266,7 +273,12 @@ struct DeviceState {
     L.add(edge_len.p, 0, capE, 8);
     L.add(qkeys.p, EMPTY_KEY, capQ, 8);
     L.add(rpv_cnt.p, 0, capQ, 4);
-    L.add(nodes.p, EMPTY_KEY, capN, 16, 0ull);  // key EMPTY, state 0, parent 0
+    if (nodes.p) L.add(nodes.p, EMPTY_KEY, capN, 16, 0ull);  // key EMPTY, state 0, parent 0
+    if (tet_slots.p) {  // builds count components once
+      L.add(cell_b0.p, 0, ns, 4);
+      L.add(face_b0.p, 0, capF, 4);
+      L.add(edge_b0.p, 0, capE, 4);
+    }
     L.add(cnt(), 0, NCOUNTERS + 8 + (size_t)NSPREAD * NCOUNTERS, 8);
     if (touch.p) L.add(touch.p, 0, touch_words(), 4);
     if (removed.p) L.add(removed.p, 0, capN, 4);
@@ -303,7 +315,11 @@ struct DeviceState {
     a.edge_len = edge_len.as<long long>();
     a.Q = HashTab{qkeys.as<unsigned long long>(), capQ - 1};
     a.rpv_cnt = rpv_cnt.as<int>();
-    a.N = NodeTab{nodes.as<NodeRec>(), capN - 1};
+    a.N = NodeTab{nodes.as<NodeRec>(), nodes.p ? capN - 1 : 0};
+    a.pref = pref.as<PieceRef>();
+    a.tet_slots = tet_slots.p ? tet_slots.as<int2>() : nullptr;
+    a.pparent = pparent.as<int>();
+    a.rparent = rparent.as<int>();
     a.tet_U = tetU.p ? tetU.as<double>() : nullptr;
     a.deferred = deferred.as<int4>();
     a.deferred_cap = def_cap;
@@ -330,7 +346,12 @@ struct DeviceState {
     return a;
   }
 
-  // components of every live element piece: fresh union-find and root counts
+  // components of a build's elements (their counts were zeroed with the tables)
+  void build_components(const ShapeArgs& a, hipStream_t s) {
+    hip_check(launch_glue_pieces(a, cell_b0.as<int>(), face_b0.as<int>(), edge_b0.as<int>(), s), "glue");
+  }
+
+  // a session's components of every live element piece: fresh union-find and root counts
   // (with a.touch_* set: of the touched elements only, then the flags are cleared)
   void components(const ShapeArgs& a, hipStream_t s) {
     if (a.touch_cell) {
@@ -913,7 +934,7 @@ static bool run_batch(const rpd_mesh* const* meshes, const rpd_sites* sites, int
   hip_check(launch_clip_slow(a, D.slow.as<unsigned char>(), D.waves, s), "deferred clip kernel");
   tm.mark(2, s);
   hip_check(launch_emit(a, s), "emission");
-  D.components(a, s);
+  D.build_components(a, s);
   if (!collect(D, hd, dshapes_p, meshes, s, tm, outs, st)) return false;
   learn_costs(items, (const unsigned*)ticks_host.p, hd, meshes);
   st.n_items = (int64_t)items.size();

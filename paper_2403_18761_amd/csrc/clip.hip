@@ -260,9 +260,11 @@ __device__ __forceinline__ void emit_out(CL& c, const ShapeDesc& sd, int tl, Emi
   out.my = (double)my * 0.25 + out.vol * o.y;
   out.mz = (double)mz * 0.25 + out.vol * o.z;
   out.chi = e.sv - e.se + sf - L;
-  out.rec = base;
-  out.word = piece_word(e.nface, e.nedge, e.nrpv, cell_glue);
   a.pout[p_slot] = out;
+  PieceRef ref;
+  ref.rec = base;
+  ref.word = piece_word(e.nface, e.nedge, e.nrpv, cell_glue);
+  a.pref[p_slot] = ref;
 }
 
 // Room for n records in the pool, from the calling lane: the first, or -1 when the pool is full.
@@ -779,6 +781,7 @@ __global__ __launch_bounds__(64) void k_candidates(ShapeArgs a) {
       d.first = base + first;
       d.m = m;
       a.pdesc[base + p] = d;
+      if (p == first && a.tet_slots) a.tet_slots[sd.tet_off + t0 + lt] = make_int2(base + first, m);
       if (m > a.kmax) {
         if (p == first) defer_item(a, shape, t0 + lt, -1, base + first);
       } else {
@@ -874,7 +877,7 @@ __global__ __launch_bounds__(64) void k_clip_pieces(ShapeArgs a) {
         n_pairs += sd.sign;  // live pieces
         emit_scan(cl, sd.nu + 14 * (size_t)d.t, sd.L, e);
       } else {
-        a.pout[p].word = 0;
+        a.pref[p].word = 0;
         if (r == CLIP_DEFER) {
           stat_add(a, C_DEFER_CLIP, 1ull);
           defer_item(a, d.shape, d.t, p, d.first);
@@ -1185,6 +1188,7 @@ __global__ __launch_bounds__(64, LDS ? 1 : 2) void k_clip_slow(ShapeArgs a, unsi
       }
       first = __builtin_amdgcn_readfirstlane(q);
       if (first < 0) continue;
+      if (lane == 0 && a.tet_slots) a.tet_slots[sd.tet_off + t] = make_int2(first, m);
       for (int x = lane; x < m; x += 64) {
         PieceDesc d;
         d.t = t;
@@ -1193,7 +1197,7 @@ __global__ __launch_bounds__(64, LDS ? 1 : 2) void k_clip_slow(ShapeArgs a, unsi
         d.m = m;
         a.pdesc[first + x] = d;
         a.psite[first + x] = scand[x];
-        a.pout[first + x].word = 0;
+        a.pref[first + x].word = 0;
       }
     }
     if (lane < CL)
@@ -1221,7 +1225,7 @@ __global__ __launch_bounds__(64, LDS ? 1 : 2) void k_clip_slow(ShapeArgs a, unsi
       cl.env.ci = ci;
       cl.env.si = a.site[scand[ci]];
       cl.env.site_i = scand[ci];
-      a.pout[first + ci].word = 0;
+      a.pref[first + ci].word = 0;
       int r = clip_piece(cl, m);
       n64 += cl.n64;
       nex += cl.nex;

@@ -14,7 +14,9 @@ namespace rpd {
 // The two happen in one launch, in either order. Each records the piece's gluing bits in its own half of the
 // piece's tag pair; a scan after the launch flags the element for a new union-find only where the two differ (a
 // piece put back with the same gluing bits leaves the element's forest as it was).
+template <bool HASH>
 __device__ inline void node_emit(const ShapeArgs& a, int sign, unsigned long long key, int glue) {
+  if (!HASH) return;
   int ns = node_insert(a.N, key, a.status);
   if (ns < 0) return;
   atomicAdd(&a.N.rec[ns].st, sign * (NODE_UNIT + glue));  // removal re-emits the same bits, so this is exact
@@ -93,6 +95,7 @@ __device__ inline int cell_slot(CellSums& S, int site) {
   return -1;
 }
 
+template <bool HASH>
 __device__ __forceinline__ void emit_cells(const ShapeArgs& a) {
   static_assert(CELL_SLOTS == 256 && EMIT_NT == CELL_SLOTS, "one slot per thread; the hash takes the top 8 bits");
   __shared__ CellSums S;
@@ -111,11 +114,12 @@ __device__ __forceinline__ void emit_cells(const ShapeArgs& a) {
     for (int q = 0; q < EMIT_PIECES / EMIT_NT; ++q) {
       const int p = base + q * EMIT_NT + tid;
       if (p >= np_all) break;
+      const unsigned word = a.pref[p].word;
+      if (!(word & 1u)) continue;
       const PieceOut o = a.pout[p];
-      if (!(o.word & 1u)) continue;
       const PieceDesc d = a.pdesc[p];
       const ShapeDesc& sd = a.shapes[d.shape];
-      const int i = a.psite[p], sign = sd.sign, glue = pw_glue(o.word);
+      const int i = a.psite[p], sign = sd.sign, glue = pw_glue(word);
       const int t = (int)(sd.tet_off + d.t);
       const double v[4] = {o.vol, o.mx, o.my, o.mz};
       const int s = cell_slot(S, i);
@@ -134,7 +138,9 @@ __device__ __forceinline__ void emit_cells(const ShapeArgs& a) {
         for (int k = 0; k < 4; ++k)
           acc128((unsigned long long*)&a.cell_geo[8 * (size_t)i + 2 * k], signed128(fixed80(v[k]), sign));
       }
-      node_emit(a, sign, node_key(1, i, t), glue);
+      if (!HASH) a.pparent[p] = p;
+      node_emit<HASH>(a, sign, node_key(1, i, t), glue);
+      ++nodes;
       keep_term(a, 1, t, i, -1, -1, -1, glue, o.chi);
       if (a.flags & RPD_KEEP_PIECES) {
         const unsigned long long idx = atomicAdd(&a.counters[C_PIECES], 1ull);
@@ -164,10 +170,15 @@ __device__ __forceinline__ void emit_cells(const ShapeArgs& a) {
     }
     __syncthreads();
   }
+  if (HASH) return;
+  for (int off = 32; off > 0; off >>= 1) nodes += __shfl_xor(nodes, off);
+  if ((tid & 63) == 0 && nodes) stat_add(a, C_NODES, nodes);
 }
 
 // one element record
-__device__ __forceinline__ void emit_record(const ShapeArgs& a, int r, unsigned long long& rpvs) {
+template <bool HASH>
+__device__ __forceinline__ void emit_record(const ShapeArgs& a, int r, unsigned long long& nodes,
+                                            unsigned long long& rpvs) {
   const ElemRec R = a.recs[r];
   const int kind = R.z >> REC_SHIFT;
   if (kind == REC_NONE) return;
@@ -182,8 +193,13 @@ __device__ __forceinline__ void emit_record(const ShapeArgs& a, int r, unsigned 
     if (fs >= 0) {
       atomicAdd((unsigned long long*)&a.face_chi[fs], (unsigned long long)(sign * R.num));
       atomicAdd(&a.face_np[fs], sign);
-      node_emit(a, sign, node_key(2, fs, t), low);
+      node_emit<HASH>(a, sign, node_key(2, fs, t), low);
+      if (!HASH) {
+        a.recs[r].num = fs;
+        a.rparent[r] = r;
+      }
     }
+    ++nodes;
     keep_term(a, 2, t, i, R.j, -1, -1, low, R.num);
     return;
   }
@@ -193,8 +209,13 @@ __device__ __forceinline__ void emit_record(const ShapeArgs& a, int r, unsigned 
       atomicAdd((unsigned long long*)&a.edge_chi[es], (unsigned long long)(sign * R.num));
       atomicAdd(&a.edge_np[es], sign);
       atomicAdd((unsigned long long*)&a.edge_len[es], (unsigned long long)(sign * fixed56(R.len)));
-      node_emit(a, sign, node_key(3, es, t), low);
+      node_emit<HASH>(a, sign, node_key(3, es, t), low);
+      if (!HASH) {
+        a.recs[r].num = es;
+        a.rparent[r] = r;
+      }
     }
+    ++nodes;
     keep_term(a, 3, t, i, R.j, R.k, -1, low, R.num);
     return;
   }
@@ -206,36 +227,182 @@ __device__ __forceinline__ void emit_record(const ShapeArgs& a, int r, unsigned 
   keep_term(a, 4, t, i, R.j, R.k, low, 0, 1);
 }
 
-// One launch for everything (blockIdx.y: cells, the chunks' records, the pool's records). Bound by the random accesses
-// of the table inserts, all of which are in flight at once over a grid that fills the chip.
-__global__ __launch_bounds__(EMIT_NT) void k_emit(ShapeArgs a) {
-  if (*a.status & ST_TABLE_FULL) return;  // some slots were never filled; the call is redone with larger buffers
-  if (blockIdx.y == 0) {
-    emit_cells(a);
-    return;
-  }
+// The records of a pass: f(r) for every one, the chunks' ranges in blockIdx.y 1 and the pool in blockIdx.y 2 of a launch
+// of EMIT_NT threads per workgroup.
+template <typename F>
+__device__ __forceinline__ void for_records(const ShapeArgs& a, F f) {
   const int tid = threadIdx.x;
-  unsigned long long rpvs = 0;
   if (blockIdx.y == 1) {
     const int nchunks = (int)a.counters[C_CHUNKS];
     const int per = EMIT_NT / 64;
     for (int c = blockIdx.x * per + (tid >> 6); c < nchunks; c += gridDim.x * per) {
       const int n = a.chunk_recs[c];
-      for (int q = tid & 63; q < n; q += 64) emit_record(a, c * REC_CHUNK + q, rpvs);
+      for (int q = tid & 63; q < n; q += 64) f(c * REC_CHUNK + q);
     }
   } else {
     const int n = (int)min(a.counters[C_REC_POOL], (unsigned long long)a.pool_cap);
     const int r0 = (a.pcap / CHUNK) * REC_CHUNK;
-    for (int q = blockIdx.x * EMIT_NT + tid; q < n; q += gridDim.x * EMIT_NT) emit_record(a, r0 + q, rpvs);
+    for (int q = blockIdx.x * EMIT_NT + tid; q < n; q += gridDim.x * EMIT_NT) f(r0 + q);
   }
-  for (int off = 32; off > 0; off >>= 1) rpvs += __shfl_xor(rpvs, off);
-  if ((tid & 63) == 0 && rpvs) stat_add(a, C_RPV, rpvs);
+}
+
+// One launch for everything (blockIdx.y: cells, the chunks' records, the pool's records). Bound by the random accesses
+// of the table inserts, all of which are in flight at once over a grid that fills the chip. HASH (sessions): every
+// element piece goes into the table N as well.
+template <bool HASH>
+__global__ __launch_bounds__(EMIT_NT) void k_emit(ShapeArgs a) {
+  if (*a.status & ST_TABLE_FULL) return;  // some slots were never filled; the call is redone with larger buffers
+  if (blockIdx.y == 0) {
+    emit_cells<HASH>(a);
+    return;
+  }
+  unsigned long long nodes = 0, rpvs = 0;
+  for_records(a, [&](int r) { emit_record<HASH>(a, r, nodes, rpvs); });
+  for (int off = 32; off > 0; off >>= 1) {
+    rpvs += __shfl_xor(rpvs, off);
+    nodes += __shfl_xor(nodes, off);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    if (rpvs) stat_add(a, C_RPV, rpvs);
+    if (!HASH && nodes) stat_add(a, C_NODES, nodes);
+  }
 }
 
 // The counts are known on the device only: a grid of the workgroups that fit the chip, grid-stride.
+static int pass_grid(const ShapeArgs& a) { return std::max(1, std::min(a.pcap / (4 * CHUNK), 2048)); }
+
 hipError_t launch_emit(const ShapeArgs& a, hipStream_t s) {
-  const int grid = std::max(1, std::min(a.pcap / (4 * CHUNK), 2048));
-  hipLaunchKernelGGL(k_emit, dim3(grid, 3), dim3(EMIT_NT), 0, s, a);
+  if (a.tet_slots) hipLaunchKernelGGL(k_emit<false>, dim3(pass_grid(a), 3), dim3(EMIT_NT), 0, s, a);
+  else hipLaunchKernelGGL(k_emit<true>, dim3(pass_grid(a), 3), dim3(EMIT_NT), 0, s, a);
+  return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------------------------------------------
+// components of a build's elements (Sec. 4.1.1): union-find over the pieces and records themselves
+// ---------------------------------------------------------------------------------------------------------------
+__device__ inline int uf_find(int* parent, int x) {
+  while (true) {
+    const int p = parent[x];
+    if (p == x) return x;
+    const int gp = parent[p];
+    if (gp != p) parent[x] = gp;
+    x = p;
+  }
+}
+// hook the larger root under the smaller with CAS; path halving
+__device__ inline void uf_union(int* parent, int a, int b) {
+  while (true) {
+    a = uf_find(parent, a);
+    b = uf_find(parent, b);
+    if (a == b) return;
+    if (a < b) {
+      const int t = a;
+      a = b;
+      b = t;
+    }
+    if (atomicCAS(&parent[a], a, b) == a) return;
+  }
+}
+
+// For the gluing bits g of an element piece of site i in tet t: f(q, m) for the nonempty piece q of the same site in
+// every face-adjacent tet of higher number across a face in g, m its gluing bit for that face. A bit whose neighbour
+// has no such piece breaks an invariant. (Each glued pair is met once, from its lower tet; that the other side agrees
+// is checked there, and that no bit is left over by counting.)
+template <typename F>
+__device__ __forceinline__ void for_glued(const ShapeArgs& a, const PieceDesc& d, int i, int g, F f) {
+  const ShapeDesc& sd = a.shapes[d.shape];
+  const int4 nb = reinterpret_cast<const int4*>(sd.tn)[d.t];
+  for (; g; g &= g - 1) {
+    const int face = __builtin_ctz(g);
+    const int t2 = face == 0 ? nb.x : face == 1 ? nb.y : face == 2 ? nb.z : nb.w;
+    if (t2 < d.t) continue;  // the boundary never carries a bit; the other side matches lower ids
+    const int4 nb2 = reinterpret_cast<const int4*>(sd.tn)[t2];
+    const int2 run = a.tet_slots[sd.tet_off + t2];
+    const int f2 = nb2.x == d.t ? 0 : nb2.y == d.t ? 1 : nb2.z == d.t ? 2 : 3;
+    int q = -1;
+    for (int c = 0; c < run.y; ++c)
+      if (a.psite[run.x + c] == i) {
+        q = run.x + c;
+        break;
+      }
+    const PieceRef ref = q >= 0 ? a.pref[q] : PieceRef{0, 0u};
+    if (!(ref.word & 1u)) atomicOr(a.status, ST_INTERNAL);
+    else f(q, ref, 1 << f2);
+  }
+}
+
+// Every gluing bit matched and united. A tet's pieces sit in consecutive slots, in the spatial order of the tets, so
+// a lookup reads a few neighbouring lines, where one in a hash table of all element pieces reads a random one.
+__global__ __launch_bounds__(EMIT_NT) void k_glue_pieces(ShapeArgs a) {
+  if (*a.status & ST_TABLE_FULL) return;
+  unsigned long long bits = 0, pairs = 0;
+  if (blockIdx.y == 0) {
+    const int np_all = (int)min(a.counters[C_PIECE_SLOTS], (unsigned long long)a.pcap);
+    for (int p = blockIdx.x * EMIT_NT + threadIdx.x; p < np_all; p += gridDim.x * EMIT_NT) {
+      const unsigned w = a.pref[p].word;
+      const int g = (w & 1u) ? pw_glue(w) & 15 : 0;
+      if (!g) continue;
+      bits += __popc(g);
+      for_glued(a, a.pdesc[p], a.psite[p], g, [&](int q, const PieceRef& ref, int bit) {
+        if (!(pw_glue(ref.word) & bit)) {
+          atomicOr(a.status, ST_INTERNAL);
+          return;
+        }
+        ++pairs;
+        uf_union(a.pparent, p, q);
+      });
+    }
+  } else {
+    for_records(a, [&](int r) {
+      const ElemRec R = a.recs[r];
+      const int kind = R.z >> REC_SHIFT, g = R.z & 15;
+      if ((kind != REC_FACE && kind != REC_EDGE) || !g) return;
+      bits += __popc(g);
+      for_glued(a, a.pdesc[R.p], a.psite[R.p], g, [&](int, const PieceRef& ref, int bit) {
+        const int nf = pw_faces(ref.word);
+        const int q0 = ref.rec + (kind == REC_FACE ? 0 : nf), n = kind == REC_FACE ? nf : pw_edges(ref.word);
+        for (int q = q0; q < q0 + n; ++q) {
+          if (a.recs[q].j != R.j || a.recs[q].k != R.k) continue;
+          if (!(a.recs[q].z & bit)) break;
+          ++pairs;
+          uf_union(a.rparent, r, q);
+          return;
+        }
+        atomicOr(a.status, ST_INTERNAL);
+      });
+    });
+  }
+  for (int off = 32; off > 0; off >>= 1) {
+    bits += __shfl_xor(bits, off);
+    pairs += __shfl_xor(pairs, off);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    if (bits) stat_add(a, C_GLUE_BITS, bits);
+    if (pairs) stat_add(a, C_GLUE_PAIRS, pairs);
+  }
+}
+
+// one root per component
+__global__ __launch_bounds__(EMIT_NT) void k_count_piece_roots(ShapeArgs a, int* cell_b0, int* face_b0, int* edge_b0) {
+  if (*a.status & ST_TABLE_FULL) return;
+  if (blockIdx.y == 0) {
+    if (blockIdx.x == 0 && threadIdx.x == 0 && stat_sum(a, C_GLUE_BITS) != 2 * stat_sum(a, C_GLUE_PAIRS))
+      atomicOr(a.status, ST_INTERNAL);  // a gluing bit without its counterpart
+    const int np_all = (int)min(a.counters[C_PIECE_SLOTS], (unsigned long long)a.pcap);
+    for (int p = blockIdx.x * EMIT_NT + threadIdx.x; p < np_all; p += gridDim.x * EMIT_NT)
+      if ((a.pref[p].word & 1u) && a.pparent[p] == p) atomicAdd(&cell_b0[a.psite[p]], 1);
+    return;
+  }
+  for_records(a, [&](int r) {
+    const int kind = a.recs[r].z >> REC_SHIFT;
+    if ((kind == REC_FACE || kind == REC_EDGE) && a.rparent[r] == r)
+      atomicAdd(&(kind == REC_FACE ? face_b0 : edge_b0)[(int)a.recs[r].num], 1);
+  });
+}
+
+hipError_t launch_glue_pieces(const ShapeArgs& a, int* cell_b0, int* face_b0, int* edge_b0, hipStream_t s) {
+  hipLaunchKernelGGL(k_glue_pieces, dim3(pass_grid(a), 3), dim3(EMIT_NT), 0, s, a);
+  hipLaunchKernelGGL(k_count_piece_roots, dim3(pass_grid(a), 3), dim3(EMIT_NT), 0, s, a, cell_b0, face_b0, edge_b0);
   return hipGetLastError();
 }
 

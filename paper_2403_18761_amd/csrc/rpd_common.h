@@ -151,8 +151,10 @@ struct PieceDesc {
 struct PieceOut {
   double vol, mx, my, mz;  // volume and first moment (absolute coordinates)
   long long chi;           // fractional chi numerator of the cell term
-  int rec;                 // first of its element records: faces, then edges, then RPVs
-  unsigned word;           // piece_word()
+};
+struct PieceRef {
+  int rec;        // first of the piece's element records: faces, then edges, then RPVs
+  unsigned word;  // piece_word(); 0: the piece is empty
 };
 // bit 0: the piece is nonempty; 7 bits each: faces, edges and RPVs among its records; 8 bits: gluing bits (interior
 // faces of the tet the piece touches) and, above them, boundary contact bits. A piece of at most 64 vertices has at
@@ -170,7 +172,7 @@ struct ElemRec {
   int j, k;       // k = -1: a face
   int z;          // REC_* kind in the top bits; below: gluing bits (faces, edges) or l (RPVs)
   int p;          // piece slot
-  long long num;  // fractional chi numerator (faces, edges)
+  long long num;  // fractional chi numerator (faces, edges); in a build, the element's table slot once emitted
   double len;     // segment length (edges)
 };
 constexpr int REC_NONE = 0, REC_FACE = 1, REC_EDGE = 2, REC_RPV = 3, REC_SHIFT = 24;
@@ -250,6 +252,13 @@ struct ShapeArgs {
   PieceDesc* pdesc;      // [pcap] the pass's pieces
   int* psite;            // [pcap] their sites (batch-global)
   PieceOut* pout;        // [pcap]
+  PieceRef* pref;        // [pcap]
+  // Builds find components over the pieces and records themselves: the pieces that glue to a piece are found through
+  // the slots of the face-adjacent tet. (Sessions enter them into the table N, which lives from round to round, and
+  // leave these null.)
+  int2* tet_slots;       // [total tets] first piece slot and candidates of every tet
+  int* pparent;          // [pcap] union-find parents of the cells' pieces
+  int* rparent;          // [records] and of the faces' and edges'
   int pcap;              // a whole number of chunks
   ElemRec* recs;         // [pcap / CHUNK ranges of REC_CHUNK, then the pool]
   int* chunk_recs;       // [pcap / CHUNK] records in the chunk's own range

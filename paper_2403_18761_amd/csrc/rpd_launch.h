@@ -16,6 +16,8 @@ hipError_t launch_clip_slow(const ShapeArgs& a, unsigned char* scratch, int wave
 
 // emit.hip: the sums and element pieces of a pass's pieces
 hipError_t launch_emit(const ShapeArgs& a, hipStream_t s);
+// components of a build's elements (a.tet_slots set); the counts must be zero before
+hipError_t launch_glue_pieces(const ShapeArgs& a, int* cell_b0, int* face_b0, int* edge_b0, hipStream_t s);
 
 // reduce.hip
 hipError_t launch_fill_u64(unsigned long long* p, unsigned long long v, size_t n, hipStream_t s);
