@@ -68,8 +68,8 @@ typedef int32_t rpd_status;
 #define RPD_KEEP_PIECES (1u << 5)       /* keep per-piece records (rpd_pieces) for sampled comparisons */
 #define RPD_OWNER_WEIGHTS (1u << 6)     /* rpd_mesh_create: ownership weights even when L / k(sigma) fits (below) */
 #define RPD_SHUFFLE_QUEUE (1u << 7)     /* test-only: process the work items in a shuffled order (same results) */
-#define RPD_ESTIMATED_ORDER (1u << 8)   /* order the work by the static estimate even when a mesh has measured times */
-#define RPD_NO_SPLIT (1u << 9)          /* never dispatch a heavy workgroup block in parts (same results, for timing) */
+#define RPD_ESTIMATED_ORDER (1u << 8)   /* no effect (the work is no longer ordered by measured times) */
+#define RPD_NO_SPLIT (1u << 9)          /* take every workgroup block whole in the candidate search (same results, for timing) */
 
 /*
  * A prepared tet mesh (device resident): vertex/tet arrays, face adjacency, the multiplicity k(sigma) of every
@@ -133,7 +133,7 @@ typedef struct rpd_stats {
   int64_t n_defer_kmax;   /* tets deferred because more candidates than the clip budget remained */
   int64_t n_defer_clip;   /* pieces deferred by the fast path: a predicate undecided in FP64, or over 64 vertices */
   int64_t n_split;        /* workgroup blocks redone in smaller chunks because their site list overflowed */
-  int64_t n_items;        /* work items of the candidate kernel (blocks, and parts of blocks that were heavy before) */
+  int64_t n_items;        /* work items of the candidate kernel (parts of blocks; whole blocks with RPD_NO_SPLIT) */
   int64_t n_big;          /* pieces over the fast path's 16 vertex slots, redone there with a 64-slot polytope */
 } rpd_stats;
 
@@ -144,9 +144,8 @@ typedef struct rpd_result rpd_result;
  * Errors: RPD_E_INVALID (off-grid or out-of-range values, bad indices, non-positive orientation),
  * RPD_E_MESH (a face in more than two tets, more than one component, lcm of multiplicities of 2^31 or more). */
 rpd_status rpd_mesh_create(const rpd_mesh_desc* desc, uint32_t flags, void* stream, rpd_mesh** out);
-/* A mesh keeps one piece of mutable state: the time each of its blocks took in the last rpd_build that used it,
- * which orders the next build's work (heaviest first). It changes no result. Builds that share a mesh may run
- * from several threads (the hint is locked); rpd_mesh_free must not overlap a build that uses the mesh. */
+/* A mesh does not change after its creation: builds that share it may run from several threads; rpd_mesh_free must not
+ * overlap a build that uses the mesh. */
 rpd_status rpd_mesh_get_info(const rpd_mesh* mesh, rpd_mesh_info* info);
 void rpd_mesh_free(rpd_mesh* mesh);
 

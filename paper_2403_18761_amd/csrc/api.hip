@@ -166,7 +166,7 @@ struct DeviceState {
   int def_cap = 0, piece_cap = 0, term_cap = 0, pcap = 0, pool_cap = 0, big_cap = 0;
   DBuf site, status, cell_chi, cell_geo, cell_np, cell_b0;
   DBuf fkeys, face_chi, face_np, face_b0, ekeys, edge_chi, edge_np, edge_len, edge_b0, qkeys, rpv_cnt;
-  DBuf pdesc, psite, pout, pref, recs, chunk_recs, tet_slots, pparent, rparent;
+  DBuf pdesc, psite, order, pout, pref, recs, chunk_recs, tet_slots, pparent, rparent;
   DBuf nodes, glist, gseg, clist, cseg, bigp, deferred, deferred2, pieces, terms, counters, tetU, slow, touch, removed;
   int waves = 0;
 
@@ -220,8 +220,9 @@ struct DeviceState {
       pdesc.alloc(sizeof(PieceDesc) * (size_t)pcap);
       psite.alloc(sizeof(int) * (size_t)pcap);
       pout.alloc(sizeof(PieceOut) * (size_t)pcap);
-      chunk_recs.alloc(sizeof(int) * (size_t)(pcap / CHUNK));
-      const size_t nrec = (size_t)(pcap / CHUNK) * REC_CHUNK + (size_t)pool_cap;
+      chunk_recs.alloc(sizeof(int) * (size_t)chunk_cap(pcap));
+      order.alloc(sizeof(int) * NCLASS * (size_t)pcap);
+      const size_t nrec = (size_t)chunk_cap(pcap) * REC_CHUNK + (size_t)pool_cap;
       recs.alloc(sizeof(ElemRec) * nrec);
       pref.alloc(sizeof(PieceRef) * (size_t)pcap);
       if (!keep_U) {
@@ -300,6 +301,7 @@ struct DeviceState {
     a.shapes = shapes;
     a.nshapes = nsh;
     a.items = items;
+    a.item_mul = 1;
     a.nitems = nitems;
     a.ns = ns_cap;
     a.site = site.as<float4>();
@@ -329,6 +331,7 @@ struct DeviceState {
     a.psite = psite.as<int>();
     a.pout = pout.as<PieceOut>();
     a.pcap = pcap;
+    a.order = order.as<int>();
     a.recs = recs.as<ElemRec>();
     a.chunk_recs = chunk_recs.as<int>();
     a.pool_cap = pool_cap;
@@ -721,6 +724,16 @@ static std::vector<ShapeDesc> shape_table(const rpd_mesh* const* meshes, const i
     d.tet_off = *nt_tot;
     d.sign = +1;
     d.pad = 0;
+    d.blkbox = m->grpbox[0].as<float>();
+    // Groups whose site lists the blocks share: a list is worth its scan of all sites when it serves many blocks, and
+    // is short when the group is small. Dense sites (over two per block) make the lists of larger groups as long as the
+    // shape's site list; with very many sites the scans for small groups cost more than they save.
+    const int level = d.ns > 2 * m->nblk ? 0 : d.ns > 8192 ? 2 : 1;
+    d.grp = level ? m->grp[level].as<int>() : nullptr;
+    d.grpbox = m->grpbox[level].as<float>();
+    d.ngrp = m->ngrp[level];
+    d.grp_off = d.item_off = 0;
+    d.parts = TB / SPLIT_TETS;
     *ns_tot += nsites[k];
     *nt_tot += m->nt;
   }
@@ -731,88 +744,18 @@ static std::vector<ShapeDesc> shape_table(const rpd_mesh* const* meshes, const i
   return hd;
 }
 
-// (shape, block) work items, heaviest first. The hardware dispatcher hands workgroups to compute units in grid
-// order as they free up, so a heavy item dispatched late sets the kernel's tail. The cost of an item is its
-// fast-kernel time in the last build on the same mesh when every mesh of the call has one (and
-// RPD_ESTIMATED_ORDER is not set), else the estimate shape sites x block tets (the box filter scans every site of the shape; clipping grows with the tets).
-// Ties keep the shapes' order and the blocks' Morton order. The order never changes a result.
-static std::vector<int2> work_items(const std::vector<ShapeDesc>& hd, const rpd_mesh* const* meshes,
-                                    unsigned flags) {
-  const int nsh = (int)hd.size();
-  std::vector<int2> items;
-  std::vector<unsigned long long> cost;
-  bool learned = (flags & RPD_ESTIMATED_ORDER) == 0;
-  for (int k = 0; k < nsh && learned; ++k) {
-    rpd_mesh* m = const_cast<rpd_mesh*>(meshes[k]);
-    std::lock_guard<std::mutex> g(m->cost_mu);
-    learned = (int)m->blk_cost.size() == hd[k].nblk;
-  }
-  for (int k = 0; k < nsh; ++k) {
-    rpd_mesh* m = const_cast<rpd_mesh*>(meshes[k]);
-    std::unique_lock<std::mutex> g(m->cost_mu, std::defer_lock);
-    if (learned) g.lock();
-    for (int b = 0; b < hd[k].nblk; ++b) {
-      items.push_back(make_int2(k, b));
-      cost.push_back(learned ? (unsigned long long)m->blk_cost[b]
-                             : (unsigned long long)hd[k].ns * (unsigned long long)(m->hblk[b + 1] - m->hblk[b]));
-    }
-  }
-  // With measured times, a block that could set the kernel's tail (more than twice the mean, and more than half the
-  // time the kernel needs per workgroup slot: the total over about four resident workgroups per compute unit) is
-  // dispatched in parts of SPLIT_TETS tets, each part its own workgroup with its own site box. Where items are short
-  // against the kernel (large batches) nothing is split, since every part scans the sites again.
-  if (learned && !(flags & RPD_NO_SPLIT) && !items.empty()) {
-    unsigned long long sum = 0;
-    for (unsigned long long c : cost) sum += c;
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) !=
-                                                hipSuccess || cus <= 0)
-      cus = 256;
-    const unsigned long long heavy = std::max(2 * (sum / items.size()), sum / (8ull * (unsigned long long)cus)) + 1;
-    const size_t n0 = items.size();
-    for (size_t q = 0; q < n0; ++q) {
-      const int k = items[q].x, b = items[q].y;
-      const int n = meshes[k]->hblk[b + 1] - meshes[k]->hblk[b];
-      if (cost[q] < heavy || n <= SPLIT_TETS) continue;
-      const int parts = (n + SPLIT_TETS - 1) / SPLIT_TETS;
-      const unsigned long long c = cost[q] / parts + 1;
-      items[q].y = b | (1 << ITEM_PART_SHIFT);
-      cost[q] = c;
-      for (int p = 2; p <= parts; ++p) {
-        items.push_back(make_int2(k, b | (p << ITEM_PART_SHIFT)));
-        cost.push_back(c);
-      }
-    }
-  }
-  // stable counting sort, descending, on the top bits of the cost range: about one bucket per item, 2^16 at most
-  int bits = 8;
-  while (bits < 16 && ((size_t)1 << bits) < items.size()) ++bits;
-  const unsigned long long top = (1ull << bits) - 1;
-  unsigned long long cmax = 1;
-  for (unsigned long long c : cost) cmax = std::max(cmax, c);
-  int shift = 0;
-  while ((cmax >> shift) > top) ++shift;
-  std::vector<int> start((size_t)top + 2, 0);
-  for (unsigned long long c : cost) ++start[top - (c >> shift) + 1];
-  for (size_t d = 0; d <= top; ++d) start[d + 1] += start[d];
-  std::vector<int2> out(items.size());
-  for (size_t k = 0; k < items.size(); ++k) out[start[top - (cost[k] >> shift)]++] = items[k];
-  return out;
+// Parts in which a build takes a shape's blocks: two (items of up to 32 tets), or eight where the call has so few
+// blocks that the chip would be idle or the shape so many sites that an item of a few tets is already long.
+static int block_parts(long long nblk_call, int nblk, int ns, unsigned flags) {
+  if (flags & RPD_NO_SPLIT) return 1;
+  return nblk_call <= 1024 || ns > 2 * nblk ? 8 : 2;
 }
 
-// Records the fast-kernel time of every item as its mesh's block costs (see work_items).
-static void learn_costs(const std::vector<int2>& items, const unsigned* ticks,
-                        const std::vector<ShapeDesc>& hd, const rpd_mesh* const* meshes) {
-  const int nsh = (int)hd.size();
-  std::vector<std::vector<unsigned>> per(nsh);
-  for (int k = 0; k < nsh; ++k) per[k].assign(hd[k].nblk, 0);
-  for (size_t k = 0; k < items.size(); ++k)  // a split block's cost is the sum of its parts'
-    per[items[k].x][items[k].y & ((1 << ITEM_PART_SHIFT) - 1)] += ticks[k];
-  for (int k = 0; k < nsh; ++k) {  // a mesh that several shapes share keeps the last one's times
-    rpd_mesh* m = const_cast<rpd_mesh*>(meshes[k]);
-    std::lock_guard<std::mutex> g(m->cost_mu);
-    m->blk_cost.swap(per[k]);
-  }
+// The grid permutation of RPD_SHUFFLE_QUEUE: a multiplier coprime to the item count.
+static unsigned shuffle_mul(int nitems) {
+  for (unsigned p : {7919u, 104729u, 1299709u})
+    if (nitems % (int)p) return p;
+  return 1;
 }
 
 // What the site upload leaves in flight: kept by the caller until its stream has been synchronised.
@@ -881,63 +824,76 @@ static bool run_batch(const rpd_mesh* const* meshes, const rpd_sites* sites, int
   for (int k = 0; k < nsh; ++k) nsites[k] = sites[k].n_sites;
   long long ns_tot = 0, nt_tot = 0;
   std::vector<ShapeDesc> hd = shape_table(meshes, nsites.data(), nsh, &ns_tot, &nt_tot);
-  // the tables are cleared on the device while the host orders the work
+  // the tables are cleared on the device while the host prepares the launches
   DeviceState D;
   D.alloc(nsh, (int)ns_tot, nt_tot, scale, (o.flags & RPD_KEEP_PIECES) != 0, false, fast_slots(o));
   D.clear(s);
-  std::vector<int2> items = work_items(hd, meshes, o.flags);
-  if (o.flags & RPD_SHUFFLE_QUEUE) {  // a fixed permutation: results must not depend on the processing order
-    unsigned long long x = 0x9E3779B97F4A7C15ull;
-    for (size_t k = items.size(); k > 1; --k) {
-      x ^= x << 13;
-      x ^= x >> 7;
-      x ^= x << 17;
-      std::swap(items[k - 1], items[x % k]);
-    }
+  long long nblk = 0, nitems_all = 0, ngrp = 0, grp_cap = 0, nparts = 0;
+  int most = 0;
+  for (int k = 0; k < nsh; ++k) {
+    nblk += hd[k].nblk;
+    most = std::max(most, hd[k].ns);
   }
-  // the shape table, the site sources and the work items go up in one copy from pinned memory; then one launch
+  for (int k = 0; k < nsh; ++k) {
+    ShapeDesc& d = hd[k];
+    d.parts = block_parts(nblk, d.nblk, d.ns, o.flags);
+    d.item_off = (int)nitems_all;
+    d.grp_off = (int)ngrp;
+    nitems_all += (long long)d.nblk * d.parts;
+    ngrp += d.ngrp;
+    grp_cap += (long long)d.ngrp * std::min(d.ns, GROUP_CAP / 2);
+    nparts += meshes[k]->nparts[d.parts == 8 ? 3 : d.parts == 2 ? 1 : 0];
+    if (nitems_all >= (1ll << 31)) throw Failure{RPD_E_INVALID, "2^31 or more work items in one call"};
+  }
+  const int nitems = (int)nitems_all;
+  if (most <= 512) ngrp = 0;  // every block looks at the few sites itself
+  grp_cap = std::min(grp_cap, 1ll << 28);  // (a list that finds no room: its blocks look at all sites)
+  // the shape table and the site sources go up in one copy from pinned memory; then one launch
   // validates and packs every shape's sites (host site arrays are staged first)
   const size_t off_src = (sizeof(ShapeDesc) * nsh + 15) / 16 * 16;
-  const size_t off_items = off_src + (sizeof(SiteSrc) * nsh + 15) / 16 * 16;
-  const size_t stage_bytes = off_items + sizeof(int2) * std::max<size_t>(items.size(), 1);
+  const size_t stage_bytes = off_src + sizeof(SiteSrc) * nsh;
   HostPinned stage(stage_bytes);  // released (back to the pool) after the stream is drained (below)
   DBuf dstage(stage_bytes);
   SiteUpload su = site_sources(sites, hd, dev, s);
   std::memcpy(stage.p, hd.data(), sizeof(ShapeDesc) * nsh);
   std::memcpy((unsigned char*)stage.p + off_src, su.src.data(), sizeof(SiteSrc) * nsh);
-  if (!items.empty()) std::memcpy((unsigned char*)stage.p + off_items, items.data(), sizeof(int2) * items.size());
   hip_check(hipMemcpyAsync(dstage.p, stage.p, stage_bytes, hipMemcpyHostToDevice, s), "upload");
   const ShapeDesc* dshapes_p = (const ShapeDesc*)dstage.p;
-  const int2* ditems_p = (const int2*)(dstage.as<unsigned char>() + off_items);
   int max_n = 0;
   for (int k = 0; k < nsh; ++k) max_n = std::max(max_n, sites[k].n_sites);
   hip_check(launch_validate_sites_multi((const SiteSrc*)(dstage.as<unsigned char>() + off_src), nsh, max_n,
                                         D.site.as<float4>(), D.status.as<int>(), s),
             "validate sites");
   const int kmax = o.clip_budget > 0 ? std::min(o.clip_budget, KMAX) : KMAX;
-  ShapeArgs a = D.args(dshapes_p, ditems_p, (int)items.size(), o.flags, kmax);
-  HostPinned ticks_host(sizeof(unsigned) * items.size() + 16);  // pinned: the copy does not stall the host
-  struct DrainOnExit {  // an early exit (exception) must not leave the copy into ticks_host pending
+  ShapeArgs a = D.args(dshapes_p, nullptr, nitems, o.flags, kmax);
+  // a fixed permutation: results must not depend on the processing order
+  a.item_mul = (o.flags & RPD_SHUFFLE_QUEUE) ? shuffle_mul(nitems) : 1;
+  DBuf grp_run, grp_site, grp_id;
+  if (ngrp) {
+    grp_run.alloc(sizeof(int2) * (size_t)ngrp);
+    grp_site.alloc(sizeof(float4) * (size_t)grp_cap);
+    grp_id.alloc(sizeof(int) * (size_t)grp_cap);
+    a.ngrp = (int)ngrp;
+    a.grp_run = grp_run.as<int2>();
+    a.grp_site = grp_site.as<float4>();
+    a.grp_id = grp_id.as<int>();
+    a.grp_cap = (int)grp_cap;
+  }
+  struct DrainOnExit {  // an early exit (exception) must not release what the queued work still uses
     hipStream_t s;
     ~DrainOnExit() { (void)hipStreamSynchronize(s); }
   } drain{s};
-  DBuf dcost(sizeof(unsigned) * std::max<size_t>(items.size(), 1));
-  a.item_cost = dcost.as<unsigned>();
   Timing tm((o.flags & RPD_TIMING) != 0);
   tm.mark(0, s);
   hip_check(launch_candidates(a, s), "candidate kernel");
   hip_check(launch_clip_pieces(a, o.precision, fast_slots(o), s), "clip kernel");
   tm.mark(1, s);
-  if (!items.empty())  // read by the host after collect's synchronisation
-    hip_check(hipMemcpyAsync(ticks_host.p, dcost.p, sizeof(unsigned) * items.size(), hipMemcpyDeviceToHost, s),
-              "download");
   hip_check(launch_clip_slow(a, D.slow.as<unsigned char>(), D.waves, s), "deferred clip kernel");
   tm.mark(2, s);
   hip_check(launch_emit(a, s), "emission");
   D.build_components(a, s);
   if (!collect(D, hd, dshapes_p, meshes, s, tm, outs, st)) return false;
-  learn_costs(items, (const unsigned*)ticks_host.p, hd, meshes);
-  st.n_items = (int64_t)items.size();
+  st.n_items = nparts;
   st.ms_clip = tm.ms(0, 1);
   st.ms_deferred = tm.ms(1, 2);
   st.ms_reduce = tm.ms(2, 3);
@@ -1299,8 +1255,7 @@ struct rpd_session {
   rpd::ShapeDesc hd{};
   rpd::DeviceState D;
   rpd::DBuf dshapes;  // [0] the shape before a round's insertions, [1] after them (the current state)
-  rpd::DBuf all_items, items, table, tet_block, dirty, sel, selpos, best, ref, tet_used, ints;
-  rpd::DBuf order;  // [nblk] blocks by their fast-kernel time in the initial build, heaviest first
+  rpd::DBuf items, table, tet_block, dirty, sel, selpos, best, ref, tet_used, ints;
   rpd::RoundState r{};
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
@@ -1401,12 +1356,9 @@ static bool session_init(rpd_session* S, const rpd_sites* sites, const rpd_sites
   std::vector<int> tb(nt);
   for (int b = 0; b < nblk; ++b)
     for (int t = m->hblk[b]; t < m->hblk[b + 1]; ++t) tb[t] = b;
-  std::vector<int2> all(nblk);
-  for (int b = 0; b < nblk; ++b) all[b] = make_int2(0, b);
   ShapeDesc two[2] = {S->hd, S->hd};
   two[0].sign = -1;  // the state before a round's insertions: its dirty pieces are taken back
   S->dshapes.alloc(sizeof(two));
-  S->all_items.alloc(sizeof(int2) * (size_t)nblk);
   S->items.alloc(sizeof(int2) * 2 * (size_t)nblk * (TB / SPLIT_TETS));  // every dirty block in parts, twice
   S->tet_block.alloc(sizeof(int) * (size_t)nt);
   S->dirty.alloc(sizeof(unsigned long long) * (size_t)nblk);
@@ -1416,8 +1368,6 @@ static bool session_init(rpd_session* S, const rpd_sites* sites, const rpd_sites
   S->selpos.alloc(sizeof(int) * (size_t)S->max_sites);
   S->ints.alloc(sizeof(int) * SI_COUNT);
   hip_check(hipMemcpyAsync(S->dshapes.p, two, sizeof(two), hipMemcpyHostToDevice, s), "upload");
-  hip_check(hipMemcpyAsync(S->all_items.p, all.data(), sizeof(int2) * all.size(), hipMemcpyHostToDevice, s),
-            "upload");
   hip_check(hipMemcpyAsync(S->tet_block.p, tb.data(), sizeof(int) * tb.size(), hipMemcpyHostToDevice, s), "upload");
   hip_check(launch_fill_i32(S->dirty.as<int>(), 0, 2 * (size_t)nblk, s), "fill");
   hip_check(launch_fill_i32(S->selpos.as<int>(), -1, S->max_sites, s), "fill");
@@ -1425,9 +1375,7 @@ static bool session_init(rpd_session* S, const rpd_sites* sites, const rpd_sites
   hip_check(launch_fill_i32(S->ints.as<int>() + SI_NS, S->hd.ns, 1, s), "fill");
 
   ShapeDesc* ds = S->dshapes.as<ShapeDesc>();
-  ShapeArgs a = D.args(ds + 1, S->all_items.as<int2>(), nblk, S->o.flags, S->kmax);
-  DBuf ticks(sizeof(unsigned) * (size_t)nblk);
-  a.item_cost = ticks.as<unsigned>();  // item k is block k
+  ShapeArgs a = D.args(ds + 1, nullptr, nblk * S->hd.parts, S->o.flags, S->kmax);
   clip_pass(S, a);
   D.components(a, s);
   hip_check(hipStreamSynchronize(s), "synchronize");
@@ -1435,16 +1383,6 @@ static bool session_init(rpd_session* S, const rpd_sites* sites, const rpd_sites
   hip_check(hipMemcpy(&hst, D.status.p, sizeof(int), hipMemcpyDeviceToHost), "download");
   if (hst & ST_TABLE_FULL) return false;
   status_error(hst);
-  {  // the rounds scan the blocks heaviest first (k_dirty_items)
-    std::vector<unsigned> cost(nblk);
-    hip_check(hipMemcpy(cost.data(), ticks.p, sizeof(unsigned) * (size_t)nblk, hipMemcpyDeviceToHost), "download");
-    std::vector<int> ord(nblk);
-    std::iota(ord.begin(), ord.end(), 0);
-    std::stable_sort(ord.begin(), ord.end(), [&](int x, int y) { return cost[x] > cost[y]; });
-    S->order.alloc(sizeof(int) * (size_t)nblk);
-    hip_check(hipMemcpy(S->order.p, ord.data(), sizeof(int) * (size_t)nblk, hipMemcpyHostToDevice), "upload");
-  }
-
   int* ints = S->ints.as<int>();
   RoundState& r = S->r;
   r.nsel = ints + SI_NSEL;
@@ -1458,7 +1396,6 @@ static bool session_init(rpd_session* S, const rpd_sites* sites, const rpd_sites
   r.mode = S->mode;
   r.tet_block = S->tet_block.as<int>();
   r.dirty = S->dirty.as<unsigned long long>();
-  r.order = S->order.as<int>();
   r.items = S->items.as<int2>();
   r.blk = m->blk.as<int>();
   r.clist = D.clist.as<int>();

@@ -17,6 +17,7 @@
 #include <climits>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "rpd_device.h"
 #include "rpd_launch.h"
@@ -275,7 +276,7 @@ __device__ inline int pool_records(const ShapeArgs& a, int n) {
     atomicOr(a.status, ST_TABLE_FULL);
     return -1;
   }
-  return (a.pcap / CHUNK) * REC_CHUNK + (int)q;
+  return chunk_cap(a.pcap) * REC_CHUNK + (int)q;
 }
 
 // A piece clipped outside its chunk's pass: terms to its slot, records to the pool.
@@ -293,25 +294,6 @@ __device__ inline void defer_item(const ShapeArgs& a, int shape, int t, int p, i
   const unsigned long long idx = atomicAdd(&a.counters[C_DEFER_ITEMS], 1ull);
   if (idx < (unsigned long long)a.deferred_cap) a.deferred[idx] = make_int4(shape, t, p, first);
   else atomicOr(a.status, ST_TABLE_FULL);
-}
-
-// The next chunk of a split item: the next tet while tets are taken one at a time (up to single_end), else the next
-// SUB tets. False past the item's last tet.
-__device__ inline bool next_chunk(int& sub, int& sub_n, int& single_end, int ntb_all) {
-  if (single_end > sub + 1) {
-    sub += 1;
-    sub_n = 1;
-    return true;
-  }
-  if (single_end > sub) {  // the last single tet of its chunk: on with the chunk after it
-    sub = single_end;
-    single_end = 0;
-  } else {
-    sub += SUB;
-  }
-  if (sub >= ntb_all) return false;
-  sub_n = min(SUB, ntb_all - sub);
-  return true;
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -388,6 +370,74 @@ __device__ inline float wave_maxf(float v) {
   return v;
 }
 
+// Per group of neighbouring blocks (a block, or an octree cell of two or four times a block's side), the shape's sites
+// that its blocks have to look at: a few hundred instead of all of the shape's (up to 20,000 on the 128^3 genus-3
+// solid, where the scans of all sites were most of the candidate kernel). Site j is listed when
+//   min over the box of d_j  <=  min over sites s of (max over the box of d_s)  +  the squared diagonal of a block.
+// Every test that a block's candidate search makes compares g = d - |x - o|^2 (o and x in the block's box) of a site
+// against a bound at most min_s max d_s, and |x - o| is at most the block's diagonal: a site left out here fails them
+// all, so the search finds what it would among all sites.
+__global__ __launch_bounds__(256) void k_group_sites(ShapeArgs a) {
+  __shared__ double s_red[4];
+  __shared__ int s_list[GROUP_CAP];
+  __shared__ int s_n, s_at;
+  int lo = 0, hi = a.nshapes - 1;  // the shape of this group
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (a.shapes[mid].grp_off <= (int)blockIdx.x) lo = mid;
+    else hi = mid - 1;
+  }
+  const ShapeDesc& sd = a.shapes[lo];
+  const int g = blockIdx.x, lane = threadIdx.x & 63;
+  const float* bx = sd.grpbox + 7 * (size_t)(g - sd.grp_off);
+  const float x0 = bx[0], y0 = bx[1], z0 = bx[2], x1 = bx[3], y1 = bx[4], z1 = bx[5];
+  const float4* ssite = a.site + sd.site_off;
+  if (threadIdx.x == 0) s_n = 0;
+  double u = INFINITY;
+  for (int j = threadIdx.x; j < sd.ns; j += 256) {
+    const float4 s = ssite[j];
+    const double dx = fmax((double)s.x - x0, (double)x1 - s.x), dy = fmax((double)s.y - y0, (double)y1 - s.y),
+                 dz = fmax((double)s.z - z0, (double)z1 - s.z);
+    u = fmin(u, dx * dx + dy * dy + dz * dz - (double)s.w * s.w);
+  }
+  u = wave_min(u);
+  if (lane == 0) s_red[threadIdx.x >> 6] = u;
+  __syncthreads();
+  u = fmin(fmin(s_red[0], s_red[1]), fmin(s_red[2], s_red[3])) + (double)bx[6];
+  for (int base = 0; base < sd.ns; base += 256) {
+    const int j = base + threadIdx.x;
+    bool take = false;
+    if (j < sd.ns) {
+      const float4 s = ssite[j];
+      const double dx = fmax(0.0, fmax((double)x0 - s.x, (double)s.x - x1)),
+                   dy = fmax(0.0, fmax((double)y0 - s.y, (double)s.y - y1)),
+                   dz = fmax(0.0, fmax((double)z0 - s.z, (double)s.z - z1));
+      take = dx * dx + dy * dy + dz * dz - (double)s.w * s.w <= u;
+    }
+    const unsigned long long m = __ballot(take);
+    if (!m) continue;
+    int at = 0;
+    if (lane == 0) at = atomicAdd(&s_n, __popcll(m));
+    at = __shfl(at, 0) + __popcll(m & ((1ull << lane) - 1ull));
+    if (take && at < GROUP_CAP) s_list[at] = j;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {  // a list that does not fit: the blocks look at all sites
+    s_at = -1;
+    if (s_n <= GROUP_CAP) {
+      const unsigned long long q = atomicAdd(&a.counters[C_GROUP_SITES], (unsigned long long)s_n);
+      if (q + s_n <= (unsigned long long)a.grp_cap) s_at = (int)q;
+    }
+    a.grp_run[g] = make_int2(s_at, s_n);
+  }
+  __syncthreads();
+  if (s_at < 0) return;
+  for (int q = threadIdx.x; q < s_n; q += 256) {
+    a.grp_site[s_at + q] = ssite[s_list[q]];
+    a.grp_id[s_at + q] = s_list[q];
+  }
+}
+
 // g_j at the four tet vertices (tet-local frame, exact in FP64)
 __device__ __forceinline__ void g4(const float4* tv, const float4& s, double* g) {
   const float4 o = tv[0];
@@ -403,8 +453,9 @@ __device__ __forceinline__ void g4(const float4* tv, const float4& s, double* g)
 // sorted by the power distance at the centroid, and a dominator has the smaller one, so rounds of three dominators
 // taken in list order (each tested against the candidates after them) find the dominated candidates the three-at-a-time
 // way; the rounds run while candidates remain past the dominators. Returns the new count; order is kept.
-__device__ __forceinline__ int refine_candidates(const float4* tv, const float4* sites, unsigned char* cand, float* key,
-                                                 int m) {
+// (Of a full list the budget decides where the tet goes, so the rounds are part of what a tet's path depends on. A list
+// that cannot be over the budget is instead cut down to the candidates that no earlier one beats, by refine_all.)
+__device__ __forceinline__ int refine_candidates(const float4* tv, const float4* sites, unsigned char* cand, int m) {
   for (int d = 0; d + 3 < m; d += 3) {
     double g0[4], g1[4], g2[4];
     g4(tv, sites[cand[d]], g0);
@@ -417,103 +468,264 @@ __device__ __forceinline__ int refine_candidates(const float4* tv, const float4*
       const bool dom = (g[0] > g0[0] && g[1] > g0[1] && g[2] > g0[2] && g[3] > g0[3]) ||
                        (g[0] > g1[0] && g[1] > g1[1] && g[2] > g1[2] && g[3] > g1[3]) ||
                        (g[0] > g2[0] && g[1] > g2[1] && g[2] > g2[2] && g[3] > g2[3]);
-      if (!dom) {
-        cand[w] = cand[c];
-        key[w] = key[c];
-        ++w;
-      }
+      if (!dom) cand[w++] = cand[c];
     }
     m = w;
   }
   return m;
 }
 
-// One wavefront per work item (a block, or a part of one). Latency-bound (site scans through the caches, FP64 values on
-// a few dozen sites per tet); 17.5 KB of LDS, so nine items fit a compute unit.
-__global__ __launch_bounds__(64) void k_candidates(ShapeArgs a) {
-  static_assert(SLMAX <= 256, "candidate bytes index the site list");
-  static_assert(TB * KRAW < 32768, "piece offsets are 16-bit");
+__device__ __forceinline__ int refine_all(const float4* tv, const float4* sites, unsigned char* cand, int m) {
+  int w = 1;
+  for (int c = 1; c < m; ++c) {
+    double g[4];
+    const unsigned char cc = cand[c];
+    g4(tv, sites[cc], g);
+    bool dom = false;
+    for (int d = 0; d < w && !dom; ++d) {
+      double e[4];
+      g4(tv, sites[cand[d]], e);
+      dom = g[0] > e[0] && g[1] > e[1] && g[2] > e[2] && g[3] > e[3];
+    }
+    if (!dom) cand[w++] = cc;
+  }
+  return min(w, m);
+}
+
+// Which tets the candidate kernel takes next. It starts with ITEM_TETS of the item's, sharing the sites of their block's
+// box; where those overflow the shared list, with chunks of SUB tets and the sites of their boxes, and where a chunk's
+// overflow it, with DIRECT tets at a time that look among the source sites themselves.
+struct TetRun {
+  int sub, n;      // tets [sub, sub + n) of the item
+  int direct_end;  // tets up to here are taken DIRECT at a time
+  int all;
+  bool split;
+  static constexpr int DIRECT = 4;
+  __device__ bool direct() const { return direct_end > sub; }
+  __device__ void chunks() {
+    split = true;
+    n = min(SUB, all - sub);
+  }
+  __device__ void directly() {
+    direct_end = sub + n;
+    n = min(DIRECT, n);
+  }
+  __device__ bool next() {
+    sub += n;
+    if (!split) {
+      n = min(ITEM_TETS, all - sub);
+      return sub < all;
+    }
+    if (direct_end > sub) {
+      n = min(DIRECT, direct_end - sub);
+      return true;
+    }
+    direct_end = 0;
+    n = min(SUB, all - sub);
+    return sub < all;
+  }
+};
+
+// One wavefront per work item (a part of a block, or all of it). A tet goes to the large-capacity kernel only for
+// reasons that depend on its own candidates (more than fit its list, or the clip budget), never on its neighbours' or
+// on sites that own nothing in it: an incremental update, which recomputes a tet's pieces to take them back, must take
+// the path that added them.
+__global__ __launch_bounds__(64, 3) void k_candidates(ShapeArgs a) {
+  static_assert(SLMAX <= 256 && TetRun::DIRECT * KRAW <= SLMAX, "candidate bytes index the site list");
+  constexpr int IT = ITEM_TETS;
   __shared__ float4 s_site[SLMAX];
   __shared__ int s_sid[SLMAX];
-  __shared__ unsigned char s_cand[TB][KRAW];
-  __shared__ float s_key[TB][KRAW];  // the candidates' sort keys
-  __shared__ int s_m[TB];            // candidates of each tet; -1: left to the large-capacity kernel without a list
-  __shared__ short s_off[TB + 1];
-  __shared__ short s_order[TB];
+  __shared__ unsigned char s_raw[IT][KRAW];   // candidates (list positions) as found
+  __shared__ unsigned char s_cand[IT][KRAW];  // ... and sorted
+  __shared__ float s_key[IT][KRAW];           // sort keys
+  __shared__ int s_m[IT];                     // candidates of each tet
+  __shared__ short s_off[IT + 1];
+  __shared__ short s_order[IT];
   __shared__ int s_nsl;
 
   const int tid = threadIdx.x, lane = tid;
   const int nitems = a.nitems_dev ? *a.nitems_dev : a.nitems;
   unsigned long long n_cand = 0;
-  // Work items are (shape, block or part of a block), ordered heaviest first. In a build the grid covers them, one
-  // item per workgroup, and the hardware dispatcher hands them to compute units in that order as they free up,
-  // which is the work queue. The passes of an incremental round read the item count on the device and launch a
-  // grid sized to the resident workgroups, each taking items in grid-stride order.
+  // A build's grid covers the items (every block of every shape, in a.parts parts), one item per workgroup. The passes
+  // of an incremental round read a list of items whose length is known on the device only and launch a grid sized to
+  // the resident workgroups, each taking items in grid-stride order.
   for (int item = blockIdx.x; item < nitems; item += gridDim.x) {
-  const unsigned long long clock0 = wall_clock64();
-  const int2 wi = a.items[item];
-  const int shape = __builtin_amdgcn_readfirstlane(wi.x & 0xffff);
+  int shape, blk, tb0, ntb_all;
+  unsigned long long item_mask = ~0ull;  // the tets of the item to clip, relative to its first tet
+  if (a.items) {
+    const int2 wi = a.items[item];
+    shape = __builtin_amdgcn_readfirstlane(wi.x & 0xffff);
+    const unsigned tet_mask16 = (unsigned)wi.x >> 16;  // the tets a new sphere can reach, or 0: all
+    if (tet_mask16) item_mask = (unsigned long long)tet_mask16;
+    blk = wi.y & ((1 << ITEM_PART_SHIFT) - 1);
+    const int part = wi.y >> ITEM_PART_SHIFT;  // (only parts that exist are listed)
+    const int* bk = a.shapes[shape].blk;
+    tb0 = bk[blk] + (part - 1) * SPLIT_TETS;
+    ntb_all = min(SPLIT_TETS, bk[blk + 1] - tb0);
+  } else {
+    const int it = a.item_mul == 1 ? item : (int)((unsigned long long)item * a.item_mul % (unsigned)nitems);
+    int lo = 0, hi = a.nshapes - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (a.shapes[mid].item_off <= it) lo = mid;
+      else hi = mid - 1;
+    }
+    shape = lo;
+    const int local = it - a.shapes[shape].item_off, parts = a.shapes[shape].parts, pt = TB / parts;
+    blk = local / parts;
+    const int* bk = a.shapes[shape].blk;
+    tb0 = bk[blk] + (local % parts) * pt;
+    ntb_all = min(pt, bk[blk + 1] - tb0);
+    if (ntb_all <= 0) continue;
+  }
   const ShapeDesc sd = a.shapes[shape];
-  const int blk = wi.y & ((1 << ITEM_PART_SHIFT) - 1), part = wi.y >> ITEM_PART_SHIFT;
-  // the tets of the item to clip, relative to its first tet (an incremental update names the tets a new sphere can
-  // reach; every other item takes all)
-  const unsigned tet_mask16 = (unsigned)wi.x >> 16;
-  const unsigned long long item_mask = tet_mask16 ? (unsigned long long)tet_mask16 : ~0ull;
-  int tb0 = sd.blk[blk];
-  int ntb_all = sd.blk[blk + 1] - tb0;
-  if (part > 0) {  // one part of a heavy block (the host only makes parts that exist)
-    tb0 += (part - 1) * SPLIT_TETS;
-    ntb_all = min(SPLIT_TETS, ntb_all - (part - 1) * SPLIT_TETS);
-  }
-  // A block whose shared site list overflows is redone in chunks of SUB tets (smaller boxes, shorter lists), and a
-  // chunk that still overflows one tet at a time, each with its own candidates found among all of the shape's
-  // sites. A tet then goes to the large-capacity kernel only for reasons that depend on its own candidates (more
-  // than fit the list, or the clip budget), never on its neighbours' or on sites that own nothing in it: an
-  // incremental update, which recomputes a tet's pieces to take them back, must take the path that added them.
-  int sub = 0, sub_n = ntb_all, single_end = 0;  // tets [sub, single_end): one at a time
-  bool split = false;
-  while (true) {
-  const int t0 = tb0 + sub;
-  const int ntb = sub_n;
-  const bool single = single_end > sub;
-  const unsigned long long cmask = item_mask >> sub;  // bit lt: tet t0 + lt is clipped
-  if (split && !(cmask & (ntb >= 64 ? ~0ull : (1ull << ntb) - 1ull))) {  // a chunk without such tets
-    if (!next_chunk(sub, sub_n, single_end, ntb_all)) break;
-    continue;
-  }
-  int tpt = 1;  // lanes per tet in the candidate phase
-  while (tpt < 64 && 2 * tpt * ntb <= 64) tpt *= 2;
-
-  // ---- 1. the tets' bounding box 
-  float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-  {
-    if (!single && tid < ntb && ((cmask >> tid) & 1ull)) {
-      const float4* tp = sd.tp + 4 * (size_t)(t0 + tid);
-      for (int v = 0; v < 4; ++v) {
-        float4 p = tp[v];
-        lo[0] = fminf(lo[0], p.x);
-        lo[1] = fminf(lo[1], p.y);
-        lo[2] = fminf(lo[2], p.z);
-        hi[0] = fmaxf(hi[0], p.x);
-        hi[1] = fmaxf(hi[1], p.y);
-        hi[2] = fmaxf(hi[2], p.z);
-      }
+  // the sites to look among: the block's group's, or all
+  const float4* src = a.site + sd.site_off;
+  const int* src_id = nullptr;
+  int nsrc = sd.ns;
+  if (a.grp_run) {
+    const int2 r = a.grp_run[sd.grp_off + (sd.grp ? sd.grp[blk] : blk)];
+    if (r.x >= 0) {
+      src = a.grp_site + r.x;
+      src_id = a.grp_id + r.x;
+      nsrc = r.y;
     }
   }
-  for (int k = 0; k < 3; ++k) {
-    lo[k] = wave_minf(lo[k]);
-    hi[k] = wave_maxf(hi[k]);
-  }
-  s_m[tid] = 0;
+  auto source = [&](int q, int& id) {
+    id = sd.site_off + (src_id ? src_id[q] : q);
+    return src[q];
+  };
+  const bool all_slow = (a.flags & RPD_FORCE_SLOW_PATH) != 0;
+  TetRun run{0, min(IT, ntb_all), 0, ntb_all, false};
+  do {
+  const int t0 = tb0 + run.sub;
+  const int ntb = run.n;
+  const unsigned long long cmask = item_mask >> run.sub;  // bit lt: tet t0 + lt is clipped
+  if (run.split && !(cmask & ((1ull << ntb) - 1ull))) continue;  // a chunk without such tets
+  __syncthreads();  // the shared arrays of the chunk before are free
+  if (tid < IT) s_m[tid] = 0;
   if (tid == 0) s_nsl = 0;
   __syncthreads();
+  bool tight = false;
+  if (!run.direct()) {
+    // ---- 1. the sites that can own a point of a box around the tets: min over the box of g_j <= min over j of max over
+    //         the box (g_j(x) = d_j(x) - |x - o|^2 with o the box's low corner is affine; values exact in FP64). The box
+    //         is the block's, or the chunk's own.
+    float lo[3], hi[3];
+    if (!run.split) {
+      const float* bx = sd.blkbox + 7 * (size_t)blk;
+      for (int k = 0; k < 3; ++k) {
+        lo[k] = bx[k];
+        hi[k] = bx[3 + k];
+      }
+    } else {
+      for (int k = 0; k < 3; ++k) {
+        lo[k] = INFINITY;
+        hi[k] = -INFINITY;
+      }
+      if (tid < ntb && ((cmask >> tid) & 1ull)) {
+        const float4* tp = sd.tp + 4 * (size_t)(t0 + tid);
+        for (int v = 0; v < 4; ++v) {
+          const float4 p = tp[v];
+          lo[0] = fminf(lo[0], p.x);
+          lo[1] = fminf(lo[1], p.y);
+          lo[2] = fminf(lo[2], p.z);
+          hi[0] = fmaxf(hi[0], p.x);
+          hi[1] = fmaxf(hi[1], p.y);
+          hi[2] = fmaxf(hi[2], p.z);
+        }
+      }
+      for (int k = 0; k < 3; ++k) {
+        lo[k] = wave_minf(lo[k]);
+        hi[k] = wave_maxf(hi[k]);
+      }
+    }
+    const double bx = lo[0], by = lo[1], bz = lo[2];
+    const double ex = (double)hi[0] - bx, ey = (double)hi[1] - by, ez = (double)hi[2] - bz;
+    auto range = [&](const float4& s, double& gmin, double& gmax) {
+      const double ax = (double)s.x - bx, ay = (double)s.y - by, az = (double)s.z - bz;
+      const double D = ax * ax + ay * ay + az * az - (double)s.w * s.w;
+      const double wx = -2.0 * ex * ax, wy = -2.0 * ey * ay, wz = -2.0 * ez * az;
+      gmin = D + fmin(0.0, wx) + fmin(0.0, wy) + fmin(0.0, wz);
+      gmax = D + fmax(0.0, wx) + fmax(0.0, wy) + fmax(0.0, wz);
+    };
+    double u = INFINITY;
+    for (int q = tid; q < nsrc; q += 64) {
+      double gmin, gmax;
+      range(src[q], gmin, gmax);
+      u = fmin(u, gmax);
+    }
+    u = wave_min(u);
+    int n = 0;
+    for (int q0 = 0; q0 < nsrc; q0 += 64) {
+      const int q = q0 + tid;
+      bool take = false;
+      int id = 0;
+      float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (q < nsrc) {
+        double gmin, gmax;
+        s = source(q, id);
+        range(s, gmin, gmax);
+        take = gmin <= u;
+      }
+      const unsigned long long mk = __ballot(take);
+      const int at = n + __popcll(mk & ((1ull << lane) - 1ull));
+      if (take && at < SLMAX) {
+        s_site[at] = s;
+        s_sid[at] = id;
+      }
+      n += __popcll(mk);
+    }
+    if (n > SLMAX && !all_slow) {
+      if (!run.split && tid == 0) stat_add(a, C_SPLIT, 1ull);
+      if (!run.split) run.chunks();
+      else run.directly();
+      run.sub -= run.n;  // next() comes back to the same tets
+      continue;
+    }
+    n = min(n, SLMAX);
+    __syncthreads();
+    // At most as many sites as a tet may keep candidates: no tet can be over the budget. The list is then cut down to
+    // the sites that no owner of a box corner or of the centre beats on the whole box (exact in FP64): such a site owns
+    // nothing here and its bisectors constrain no piece. (25 sites go down to 7 on the torus.)
+    tight = n <= a.kmax && !all_slow;
+    if (tight) {
+      const float4 s = s_site[min(lane, n - 1)];
+      const int id = s_sid[min(lane, n - 1)];
+      const double cx = 0.5 * ex + bx, cy = 0.5 * ey + by, cz = 0.5 * ez + bz;
+      const double ax = s.x - cx, ay = s.y - cy, az = s.z - cz;
+      const double Dc = ax * ax + ay * ay + az * az - (double)s.w * s.w;
+      bool keep = lane < n;
+      for (int c = 0; c < 9; ++c) {
+        // d at corner c (c = 8: the centre) up to a term common to all sites
+        const double d = c == 8 ? Dc : Dc - ((c & 1) ? ex : -ex) * ax - ((c & 2) ? ey : -ey) * ay - ((c & 4) ? ez : -ez) * az;
+        const double dmin = wave_min(lane < n ? d : INFINITY);
+        const int w = __builtin_ctzll(__ballot(lane < n && d == dmin));
+        const double Dw = __shfl(Dc, w);
+        const double fx = fabs((double)s.x - __shfl(s.x, w)), fy = fabs((double)s.y - __shfl(s.y, w)),
+                     fz = fabs((double)s.z - __shfl(s.z, w));
+        keep = keep && !(Dc - Dw > ex * fx + ey * fy + ez * fz);
+      }
+      const unsigned long long mk = __ballot(keep);
+      __syncthreads();
+      if (keep) {
+        const int at = __popcll(mk & ((1ull << lane) - 1ull));
+        s_site[at] = s;
+        s_sid[at] = id;
+      }
+      n = __popcll(mk);
+    }
+    if (tid == 0) s_nsl = n;
+    __syncthreads();
+  }
 
-  // ---- 2. sites that can own a point of the box: min over the box of g_j <= min over j of max over the box
-  //        (g_j(x) = d_j(x) - |x - o|^2 is affine; values exact in FP64); for a single tet, the same test on the
-  //        tet itself (its exact candidates)
-  const float4* ssite = a.site + sd.site_off;
-  if (single) {
-    const float4* tv = sd.tp + 4 * (size_t)t0;
+  // ---- 2. candidates of every tet: sites whose minimum over the tet is <= min_j max over the tet
+  int tpt = 2;  // lanes per tet
+  while (tpt < 64 && 2 * tpt * ntb <= 64) tpt *= 2;
+  const int lt = tid / tpt, h = tid % tpt;
+  auto tet_candidates = [&](int n, auto get, auto place, auto dominators) {  // get(q, id): site q; place(q, s, id): its
+    constexpr bool DOM = decltype(dominators)::value;                        // list position
+    const float4* tv = sd.tp + 4 * (size_t)(t0 + lt);
     const float4 o = tv[0];
     double y[3][3];
     for (int v = 1; v < 4; ++v) {
@@ -521,128 +733,24 @@ __global__ __launch_bounds__(64) void k_candidates(ShapeArgs a) {
       y[v - 1][1] = (double)tv[v].y - o.y;
       y[v - 1][2] = (double)tv[v].z - o.z;
     }
-    // the five dominators of the candidate phase among all of the shape's sites (lowest index on ties): the site
-    // attaining U and the owner of each vertex; a site one of them beats at all four vertices is not collected, so
-    // that the list holds the tet's exact candidates less those (which the candidate phase drops anyway)
-    double dv[5];
-    int dj[5];
-    for (int k = 0; k < 5; ++k) {
-      dv[k] = INFINITY;
-      dj[k] = 0x7fffffff;
-    }
-    for (int j = tid; j < sd.ns; j += 64) {
-      const float4 s = ssite[j];
-      const double ax_ = (double)s.x - o.x, ay_ = (double)s.y - o.y, az_ = (double)s.z - o.z;
-      double gq[4];
-      gq[0] = ax_ * ax_ + ay_ * ay_ + az_ * az_ - (double)s.w * s.w;
-      for (int v = 0; v < 3; ++v) gq[v + 1] = gq[0] - 2.0 * (y[v][0] * ax_ + y[v][1] * ay_ + y[v][2] * az_);
-      const double gmx = fmax(fmax(gq[0], gq[1]), fmax(gq[2], gq[3]));
-      for (int k = 0; k < 5; ++k) {
-        const double x = k == 0 ? gmx : gq[k - 1];
-        if (x < dv[k] || (x == dv[k] && j < dj[k])) {
-          dv[k] = x;
-          dj[k] = j;
-        }
-      }
-    }
-    for (int off = 32; off > 0; off >>= 1)
-      for (int k = 0; k < 5; ++k) {
-        const double x2 = __shfl_xor(dv[k], off);
-        const int j2 = __shfl_xor(dj[k], off);
-        if (x2 < dv[k] || (x2 == dv[k] && j2 < dj[k])) {
-          dv[k] = x2;
-          dj[k] = j2;
-        }
-      }
-    const double U = dv[0];
-    double gb[5][4];
-    for (int k = 0; k < 5; ++k) {
-      const float4 s = ssite[dj[k]];
-      const double ax_ = (double)s.x - o.x, ay_ = (double)s.y - o.y, az_ = (double)s.z - o.z;
-      gb[k][0] = ax_ * ax_ + ay_ * ay_ + az_ * az_ - (double)s.w * s.w;
-      for (int v = 0; v < 3; ++v) gb[k][v + 1] = gb[k][0] - 2.0 * (y[v][0] * ax_ + y[v][1] * ay_ + y[v][2] * az_);
-    }
-    for (int j = tid; j < sd.ns; j += 64) {
-      const float4 s = ssite[j];
-      const double ax_ = (double)s.x - o.x, ay_ = (double)s.y - o.y, az_ = (double)s.z - o.z;
-      double g[4];
+    const double ycx = (y[0][0] + y[1][0] + y[2][0]) * 0.25, ycy = (y[0][1] + y[1][1] + y[2][1]) * 0.25,
+                 ycz = (y[0][2] + y[1][2] + y[2][2]) * 0.25;
+    double ax_, ay_, az_;
+    auto values = [&](const float4& s, double* g) {
+      ax_ = (double)s.x - o.x;
+      ay_ = (double)s.y - o.y;
+      az_ = (double)s.z - o.z;
       g[0] = ax_ * ax_ + ay_ * ay_ + az_ * az_ - (double)s.w * s.w;
       for (int v = 0; v < 3; ++v) g[v + 1] = g[0] - 2.0 * (y[v][0] * ax_ + y[v][1] * ay_ + y[v][2] * az_);
-      const double gmn = fmin(fmin(g[0], g[1]), fmin(g[2], g[3]));
-      bool dom = false;
-      for (int k = 0; k < 5; ++k)
-        dom = dom || (g[0] > gb[k][0] && g[1] > gb[k][1] && g[2] > gb[k][2] && g[3] > gb[k][3]);
-      if (gmn <= U && !dom) {
-        const int q = atomicAdd(&s_nsl, 1);
-        if (q < SLMAX) {
-          s_site[q] = s;
-          s_sid[q] = sd.site_off + j;
-        }
-      }
-    }
-  } else {
-  const double bx = lo[0], by = lo[1], bz = lo[2];
-  const double ex = (double)hi[0] - bx, ey = (double)hi[1] - by, ez = (double)hi[2] - bz;
-  double umin = INFINITY;
-  for (int j = tid; j < sd.ns; j += 64) {
-    float4 s = ssite[j];
-    double ax_ = (double)s.x - bx, ay_ = (double)s.y - by, az_ = (double)s.z - bz;
-    double D = ax_ * ax_ + ay_ * ay_ + az_ * az_ - (double)s.w * s.w;
-    double gmax = D + fmax(0.0, -2.0 * ex * ax_) + fmax(0.0, -2.0 * ey * ay_) + fmax(0.0, -2.0 * ez * az_);
-    umin = fmin(umin, gmax);
-  }
-  const double UB = wave_min(umin);
-  for (int j = tid; j < sd.ns; j += 64) {
-    float4 s = ssite[j];
-    double ax_ = (double)s.x - bx, ay_ = (double)s.y - by, az_ = (double)s.z - bz;
-    double D = ax_ * ax_ + ay_ * ay_ + az_ * az_ - (double)s.w * s.w;
-    double gmin = D + fmin(0.0, -2.0 * ex * ax_) + fmin(0.0, -2.0 * ey * ay_) + fmin(0.0, -2.0 * ez * az_);
-    if (gmin <= UB) {
-      int q = atomicAdd(&s_nsl, 1);
-      if (q < SLMAX) {
-        s_site[q] = s;
-        s_sid[q] = sd.site_off + j;
-      }
-    }
-  }
-  }
-  __syncthreads();
-  const int nsl = s_nsl;
-  if (nsl > SLMAX && !(a.flags & RPD_FORCE_SLOW_PATH)) {
-    if (!split && ntb > SUB) {  // chunks of SUB tets
-      split = true;
-      sub_n = SUB;
-      if (tid == 0) stat_add(a, C_SPLIT, 1ull);
-      __syncthreads();
-      continue;
-    }
-    if (!single) {  // one tet at a time, each with its exact candidates
-      split = true;
-      single_end = sub + ntb;
-      sub_n = 1;
-      __syncthreads();
-      continue;
-    }
-  }
-  const bool block_overflow = nsl > SLMAX || (a.flags & RPD_FORCE_SLOW_PATH);
-
-  // ---- 3. candidates of every tet: sites whose minimum over the tet is <= min_j max over the tet
-  if (!block_overflow) {
-    const int lt = tid / tpt, h = tid % tpt;
-    if (lt < ntb && ((cmask >> lt) & 1ull)) {
-      const float4* tv = sd.tp + 4 * (size_t)(t0 + lt);
-      const float4 o = tv[0];
-      double y[3][3];
-      for (int v = 1; v < 4; ++v) {
-        y[v - 1][0] = (double)tv[v].x - o.x;
-        y[v - 1][1] = (double)tv[v].y - o.y;
-        y[v - 1][2] = (double)tv[v].z - o.z;
-      }
-      const double ycx = (y[0][0] + y[1][0] + y[2][0]) * 0.25, ycy = (y[0][1] + y[1][1] + y[2][1]) * 0.25,
-                   ycz = (y[0][2] + y[1][2] + y[2][2]) * 0.25;
-      // five dominators, each a site with its list position and id (the lowest id on ties, so that the choice does
-      // not depend on the list's order): [0] attains U = min over sites of the maximum of g over the tet, [1 + v]
-      // the minimum of g at vertex v (that vertex's owner)
+    };
+    double U;
+    // five dominators, each a site with its list position and id (the lowest id on ties, so that the choice does
+    // not depend on the list's order): [0] attains U = min over sites of the maximum of g over the tet, [1 + v]
+    // the minimum of g at vertex v (that vertex's owner). A site that one of them beats at all four vertices owns no
+    // point of the tet and its bisector constrains no piece (the dominator is a candidate, and its own bisector already
+    // does), so it is not a candidate; the same test among all candidates follows once they are sorted.
+    double gb[DOM ? 5 : 1][4];
+    if constexpr (DOM) {
       double dv[5];
       int dq[5], did[5];
       for (int k = 0; k < 5; ++k) {
@@ -650,14 +758,12 @@ __global__ __launch_bounds__(64) void k_candidates(ShapeArgs a) {
         dq[k] = 0;
         did[k] = 0x7fffffff;
       }
-      for (int q = h; q < nsl; q += tpt) {
-        float4 s = s_site[q];
-        double ax_ = (double)s.x - o.x, ay_ = (double)s.y - o.y, az_ = (double)s.z - o.z;
+      for (int q = h; q < n; q += tpt) {
+        int id;
+        const float4 s = get(q, id);
         double gq[4];
-        gq[0] = ax_ * ax_ + ay_ * ay_ + az_ * az_ - (double)s.w * s.w;
-        for (int v = 0; v < 3; ++v) gq[v + 1] = gq[0] - 2.0 * (y[v][0] * ax_ + y[v][1] * ay_ + y[v][2] * az_);
+        values(s, gq);
         const double gmx = fmax(fmax(gq[0], gq[1]), fmax(gq[2], gq[3]));
-        const int id = s_sid[q];
         for (int k = 0; k < 5; ++k) {
           const double x = k == 0 ? gmx : gq[k - 1];
           if (x < dv[k] || (x == dv[k] && id < did[k])) {
@@ -677,124 +783,182 @@ __global__ __launch_bounds__(64) void k_candidates(ShapeArgs a) {
             did[k] = id2;
           }
         }
-      const double U = dv[0];
-      if (a.tet_U && sd.sign > 0 && h == 0) a.tet_U[sd.tet_off + t0 + lt] = U;
-      // the dominators' g at the four vertices: a site that one of them beats at all four owns no point of the tet
-      // and its bisector constrains no piece (the dominator is a candidate, and its own bisector already does), so
-      // it is not a candidate; the same test among all candidates follows once they are sorted
-      double gb[5][4];
+      U = dv[0];
       for (int k = 0; k < 5; ++k) {
-        const float4 s = s_site[dq[k]];
-        const double ax_ = (double)s.x - o.x, ay_ = (double)s.y - o.y, az_ = (double)s.z - o.z;
-        gb[k][0] = ax_ * ax_ + ay_ * ay_ + az_ * az_ - (double)s.w * s.w;
-        for (int v = 0; v < 3; ++v) gb[k][v + 1] = gb[k][0] - 2.0 * (y[v][0] * ax_ + y[v][1] * ay_ + y[v][2] * az_);
+        int id;
+        values(get(dq[k], id), gb[k]);
       }
-      for (int q = h; q < nsl; q += tpt) {
-        float4 s = s_site[q];
-        double ax_ = (double)s.x - o.x, ay_ = (double)s.y - o.y, az_ = (double)s.z - o.z;
-        double g[4];
-        g[0] = ax_ * ax_ + ay_ * ay_ + az_ * az_ - (double)s.w * s.w;
-        for (int v = 0; v < 3; ++v) g[v + 1] = g[0] - 2.0 * (y[v][0] * ax_ + y[v][1] * ay_ + y[v][2] * az_);
-        const double gmn = fmin(fmin(g[0], g[1]), fmin(g[2], g[3]));
-        bool dom = false;
+    } else {
+      U = INFINITY;
+      for (int q = h; q < n; q += tpt) {
+        int id;
+        double gq[4];
+        values(get(q, id), gq);
+        U = fmin(U, fmax(fmax(gq[0], gq[1]), fmax(gq[2], gq[3])));
+      }
+      for (int off = 1; off < tpt; off <<= 1) U = fmin(U, __shfl_xor(U, off));
+    }
+    if (a.tet_U && sd.sign > 0 && h == 0) a.tet_U[sd.tet_off + t0 + lt] = U;
+    for (int q = h; q < n; q += tpt) {
+      int id;
+      const float4 s = get(q, id);
+      double g[4];
+      values(s, g);
+      const double gmn = fmin(fmin(g[0], g[1]), fmin(g[2], g[3]));
+      bool dom = false;
+      if constexpr (DOM)
         for (int k = 0; k < 5; ++k)
           dom = dom || (g[0] > gb[k][0] && g[1] > gb[k][1] && g[2] > gb[k][2] && g[3] > gb[k][3]);
-        const double D = g[0];
-        if (gmn <= U && !dom) {
-          int pos = atomicAdd(&s_m[lt], 1);
-          if (pos < KRAW) {
-            s_cand[lt][pos] = (unsigned char)q;
-            s_key[lt][pos] = (float)(D - 2.0 * (ycx * ax_ + ycy * ay_ + ycz * az_));
-          }
+      if (gmn <= U && !dom) {
+        const int pos = atomicAdd(&s_m[lt], 1);
+        if (pos < KRAW) {
+          s_raw[lt][pos] = (unsigned char)place(q, s, id);
+          s_key[lt][pos] = (float)(g[0] - 2.0 * (ycx * ax_ + ycy * ay_ + ycz * az_));
         }
       }
     }
+  };
+  const bool active = lt < ntb && ((cmask >> lt) & 1ull) && !all_slow;
+  auto from_list = [&](int q, int& id) {
+    id = s_sid[q];
+    return s_site[q];
+  };
+  auto in_list = [](int q, const float4&, int) { return q; };
+  if (run.direct()) {
+    if (active)
+      tet_candidates(nsrc, source,
+                     [&](int, const float4& s, int id) {
+                       const int at = atomicAdd(&s_nsl, 1);  // at most DIRECT x KRAW of them
+                       s_site[at] = s;
+                       s_sid[at] = id;
+                       return at;
+                     },
+                     std::true_type{});
+  } else if (tight) {
+    if (active) tet_candidates(s_nsl, from_list, in_list, std::false_type{});
+  } else if (active) {
+    tet_candidates(s_nsl, from_list, in_list, std::true_type{});
   }
   __syncthreads();
-  // sort each tet's candidates by (power distance at the centroid, site id) and drop the dominated ones
-  if (tid < ntb && ((cmask >> tid) & 1ull)) {
-    int m = s_m[tid];
-    if (!block_overflow && m <= KRAW) {
-      for (int x = 1; x < m; ++x) {
-        const float kx = s_key[tid][x];
-        const unsigned char cx = s_cand[tid][x];
-        const int ix = s_sid[cx];
-        int y = x - 1;
-        while (y >= 0 && (s_key[tid][y] > kx || (s_key[tid][y] == kx && s_sid[s_cand[tid][y]] > ix))) {
-          s_key[tid][y + 1] = s_key[tid][y];
-          s_cand[tid][y + 1] = s_cand[tid][y];
-          --y;
-        }
-        s_key[tid][y + 1] = kx;
-        s_cand[tid][y + 1] = cx;
-      }
-      m = refine_candidates(sd.tp + 4 * (size_t)(t0 + tid), s_site, s_cand[tid], s_key[tid], m);
+  // ---- 3. each tet's candidates sorted by (power distance at the centroid, site id), one lane per candidate ranking
+  //         it among its tet's, and the dominated ones dropped
+  const bool mine = tid < ntb && ((cmask >> tid) & 1ull);
+  int m = mine ? s_m[tid] : 0;
+  if (mine && all_slow) m = KRAW + 1;
+  {
+    const int mr = m <= KRAW ? m : 0;
+    int incl = mr;
+    for (int off = 1; off < IT; off <<= 1) {
+      const int v = __shfl_up(incl, off);
+      if (lane >= off) incl += v;
     }
+    if (tid < IT) s_off[tid] = (short)(incl - mr);
+    if (tid == IT - 1) s_off[IT] = (short)incl;
+  }
+  __syncthreads();
+  for (int e = tid; e < s_off[IT]; e += 64) {
+    int lo_ = 0, hi_ = IT - 1;  // the last tet with s_off <= e
+    while (lo_ < hi_) {
+      const int mid = (lo_ + hi_ + 1) >> 1;
+      if (s_off[mid] <= e) lo_ = mid;
+      else hi_ = mid - 1;
+    }
+    const int c = e - s_off[lo_], n = s_m[lo_];
+    const float kx = s_key[lo_][c];
+    const unsigned char cx = s_raw[lo_][c];
+    const int ix = s_sid[cx];
+    int rank = 0;
+    for (int x = 0; x < n; ++x) {
+      const float k = s_key[lo_][x];
+      rank += (k < kx || (k == kx && s_sid[s_raw[lo_][x]] < ix)) ? 1 : 0;
+    }
+    s_cand[lo_][rank] = cx;
+  }
+  __syncthreads();
+  if (mine) {
     // a tet over the budget goes to the large-capacity kernel, with its sorted, refined candidates when they fit the
     // list (else that kernel finds them among all sites); either way the choice depends on its own candidates only
-    if (block_overflow || m > a.kmax) stat_add(a, block_overflow ? C_DEFER_BLOCK : C_DEFER_KMAX, 1ull);
-    if (block_overflow || m > KRAW) {
-      m = -1;
+    const float4* tv = sd.tp + 4 * (size_t)(t0 + tid);
+    if (tight) m = refine_all(tv, s_site, s_cand[tid], m);
+    else if (m <= KRAW) m = refine_candidates(tv, s_site, s_cand[tid], m);
+    if (m > a.kmax) stat_add(a, all_slow ? C_DEFER_BLOCK : C_DEFER_KMAX, 1ull);
+    if (m > KRAW) {
+      m = 0;
       defer_item(a, shape, t0 + tid, -1, -1);
     }
     s_m[tid] = m;
   }
-  __syncthreads();
-  // pieces are laid out tet by tet with the tets ordered by candidate count, largest first: every piece of a tet
-  // loops over the same planes, so a wavefront's lanes then have similar trip counts
+  // ---- 4. piece slots, tet by tet with the tets ordered by candidate count, largest first: every piece of a tet
+  //         loops over the same planes, so a wavefront's lanes then have similar trip counts
   {
-    const int mt = tid < ntb ? max(s_m[tid], 0) : 0;
     int rank = 0, off = 0;
-    for (int u = 0; u < TB; ++u) {
-      const int mu = __shfl(mt, u);
-      if (mu > mt || (mu == mt && u < tid)) {
+    for (int u = 0; u < IT; ++u) {
+      const int mu = __shfl(m, u);
+      if (mu > m || (mu == m && u < tid)) {
         ++rank;
         off += mu;
       }
     }
-    s_order[rank] = (short)tid;
-    s_off[rank] = (short)off;
-    if (rank == TB - 1) s_off[TB] = (short)(off + mt);
+    __syncthreads();
+    if (tid < IT) {
+      s_order[rank] = (short)tid;
+      s_off[rank] = (short)off;
+      if (rank == IT - 1) s_off[IT] = (short)(off + m);
+    }
   }
   __syncthreads();
-  const int npairs = s_off[TB];
-  int base = 0;
-  if (lane == 0 && npairs) {
-    const unsigned long long q = atomicAdd(&a.counters[C_PIECE_SLOTS], (unsigned long long)npairs);
-    base = q + npairs <= (unsigned long long)a.pcap ? (int)q : -1;
-    if (base < 0) atomicOr(a.status, ST_TABLE_FULL);
+  const int npairs = s_off[IT];
+  // one cursor per lane: lane 0 the piece slots, lane 1 + c the class's pieces (a contiguous range of the item's, since
+  // its tets are ordered by candidate count)
+  int c0 = 0, c1 = npairs;
+  if (lane >= 1 && lane <= NCLASS) {
+    const int lim1 = min(class_first(lane), a.kmax + 1), lim0 = min(class_first(lane - 1), a.kmax + 1);
+    c0 = c1 = 0;
+    for (int q = 0; q < IT; ++q) {
+      const int mq = s_m[s_order[q]];
+      if (mq >= lim1) c0 = s_off[q + 1];
+      if (mq >= lim0) c1 = s_off[q + 1];
+    }
   }
-  base = __builtin_amdgcn_readfirstlane(base);
-  if (base >= 0) {
-    for (int p = tid; p < npairs; p += 64) {
-      int lo_ = 0, hi_ = TB - 1;  // last position j with s_off[j] <= p
+  long long at = 0;
+  if (lane <= NCLASS && c1 > c0)
+    at = (long long)atomicAdd(&a.counters[lane == 0 ? C_PIECE_SLOTS : C_CLASS + lane - 1], (unsigned long long)(c1 - c0));
+  const long long base_l = __shfl(at, 0);
+  if (base_l + npairs > (long long)a.pcap) {  // (the class cursors stay below the slots')
+    if (lane == 0) atomicOr(a.status, ST_TABLE_FULL);
+  } else {
+    const int base = (int)base_l;
+    for (int p0 = 0; p0 < npairs; p0 += 64) {
+      const int p = p0 + tid;
+      int lo_ = 0, hi_ = IT - 1;  // last position j with s_off[j] <= p
       while (lo_ < hi_) {
         const int mid = (lo_ + hi_ + 1) >> 1;
         if (s_off[mid] <= p) lo_ = mid;
         else hi_ = mid - 1;
       }
-      const int lt = s_order[lo_], first = s_off[lo_], m = s_m[lt];
-      a.psite[base + p] = s_sid[s_cand[lt][p - first]];
-      PieceDesc d;
-      d.t = t0 + lt;
-      d.shape = shape;
-      d.first = base + first;
-      d.m = m;
-      a.pdesc[base + p] = d;
-      if (p == first && a.tet_slots) a.tet_slots[sd.tet_off + t0 + lt] = make_int2(base + first, m);
-      if (m > a.kmax) {
-        if (p == first) defer_item(a, shape, t0 + lt, -1, base + first);
-      } else {
-        ++n_cand;
+      const int tl = s_order[lo_], first = s_off[lo_], mt = p < npairs ? s_m[tl] : 0;
+      int cl = 0;  // the piece's class
+      for (int c = 1; c < NCLASS; ++c) cl += mt >= class_first(c) ? 1 : 0;
+      const int cl_at = (int)__shfl(at, cl + 1), cl_c0 = __shfl(c0, cl + 1);
+      if (p < npairs) {
+        a.psite[base + p] = s_sid[s_cand[tl][p - first]];
+        PieceDesc d;
+        d.t = t0 + tl;
+        d.shape = shape;
+        d.first = base + first;
+        d.m = mt;
+        a.pdesc[base + p] = d;
+        if (p == first && a.tet_slots) a.tet_slots[sd.tet_off + t0 + tl] = make_int2(base + first, mt);
+        if (mt > a.kmax) {
+          if (p == first) defer_item(a, shape, t0 + tl, -1, base + first);
+        } else {
+          a.order[(size_t)cl * a.pcap + cl_at + (p - cl_c0)] = base + p;
+          ++n_cand;
+        }
       }
     }
   }
-  if (!split || !next_chunk(sub, sub_n, single_end, ntb_all)) break;
-  __syncthreads();  // the next chunk reuses every shared array
-  }
-  __syncthreads();  // the next item reuses every shared array
-  if (a.item_cost && tid == 0)  // the item's duration (every thread is past it), a scheduling hint for the next build
-    a.item_cost[item] = (unsigned)min(wall_clock64() - clock0, 0xffffffffull);
+  } while (run.next());
   }
   for (int off = 32; off > 0; off >>= 1) n_cand += __shfl_xor(n_cand, off);
   if (lane == 0 && n_cand) stat_add(a, C_CAND, n_cand);
@@ -808,7 +972,7 @@ __global__ __launch_bounds__(64) void k_candidates(ShapeArgs a) {
 //
 // A piece's terms are plain stores, no value of which the kernel waits for: with the sums and the element pieces
 // entered into hash tables here, a chunk spent most of its time on the round trips of those dependent atomics.
-constexpr int WIN = CHUNK + 2 * KRAW;  // candidate slots of the tets that a chunk touches
+constexpr int WIN = CHUNK + 2 * KMAX;  // candidates of the tets that a chunk touches
 
 template <typename T, int SLOTS>
 __global__ __launch_bounds__(64) void k_clip_pieces(ShapeArgs a) {
@@ -821,8 +985,12 @@ __global__ __launch_bounds__(64) void k_clip_pieces(ShapeArgs a) {
   __shared__ int s_nover;
   if (*a.status & ST_TABLE_FULL) return;  // some slots were never filled; the call is redone with larger buffers
   const int lane = threadIdx.x;
-  const int np_all = (int)min(a.counters[C_PIECE_SLOTS], (unsigned long long)a.pcap);
-  const int nchunks = (np_all + CHUNK - 1) / CHUNK;
+  // the chunks of the classes, the most candidates first (their chunks take longest)
+  int nc[NCLASS], nchunks = 0;
+  for (int c = 0; c < NCLASS; ++c) {
+    nc[c] = (int)a.counters[C_CLASS + c];
+    nchunks += (nc[c] + CHUNK - 1) / CHUNK;
+  }
   if (lane == 0) {
     s_nover = 0;
     if (blockIdx.x == 0) a.counters[C_CHUNKS] = (unsigned long long)nchunks;
@@ -830,21 +998,38 @@ __global__ __launch_bounds__(64) void k_clip_pieces(ShapeArgs a) {
   long long n_pairs = 0;
   unsigned long long n64 = 0;
   for (int chunk = blockIdx.x; chunk < nchunks; chunk += gridDim.x) {
-    const int p = chunk * CHUNK + lane;
-    const int last = min(CHUNK, np_all - chunk * CHUNK) - 1;
-    PieceDesc d = a.pdesc[chunk * CHUNK + min(lane, last)];
-    const bool run = lane <= last && d.m <= a.kmax;
-    // the candidates of the chunk's tets are consecutive slots
-    const int w0 = __shfl(d.first, 0), w1 = min(__shfl(d.first + d.m, last), w0 + WIN);
+    int cls = NCLASS - 1, k0 = chunk;
+    while (k0 >= (nc[cls] + CHUNK - 1) / CHUNK) {
+      k0 -= (nc[cls] + CHUNK - 1) / CHUNK;
+      --cls;
+    }
+    k0 *= CHUNK;
+    const int last = min(CHUNK, nc[cls] - k0) - 1;
+    const int p = a.order[(size_t)cls * a.pcap + k0 + min(lane, last)];
+    const PieceDesc d = a.pdesc[p];
+    const bool run = lane <= last;
+    // the candidates of the chunk's tets, tet by tet (a tet's pieces are consecutive entries): the lanes' own sites,
+    // what the first lane's tet has before it and what the last one's has after it
+    const int ci = p - d.first;
+    const int before = __shfl(ci, 0), after = __shfl(d.m - 1 - ci, last), p_first = __shfl(d.first, 0), p_last = __shfl(p, last);
     __syncthreads();
-    for (int q = w0 + lane; q < w1; q += 64) {
-      const int s = a.psite[q];
-      s_csid[q - w0] = s;
-      s_csite[q - w0] = a.site[s];
+    for (int q = lane; q < before + last + 1 + after; q += 64) {
+      const int e = q - before;  // relative to the chunk
+      const int s = e < 0 ? p_first + q : e > last ? p_last + (e - last) : -1;
+      if (s >= 0) {
+        const int id = a.psite[s];
+        s_csid[q] = id;
+        s_csite[q] = a.site[id];
+      }
+    }
+    if (run) {
+      const int id = a.psite[p];
+      s_csid[before + lane] = id;
+      s_csite[before + lane] = a.site[id];
     }
     __syncthreads();
     const ShapeDesc& sd = a.shapes[d.shape];
-    const int co = d.first - w0;
+    const int co = before + lane - ci;  // where the tet's candidates start
     auto bind = [&](TetEnv& env, int t, int c0, int ci) {
       env.tv = sd.tp + 4 * (size_t)t;
       env.o = env.tv[0];
@@ -911,9 +1096,10 @@ __global__ __launch_bounds__(64) void k_clip_pieces(ShapeArgs a) {
     const int nover = s_nover;
     if (nover) {
       if (lane < nover) {
-        const int src = s_over[lane];
-        const int pb = chunk * CHUNK + src;
+        const int src = s_over[lane];  // the lane that had the piece
+        const int pb = a.order[(size_t)cls * a.pcap + k0 + src];
         const PieceDesc db = a.pdesc[pb];
+        const int cb0 = before + src - (pb - db.first);
         const ShapeDesc& sb = a.shapes[db.shape];
         const int m = db.m;
         constexpr size_t CB = sizeof(typename Coord4<T>::type) * BIG_VCAP;
@@ -941,8 +1127,8 @@ __global__ __launch_bounds__(64) void k_clip_pieces(ShapeArgs a) {
             cb.env.tv = sb.tp + 4 * (size_t)db.t;
             cb.env.o = cb.env.tv[0];
             cb.env.face64 = sb.tf + 4 * (size_t)db.t;
-            cb.env.sid = s_csid + (db.first - w0);
-            cb.env.csite = s_csite + (db.first - w0);
+            cb.env.sid = s_csid + cb0;
+            cb.env.csite = s_csite + cb0;
             cb.env.site = nullptr;
             cb.env.ncs = INT_MAX;
             cb.env.ci = pb - db.first;
@@ -1260,13 +1446,14 @@ __global__ __launch_bounds__(64, LDS ? 1 : 2) void k_clip_slow(ShapeArgs a, unsi
 // chunks in grid-stride order (workgroups past the last chunk exit at once).
 template <typename T, int SLOTS>
 static hipError_t launch_pieces(const ShapeArgs& a, hipStream_t s) {
-  const int grid = std::max(1, std::min(a.pcap / CHUNK, 8192));
+  const int grid = std::max(1, std::min(chunk_cap(a.pcap), 8192));
   hipLaunchKernelGGL((k_clip_pieces<T, SLOTS>), dim3(grid), dim3(64), 0, s, a);
   return hipGetLastError();
 }
 
 hipError_t launch_candidates(const ShapeArgs& a, hipStream_t s) {
   if (a.nitems == 0) return hipSuccess;
+  if (a.ngrp > 0) hipLaunchKernelGGL(k_group_sites, dim3(a.ngrp), dim3(256), 0, s, a);
   hipLaunchKernelGGL(k_candidates, dim3(a.nitems), dim3(64), 0, s, a);
   return hipGetLastError();
 }

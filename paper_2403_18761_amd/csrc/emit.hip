@@ -9,6 +9,17 @@
 
 namespace rpd {
 
+// Workgroups go to the chip's eight dies in turn, each die with an L2 cache of its own: die x takes the x-th eighth of
+// the items, so that neighbouring items (pieces of neighbouring tets, which look at the same lines) share a cache.
+// f(k) for the items of this thread, in [0, n), by unit consecutive items.
+constexpr int DIES = 8;
+template <typename F>
+__device__ __forceinline__ void for_items(int n, int unit, int first, int step, F f) {  // first, step: among the die's threads
+  const int per = ((n + DIES - 1) / DIES + unit - 1) / unit * unit;
+  const int k0 = (int)(blockIdx.x % DIES) * per, k1 = min(n, k0 + per);
+  for (int k = k0 + first; k < k1; k += step) f(k);
+}
+
 // One element piece (element, tet) is emitted exactly once per shape: adding sets its gluing bits and count,
 // removing (the same piece recomputed from the state before an incremental update, sign -1) takes both back.
 // The two happen in one launch, in either order. Each records the piece's gluing bits in its own half of the
@@ -102,7 +113,10 @@ __device__ __forceinline__ void emit_cells(const ShapeArgs& a) {
   const int tid = threadIdx.x;
   const int np_all = (int)min(a.counters[C_PIECE_SLOTS], (unsigned long long)a.pcap);
   unsigned long long nodes = 0;
-  for (int base = blockIdx.x * EMIT_PIECES; base < np_all; base += gridDim.x * EMIT_PIECES) {
+  const int per = ((np_all + DIES - 1) / DIES + EMIT_PIECES - 1) / EMIT_PIECES * EMIT_PIECES;
+  const int end = min(np_all, (int)(blockIdx.x % DIES + 1) * per);
+  for (int base = (int)(blockIdx.x % DIES) * per + (int)(blockIdx.x / DIES) * EMIT_PIECES; base < end;
+       base += (int)(gridDim.x / DIES) * EMIT_PIECES) {
     S.site[tid] = -1;
     S.np[tid] = 0;
     S.chi[tid] = 0;
@@ -113,7 +127,7 @@ __device__ __forceinline__ void emit_cells(const ShapeArgs& a) {
     __syncthreads();
     for (int q = 0; q < EMIT_PIECES / EMIT_NT; ++q) {
       const int p = base + q * EMIT_NT + tid;
-      if (p >= np_all) break;
+      if (p >= end) break;
       const unsigned word = a.pref[p].word;
       if (!(word & 1u)) continue;
       const PieceOut o = a.pout[p];
@@ -233,17 +247,23 @@ template <typename F>
 __device__ __forceinline__ void for_records(const ShapeArgs& a, F f) {
   const int tid = threadIdx.x;
   if (blockIdx.y == 1) {
-    const int nchunks = (int)a.counters[C_CHUNKS];
     const int per = EMIT_NT / 64;
-    for (int c = blockIdx.x * per + (tid >> 6); c < nchunks; c += gridDim.x * per) {
-      const int n = a.chunk_recs[c];
-      for (int q = tid & 63; q < n; q += 64) f(c * REC_CHUNK + q);
-    }
+    for_items((int)a.counters[C_CHUNKS], 1, (int)(blockIdx.x / DIES) * per + (tid >> 6), (int)(gridDim.x / DIES) * per,
+              [&](int c) {
+                const int n = a.chunk_recs[c];
+                for (int q = tid & 63; q < n; q += 64) f(c * REC_CHUNK + q);
+              });
   } else {
     const int n = (int)min(a.counters[C_REC_POOL], (unsigned long long)a.pool_cap);
-    const int r0 = (a.pcap / CHUNK) * REC_CHUNK;
+    const int r0 = chunk_cap(a.pcap) * REC_CHUNK;
     for (int q = blockIdx.x * EMIT_NT + tid; q < n; q += gridDim.x * EMIT_NT) f(r0 + q);
   }
+}
+// f(p) for every piece slot
+template <typename F>
+__device__ __forceinline__ void for_pieces(const ShapeArgs& a, F f) {
+  for_items((int)min(a.counters[C_PIECE_SLOTS], (unsigned long long)a.pcap), EMIT_NT,
+            (int)(blockIdx.x / DIES) * EMIT_NT + threadIdx.x, (int)(gridDim.x / DIES) * EMIT_NT, f);
 }
 
 // One launch for everything (blockIdx.y: cells, the chunks' records, the pool's records). Bound by the random accesses
@@ -269,7 +289,7 @@ __global__ __launch_bounds__(EMIT_NT) void k_emit(ShapeArgs a) {
 }
 
 // The counts are known on the device only: a grid of the workgroups that fit the chip, grid-stride.
-static int pass_grid(const ShapeArgs& a) { return std::max(1, std::min(a.pcap / (4 * CHUNK), 2048)); }
+static int pass_grid(const ShapeArgs& a) { return DIES * std::max(1, std::min(a.pcap / (4 * CHUNK), 2048) / DIES); }
 
 hipError_t launch_emit(const ShapeArgs& a, hipStream_t s) {
   if (a.tet_slots) hipLaunchKernelGGL(k_emit<false>, dim3(pass_grid(a), 3), dim3(EMIT_NT), 0, s, a);
@@ -312,10 +332,11 @@ template <typename F>
 __device__ __forceinline__ void for_glued(const ShapeArgs& a, const PieceDesc& d, int i, int g, F f) {
   const ShapeDesc& sd = a.shapes[d.shape];
   const int4 nb = reinterpret_cast<const int4*>(sd.tn)[d.t];
+  // the boundary never carries a bit; the other side matches lower ids
+  g &= (nb.x > d.t ? 1 : 0) | (nb.y > d.t ? 2 : 0) | (nb.z > d.t ? 4 : 0) | (nb.w > d.t ? 8 : 0);
   for (; g; g &= g - 1) {
     const int face = __builtin_ctz(g);
     const int t2 = face == 0 ? nb.x : face == 1 ? nb.y : face == 2 ? nb.z : nb.w;
-    if (t2 < d.t) continue;  // the boundary never carries a bit; the other side matches lower ids
     const int4 nb2 = reinterpret_cast<const int4*>(sd.tn)[t2];
     const int2 run = a.tet_slots[sd.tet_off + t2];
     const int f2 = nb2.x == d.t ? 0 : nb2.y == d.t ? 1 : nb2.z == d.t ? 2 : 3;
@@ -337,11 +358,10 @@ __global__ __launch_bounds__(EMIT_NT) void k_glue_pieces(ShapeArgs a) {
   if (*a.status & ST_TABLE_FULL) return;
   unsigned long long bits = 0, pairs = 0;
   if (blockIdx.y == 0) {
-    const int np_all = (int)min(a.counters[C_PIECE_SLOTS], (unsigned long long)a.pcap);
-    for (int p = blockIdx.x * EMIT_NT + threadIdx.x; p < np_all; p += gridDim.x * EMIT_NT) {
+    for_pieces(a, [&](int p) {
       const unsigned w = a.pref[p].word;
       const int g = (w & 1u) ? pw_glue(w) & 15 : 0;
-      if (!g) continue;
+      if (!g) return;
       bits += __popc(g);
       for_glued(a, a.pdesc[p], a.psite[p], g, [&](int q, const PieceRef& ref, int bit) {
         if (!(pw_glue(ref.word) & bit)) {
@@ -351,7 +371,7 @@ __global__ __launch_bounds__(EMIT_NT) void k_glue_pieces(ShapeArgs a) {
         ++pairs;
         uf_union(a.pparent, p, q);
       });
-    }
+    });
   } else {
     for_records(a, [&](int r) {
       const ElemRec R = a.recs[r];
@@ -388,9 +408,9 @@ __global__ __launch_bounds__(EMIT_NT) void k_count_piece_roots(ShapeArgs a, int*
   if (blockIdx.y == 0) {
     if (blockIdx.x == 0 && threadIdx.x == 0 && stat_sum(a, C_GLUE_BITS) != 2 * stat_sum(a, C_GLUE_PAIRS))
       atomicOr(a.status, ST_INTERNAL);  // a gluing bit without its counterpart
-    const int np_all = (int)min(a.counters[C_PIECE_SLOTS], (unsigned long long)a.pcap);
-    for (int p = blockIdx.x * EMIT_NT + threadIdx.x; p < np_all; p += gridDim.x * EMIT_NT)
+    for_pieces(a, [&](int p) {
       if ((a.pref[p].word & 1u) && a.pparent[p] == p) atomicAdd(&cell_b0[a.psite[p]], 1);
+    });
     return;
   }
   for_records(a, [&](int r) {

@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 #include <rocprim/device/device_radix_sort.hpp>
 
+#include <algorithm>
 #include <cmath>
 #include <numeric>
 #include <vector>
@@ -281,6 +282,47 @@ __global__ void k_tet_roots(int* par, int nt, int* roots) {
   if (local) atomicAdd(roots, local);
 }
 
+// box of the tets of every block b, [blk[b], blk[b + 1]): low corner, high corner, and its squared diagonal rounded up
+__global__ __launch_bounds__(64) void k_block_boxes(const float4* tp, const int* blk, float* box) {
+  const int b = blockIdx.x;
+  float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+  for (long long q = 4ll * blk[b] + threadIdx.x; q < 4ll * blk[b + 1]; q += 64) {
+    const float4 p = tp[q];
+    lo[0] = fminf(lo[0], p.x);
+    lo[1] = fminf(lo[1], p.y);
+    lo[2] = fminf(lo[2], p.z);
+    hi[0] = fmaxf(hi[0], p.x);
+    hi[1] = fmaxf(hi[1], p.y);
+    hi[2] = fmaxf(hi[2], p.z);
+  }
+  float dd = 0.f;
+  for (int k = 0; k < 3; ++k) {
+    for (int off = 32; off > 0; off >>= 1) {
+      lo[k] = fminf(lo[k], __shfl_xor(lo[k], off));
+      hi[k] = fmaxf(hi[k], __shfl_xor(hi[k], off));
+    }
+    dd += (hi[k] - lo[k]) * (hi[k] - lo[k]);
+    if (threadIdx.x == 0) {
+      box[7 * (size_t)b + k] = lo[k];
+      box[7 * (size_t)b + 3 + k] = hi[k];
+    }
+  }
+  if (threadIdx.x == 0) box[7 * (size_t)b + 6] = dd * 1.000001f;
+}
+// box of the blocks [first[g], first[g + 1]) of every group g, with the largest squared diagonal among them
+__global__ void k_group_boxes(const float* blkbox, const int* first, int ng, float* box) {
+  for (int g = blockIdx.x * blockDim.x + threadIdx.x; g < ng; g += gridDim.x * blockDim.x) {
+    float v[7];
+    for (int k = 0; k < 7; ++k) v[k] = blkbox[7 * (size_t)first[g] + k];
+    for (int b = first[g] + 1; b < first[g + 1]; ++b)
+      for (int k = 0; k < 7; ++k) {
+        const float x = blkbox[7 * (size_t)b + k];
+        v[k] = k < 3 ? fminf(v[k], x) : fmaxf(v[k], x);
+      }
+    for (int k = 0; k < 7; ++k) box[7 * (size_t)g + k] = v[k];
+  }
+}
+
 static int gsz(size_t n) {
   size_t g = (n + 255) / 256;
   if (g > 65536) g = 65536;
@@ -465,6 +507,38 @@ void mesh_prepare(rpd_mesh* m, const rpd_mesh_desc* d, uint32_t flags, hipStream
     m->hblk = starts;
     m->blk.alloc(sizeof(int) * starts.size());
     hip_check(hipMemcpyAsync(m->blk.p, starts.data(), sizeof(int) * starts.size(), hipMemcpyHostToDevice, s), "upload");
+    for (int q = 0; q < 4; ++q) {
+      const int pt = TB >> q;
+      for (int b = 0; b < m->nblk; ++b) m->nparts[q] += (starts[b + 1] - starts[b] + pt - 1) / pt;
+    }
+    m->ngrp[0] = m->nblk;
+    m->grpbox[0].alloc(sizeof(float) * 7 * (size_t)m->nblk);
+    hipLaunchKernelGGL(k_block_boxes, dim3(m->nblk), dim3(64), 0, s, m->tp.as<float4>(), m->blk.as<int>(),
+                       m->grpbox[0].as<float>());
+    std::vector<int> grp[3], first[3];
+    DBuf dfirst[3];
+    // the runs of blocks inside one octree cell of about four and of about eight times the mean tet size
+    const int lv = std::max(0, (int)std::lround(std::log2(std::max(1.0, edge))));
+    for (int q = 1; q < 3; ++q) {
+      const int sh = std::min(63, std::max(shift, 3 * (lv + 1 + q)));
+      grp[q].resize(m->nblk);
+      for (int b = 0; b < m->nblk; ++b) {
+        if (b == 0 || (keys[starts[b]] >> sh) != (keys[starts[b - 1]] >> sh)) first[q].push_back(b);
+        grp[q][b] = (int)first[q].size() - 1;
+      }
+      m->ngrp[q] = (int)first[q].size();
+      first[q].push_back(m->nblk);
+      m->grp[q].alloc(sizeof(int) * (size_t)m->nblk);
+      m->grpbox[q].alloc(sizeof(float) * 7 * (size_t)m->ngrp[q]);
+      dfirst[q].alloc(sizeof(int) * first[q].size());
+      hip_check(hipMemcpyAsync(m->grp[q].p, grp[q].data(), sizeof(int) * grp[q].size(), hipMemcpyHostToDevice, s),
+                "upload");
+      hip_check(hipMemcpyAsync(dfirst[q].p, first[q].data(), sizeof(int) * first[q].size(), hipMemcpyHostToDevice, s),
+                "upload");
+      hipLaunchKernelGGL(k_group_boxes, dim3(gsz(m->ngrp[q])), dim3(256), 0, s, m->grpbox[0].as<float>(),
+                         dfirst[q].as<int>(), m->ngrp[q], m->grpbox[q].as<float>());
+    }
+    hip_check(hipGetLastError(), "block groups");
     hip_check(hipStreamSynchronize(s), "sync");
   }
   (void)hipGetDevice(&m->device);

@@ -12,10 +12,15 @@ constexpr int KMAX = 28;     // candidate sites per tet kept for clipping (plane
 constexpr int KRAW = 40;     // candidate sites per tet before the dominance refinement
 constexpr int SLMAX = 256;   // sites in a workgroup's shared candidate list
 constexpr int SUB = 8;       // tets per chunk when a block's site list overflows
-// Work items are (shape + (tet mask << 16), block + (part << ITEM_PART_SHIFT)): part 0 is the whole block, part
-// p >= 1 its tets [(p - 1) SPLIT_TETS, p SPLIT_TETS) (heavy blocks are dispatched in parts so that no workgroup sets
-// the kernel's tail). A nonzero tet mask (parts only) names the part's tets to clip, bit k for its tet k; zero
-// means all. Shapes per call < 2^16.
+constexpr int GROUP_CAP = 2048; // sites listed per group of blocks
+constexpr int ITEM_TETS = 32;   // tets per work item of the candidate kernel
+// Pieces are clipped in classes of tets with about as many candidates each, so that a wavefront's lanes do about the
+// same work: class c holds the tets with class_first(c) .. class_first(c + 1) - 1 candidates.
+constexpr int NCLASS = 6;
+__host__ __device__ constexpr int class_first(int c) { return c == 0 ? 1 : c == 1 ? 2 : c == 2 ? 3 : c == 3 ? 4 : c == 4 ? 6 : c == 5 ? 9 : 1 << 20; }
+// Listed work items are (shape + (tet mask << 16), block + (part << ITEM_PART_SHIFT)): part p >= 1 is the block's tets
+// [(p - 1) SPLIT_TETS, p SPLIT_TETS). A nonzero tet mask names the part's tets to clip, bit k for its tet k; zero means
+// all. Shapes per call < 2^16.
 constexpr int ITEM_PART_SHIFT = 20;  // blocks per mesh < 2^20
 constexpr int SPLIT_TETS = 16;       // = the width of the tet mask
 // Large-capacity (deferred) path.
@@ -45,8 +50,11 @@ enum {
   C_GLUE_BITS,    // gluing bits of the pieces whose components are (re)computed
   C_GLUE_PAIRS,   // glued pairs matched
   C_TERMS,        // per-piece element terms kept with RPD_KEEP_PIECES (cursor)
+  C_GROUP_SITES,  // entries of the groups' site lists (cursor)
   // the cursors of one clipping pass (an incremental pass resets the PASS_CURSORS of them together)
   C_PIECE_SLOTS,  // piece slots handed out
+  C_CLASS,        // pieces of each class
+  C_CLASS_END = C_CLASS + NCLASS - 1,
   C_CHUNKS,       // chunks of the piece kernel (the large-capacity kernel hands out slots after them)
   C_REC_POOL,     // element records outside the chunks' own ranges
   C_DEFER_ITEMS,  // items for the large-capacity kernel
@@ -177,11 +185,12 @@ struct ElemRec {
 };
 constexpr int REC_NONE = 0, REC_FACE = 1, REC_EDGE = 2, REC_RPV = 3, REC_SHIFT = 24;
 
-// Pieces are clipped 64 consecutive slots (a chunk) per wavefront. A chunk's records go to its own range of REC_CHUNK
+// Pieces are clipped 64 consecutive entries of a class (a chunk) per wavefront. A chunk's records go to its own range of REC_CHUNK
 // records when they fit (no cursor shared between wavefronts), else, like those of every piece computed outside its
 // chunk's pass, to the pool behind the chunks' ranges.
 constexpr int CHUNK = 64;
 constexpr int REC_CHUNK = 128;
+__host__ __device__ inline int chunk_cap(int pcap) { return pcap / CHUNK + NCLASS; }
 
 // per-piece record kept with RPD_KEEP_PIECES
 struct PieceRec {
@@ -210,6 +219,13 @@ struct ShapeDesc {
   long long L;
   int site_off, ns;    // sites [site_off, site_off + ns) of the batch
   long long tet_off;   // batch-global id of the shape's tet 0
+  const float* blkbox; // [7 nblk] box of every block (low corner, high corner; the seventh value as in grpbox)
+  // groups of neighbouring blocks that share a site list: the group of every block (null: every block is one), the
+  // groups' boxes with the largest squared diagonal of a block in the group, and the first group, the first work item
+  // and the parts per block of the shape in the call
+  const int* grp;
+  const float* grpbox;  // [7 ngrp]
+  int ngrp, grp_off, item_off, parts;
   int sign;            // +1: the shape's pieces are added; -1: an incremental update takes them back (the state
                        // before the round's insertions)
   int pad;
@@ -220,8 +236,14 @@ struct ShapeDesc {
 struct ShapeArgs {
   const ShapeDesc* shapes;
   int nshapes;
-  const int2* items;     // (shape, block and part) work items, heaviest first
+  const int2* items;     // (shape, block and part) work items, or null: every block of every shape in its parts
+  unsigned item_mul;     // item k of the grid is item k item_mul mod nitems (1, or coprime to nitems)
   int nitems;            // number of items, or the grid size when nitems_dev is set
+  int ngrp;              // groups of all shapes (0: no group lists)
+  int2* grp_run;         // [ngrp] first entry and length of a group's site list (-1: look at all sites), or null
+  float4* grp_site;      // [grp_cap] the listed sites and their ids (local to the shape)
+  int* grp_id;
+  int grp_cap;
   const int* nitems_dev; // optional: the item count in device memory (graph-captured rounds)
   // ---- sites (all shapes)
   int ns;
@@ -251,6 +273,7 @@ struct ShapeArgs {
   double* tet_U;         // optional [total tets]: U_t of the candidate test, kept for the incremental update
   PieceDesc* pdesc;      // [pcap] the pass's pieces
   int* psite;            // [pcap] their sites (batch-global)
+  int* order;            // [NCLASS][pcap] the piece slots of each class (a tet's one after the other)
   PieceOut* pout;        // [pcap]
   PieceRef* pref;        // [pcap]
   // Builds find components over the pieces and records themselves: the pieces that glue to a piece are found through
@@ -260,8 +283,8 @@ struct ShapeArgs {
   int* pparent;          // [pcap] union-find parents of the cells' pieces
   int* rparent;          // [records] and of the faces' and edges'
   int pcap;              // a whole number of chunks
-  ElemRec* recs;         // [pcap / CHUNK ranges of REC_CHUNK, then the pool]
-  int* chunk_recs;       // [pcap / CHUNK] records in the chunk's own range
+  ElemRec* recs;         // [chunk_cap(pcap) ranges of REC_CHUNK, then the pool]
+  int* chunk_recs;       // [chunk_cap(pcap)] records in the chunk's own range
   int pool_cap;          // records of the pool
   int4* deferred;        // items of the large-capacity path: (shape, local tet, piece slot or -1 for all of the tet's
                          // candidates, the tet's first piece slot or -1 when its candidates are yet to be found)
@@ -279,7 +302,6 @@ struct ShapeArgs {
   int* status;
   unsigned flags;        // RPD_FORCE_* / RPD_KEEP_PIECES as in rpd.h
   int kmax;              // fast-path candidate budget (<= KMAX)
-  unsigned* item_cost;   // optional [nitems]: wall-clock ticks each work item took in the candidate kernel
 };
 
 // shape of a batch-global id by binary search over the shapes' offsets
@@ -320,9 +342,8 @@ struct RoundState {
   int mode;                   // 0: caller's per-tet table, hashed pick; 1: shrunk spheres at the furthest surface face
   const int* tet_block;       // [nt] workgroup block of every tet
   unsigned long long* dirty;  // [nblk] per block, the mask of its dirty tets (bit k: the block's tet k)
-  const int* order;           // [nblk] blocks by their time in the initial build, heaviest first (scan order)
   const int* blk;             // [nblk + 1] first tet of every block
-  int2* items;                // [8 nblk] dirty (shape 0 or 1 and tet mask, block part) items, in about that order
+  int2* items;                // [8 nblk] dirty (shape 0 or 1 and tet mask, block part) items
   const int* clist;           // the live cell pieces' slots, per segment of clen table slots (the gluing pass
   const int* cseg;            // writes them): cseg[b] of them at clist[b clen]
   unsigned clen;

@@ -4,7 +4,6 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
-#include <mutex>
 #include <string>
 #include <vector>
 
@@ -92,10 +91,12 @@ struct rpd_mesh {
   rpd::DBuf blk;   // int [nblk + 1]: workgroup blocks over the internal order
   int32_t nblk = 0;
   std::vector<int> hblk;  // host copy of blk
-  // Fast-kernel time of every block in the last build that used this mesh: a dispatch-order hint for the next
-  // build (heaviest first); never read by any kernel.
-  std::mutex cost_mu;
-  std::vector<unsigned> blk_cost;
+  // Groups of blocks that share a site list: level 0: every block is one; levels 1 and 2: the blocks in an octree cell
+  // of about four and eight times the mean tet size. The group of every block, and the groups' boxes with the largest
+  // squared diagonal of a block in them.
+  rpd::DBuf grp[3], grpbox[3];  // int [nblk] (level 0: none); float [7 ngrp]
+  int32_t ngrp[3] = {0, 0, 0};
+  int32_t nparts[4] = {0, 0, 0, 0};  // nonempty parts when every block is taken in 1, 2, 4 or 8 parts
 };
 
 namespace rpd {

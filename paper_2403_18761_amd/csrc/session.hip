@@ -238,12 +238,10 @@ __global__ void k_mark_dirty(RoundState r, const float4* tp, int nt, const float
 // dirty tets -> work items, then clear the masks. Every part of SPLIT_TETS tets that holds a dirty tet becomes two
 // items with the mask of its dirty tets: in any other tet no new sphere owns a point, so none of its pieces change.
 // Dirty tets cluster where spheres go in, which is where the sites are densest, and parts spread them over more
-// workgroups. Any order gives the same sums (integers); the blocks are scanned heaviest first so that the items
-// come out in about that order, which shortens the clipping kernel's tail.
+// workgroups. Any order gives the same sums (integers).
 __global__ void k_dirty_items(RoundState r, int nblk) {
   static_assert(SPLIT_TETS == 16 && TB <= 64, "16-bit part masks of a 64-bit block mask");
-  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < nblk; k += gridDim.x * blockDim.x) {
-    const int b = r.order[k];
+  for (int b = blockIdx.x * blockDim.x + threadIdx.x; b < nblk; b += gridDim.x * blockDim.x) {
     const unsigned long long mask = r.dirty[b];
     if (!mask) continue;
     r.dirty[b] = 0;
