@@ -1,0 +1,38 @@
+// Counting sort of points into the cells of a grid, in Morton order (internal).
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "rpd_common.h"
+
+namespace rpd {
+
+// float -> unsigned with the same order (negative values included)
+__device__ inline unsigned order_bits(float f) {
+  const unsigned b = __float_as_uint(f);
+  return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
+}
+__device__ inline float from_order_bits(unsigned k) {
+  return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
+}
+
+// The cells are those of a 64^3 grid over the points' box, or, with directions, of a 32^3 grid for each of the six
+// dominant axes of a point's direction. Runs are at most len consecutive points of one coarse cell (64 cells), so that
+// no run spans a jump of the Morton curve: a few runs as wide as the whole set took longer than all others together.
+struct CellSort {
+  unsigned* box;   // [6] the points' box as order-preserving bits: low corner, complement of the high corner
+  int* n_runs;
+  int* tiles;      // per tile of cells, the first position
+  int* cells;      // per cell, the first position within its tile
+  int* order;      // [n] the points' indices by cell (any order within a cell)
+  int* rank;       // [n] a point's number in its cell
+  int2* runs;      // [cell_sort_runs(n, len)] first position and number; the first n_runs of them are in use
+};
+size_t cell_sort_runs(long long n, int len);
+size_t cell_sort_bytes(long long n, int len);
+CellSort cell_sort_layout(void* memory, long long n, int len);  // memory 8-byte aligned
+// point k is the mean of npt vectors (3 floats each) at pts + stride k; dirs: null, or 3 floats per point
+hipError_t launch_cell_sort(const float* pts, int stride, int npt, const float* dirs, int n, int len,
+                            const CellSort& S, hipStream_t s);
+
+}  // namespace rpd
