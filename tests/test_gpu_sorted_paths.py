@@ -1,7 +1,7 @@
-"""The sorted, culled path of rpd_envelope_distance against its brute-force path, which the same inputs take when they
-come in small parts (each below the rule's sizes). Both paths evaluate an element with the same expressions and take a
-minimum, so they differ at most by the contraction of those expressions: the bar is that of the comparison with the
-FP64 oracle (1e-5 + 1e-5 |d|)."""
+"""The sorted, culled paths of rpd_envelope_distance and rpd_shrink_spheres against their brute-force paths, which the
+same inputs take when they come in small parts (each below the rule's sizes). Both paths evaluate an element or a
+triangle with the same expressions and take a minimum, so they differ at most by the contraction of those expressions:
+the bars are those of the comparisons with the FP64 oracle (1e-5 + 1e-5 |d|; 1e-5 + 1e-4 r)."""
 import numpy as np
 import pytest
 
@@ -60,3 +60,38 @@ def test_envelope_sorted_matches_brute_force(case):
     tie = np.concatenate([p[1].cpu().numpy() for p in parts])
     _same(d, want, 1e-5 + 1e-5 * np.abs(want))
     np.testing.assert_array_equal(near[d == want], tie[d == want])
+
+
+@pytest.mark.parametrize("case", ["own", "no_own", "long", "short", "mixed", "not_finite", "degenerate"])
+def test_shrink_sorted_matches_brute_force(case):
+    import torch
+
+    from paper_2403_18761_amd import rpd
+
+    tri, n, cen, _, _ = synth.surface_pins(synth.torus_core(64, 64, 1))
+    tri, n, cen = (np.array(a, np.float32) for a in (tri, n, cen))
+    own = np.arange(len(tri), dtype=np.int32)
+    keep = np.arange(0, len(cen), 4)[:3001]  # ragged runs
+    n, cen, own = n[keep], cen[keep], own[keep]
+    if case in ("long", "short"):
+        n *= np.float32(1.7 if case == "long" else 0.6)
+    elif case == "mixed":
+        n[::2] *= np.float32(0.3)
+        n[::3] *= np.float32(5)
+    elif case == "not_finite":
+        tri[7, 0, 0], tri[11, 1, 2], tri[len(tri) // 2, 2, 1], tri[13] = np.inf, -np.inf, np.nan, 1e25
+    elif case == "degenerate":
+        tri[::5, 1] = tri[::5, 0]
+        tri[::7] = tri[0]
+    assert len(cen) >= 2048 and len(cen) * len(tri) >= 40_000_000
+    log(f"case: sorted shrinking {case}")
+    t, p, m = _dev(tri), _dev(cen), _dev(n)
+    o = None if case == "no_own" else _dev(own, torch.int32)
+    part = lambda a, k: None if a is None else a[k:k + 1000].contiguous()
+    got = rpd.shrink_spheres(t, p, m, o).cpu().numpy()
+    want = np.concatenate([rpd.shrink_spheres(t, part(p, k), part(m, k), part(o, k)).cpu().numpy()
+                           for k in range(0, len(cen), 1000)])
+    tol = 1e-5 + 1e-4 * np.abs(want[:, 3])
+    _same(got[:, 3], want[:, 3], tol)
+    for c in range(3):  # centre = pin + r normal
+        _same(got[:, c], want[:, c], tol * np.maximum(1, np.abs(n).max()))
