@@ -45,7 +45,7 @@ template <typename CL>
 struct EmitAcc {
   typedef typename CL::Real T;
   typedef typename CL::MaskT Mask;
-  long long sv, se;         // vertex and edge weights
+  MaskCounts w;             // vertices less edges (emit_out: plus faces) by their face mask
   T gx, gy, gz;             // vertex sums
   int nv;
   unsigned planes;          // planes present (Topo32: at most 32 of them)
@@ -56,11 +56,11 @@ struct EmitAcc {
 
 // vertex pass: vertex and edge weights, the first vertex of every face (kept in the clipper's table), the records
 template <typename CL>
-__device__ __forceinline__ void emit_scan(CL& c, const unsigned* nu, long long L, EmitAcc<CL>& e) {
+__device__ __forceinline__ void emit_scan(CL& c, EmitAcc<CL>& e) {
   typedef typename CL::TopoT Topo;
   typedef typename Topo::W W;
   const int i = c.env.site_i;  // batch-global site id
-  e.sv = e.se = 0;
+  e.w.lo = e.w.hi = 0;
   e.gx = e.gy = e.gz = 0;
   e.nv = e.nface = e.nedge = e.nrpv = 0;
   e.planes = 0;
@@ -74,7 +74,7 @@ __device__ __forceinline__ void emit_scan(CL& c, const unsigned* nu, long long L
     e.gz += v.z;
     ++e.nv;
     const int p0 = Topo::plane(w, 0), p1 = Topo::plane(w, 1), p2 = Topo::plane(w, 2);
-    e.sv += w_vertex(p0, p1, p2, nu, L);
+    e.w.add(face_bit(p0) | face_bit(p1) | face_bit(p2), 1);
     bool above[3];  // the plane is a bisector against a higher site
     for (int f = 0; f < 3; ++f) {
       const int p = Topo::plane(w, f);
@@ -88,7 +88,7 @@ __device__ __forceinline__ void emit_scan(CL& c, const unsigned* nu, long long L
     for (int f = 0; f < 3; ++f) {
       if (k < Topo::nb(w, f)) {
         const int f1 = f == 2 ? 0 : f + 1, f2 = f == 0 ? 2 : f - 1;
-        e.se += w_edge(Topo::plane(w, f1), Topo::plane(w, f2), nu, L);
+        e.w.add(face_bit(Topo::plane(w, f1)) | face_bit(Topo::plane(w, f2)), -1);
         if (above[f1] && above[f2]) {
           ++e.nedge;
           e.edge[f] |= CL::bit(k);
@@ -163,7 +163,6 @@ __device__ __forceinline__ void emit_out(CL& c, const ShapeDesc& sd, int tl, Emi
   const T ax = e.gx * inv_nv, ay = e.gy * inv_nv, az = e.gz * inv_nv;
 
   // ---- face cycles, by ascending plane (volume fans, face terms): one vertex per trip, the first of a face starts it
-  long long sf = 0;
   int cell_glue = 0;
   T vol = 0, mx = 0, my = 0, mz = 0;
   int rf = base;
@@ -181,7 +180,7 @@ __device__ __forceinline__ void emit_out(CL& c, const ShapeDesc& sd, int tl, Emi
   int p = next_face(-1);
   bool start = true, felem = false;
   int r = 0, nxt = 0, acur = 0, sp = -1, steps = 0, fglue = 0;
-  long long fchi = 0;
+  long long fchi = 0, fe = 0, fv = 0;  // fe, fv: read in one trip, added in the next (not waited for)
   T Rx = 0, Ry = 0, Rz = 0, Cx = 0, Cy = 0, Cz = 0;
   while (p >= 0) {
     if (start) {
@@ -192,6 +191,8 @@ __device__ __forceinline__ void emit_out(CL& c, const ShapeDesc& sd, int tl, Emi
     const auto N = c.st.get(nxt);
     const int epn = pos_of<Topo>(wn, p);
     const int ea = start ? 0 : pos_of<Topo>(wn, acur);
+    fchi += fv - fe;
+    fe = fv = 0;
     if (ea < 0 || epn < 0 || steps > CL::SLOTS) {  // a broken polytope: the call fails
       atomicOr(a.status, ST_INTERNAL);
       start = true;
@@ -203,7 +204,7 @@ __device__ __forceinline__ void emit_out(CL& c, const ShapeDesc& sd, int tl, Emi
     }
     if (start) {
       r = nxt;
-      sf += (p < 4) ? (long long)nu[10 + p] : L;
+      e.w.add(face_bit(p), 1);
       if (p < 4) cell_glue |= inner(p) ? 1 << p : 16 << p;  // glue across an interior face; boundary contact
       sp = c.env.plane_site(p);
       felem = p >= 4 && sp > i;
@@ -213,20 +214,21 @@ __device__ __forceinline__ void emit_out(CL& c, const ShapeDesc& sd, int tl, Emi
       Rx = N.x;
       Ry = N.y;
       Rz = N.z;
-      if (felem) fchi += wv_of<Topo>(wn, nu, L);
+      if (felem) fv = wv_of<Topo>(wn, nu, L);
       acur = Topo::plane(wn, epn == 2 ? 0 : epn + 1);
       nxt = Topo::nb(wn, epn == 0 ? 2 : epn - 1);
       start = false;
     } else {
       const bool closed = nxt == r;
       if (felem) {  // the edge to nxt lies on planes {p, acur}
-        fchi -= w_edge(p, acur, nu, L);
-        if (!closed) fchi += wv_of<Topo>(wn, nu, L);
+        fe = w_edge(p, acur, nu, L);
+        if (!closed) fv = wv_of<Topo>(wn, nu, L);
         fglue |= inner(acur);
       }
       if (closed) {
-        if (felem && rf < base + e.nface) put(rf++, sp, -1, (REC_FACE << REC_SHIFT) | fglue, fchi, 0.0);
+        if (felem && rf < base + e.nface) put(rf++, sp, -1, (REC_FACE << REC_SHIFT) | fglue, fchi - fe, 0.0);
         felem = false;
+        fe = 0;
         start = true;
         p = next_face(p);
       } else {
@@ -260,7 +262,7 @@ __device__ __forceinline__ void emit_out(CL& c, const ShapeDesc& sd, int tl, Emi
   out.mx = (double)mx * 0.25 + out.vol * o.x;
   out.my = (double)my * 0.25 + out.vol * o.y;
   out.mz = (double)mz * 0.25 + out.vol * o.z;
-  out.chi = e.sv - e.se + sf - L;
+  out.chi = e.w.sum(nu, L) - L;
   a.pout[p_slot] = out;
   PieceRef ref;
   ref.rec = base;
@@ -283,7 +285,7 @@ __device__ inline int pool_records(const ShapeArgs& a, int n) {
 template <typename CL>
 __device__ __forceinline__ void emit_alone(CL& c, const ShapeDesc& sd, int tl, int p_slot, const ShapeArgs& a) {
   EmitAcc<CL> e;
-  emit_scan(c, sd.nu + 14 * (size_t)tl, sd.L, e);
+  emit_scan(c, e);
   const int base = pool_records(a, e.records());
   if (base >= 0) emit_out(c, sd, tl, e, p_slot, base, a);
 }
@@ -1060,7 +1062,7 @@ __global__ __launch_bounds__(64) void k_clip_pieces(ShapeArgs a) {
       n64 += cl.n64;
       if (r == CLIP_OK) {
         n_pairs += sd.sign;  // live pieces
-        emit_scan(cl, sd.nu + 14 * (size_t)d.t, sd.L, e);
+        emit_scan(cl, e);
       } else {
         a.pref[p].word = 0;
         if (r == CLIP_DEFER) {

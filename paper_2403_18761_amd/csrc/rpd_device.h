@@ -555,6 +555,32 @@ __device__ inline long long w_edge(int p0, int p1, const unsigned* nu, long long
   return w_mask(face_bit(p0) | face_bit(p1), nu, L);
 }
 
+// A signed count of elements per face mask, 8 bits each (a piece of 64 vertices has at most 96 edges): the weights are
+// read once for their sum, where one read per element waited on memory in every trip of the emission's loops (piece
+// kernel on the 128^3 genus-3 solid: 1.59 -> 1.48 ms).
+struct MaskCounts {
+  unsigned long long lo, hi;  // sum of count << 8 mask, masks 0..7 and 8..15
+  __device__ void add(unsigned fm, int sign) {
+    const unsigned long long v = (unsigned long long)(long long)sign << (8 * (fm & 7u));
+    if (fm < 8) lo += v;
+    else hi += v;
+  }
+  __device__ long long sum(const unsigned* nu, long long L) const {
+    long long r = 0;
+    for (int half = 0; half < 2; ++half) {
+      unsigned long long x = half ? hi : lo;
+#pragma unroll
+      for (int f = 0; f < 8; ++f) {
+        const int c = (int)(signed char)(x & 0xffu);
+        x = (x - (unsigned long long)(long long)c) >> 8;  // the rest, its borrow returned
+        const unsigned fm = 8 * half + f, e = weight_entry(fm);
+        r += (long long)c * (e == 14u ? L : (long long)nu[e]);
+      }
+    }
+    return r;
+  }
+};
+
 // ---------------------------------------------------------------------------------------------------------------
 // hash tables (open addressing, linear probing)
 // ---------------------------------------------------------------------------------------------------------------
