@@ -690,6 +690,7 @@ struct Clipper {
   typedef Topo TopoT;
   typedef Mask MaskT;
   static constexpr int SLOTS = VCAP;
+  static constexpr int UNROLL = VCAP <= 16 ? VCAP / 4 : 1;  // of the loops over groups of four slots
   static constexpr bool FEW_PLANES = sizeof(W) == 4;  // Topo32: plane ids below 32
   typename StoreOf<T, Topo, VCAP>::type st;
   Tab tab;  // per plane id: 0 or (slot + 1); all zero between operations
@@ -753,13 +754,33 @@ struct Clipper {
   }
 
   __device__ int clip(int q, const Plane<T>& P) {
-    Mask out = 0;
+    // The sides of four slots at a time, live or not, so that their reads are in flight together (one slot at a time,
+    // each trip waited for its own); the undecided ones are resolved after them.
+    Mask out = 0, undecided = 0;
     const bool force = (flags & (RPD_FORCE_FP64 | RPD_FORCE_EXACT)) != 0;
-    for (Mask m = live; m; m &= m - 1) {
-      int k = ctz_mask(m);
-      typename Coord4<T>::type v = st.get(k);
-      int s = force ? 0 : side_fast(P, v.x, v.y, v.z, v.w);
-      if (s == 0) s = resolve(k, q);
+    static_assert(VCAP % 4 == 0, "groups of four slots");
+#pragma unroll UNROLL
+    for (int g = 0; g < VCAP; g += 4) {
+      if (!((live >> g) & (Mask)15)) continue;
+      typename Coord4<T>::type v[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) v[c] = st.get(g + c);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int s = side_fast(P, v[c].x, v[c].y, v[c].z, v[c].w);
+        if (s < 0) out |= bit(g + c);
+        if (s == 0) undecided |= bit(g + c);
+      }
+    }
+    out &= live;
+    undecided &= live;
+    if (force) {
+      out = 0;
+      undecided = live;
+    }
+    for (Mask m = undecided; m; m &= m - 1) {
+      const int k = ctz_mask(m);
+      const int s = resolve(k, q);
       if (s == 0) return CLIP_DEFER;
       if (s < 0) out |= bit(k);
     }
@@ -776,14 +797,20 @@ struct Clipper {
     // the lanes' crossings sit at different vertices)
     Mask cross[3] = {0, 0, 0};
     int ncross = 0;
-    for (Mask m = kept; m; m &= m - 1) {
-      const int k = ctz_mask(m);
-      const W w = st.topo(k);
-      for (int e = 0; e < 3; ++e)
-        if (out & bit(Topo::nb(w, e))) {
-          cross[e] |= bit(k);
-          ++ncross;
-        }
+#pragma unroll UNROLL
+    for (int g = 0; g < VCAP; g += 4) {
+      if (!((kept >> g) & (Mask)15)) continue;
+      W w[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) w[c] = st.topo(g + c);
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int e = 0; e < 3; ++e) cross[e] |= ((out >> (Topo::nb(w[c], e) & (8 * (int)sizeof(Mask) - 1))) & 1) << (g + c);
+    }
+    for (int e = 0; e < 3; ++e) {
+      cross[e] &= kept;
+      ncross += popc_mask(cross[e]);
     }
     if (ncross > popc_mask(freem)) return CLIP_FULL;  // out of vertex slots
     Mask added = 0;
