@@ -1218,6 +1218,8 @@ __global__ __launch_bounds__(64, LDS ? 1 : 2) void k_clip_slow(ShapeArgs a, unsi
   __shared__ float4 s_tv4[4];
   __shared__ double4 s_tf4[4];
   __shared__ float4 s_csite[SC];
+  constexpr int NDOM = 6;
+  __shared__ double s_dom[NDOM][4];
   if (*a.status & ST_TABLE_FULL) return;  // the call is redone with larger buffers
   const int n_main = (int)min(min(a.counters[C_DEFER_ITEMS], (unsigned long long)a.deferred_cap),
                               (unsigned long long)item_end);
@@ -1279,17 +1281,55 @@ __global__ __launch_bounds__(64, LDS ? 1 : 2) void k_clip_slow(ShapeArgs a, unsi
       __syncthreads();
     } else {
       // candidates among ALL sites of the shape (same exact test as the fast kernel)
-      double U = INFINITY;
+      // the sites least at each vertex, at the centre and in their largest vertex value: what one of these beats at all
+      // four vertices is left out of the list at once
+      double lv[NDOM];
+      int ls[NDOM];
+      for (int q = 0; q < NDOM; ++q) {
+        lv[q] = INFINITY;
+        ls[q] = 0;
+      }
       for (int j = lane; j < sd.ns; j += 64) {
         float4 s = ssite[j];
         double ax_ = (double)s.x - o.x, ay_ = (double)s.y - o.y, az_ = (double)s.z - o.z;
         double D = ax_ * ax_ + ay_ * ay_ + az_ * az_ - (double)s.w * s.w;
-        double gmx = D;
-        for (int v = 0; v < 3; ++v) gmx = fmax(gmx, D - 2.0 * (y[v][0] * ax_ + y[v][1] * ay_ + y[v][2] * az_));
-        U = fmin(U, gmx);
+        double g[NDOM];
+        g[0] = D;
+        g[4] = D;
+        for (int v = 0; v < 3; ++v) {
+          g[1 + v] = D - 2.0 * (y[v][0] * ax_ + y[v][1] * ay_ + y[v][2] * az_);
+          g[4] = fmax(g[4], g[1 + v]);
+        }
+        g[5] = D - 2.0 * (ycx * ax_ + ycy * ay_ + ycz * az_);
+        for (int q = 0; q < NDOM; ++q)
+          if (g[q] < lv[q]) {
+            lv[q] = g[q];
+            ls[q] = j;
+          }
       }
-      for (int off = 32; off > 0; off >>= 1) U = fmin(U, __shfl_xor(U, off));
+      for (int q = 0; q < NDOM; ++q)
+        for (int off = 32; off > 0; off >>= 1) {
+          const double v = __shfl_xor(lv[q], off);
+          const int j = __shfl_xor(ls[q], off);
+          if (v < lv[q] || (v == lv[q] && j < ls[q])) {
+            lv[q] = v;
+            ls[q] = j;
+          }
+        }
+      const double U = lv[4];
       if (a.tet_U && sd.sign > 0 && lane == 0) a.tet_U[sd.tet_off + t] = U;
+      __syncthreads();  // the last item's dominators have been read
+      if (lane < NDOM) {
+        int j = 0;
+        for (int q = 0; q < NDOM; ++q) j = lane == q ? ls[q] : j;
+        const float4 s = ssite[j];
+        const double ax_ = (double)s.x - o.x, ay_ = (double)s.y - o.y, az_ = (double)s.z - o.z;
+        const double D = ax_ * ax_ + ay_ * ay_ + az_ * az_ - (double)s.w * s.w;
+        s_dom[lane][0] = D;
+        for (int v = 0; v < 3; ++v) s_dom[lane][1 + v] = D - 2.0 * (y[v][0] * ax_ + y[v][1] * ay_ + y[v][2] * az_);
+      }
+      __syncthreads();
+      int raw = 0;  // candidates before that
       for (int base = 0; base < sd.ns; base += 64) {
         const int j = base + lane;
         bool take = false;
@@ -1298,9 +1338,16 @@ __global__ __launch_bounds__(64, LDS ? 1 : 2) void k_clip_slow(ShapeArgs a, unsi
           float4 s = ssite[j];
           double ax_ = (double)s.x - o.x, ay_ = (double)s.y - o.y, az_ = (double)s.z - o.z;
           double D = ax_ * ax_ + ay_ * ay_ + az_ * az_ - (double)s.w * s.w;
-          double gmn = D;
-          for (int v = 0; v < 3; ++v) gmn = fmin(gmn, D - 2.0 * (y[v][0] * ax_ + y[v][1] * ay_ + y[v][2] * az_));
+          double gmn = D, g[4];
+          g[0] = D;
+          for (int v = 0; v < 3; ++v) {
+            g[1 + v] = D - 2.0 * (y[v][0] * ax_ + y[v][1] * ay_ + y[v][2] * az_);
+            gmn = fmin(gmn, g[1 + v]);
+          }
           take = gmn <= U;
+          raw += take ? 1 : 0;
+          for (int q = 0; q < NDOM && take; ++q)
+            take = !(s_dom[q][0] < g[0] && s_dom[q][1] < g[1] && s_dom[q][2] < g[2] && s_dom[q][3] < g[3]);
           kk = D - 2.0 * (ycx * ax_ + ycy * ay_ + ycz * az_);
         }
         unsigned long long mask = __ballot(take);
@@ -1311,11 +1358,13 @@ __global__ __launch_bounds__(64, LDS ? 1 : 2) void k_clip_slow(ShapeArgs a, unsi
         }
         m += __popcll(mask);
       }
-      if (m > KC) {
-        if (lane == 0) {
-          if (LDS) push_overflow(a, di);
-          else atomicOr(a.status, ST_SLOW_CAPACITY);
-        }
+      for (int off = 32; off > 0; off >>= 1) raw += __shfl_xor(raw, off);
+      if (raw > SLOW_KMAX) {
+        if (lane == 0) atomicOr(a.status, ST_SLOW_CAPACITY);
+        continue;
+      }
+      if (m > KC) {  // (the LDS variant only)
+        if (lane == 0) push_overflow(a, di);
         continue;
       }
       __syncthreads();
