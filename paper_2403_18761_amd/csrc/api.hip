@@ -1255,7 +1255,7 @@ struct rpd_session {
   rpd::ShapeDesc hd{};
   rpd::DeviceState D;
   rpd::DBuf dshapes;  // [0] the shape before a round's insertions, [1] after them (the current state)
-  rpd::DBuf items, table, tet_block, dirty, sel, selpos, best, ref, tet_used, ints;
+  rpd::DBuf items, table, dirty, sel, selpos, best, ref, tet_used, ints;
   rpd::RoundState r{};
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
@@ -1353,14 +1353,10 @@ static bool session_init(rpd_session* S, const rpd_sites* sites, const rpd_sites
               "validate table");
     hip_check(hipStreamSynchronize(s), "synchronize");  // the staging buffers are released next
   }
-  std::vector<int> tb(nt);
-  for (int b = 0; b < nblk; ++b)
-    for (int t = m->hblk[b]; t < m->hblk[b + 1]; ++t) tb[t] = b;
   ShapeDesc two[2] = {S->hd, S->hd};
   two[0].sign = -1;  // the state before a round's insertions: its dirty pieces are taken back
   S->dshapes.alloc(sizeof(two));
   S->items.alloc(sizeof(int2) * 2 * (size_t)nblk * (TB / SPLIT_TETS));  // every dirty block in parts, twice
-  S->tet_block.alloc(sizeof(int) * (size_t)nt);
   S->dirty.alloc(sizeof(unsigned long long) * (size_t)nblk);
   S->sel.alloc(sizeof(int) * (size_t)S->max_insert);
   S->best.alloc(8 * (size_t)S->max_insert);
@@ -1368,7 +1364,6 @@ static bool session_init(rpd_session* S, const rpd_sites* sites, const rpd_sites
   S->selpos.alloc(sizeof(int) * (size_t)S->max_sites);
   S->ints.alloc(sizeof(int) * SI_COUNT);
   hip_check(hipMemcpyAsync(S->dshapes.p, two, sizeof(two), hipMemcpyHostToDevice, s), "upload");
-  hip_check(hipMemcpyAsync(S->tet_block.p, tb.data(), sizeof(int) * tb.size(), hipMemcpyHostToDevice, s), "upload");
   hip_check(launch_fill_i32(S->dirty.as<int>(), 0, 2 * (size_t)nblk, s), "fill");
   hip_check(launch_fill_i32(S->selpos.as<int>(), -1, S->max_sites, s), "fill");
   hip_check(launch_fill_i32(S->ints.as<int>(), 0, SI_COUNT, s), "fill");
@@ -1394,7 +1389,6 @@ static bool session_init(rpd_session* S, const rpd_sites* sites, const rpd_sites
   r.tet_used = S->tet_used.as<int>();
   r.table = S->table.as<float4>();
   r.mode = S->mode;
-  r.tet_block = S->tet_block.as<int>();
   r.dirty = S->dirty.as<unsigned long long>();
   r.items = S->items.as<int2>();
   r.blk = m->blk.as<int>();
@@ -1432,8 +1426,8 @@ static void session_round(rpd_session* S) {
   a.nitems = std::min(2 * m->nblk * (TB / SPLIT_TETS), 10 * cus);
   D.set_touch(a);
   D.set_touch(a_new);
-  hip_check(launch_round_front(S->r, a_new, D.cell_b0.as<int>(), m->tp.as<float4>(), m->nt,
-                               m->nblk, s),
+  hip_check(launch_round_front(S->r, a_new, D.cell_b0.as<int>(), m->tp.as<float4>(),
+                               m->grpbox[0].as<float>(), m->nblk, s),
             "round selection");
   clip_pass(S, a);
   hip_check(launch_touch_removed(a_new, s), "changed pieces");

@@ -504,7 +504,6 @@ void mesh_prepare(rpd_mesh* m, const rpd_mesh_desc* d, uint32_t flags, hipStream
     }
     starts.push_back(nt);
     m->nblk = (int)starts.size() - 1;
-    m->hblk = starts;
     m->blk.alloc(sizeof(int) * starts.size());
     hip_check(hipMemcpyAsync(m->blk.p, starts.data(), sizeof(int) * starts.size(), hipMemcpyHostToDevice, s), "upload");
     for (int q = 0; q < 4; ++q) {

@@ -340,7 +340,6 @@ struct RoundState {
                               // (internal tet, face) (mode 1)
   const int* perm;            // [nt] internal -> caller tet
   int mode;                   // 0: caller's per-tet table, hashed pick; 1: shrunk spheres at the furthest surface face
-  const int* tet_block;       // [nt] workgroup block of every tet
   unsigned long long* dirty;  // [nblk] per block, the mask of its dirty tets (bit k: the block's tet k)
   const int* blk;             // [nblk + 1] first tet of every block
   int2* items;                // [8 nblk] dirty (shape 0 or 1 and tet mask, block part) items

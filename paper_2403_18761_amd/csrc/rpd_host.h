@@ -90,7 +90,6 @@ struct rpd_mesh {
   rpd::DBuf perm;  // int [nt]: internal -> caller tet index
   rpd::DBuf blk;   // int [nblk + 1]: workgroup blocks over the internal order
   int32_t nblk = 0;
-  std::vector<int> hblk;  // host copy of blk
   // Groups of blocks that share a site list: level 0: every block is one; levels 1 and 2: the blocks in an octree cell
   // of about four and eight times the mean tet size. The group of every block, and the groups' boxes with the largest
   // squared diagonal of a block in them.

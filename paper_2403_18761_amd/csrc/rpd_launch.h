@@ -125,7 +125,7 @@ void shrink_spheres(const float* tri, long long nt, const float* pins, const flo
                     long long n, hipStream_t st, float4* out);
 // selection, insertion and dirty marking of one round; a supplies the element tables and sites of the new shape
 hipError_t launch_round_front(const RoundState& r, const ShapeArgs& a, const int* cell_b0,
-                              const float4* tp, int nt, int nblk, hipStream_t s);
+                              const float4* tp, const float* blkbox, int nblk, hipStream_t s);
 hipError_t launch_round_end(const RoundState& r, hipStream_t s);
 
 }  // namespace rpd

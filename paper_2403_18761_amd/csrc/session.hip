@@ -209,29 +209,58 @@ __global__ __launch_bounds__(1024) void k_insert(RoundState r, float4* site) {
   }
 }
 
-// a tet is dirty if one of the new spheres passes its exact candidate test against the stored U_t
-__global__ void k_mark_dirty(RoundState r, const float4* tp, int nt, const float4* site, const double* tet_U) {
+// A tet is dirty if one of the new spheres passes its exact candidate test against the stored U_t. One wavefront per
+// workgroup block, a lane per tet. First a lane per sphere: its value g_j(x) = d_j(x) - |x - o|^2 (x and o in the
+// block) is at least the least d_j over the block's box less the box's squared diagonal, and a sphere for which that
+// exceeds the largest U_t of the block passes no test. (700k tets, 64 spheres: 50 us with every tet testing every
+// sphere, 7.5 us this way.)
+__global__ __launch_bounds__(64) void k_mark_dirty(RoundState r, const float4* tp, const float* blkbox, int nblk,
+                                                   const float4* site, const double* tet_U) {
   const int n0 = r.old_desc->ns, n1 = r.new_desc->ns;
-  if (n1 == n0) return;
-  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < nt; t += gridDim.x * blockDim.x) {
-    const float4* tv = tp + 4 * (size_t)t;
-    const float4 o = tv[0];
-    const double U = tet_U[t];
-    bool dirty = false;
-    for (int j = n0; j < n1 && !dirty; ++j) {
-      float4 s = site[j];
-      double ax = (double)s.x - o.x, ay = (double)s.y - o.y, az = (double)s.z - o.z;
-      double D = ax * ax + ay * ay + az * az - (double)s.w * s.w;
-      double gmn = D;
-      for (int v = 1; v < 4; ++v)
-        gmn = fmin(gmn, D - 2.0 * (((double)tv[v].x - o.x) * ax + ((double)tv[v].y - o.y) * ay +
-                                   ((double)tv[v].z - o.z) * az));
-      dirty = gmn <= U;
+  const int lane = threadIdx.x;
+  for (int b = blockIdx.x; b < nblk; b += gridDim.x) {
+    const int t = r.blk[b] + lane;
+    const bool in = t < r.blk[b + 1];
+    const float* bx = blkbox + 7 * (size_t)b;
+    const double U = in ? tet_U[t] : -INFINITY;
+    double most = U;
+    for (int off = 32; off > 0; off >>= 1) most = fmax(most, __shfl_xor(most, off));
+    bool dirty = false, loaded = false;
+    double ox = 0, oy = 0, oz = 0, y[3][3] = {};
+    for (int base = n0; base < n1; base += 64) {
+      bool near = false;
+      if (base + lane < n1) {
+        const float4 s = site[base + lane];
+        const double dx = fmax(0.0, fmax((double)bx[0] - s.x, (double)s.x - bx[3])),
+                     dy = fmax(0.0, fmax((double)bx[1] - s.y, (double)s.y - bx[4])),
+                     dz = fmax(0.0, fmax((double)bx[2] - s.z, (double)s.z - bx[5]));
+        const double least = dx * dx + dy * dy + dz * dz - (double)s.w * s.w - bx[6];
+        near = !(least - 1e-9 * (1.0 + fabs(least)) > most);
+      }
+      unsigned long long m = __ballot(near);
+      if (m && !loaded) {
+        loaded = true;
+        const float4* tv = tp + 4 * (size_t)(in ? t : r.blk[b]);
+        ox = tv[0].x;
+        oy = tv[0].y;
+        oz = tv[0].z;
+        for (int v = 0; v < 3; ++v) {
+          y[v][0] = (double)tv[1 + v].x - ox;
+          y[v][1] = (double)tv[1 + v].y - oy;
+          y[v][2] = (double)tv[1 + v].z - oz;
+        }
+      }
+      for (; m; m &= m - 1) {
+        const float4 s = site[base + __builtin_ctzll(m)];
+        const double ax = s.x - ox, ay = s.y - oy, az = s.z - oz;
+        const double D = ax * ax + ay * ay + az * az - (double)s.w * s.w;
+        double gmn = D;
+        for (int v = 0; v < 3; ++v) gmn = fmin(gmn, D - 2.0 * (y[v][0] * ax + y[v][1] * ay + y[v][2] * az));
+        dirty = dirty || (in && gmn <= U);
+      }
     }
-    if (dirty) {
-      const int b = r.tet_block[t];
-      atomicOr(&r.dirty[b], 1ull << (t - r.blk[b]));
-    }
+    const unsigned long long mask = __ballot(dirty);  // bit k: the block's tet k
+    if (lane == 0 && mask) r.dirty[b] = mask;
   }
 }
 
@@ -355,7 +384,7 @@ hipError_t launch_scatter_spheres(const float4* sph, const int* slot, int n, flo
 
 // the round's selection and insertion (everything before the clip passes)
 hipError_t launch_round_front(const RoundState& r, const ShapeArgs& a, const int* cell_b0,
-                              const float4* tp, int nt, int nblk, hipStream_t s) {
+                              const float4* tp, const float* blkbox, int nblk, hipStream_t s) {
   hipLaunchKernelGGL(k_round_begin, dim3(1), dim3(64), 0, s, r);
   hipLaunchKernelGGL(k_select, dim3(1), dim3(256), 0, s, r, a.cell_chi, a.cell_np, cell_b0);
   const int scan = std::min(r.cnseg, SCAN_BLOCKS);
@@ -363,7 +392,7 @@ hipError_t launch_round_front(const RoundState& r, const ShapeArgs& a, const int
   hipLaunchKernelGGL(k_pick_tet, dim3(scan), dim3(256), sizeof(unsigned long long) * r.max_insert, s, a.N, cell_b0,
                      r, tp, a.site);
   hipLaunchKernelGGL(k_insert, dim3(1), dim3(1024), 0, s, r, (float4*)a.site);
-  hipLaunchKernelGGL(k_mark_dirty, dim3(gsz(nt)), dim3(256), 0, s, r, tp, nt, a.site, a.tet_U);
+  hipLaunchKernelGGL(k_mark_dirty, dim3(nblk), dim3(64), 0, s, r, tp, blkbox, nblk, a.site, a.tet_U);
   hipLaunchKernelGGL(k_dirty_items, dim3(gsz(nblk)), dim3(256), 0, s, r, nblk);
   return hipGetLastError();
 }
