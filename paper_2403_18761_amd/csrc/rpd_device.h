@@ -619,8 +619,17 @@ __device__ inline int ht_find(const HashTab& h, unsigned long long key) {
   return -1;
 }
 
+// A node's first slot: the low bits of its tet pick one in a group of NODE_GROUP slots, the rest of the key the group.
+// Neighbouring tets of an element, which the gluing looks up together, then share a line. Per round on 700k tets: gluing
+// 276 us (each key hashed by itself), 146 (groups of 4), 159 (8); the selection's scans 60, 35, 28 us; but emission 33,
+// 41, 56 us, its atomics meeting in a line.
+constexpr unsigned NODE_GROUP = 4;
+__device__ inline unsigned node_slot(unsigned long long key, unsigned mask) {
+  const unsigned low = (unsigned)key & (NODE_GROUP - 1);
+  return (hslot(key - low, mask) & ~(NODE_GROUP - 1)) | low;
+}
 __device__ inline int node_insert(const NodeTab& h, unsigned long long key, int* status) {
-  unsigned s = hslot(key, h.mask);
+  unsigned s = node_slot(key, h.mask);
   for (unsigned probe = 0; probe <= h.mask; ++probe) {
     unsigned long long prev = atomicCAS(&h.rec[s].key, EMPTY_KEY, key);
     if (prev == EMPTY_KEY || prev == key) return (int)s;
@@ -630,7 +639,7 @@ __device__ inline int node_insert(const NodeTab& h, unsigned long long key, int*
   return -1;
 }
 __device__ inline int node_find(const NodeTab& h, unsigned long long key) {
-  unsigned s = hslot(key, h.mask);
+  unsigned s = node_slot(key, h.mask);
   for (unsigned probe = 0; probe <= h.mask; ++probe) {
     unsigned long long k = h.rec[s].key;
     if (k == key) return (int)s;
