@@ -198,19 +198,24 @@ __global__ void k_link_verts(const int* kv, const int* ve, const int* vf, const 
   }
 }
 
-__global__ void k_presence(const int* kcount, int n, int* pres, int* used, int* st) {
+// (one addition per workgroup: one per thread queued at the counter, 188 us for 1M slots)
+__global__ __launch_bounds__(256) void k_presence(const int* kcount, int n, int* pres, int* used, int* st) {
+  __shared__ int s_used;
+  if (threadIdx.x == 0) s_used = 0;
+  __syncthreads();
   int local = 0;
   for (int s = blockIdx.x * blockDim.x + threadIdx.x; s < n; s += gridDim.x * blockDim.x) {
     int k = kcount[s];
     if (k <= 0) continue;
     ++local;
     if (k >= KPRES) atomicOr(st, MS_MESH);
-    else pres[k] = 1;
+    else if (!pres[k]) pres[k] = 1;
   }
-  if (local) atomicAdd(used, local);
+  for (int off = 32; off > 0; off >>= 1) local += __shfl_xor(local, off);
+  if ((threadIdx.x & 63) == 0 && local) atomicAdd(&s_used, local);
+  __syncthreads();
+  if (threadIdx.x == 0 && s_used) atomicAdd(used, s_used);
 }
-
-// owner of every vertex, edge and face: the lowest caller tet index among the tets containing it
 __global__ void k_owners(const int* itv, const int* tedge, const int* tface, const int* perm, int nt, int* ov,
                          int* oe, int* of) {
   for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < nt; k += gridDim.x * blockDim.x) {
@@ -256,22 +261,43 @@ __device__ inline int uf_find_m(int* par, int x) {
     x = p;
   }
 }
-__global__ void k_tet_uf_init(int* par, int nt) {
-  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < nt; k += gridDim.x * blockDim.x) par[k] = k;
+__device__ inline void uf_union_m(int* par, int x, int y) {
+  while (true) {
+    x = uf_find_m(par, x);
+    y = uf_find_m(par, y);
+    if (x == y) return;
+    if (x < y) {
+      const int t = x;
+      x = y;
+      y = t;
+    }
+    if (atomicCAS(&par[x], x, y) == x) return;
+  }
+}
+// Tets are united across their shared faces, in LDS within windows of consecutive (neighbouring) tets first, which
+// become flat trees, then across windows. 64^3 torus, 131k tets: 146 us without windows, 46 us with them.
+constexpr int UF_WINDOW = 1024;
+__global__ __launch_bounds__(256) void k_tet_uf_window(const int* tn, int nt, int* par) {
+  __shared__ int s_par[UF_WINDOW];
+  const int base = blockIdx.x * UF_WINDOW, m = min(UF_WINDOW, nt - base);
+  for (int k = threadIdx.x; k < m; k += 256) s_par[k] = k;
+  __syncthreads();
+  for (int k = threadIdx.x; k < m; k += 256) {
+    const int4 nb = reinterpret_cast<const int4*>(tn)[base + k];
+    for (int f = 0; f < 4; ++f) {
+      const int b = (f == 0 ? nb.x : f == 1 ? nb.y : f == 2 ? nb.z : nb.w) - base;
+      if (b > k && b < m) uf_union_m(s_par, k, b);
+    }
+  }
+  __syncthreads();
+  for (int k = threadIdx.x; k < m; k += 256) par[base + k] = base + uf_find_m(s_par, k);
 }
 __global__ void k_tet_uf(const int* tn, int nt, int* par) {
   for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < nt; k += gridDim.x * blockDim.x) {
+    const int4 nb = reinterpret_cast<const int4*>(tn)[k];
     for (int f = 0; f < 4; ++f) {
-      int b = tn[4 * (size_t)k + f];
-      if (b < 0 || b < k) continue;
-      int x = k, y = b;
-      while (true) {
-        x = uf_find_m(par, x);
-        y = uf_find_m(par, y);
-        if (x == y) break;
-        if (x < y) { int t = x; x = y; y = t; }
-        if (atomicCAS(&par[x], x, y) == x) break;
-      }
+      const int b = f == 0 ? nb.x : f == 1 ? nb.y : f == 2 ? nb.z : nb.w;
+      if (b > k && b / UF_WINDOW != k / UF_WINDOW) uf_union_m(par, k, b);
     }
   }
 }
@@ -428,12 +454,15 @@ void mesh_prepare(rpd_mesh* m, const rpd_mesh_desc* d, uint32_t flags, hipStream
   DBuf pres(sizeof(int) * (KPRES + 8));
   hip_check(hipMemsetAsync(pres.p, 0, sizeof(int) * (KPRES + 8), s), "memset");
   int* pp = pres.as<int>();
-  hipLaunchKernelGGL(k_presence, dim3(gsz(nv)), dim3(256), 0, s, kv.as<int>(), nv, pp, pp + KPRES, pst);
-  hipLaunchKernelGGL(k_presence, dim3(gsz(ecap)), dim3(256), 0, s, ke.as<int>(), (int)ecap, pp, pp + KPRES + 1, pst);
-  hipLaunchKernelGGL(k_presence, dim3(gsz(fcap)), dim3(256), 0, s, kf.as<int>(), (int)fcap, pp, pp + KPRES + 2, pst);
+  hipLaunchKernelGGL(k_presence, dim3(std::min(gsz(nv), 1024)), dim3(256), 0, s, kv.as<int>(), nv, pp, pp + KPRES, pst);
+  hipLaunchKernelGGL(k_presence, dim3(std::min(gsz(ecap), 1024)), dim3(256), 0, s, ke.as<int>(), (int)ecap, pp,
+                     pp + KPRES + 1, pst);
+  hipLaunchKernelGGL(k_presence, dim3(std::min(gsz(fcap), 1024)), dim3(256), 0, s, kf.as<int>(), (int)fcap, pp,
+                     pp + KPRES + 2, pst);
   // components
   DBuf par(sizeof(int) * nt);
-  hipLaunchKernelGGL(k_tet_uf_init, dim3(gsz(nt)), dim3(256), 0, s, par.as<int>(), nt);
+  hipLaunchKernelGGL(k_tet_uf_window, dim3((nt + UF_WINDOW - 1) / UF_WINDOW), dim3(256), 0, s, m->tn.as<int>(), nt,
+                     par.as<int>());
   hipLaunchKernelGGL(k_tet_uf, dim3(gsz(nt)), dim3(256), 0, s, m->tn.as<int>(), nt, par.as<int>());
   hipLaunchKernelGGL(k_tet_roots, dim3(gsz(nt)), dim3(256), 0, s, par.as<int>(), nt, pp + KPRES + 3);
   hip_check(hipGetLastError(), "mesh kernels");
