@@ -62,11 +62,12 @@ __device__ inline float edge_rho(float wx, float wy, float wz, float ex, float e
 
 // triangle records: (a, 0) (e1 = b - a, 0) (e2 = c - a, 0) (unit normal m, 0) (dual basis u1 of e1, e2) (u2), as six
 // float4, in FP64 then rounded; u1.e1 = 1, u1.e2 = 0 and u2 the other way round give barycentric coordinates
-// (record k: triangle order[k], or k without an order; bound, if not null: its bounding sphere)
+// (SORTED: record k is of triangle order[k], and bound[k] its bounding sphere; else of triangle k)
+template <bool SORTED>
 __global__ void k_shrink_prep(const float* tri, long long nt, const int* order, float4* rec, float4* bound) {
   for (long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x; t < nt; t += (long long)gridDim.x * blockDim.x) {
-    const float* v = tri + 9 * (order ? (long long)order[t] : t);
-    if (bound) {
+    const float* v = tri + 9 * (SORTED ? (long long)order[t] : t);
+    if (SORTED) {
       const float c[3] = {(v[0] + v[3] + v[6]) * (1.f / 3.f), (v[1] + v[4] + v[7]) * (1.f / 3.f),
                           (v[2] + v[5] + v[8]) * (1.f / 3.f)};
       float d2 = 0.f;
@@ -110,9 +111,9 @@ __global__ void k_shrink_prep(const float* tri, long long nt, const int* order, 
 }
 
 // the smallest rho over one triangle (its record) for the pin p with normal n
-__device__ __forceinline__ float triangle_rho(const float4& A, const float4& E1, const float4& E2, const float4& M,
-                                              const float4& U1, const float4& U2, float px, float py, float pz,
-                                              float nx, float ny, float nz) {
+// (by value: with references the brute-force loop got 16 instructions more)
+__device__ __forceinline__ float triangle_rho(float4 A, float4 E1, float4 E2, float4 M, float4 U1, float4 U2, float px,
+                                              float py, float pz, float nx, float ny, float nz) {
   // vertices
   const float wx = A.x - px, wy = A.y - py, wz = A.z - pz;
   float v = rho_of(wx, wy, wz, nx, ny, nz);
@@ -293,7 +294,8 @@ void shrink_spheres(const float* tri, long long nt, const float* pins, const flo
     hip_check(launch_cell_sort(tri, 9, 3, nullptr, (int)nt, 64, T, st), "sort triangles");
     hip_check(launch_cell_sort(pins, 3, 1, normals, (int)n, 64, P, st), "sort pins");
     const unsigned g = (unsigned)std::min<long long>((nt + 255) / 256, 4096);
-    hipLaunchKernelGGL(k_shrink_prep, dim3(g), dim3(256), 0, st, tri, nt, T.order, rec.as<float4>(), bound.as<float4>());
+    hipLaunchKernelGGL(k_shrink_prep<true>, dim3(g), dim3(256), 0, st, tri, nt, T.order, rec.as<float4>(),
+                       bound.as<float4>());
     hipLaunchKernelGGL(k_shrink_clusters, dim3((unsigned)std::min<size_t>((nc + 255) / 256, 4096)), dim3(256), 0, st,
                        bound.as<float4>(), (int)nt, cluster.as<float4>());
     hipLaunchKernelGGL(k_shrink_near, dim3((unsigned)cell_sort_runs(n, 64)), dim3(SHR_NEAR), 0, st, rec.as<float4>(),
@@ -303,8 +305,8 @@ void shrink_spheres(const float* tri, long long nt, const float* pins, const flo
   }
   hip_check(launch_fill_i32(bits.as<int>(), -1, (size_t)n, st), "fill");
   if (nt > 0) {
-    hipLaunchKernelGGL(k_shrink_prep, dim3((unsigned)std::min<long long>((nt + 255) / 256, 4096)), dim3(256), 0, st,
-                       tri, nt, (const int*)nullptr, rec.as<float4>(), (float4*)nullptr);
+    hipLaunchKernelGGL(k_shrink_prep<false>, dim3((unsigned)std::min<long long>((nt + 255) / 256, 4096)), dim3(256), 0,
+                       st, tri, nt, (const int*)nullptr, rec.as<float4>(), (float4*)nullptr);
     const long long blocks = (n + SHR_THREADS * SHR_R - 1) / (SHR_THREADS * SHR_R);
     long long chunks = std::max<long long>(1, std::min<long long>((2048 + blocks - 1) / blocks, nt / 32));
     chunks = std::min<long long>(chunks, 65535);
