@@ -36,9 +36,9 @@ def flop_per_piece(workload: str) -> float:
         return float(json.load(fh)[workload]["flop_per_piece"])
 
 
-# HBM traffic of the clipping kernel from rocprofv3 FETCH_SIZE / WRITE_SIZE runs (scaled by a plain copy of known
+# HBM traffic of the clipping kernels from rocprofv3 FETCH_SIZE / WRITE_SIZE runs (scaled by a plain copy of known
 # size), valid only for the kernel sources it was measured on.
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_k_clip_fast.json")
+TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_clip.json")
 KERNEL_SOURCES = ("clip.hip", "rpd_device.h", "rpd_common.h")
 
 
@@ -99,7 +99,7 @@ def workload(name):
 def time_builds(meshes, sites, precision, steps, warmup, stream, block=0, clip_budget=0, flags=0, slots=0):
     """Times `steps` rpd_build calls (each returns with its results on the host, its stream synchronised).
     Returns a dict: mean ms per call over the timed region, median and p90 of the per-call times, the mean
-    HIP-event time of the fast clipping kernel, the pieces and the last call's statistics."""
+    HIP-event time of the clipping kernels (group lists, candidates, pieces), the pieces and the last call's statistics."""
     import torch
 
     from paper_2403_18761_amd import rpd
@@ -261,7 +261,8 @@ FLOP_SPHERE, FLOP_CONE, FLOP_SLAB = 10, 29, 30
 
 def run_envelope(args, prob):
     """One step = one rpd_envelope_distance call over every sample (inputs resident on the device; distances only,
-    as the insertion test of Sec. 4.3 uses); value = sample-element evaluations per second."""
+    as the insertion test of Sec. 4.3 uses); value = (sample, element) pairs decided per second (evaluated, or passed
+    over by their bounding spheres)."""
     import torch
 
     from paper_2403_18761_amd import rpd, synth
@@ -291,7 +292,7 @@ def run_envelope(args, prob):
     flops = len(q) * (FLOP_SPHERE * len(S) + FLOP_CONE * len(E) + FLOP_SLAB * len(F))
     achieved = flops / (kernel_ms * 1e-3) / 1e12
     print(f"# envelope: {len(S)} spheres {len(E)} cones {len(F)} slabs, {len(q)} samples: {ms:.3f} ms/call, "
-          f"kernel {kernel_ms:.3f} ms, {achieved:.1f} TFLOP/s", file=sys.stderr, flush=True)
+          f"kernels {kernel_ms:.3f} ms", file=sys.stderr, flush=True)
     dist = d.cpu().numpy()
     return dict(value=len(q) * n_el / (ms * 1e-3), ms_per_step=ms, kernel_ms=kernel_ms, achieved=achieved,
                 counts=dict(spheres=len(S), cones=len(E), slabs=len(F), samples=len(q)),
@@ -353,7 +354,7 @@ def main():
     ap.add_argument("--no-fp64", action="store_true", help="skip the all-FP64 comparison")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-estimated", action="store_true",
-                    help="skip the timing of the same builds in the static-estimate dispatch order")
+                    help="no effect (there is one dispatch order: nothing is learned from earlier builds)")
     ap.add_argument("--no-autotune", action="store_true", help="use the default launch shape (64 threads, k=28, 16 vertex slots)")
     ap.add_argument("--launch", default=None, metavar="BLOCK,K[,SLOTS]",
                     help="use this launch shape (threads per workgroup, clip budget, vertex slots: 16 if not given) "
@@ -396,15 +397,17 @@ def main():
     if args.workload == "envelope":
         r = run_envelope(args, probs[0])
         line = {
-            "metric": "sample-element distance evaluations/sec of the geometric-error metric, 1 MI355X",
+            "metric": "sample-element pairs decided/sec of the geometric-error metric, 1 MI355X",
             "value": r["value"], "unit": "evaluations/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
             "ms_per_step": r["ms_per_step"], "higher_is_better": True, "scaling": "strong", "vs_baseline": None,
             "dtype": "f32", "data": "synthetic",
             "config": {"workload": WORKLOADS[args.workload]["desc"], "name": args.workload, **r["counts"]},
-            "roofline": {"bound": "alu", "achieved": r["achieved"], "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
-                         "frac": r["achieved"] / PEAK_FP32_TFLOPS, "traffic": None, "kernel": "k_env_dist",
-                         "kernel_ms": r["kernel_ms"],
-                         "flop_per_evaluation": {"sphere": FLOP_SPHERE, "cone": FLOP_CONE, "slab": FLOP_SLAB}},
+            # the pairs that bounding spheres decide are not evaluated, so the work done is not known from the sizes
+            # and no rate of the ALUs follows from them
+            "roofline": {"bound": "alu", "achieved": None, "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s", "frac": None,
+                         "traffic": None, "kernel": "k_env_near", "kernel_ms": r["kernel_ms"],
+                         "flop_per_evaluation": {"sphere": FLOP_SPHERE, "cone": FLOP_CONE, "slab": FLOP_SLAB},
+                         "tflops_if_all_pairs_were_evaluated": r["achieved"]},
             "checks": r["checks"],
         }
         if not args.no_cpu_baseline:
@@ -454,19 +457,11 @@ def main():
     pairs, st32 = f32["n_pairs"], f32["stats"]
     print(f"# fp32+fallback: {f32['ms']:.3f} ms/RPD (median {f32['ms_median']:.3f}, p90 {f32['ms_p90']:.3f}), clip "
           f"kernel {f32['clip_ms']:.3f} ms, pairs {pairs}", file=sys.stderr, flush=True)
-    # the same builds with the work dispatched by the static cost estimate (what a first build on a mesh uses)
-    est = None
-    if not args.no_estimated:
-        e = time_builds(meshes, sites, rpd.RPD_FP32_FALLBACK, args.steps, 1, stream, tuned["block"],
-                        tuned["clip_budget"], flags=rpd.RPD_ESTIMATED_ORDER, slots=tuned["slots"])
-        est = {"ms_per_rpd": e["ms"], "ms_median": e["ms_median"], "clip_kernel_ms": e["clip_ms"]}
-        print(f"# fp32+fallback, estimated dispatch order: {e['ms']:.3f} ms/RPD, clip kernel {e['clip_ms']:.3f} ms",
-              file=sys.stderr, flush=True)
-    # the same builds without dispatching heavy blocks in parts
+    # the same builds with whole blocks as work items of the candidate kernel
     ns_ = time_builds(meshes, sites, rpd.RPD_FP32_FALLBACK, args.steps, 1, stream, tuned["block"],
                       tuned["clip_budget"], flags=rpd.RPD_NO_SPLIT, slots=tuned["slots"])
     nosplit = {"ms_per_rpd": ns_["ms"], "ms_median": ns_["ms_median"], "clip_kernel_ms": ns_["clip_ms"]}
-    print(f"# fp32+fallback, heavy blocks not split: {ns_['ms']:.3f} ms/RPD, clip kernel {ns_['clip_ms']:.3f} ms",
+    print(f"# fp32+fallback, whole blocks as work items: {ns_['ms']:.3f} ms/RPD, clip kernel {ns_['clip_ms']:.3f} ms",
           file=sys.stderr, flush=True)
     out64 = None
     if not args.no_fp64:
@@ -479,7 +474,8 @@ def main():
 
     fpp = flop_per_piece(args.workload)
     achieved = fpp * pairs / (f32["clip_ms"] * 1e-3) / 1e12
-    kernel = f"k_clip_fast<float,{tuned['block']},{tuned['slots'] if tuned['block'] == 64 else 16}>"
+    # ms_clip covers the group lists, the candidate kernel and the piece kernel
+    kernel = f"k_candidates + k_clip_pieces<float,{tuned['slots'] if tuned['block'] == 64 else 16}>"
     cnt = measured_counters(args.workload, kernel, tuned) if len(probs) == 1 else None
     roof = {"bound": "alu", "achieved": achieved, "peak": PEAK_FP32_TFLOPS, "unit": "TFLOP/s",
             "frac": achieved / PEAK_FP32_TFLOPS, "traffic": cnt["bytes_per_launch"] if cnt else None,
@@ -509,7 +505,7 @@ def main():
                    "n_tets": sum(p.n_tets for p in probs), "n_sites": sum(p.n_sites for p in probs),
                    "n_pairs": pairs, "launch": tuned},
         "ms_per_rpd": {"mean": f32["ms"], "median": f32["ms_median"], "p90": f32["ms_p90"]},
-        "estimated_order": est,
+        "estimated_order": None,
         "all_fp64": out64,
         "stats": {k: st32[k] for k in ("n_candidates", "n_deferred", "n_fp64", "n_exact", "n_faces", "n_edges",
                                        "n_rpv", "n_defer_block", "n_defer_kmax", "n_defer_clip", "n_split", "n_items", "n_big",
