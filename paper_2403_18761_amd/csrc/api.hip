@@ -279,6 +279,8 @@ struct DeviceState {
       L.add(cell_b0.p, 0, ns, 4);
       L.add(face_b0.p, 0, capF, 4);
       L.add(edge_b0.p, 0, capE, 4);
+      // (not every tet of a refused call gets slots, and the gluing looks up its neighbours')
+      L.add(tet_slots.p, 0, (size_t)nt_tot, 8);
     }
     L.add(cnt(), 0, NCOUNTERS + 8 + (size_t)NSPREAD * NCOUNTERS, 8);
     if (touch.p) L.add(touch.p, 0, touch_words(), 4);

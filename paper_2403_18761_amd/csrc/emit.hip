@@ -271,7 +271,7 @@ __device__ __forceinline__ void for_pieces(const ShapeArgs& a, F f) {
 // element piece goes into the table N as well.
 template <bool HASH>
 __global__ __launch_bounds__(EMIT_NT) void k_emit(ShapeArgs a) {
-  if (*a.status & ST_TABLE_FULL) return;  // some slots were never filled; the call is redone with larger buffers
+  if (*a.status) return;  // the call fails or is redone: slots may be unfilled, and tets without any
   if (blockIdx.y == 0) {
     emit_cells<HASH>(a);
     return;
@@ -341,6 +341,10 @@ __device__ __forceinline__ void for_glued(const ShapeArgs& a, const PieceDesc& d
     const int2 run = a.tet_slots[sd.tet_off + t2];
     const int f2 = nb2.x == d.t ? 0 : nb2.y == d.t ? 1 : nb2.z == d.t ? 2 : 3;
     int q = -1;
+    if (run.x < 0 || run.y < 0 || run.y > a.pcap - run.x) {  // not a run of piece slots
+      atomicOr(a.status, ST_INTERNAL);
+      continue;
+    }
     for (int c = 0; c < run.y; ++c)
       if (a.psite[run.x + c] == i) {
         q = run.x + c;
@@ -355,7 +359,7 @@ __device__ __forceinline__ void for_glued(const ShapeArgs& a, const PieceDesc& d
 // Every gluing bit matched and united. A tet's pieces sit in consecutive slots, in the spatial order of the tets, so
 // a lookup reads a few neighbouring lines, where one in a hash table of all element pieces reads a random one.
 __global__ __launch_bounds__(EMIT_NT) void k_glue_pieces(ShapeArgs a) {
-  if (*a.status & ST_TABLE_FULL) return;
+  if (*a.status) return;
   unsigned long long bits = 0, pairs = 0;
   if (blockIdx.y == 0) {
     for_pieces(a, [&](int p) {
@@ -404,7 +408,7 @@ __global__ __launch_bounds__(EMIT_NT) void k_glue_pieces(ShapeArgs a) {
 
 // one root per component
 __global__ __launch_bounds__(EMIT_NT) void k_count_piece_roots(ShapeArgs a, int* cell_b0, int* face_b0, int* edge_b0) {
-  if (*a.status & ST_TABLE_FULL) return;
+  if (*a.status) return;
   if (blockIdx.y == 0) {
     if (blockIdx.x == 0 && threadIdx.x == 0 && stat_sum(a, C_GLUE_BITS) != 2 * stat_sum(a, C_GLUE_PAIRS))
       atomicOr(a.status, ST_INTERNAL);  // a gluing bit without its counterpart
