@@ -978,7 +978,7 @@ __global__ __launch_bounds__(64, 3) void k_candidates(ShapeArgs a) {
   if (lane <= NCLASS && c1 > c0)
     at = (long long)atomicAdd(&a.counters[lane == 0 ? C_PIECE_SLOTS : C_CLASS + lane - 1], (unsigned long long)(c1 - c0));
   const long long base_l = __shfl(at, 0);
-  if (base_l + npairs > (long long)a.pcap) {  // (the class cursors stay below the slots')
+  if (base_l + npairs > (long long)a.pcap) {
     if (lane == 0) atomicOr(a.status, ST_TABLE_FULL);
   } else {
     const int base = (int)base_l;
@@ -993,7 +993,8 @@ __global__ __launch_bounds__(64, 3) void k_candidates(ShapeArgs a) {
       const int tl = s_order[lo_], first = s_off[lo_], mt = p < npairs ? s_m[tl] : 0;
       int cl = 0;  // the piece's class
       for (int c = 1; c < NCLASS; ++c) cl += mt >= class_first(c) ? 1 : 0;
-      const int cl_at = (int)__shfl(at, cl + 1), cl_c0 = __shfl(c0, cl + 1);
+      const long long cl_at = __shfl(at, cl + 1);
+      const int cl_c0 = __shfl(c0, cl + 1);
       if (p < npairs) {
         a.psite[base + p] = s_sid[s_cand[tl][p - first]];
         PieceDesc d;
@@ -1006,7 +1007,10 @@ __global__ __launch_bounds__(64, 3) void k_candidates(ShapeArgs a) {
         if (mt > a.kmax) {
           if (p == first) defer_item(a, shape, t0 + tl, -1, base + first);
         } else {
-          a.order[(size_t)cl * a.pcap + cl_at + (p - cl_c0)] = base + p;
+          // (items that found no slots have advanced the class cursors too, maybe before this one)
+          const long long o = cl_at + (p - cl_c0);
+          if (o < (long long)a.pcap) a.order[(size_t)cl * a.pcap + o] = base + p;
+          else atomicOr(a.status, ST_TABLE_FULL);
           ++n_cand;
         }
       }
