@@ -432,6 +432,7 @@ __device__ inline float wave_maxf(float v) {
 // against a bound at most min_s max d_s, and |x - o| is at most the block's diagonal: a site left out here fails them
 // all, so the search finds what it would among all sites.
 __global__ __launch_bounds__(256) void k_group_sites(ShapeArgs a) {
+  if (*a.status & ST_INVALID) return;
   __shared__ double s_red[4];
   __shared__ int s_list[GROUP_CAP];
   __shared__ int s_n, s_at;
@@ -597,6 +598,8 @@ __global__ __launch_bounds__(64, 3) void k_candidates(ShapeArgs a) {
   __shared__ short s_order[IT];
   __shared__ int s_nsl;
 
+  // (a shape of NaNs has no site that reaches anything: its lists would be empty)
+  if (*a.status & ST_INVALID) return;
   const int tid = threadIdx.x, lane = tid;
   const int nitems = a.nitems_dev ? *a.nitems_dev : a.nitems;
   unsigned long long n_cand = 0;

@@ -65,3 +65,32 @@ def test_some_tets_over_the_candidate_limit(N, n, precision):
         after = extract(rpd.build([mesh], [sites(few)], precision=precision), 0)
         for k in ELEMENT_ARRAYS:
             np.testing.assert_array_equal(before[k], after[k], err_msg=k)
+
+
+@pytest.mark.parametrize("bad", ["all_nan", "one_nan", "infinite", "off_grid"])
+@pytest.mark.parametrize("n", [40, 600])
+def test_invalid_sites(bad, n):
+    """Sites the kernels must not search among: over 512 of them make groups of blocks share site lists."""
+    from paper_2403_18761_amd import rpd
+
+    p = synth.cube_random(N=4, n_sites=n, seed=4)
+    log(f"case: invalid sites {bad}, {n}")
+    mesh = _mesh(p)
+    sites = [np.array(a) for a in (p.sx, p.sy, p.sz, p.sr)]
+    before = extract(rpd.build([mesh], [tuple(_dev(a) for a in sites)]), 0)
+    if bad == "all_nan":
+        sites[0][:] = np.nan
+    elif bad == "one_nan":
+        sites[3][n // 2] = np.nan
+    elif bad == "infinite":
+        sites[1][0] = np.inf
+    else:
+        sites[2][-1] = 0.1
+    for shapes in (1, 3):  # in a batch, beside valid shapes
+        ok = tuple(_dev(a) for a in (p.sx, p.sy, p.sz, p.sr))
+        with pytest.raises(rpd.RPDError) as e:
+            rpd.build([mesh] * shapes, [ok] * (shapes - 1) + [tuple(_dev(a) for a in sites)])
+        assert e.value.code == -1
+        after = extract(rpd.build([mesh], [ok]), 0)
+        for k in ELEMENT_ARRAYS:
+            np.testing.assert_array_equal(before[k], after[k], err_msg=k)
