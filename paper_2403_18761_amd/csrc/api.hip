@@ -881,10 +881,7 @@ static bool run_batch(const rpd_mesh* const* meshes, const rpd_sites* sites, int
     a.grp_id = grp_id.as<int>();
     a.grp_cap = (int)grp_cap;
   }
-  struct DrainOnExit {  // an early exit (exception) must not release what the queued work still uses
-    hipStream_t s;
-    ~DrainOnExit() { (void)hipStreamSynchronize(s); }
-  } drain{s};
+  const DrainOnExit drain{s};
   Timing tm((o.flags & RPD_TIMING) != 0);
   tm.mark(0, s);
   hip_check(launch_candidates(a, s), "candidate kernel");
@@ -1310,16 +1307,14 @@ static bool session_init(rpd_session* S, const rpd_sites* sites, const rpd_sites
   D.clear(s);
   std::vector<ShapeDesc> hd{S->hd};
   const SiteUpload su = upload_sites(D, sites, hd, dev, s);
-  struct DrainOnExit {  // the upload's buffers are released only after the stream has drained
-    hipStream_t s;
-    ~DrainOnExit() { (void)hipStreamSynchronize(s); }
-  } drain{s};
+  const DrainOnExit drain{s};
   const size_t nslots = S->mode ? 4 * (size_t)nt : (size_t)nt;
   S->tet_used.alloc(sizeof(int) * nslots);
   hip_check(launch_fill_i32(S->tet_used.as<int>(), S->mode ? 1 : 0, nslots, s), "fill");
   if (S->mode) {  // shrunk spheres at every surface face (the pins), on the grid
     DBuf tri(36 * 4 * (size_t)nt), pin(12 * 4 * (size_t)nt), nrm(12 * 4 * (size_t)nt), slot(16 * (size_t)nt),
         own(16 * (size_t)nt), cnt(sizeof(int)), sph;
+    const DrainOnExit drain{s};
     hip_check(launch_fill_i32(cnt.as<int>(), 0, 1, s), "fill");
     hip_check(launch_surface_faces(m->tp.as<float4>(), m->tn.as<int>(), nt, tri.as<float>(), pin.as<float>(),
                                    nrm.as<float>(), slot.as<int>(), cnt.as<int>(), s),

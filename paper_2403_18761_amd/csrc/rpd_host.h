@@ -73,6 +73,14 @@ struct DBuf {
   }
 };
 
+// Waits for a stream on leaving a scope. Device buffers go back to a pool that every thread and stream draws from, so
+// none may be released while queued work still uses it: declared after them, this runs before their destructors, also
+// when an exception leaves the scope.
+struct DrainOnExit {
+  hipStream_t s;
+  ~DrainOnExit() { (void)hipStreamSynchronize(s); }
+};
+
 }  // namespace rpd
 
 // the prepared mesh (opaque in the public header)

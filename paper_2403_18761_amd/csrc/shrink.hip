@@ -280,16 +280,21 @@ __global__ void k_shrink_finish(const unsigned* bits, const float* pin, const fl
 
 }  // namespace
 
+// Returns when the spheres are there: the workspaces, whose sorted orders the kernels index with, go back to the pool.
 void shrink_spheres(const float* tri, long long nt, const float* pins, const float* normals, const int* own,
                     long long n, hipStream_t st, float4* out) {
-  DBuf rec(16 * 6 * (size_t)std::max<long long>(nt, 1)), bits(4 * (size_t)std::max<long long>(n, 1));
   if (n == 0) return;
+  DBuf rec(16 * 6 * (size_t)std::max<long long>(nt, 1)), bits(4 * (size_t)n), bound, cluster, ts, ps;
+  const DrainOnExit drain{st};
   // The sorts and the starting radii are a fixed cost that brute force passes at about 40M pairs: of the 15,384 triangles
   // of a 64^3 torus, 2,000 pins take 320 us by brute force, 4,000 take 564 us and 364 us sorted, all 2,108 and 398 us.
   // Few pins on many triangles fill the chip badly (1,000 on 65k triangles: 555 us by brute force, 595 us sorted).
   if (n >= 2048 && n < (1ll << 30) && nt < (1ll << 28) && n * nt >= 40000000ll) {
     const size_t nc = (size_t)(nt + SHR_CLUSTER - 1) / SHR_CLUSTER;
-    DBuf bound(16 * (size_t)nt), cluster(16 * nc), ts(cell_sort_bytes(nt, 64)), ps(cell_sort_bytes(n, 64));
+    bound.alloc(16 * (size_t)nt);
+    cluster.alloc(16 * nc);
+    ts.alloc(cell_sort_bytes(nt, 64));
+    ps.alloc(cell_sort_bytes(n, 64));
     const CellSort T = cell_sort_layout(ts.p, nt, 64), P = cell_sort_layout(ps.p, n, 64);
     hip_check(launch_cell_sort(tri, 9, 3, nullptr, (int)nt, 64, T, st), "sort triangles");
     hip_check(launch_cell_sort(pins, 3, 1, normals, (int)n, 64, P, st), "sort pins");
@@ -301,6 +306,7 @@ void shrink_spheres(const float* tri, long long nt, const float* pins, const flo
     hipLaunchKernelGGL(k_shrink_near, dim3((unsigned)cell_sort_runs(n, 64)), dim3(SHR_NEAR), 0, st, rec.as<float4>(),
                        bound.as<float4>(), cluster.as<float4>(), T.order, (int)nt, pins, normals, own, P, out);
     hip_check(hipGetLastError(), "shrink");
+    hip_check(hipStreamSynchronize(st), "synchronize");
     return;
   }
   hip_check(launch_fill_i32(bits.as<int>(), -1, (size_t)n, st), "fill");
@@ -317,6 +323,7 @@ void shrink_spheres(const float* tri, long long nt, const float* pins, const flo
   hipLaunchKernelGGL(k_shrink_finish, dim3((unsigned)std::min<long long>((n + 255) / 256, 4096)), dim3(256), 0, st,
                      bits.as<unsigned>(), pins, normals, n, out);
   hip_check(hipGetLastError(), "shrink finish");
+  hip_check(hipStreamSynchronize(st), "synchronize");
 }
 
 }  // namespace rpd
@@ -339,6 +346,7 @@ extern "C" rpd_status rpd_shrink_spheres(const float* tris, int64_t n_tris, cons
     } else {
       rpd::DBuf t(36 * (size_t)n_tris), p(12 * (size_t)n_pins), q(12 * (size_t)n_pins), o(4 * (size_t)n_pins),
           out(16 * (size_t)n_pins);
+      const rpd::DrainOnExit drain{st};
       if (n_tris) rpd::hip_check(hipMemcpyAsync(t.p, tris, 36 * (size_t)n_tris, hipMemcpyHostToDevice, st), "upload");
       rpd::hip_check(hipMemcpyAsync(p.p, pins, 12 * (size_t)n_pins, hipMemcpyHostToDevice, st), "upload");
       rpd::hip_check(hipMemcpyAsync(q.p, normals, 12 * (size_t)n_pins, hipMemcpyHostToDevice, st), "upload");
@@ -347,8 +355,8 @@ extern "C" rpd_status rpd_shrink_spheres(const float* tris, int64_t n_tris, cons
       rpd::shrink_spheres(t.as<float>(), n_tris, p.as<float>(), q.as<float>(), own_tri ? o.as<int>() : nullptr, n_pins,
                           st, out.as<float4>());
       rpd::hip_check(hipMemcpyAsync(spheres, out.p, 16 * (size_t)n_pins, hipMemcpyDeviceToHost, st), "download");
+      rpd::hip_check(hipStreamSynchronize(st), "synchronize");
     }
-    rpd::hip_check(hipStreamSynchronize(st), "synchronize");
     return RPD_OK;
   } catch (const rpd::Failure& f) {
     rpd::set_error(f.msg);
