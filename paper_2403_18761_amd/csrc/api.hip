@@ -826,8 +826,15 @@ static bool run_batch(const rpd_mesh* const* meshes, const rpd_sites* sites, int
   for (int k = 0; k < nsh; ++k) nsites[k] = sites[k].n_sites;
   long long ns_tot = 0, nt_tot = 0;
   std::vector<ShapeDesc> hd = shape_table(meshes, nsites.data(), nsh, &ns_tot, &nt_tot);
-  // the tables are cleared on the device while the host prepares the launches
+  // the shape table and the site sources go up in one copy from pinned memory
+  const size_t off_src = (sizeof(ShapeDesc) * nsh + 15) / 16 * 16;
+  const size_t stage_bytes = off_src + sizeof(SiteSrc) * nsh;
   DeviceState D;
+  DBuf dstage(stage_bytes), grp_run, grp_site, grp_id;
+  HostPinned stage(stage_bytes);
+  SiteUpload su;
+  const DrainOnExit drain{s};
+  // the tables are cleared on the device while the host prepares the launches
   D.alloc(nsh, (int)ns_tot, nt_tot, scale, (o.flags & RPD_KEEP_PIECES) != 0, false, fast_slots(o));
   D.clear(s);
   long long nblk = 0, nitems_all = 0, ngrp = 0, grp_cap = 0, nparts = 0;
@@ -850,13 +857,8 @@ static bool run_batch(const rpd_mesh* const* meshes, const rpd_sites* sites, int
   const int nitems = (int)nitems_all;
   if (most <= 512) ngrp = 0;  // every block looks at the few sites itself
   grp_cap = std::min(grp_cap, 1ll << 28);  // (a list that finds no room: its blocks look at all sites)
-  // the shape table and the site sources go up in one copy from pinned memory; then one launch
-  // validates and packs every shape's sites (host site arrays are staged first)
-  const size_t off_src = (sizeof(ShapeDesc) * nsh + 15) / 16 * 16;
-  const size_t stage_bytes = off_src + sizeof(SiteSrc) * nsh;
-  HostPinned stage(stage_bytes);  // released (back to the pool) after the stream is drained (below)
-  DBuf dstage(stage_bytes);
-  SiteUpload su = site_sources(sites, hd, dev, s);
+  // one launch validates and packs every shape's sites (host site arrays are staged first)
+  su = site_sources(sites, hd, dev, s);
   std::memcpy(stage.p, hd.data(), sizeof(ShapeDesc) * nsh);
   std::memcpy((unsigned char*)stage.p + off_src, su.src.data(), sizeof(SiteSrc) * nsh);
   hip_check(hipMemcpyAsync(dstage.p, stage.p, stage_bytes, hipMemcpyHostToDevice, s), "upload");
@@ -870,7 +872,6 @@ static bool run_batch(const rpd_mesh* const* meshes, const rpd_sites* sites, int
   ShapeArgs a = D.args(dshapes_p, nullptr, nitems, o.flags, kmax);
   // a fixed permutation: results must not depend on the processing order
   a.item_mul = (o.flags & RPD_SHUFFLE_QUEUE) ? shuffle_mul(nitems) : 1;
-  DBuf grp_run, grp_site, grp_id;
   if (ngrp) {
     grp_run.alloc(sizeof(int2) * (size_t)ngrp);
     grp_site.alloc(sizeof(float4) * (size_t)grp_cap);
@@ -881,7 +882,6 @@ static bool run_batch(const rpd_mesh* const* meshes, const rpd_sites* sites, int
     a.grp_id = grp_id.as<int>();
     a.grp_cap = (int)grp_cap;
   }
-  const DrainOnExit drain{s};
   Timing tm((o.flags & RPD_TIMING) != 0);
   tm.mark(0, s);
   hip_check(launch_candidates(a, s), "candidate kernel");

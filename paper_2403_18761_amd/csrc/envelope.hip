@@ -504,7 +504,8 @@ void envelope_distance(const float* spheres, int ns, const int* edges, long long
   int ndev = 0;
   if (hipGetDeviceCount(&ndev) != hipSuccess || ndev <= 0) throw Failure{RPD_E_DEVICE, "no HIP device"};
 
-  DBuf d_sph, d_edge, d_tri, d_xyz, d_out, d_near;
+  DBuf d_sph, d_edge, d_tri, d_xyz, d_out, d_near, rec, work, status;
+  const DrainOnExit drain{st};
   const float4* sph = (const float4*)spheres;
   const int* edg = edges;
   const int* tri = tris;
@@ -524,7 +525,9 @@ void envelope_distance(const float* spheres, int ns, const int* edges, long long
     xyz = d_xyz.as<float>();
   }
   const size_t work_bytes = std::max(8 * (size_t)n, sorted_path(n, ns + ne + nf) ? sorted_bytes(n, ns + ne + nf) : 0);
-  DBuf rec(record_bytes(ne, nf)), work(work_bytes), status(sizeof(int));
+  rec.alloc(record_bytes(ne, nf));
+  work.alloc(work_bytes);
+  status.alloc(sizeof(int));
   hipEvent_t ev[2] = {nullptr, nullptr};
   struct EventGuard {
     hipEvent_t* e;
