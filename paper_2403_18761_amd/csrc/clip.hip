@@ -503,48 +503,48 @@ __device__ __forceinline__ void g4(const float4* tv, const float4& s, double* g)
     g[v] = D - 2.0 * (((double)tv[v].x - o.x) * ax + ((double)tv[v].y - o.y) * ay + ((double)tv[v].z - o.z) * az);
 }
 
-// Drops the candidates that another candidate beats at all four tet vertices (g is affine, so then everywhere on the
-// tet: the site owns nothing there and its bisector constrains no piece; the values are exact in FP64). The list is
-// sorted by the power distance at the centroid, and a dominator has the smaller one, so rounds of three dominators
-// taken in list order (each tested against the candidates after them) find the dominated candidates the three-at-a-time
-// way; the rounds run while candidates remain past the dominators. Returns the new count; order is kept.
-// (Of a full list the budget decides where the tet goes, so the rounds are part of what a tet's path depends on. A list
-// that cannot be over the budget is instead cut down to the candidates that no earlier one beats, by refine_all.)
-__device__ __forceinline__ int refine_candidates(const float4* tv, const float4* sites, unsigned char* cand, int m) {
+// A candidate that another one beats at all four tet vertices owns nothing on the tet, and its bisector constrains no
+// piece (g is affine, so it is beaten everywhere on the tet; the values are exact in FP64).
+//
+// The budget decides by what these rounds leave where a tet with a longer list goes: the list is sorted by the power
+// distance at the centroid, and three candidates at a time in list order drop those after them that one of them beats,
+// while candidates remain past them. beaten: bit c where any other candidate beats the list's c-th (moved along with
+// it). Returns the new count; order is kept.
+__device__ __forceinline__ int refine_candidates(const float4* tv, const float4* sites, unsigned char* cand, int m,
+                                                 unsigned long long& beaten) {
   for (int d = 0; d + 3 < m; d += 3) {
     double g0[4], g1[4], g2[4];
     g4(tv, sites[cand[d]], g0);
     g4(tv, sites[cand[d + 1]], g1);
     g4(tv, sites[cand[d + 2]], g2);
     int w = d + 3;
+    unsigned long long b = beaten & ((1ull << w) - 1ull);
     for (int c = d + 3; c < m; ++c) {
       double g[4];
       g4(tv, sites[cand[c]], g);
       const bool dom = (g[0] > g0[0] && g[1] > g0[1] && g[2] > g0[2] && g[3] > g0[3]) ||
                        (g[0] > g1[0] && g[1] > g1[1] && g[2] > g1[2] && g[3] > g1[3]) ||
                        (g[0] > g2[0] && g[1] > g2[1] && g[2] > g2[2] && g[3] > g2[3]);
-      if (!dom) cand[w++] = cand[c];
+      if (!dom) {
+        b |= ((beaten >> c) & 1ull) << w;
+        cand[w++] = cand[c];
+      }
     }
     m = w;
+    beaten = b;
   }
   return m;
 }
 
-__device__ __forceinline__ int refine_all(const float4* tv, const float4* sites, unsigned char* cand, int m) {
-  int w = 1;
-  for (int c = 1; c < m; ++c) {
-    double g[4];
-    const unsigned char cc = cand[c];
-    g4(tv, sites[cc], g);
-    bool dom = false;
-    for (int d = 0; d < w && !dom; ++d) {
-      double e[4];
-      g4(tv, sites[cand[d]], e);
-      dom = g[0] > e[0] && g[1] > e[1] && g[2] > e[2] && g[3] > e[3];
-    }
-    if (!dom) cand[w++] = cc;
-  }
-  return min(w, m);
+// A list within the budget is cut down to the candidates that no other one beats. Whatever was dropped before was beaten
+// by one of these, so the tet's list is the same however the search came to it: an incremental update takes pieces back
+// with the list that they were added with, though the sites around have changed.
+__device__ __forceinline__ int drop_beaten(unsigned char* cand, int m, unsigned long long beaten) {
+  if (!beaten) return m;
+  int w = 0;
+  for (int c = 0; c < m; ++c)
+    if (!((beaten >> c) & 1ull)) cand[w++] = cand[c];
+  return w;
 }
 
 // Which tets the candidate kernel takes next. It starts with ITEM_TETS of the item's, sharing the sites of their block's
@@ -594,6 +594,7 @@ __global__ __launch_bounds__(64, 3) void k_candidates(ShapeArgs a) {
   __shared__ unsigned char s_cand[IT][KRAW];  // ... and sorted
   __shared__ float s_key[IT][KRAW];           // sort keys
   __shared__ int s_m[IT];                     // candidates of each tet
+  __shared__ unsigned long long s_beaten[IT]; // those of them (bits of sorted positions) that another one beats
   __shared__ short s_off[IT + 1];
   __shared__ short s_order[IT];
   __shared__ int s_nsl;
@@ -660,7 +661,10 @@ __global__ __launch_bounds__(64, 3) void k_candidates(ShapeArgs a) {
   const unsigned long long cmask = item_mask >> run.sub;  // bit lt: tet t0 + lt is clipped
   if (run.split && !(cmask & ((1ull << ntb) - 1ull))) continue;  // a chunk without such tets
   __syncthreads();  // the shared arrays of the chunk before are free
-  if (tid < IT) s_m[tid] = 0;
+  if (tid < IT) {
+    s_m[tid] = 0;
+    s_beaten[tid] = 0;
+  }
   if (tid == 0) s_nsl = 0;
   __syncthreads();
   bool tight = false;
@@ -898,7 +902,7 @@ __global__ __launch_bounds__(64, 3) void k_candidates(ShapeArgs a) {
   }
   __syncthreads();
   // ---- 3. each tet's candidates sorted by (power distance at the centroid, site id), one lane per candidate ranking
-  //         it among its tet's, and the dominated ones dropped
+  //         it among its tet's and finding whether another one beats it (such a one is no further away)
   const bool mine = tid < ntb && ((cmask >> tid) & 1ull);
   int m = mine ? s_m[tid] : 0;
   if (mine && all_slow) m = KRAW + 1;
@@ -924,20 +928,32 @@ __global__ __launch_bounds__(64, 3) void k_candidates(ShapeArgs a) {
     const float kx = s_key[lo_][c];
     const unsigned char cx = s_raw[lo_][c];
     const int ix = s_sid[cx];
+    const float4* tv = sd.tp + 4 * (size_t)(t0 + lo_);
+    double gc[4];
+    g4(tv, s_site[cx], gc);
     int rank = 0;
+    bool beaten = false;
     for (int x = 0; x < n; ++x) {
       const float k = s_key[lo_][x];
-      rank += (k < kx || (k == kx && s_sid[s_raw[lo_][x]] < ix)) ? 1 : 0;
+      const int rx = s_raw[lo_][x];
+      rank += (k < kx || (k == kx && s_sid[rx] < ix)) ? 1 : 0;
+      if (k <= kx && !beaten) {
+        double g[4];
+        g4(tv, s_site[rx], g);
+        beaten = g[0] < gc[0] && g[1] < gc[1] && g[2] < gc[2] && g[3] < gc[3];
+      }
     }
     s_cand[lo_][rank] = cx;
+    if (beaten) atomicOr(&s_beaten[lo_], 1ull << rank);
   }
   __syncthreads();
   if (mine) {
     // a tet over the budget goes to the large-capacity kernel, with its sorted, refined candidates when they fit the
     // list (else that kernel finds them among all sites); either way the choice depends on its own candidates only
     const float4* tv = sd.tp + 4 * (size_t)(t0 + tid);
-    if (tight) m = refine_all(tv, s_site, s_cand[tid], m);
-    else if (m <= KRAW) m = refine_candidates(tv, s_site, s_cand[tid], m);
+    unsigned long long beaten = s_beaten[tid];
+    if (m > a.kmax && m <= KRAW) m = refine_candidates(tv, s_site, s_cand[tid], m, beaten);
+    if (m <= a.kmax) m = drop_beaten(s_cand[tid], m, beaten);
     if (m > a.kmax) stat_add(a, all_slow ? C_DEFER_BLOCK : C_DEFER_KMAX, 1ull);
     if (m > KRAW) {
       m = 0;
