@@ -16,6 +16,7 @@
 #include "rpd.h"
 #include "rpd_host.h"
 #include "rpd_launch.h"
+#include "workspace.h"
 
 namespace rpd {
 
@@ -177,16 +178,51 @@ struct DeviceState {
   // counter totals (cursors, list counts and the sums of the spread statistics) and the status word, in one
   // round trip through pinned memory
   void totals(unsigned long long* out, hipStream_t s, int* status_out = nullptr) const;
+  // what the last pass asked for, from totals
+  PassRoom asked(const unsigned long long* tot) const {
+    PassRoom r;
+    r.slots = (long long)tot[C_PIECE_SLOTS];
+    r.records = (long long)tot[C_REC_POOL];
+    // (the items handed on have a quarter of the items' room)
+    r.deferred = (long long)std::max(tot[C_DEFER_ITEMS], tot[C_DEFER2] > (unsigned long long)def2_cap() ? 4 * tot[C_DEFER2] : 0ull);
+    r.big = (long long)tot[C_BIG_POOL];
+    return r;
+  }
+  int def2_cap() const { return def_cap / 4 + 1024; }
   size_t touch_words() const { return ((size_t)ns_cap + capF + capE + 3) / 4; }
 
-  void alloc(int n_shapes, int ns, long long nt, int scale, bool keep_pieces, bool keep_U, int slots) {
+  // a pass's buffers. Memory past what a pass fills is never touched.
+  void alloc_pass(const PassRoom& room, bool components) {
+    static_assert(REC_CHUNK == 2 * CHUNK && NCLASS <= 16, "PassRoom's limits");
+    def_cap = (int)room.deferred;
+    big_cap = (int)room.big;
+    pcap = (int)room.slots;
+    pool_cap = (int)room.records;
+    deferred.alloc(16 * (size_t)def_cap);
+    deferred2.alloc(16 * (size_t)def2_cap());
+    bigp.alloc(BIG_BYTES * (size_t)big_cap);
+    pdesc.alloc(sizeof(PieceDesc) * (size_t)pcap);
+    psite.alloc(sizeof(int) * (size_t)pcap);
+    pout.alloc(sizeof(PieceOut) * (size_t)pcap);
+    chunk_recs.alloc(sizeof(int) * (size_t)chunk_cap(pcap));
+    order.alloc(sizeof(int) * NCLASS * (size_t)pcap);
+    const size_t nrec = (size_t)chunk_cap(pcap) * REC_CHUNK + (size_t)pool_cap;
+    recs.alloc(sizeof(ElemRec) * nrec);
+    pref.alloc(sizeof(PieceRef) * (size_t)pcap);
+    if (components) {
+      pparent.alloc(sizeof(int) * (size_t)pcap);
+      rparent.alloc(sizeof(int) * nrec);
+    }
+  }
+
+  // scale: of the tables; room: of a pass
+  void alloc(int n_shapes, int ns, long long nt, int scale, const PassRoom& room, bool keep_pieces, bool keep_U) {
     nsh = n_shapes;
     ns_cap = ns;
     nt_tot = nt;
     capF = pow2_cap((32 * (size_t)ns + 1024) * scale);
     capE = pow2_cap((32 * (size_t)ns + 1024) * scale);
     capQ = pow2_cap((16 * (size_t)ns + 1024) * scale);
-    def_cap = (int)std::min<size_t>((4 * (size_t)nt + 4096) * scale, 1u << 30);
     piece_cap = keep_pieces ? (int)std::min<size_t>((8 * (size_t)nt + 1024) * scale, 1u << 30) : 0;
     term_cap = keep_pieces ? (int)std::min<size_t>((24 * (size_t)nt + 4096) * scale, 1u << 30) : 0;
     site.alloc(sizeof(float4) * (size_t)ns);
@@ -206,37 +242,8 @@ struct DeviceState {
     edge_b0.alloc(4 * (size_t)capE);
     qkeys.alloc(8 * (size_t)capQ);
     rpv_cnt.alloc(4 * (size_t)capQ);
-    deferred.alloc(16 * (size_t)def_cap);
-    deferred2.alloc(16 * (size_t)(def_cap / 4 + 1024));
-    // Piece slots and records of one clipping pass. A tet has about 1 + 4 r^(1/3) candidates at r sites per tet
-    // (1.9 at 0.018, 4.9 at 0.33, 8.6 at 0.54 measured); an incremental pass clips the dirty tets twice. Memory past
-    // what a pass fills is never touched.
-    {
-      const double r = nt > 0 ? (double)ns / (double)nt : 0.0;
-      const double per = (4.0 + 12.0 * std::cbrt(r * r)) * scale;
-      const double n = std::min((double)nt * per + 16384.0 * scale, 8.0e8);
-      pcap = (int)((size_t)n / CHUNK) * CHUNK;
-      pool_cap = pcap / 2;
-      pdesc.alloc(sizeof(PieceDesc) * (size_t)pcap);
-      psite.alloc(sizeof(int) * (size_t)pcap);
-      pout.alloc(sizeof(PieceOut) * (size_t)pcap);
-      chunk_recs.alloc(sizeof(int) * (size_t)chunk_cap(pcap));
-      order.alloc(sizeof(int) * NCLASS * (size_t)pcap);
-      const size_t nrec = (size_t)chunk_cap(pcap) * REC_CHUNK + (size_t)pool_cap;
-      recs.alloc(sizeof(ElemRec) * nrec);
-      pref.alloc(sizeof(PieceRef) * (size_t)pcap);
-      if (!keep_U) {
-        tet_slots.alloc(sizeof(int2) * (size_t)std::max<long long>(nt, 1));
-        pparent.alloc(sizeof(int) * (size_t)pcap);
-        rparent.alloc(sizeof(int) * nrec);
-      }
-    }
-    // pieces over the fast kernel's vertex slots: about 1 in 10^4 on the benchmark shapes with 16 slots, up to 1 in
-    // 10^2 with 12; an incremental session gets room for four times as many per pass as a build (its pool must
-    // never run out)
-    const long long per_big = slots == 12 ? (keep_U ? 8 : 32) : (keep_U ? 64 : 256);
-    big_cap = (int)std::min<size_t>((nt / per_big + 1024) * (size_t)scale, 1u << 20);
-    bigp.alloc(BIG_BYTES * (size_t)big_cap);
+    alloc_pass(room, !keep_U);
+    if (!keep_U) tet_slots.alloc(sizeof(int2) * (size_t)std::max<long long>(nt, 1));
     pieces.alloc(sizeof(PieceRec) * (size_t)std::max(piece_cap, 1));
     terms.alloc(sizeof(TermRec) * (size_t)std::max(term_cap, 1));
     counters.alloc(8 * (NCOUNTERS + 8 + (size_t)NSPREAD * NCOUNTERS));
@@ -328,7 +335,7 @@ struct DeviceState {
     a.deferred = deferred.as<int4>();
     a.deferred_cap = def_cap;
     a.deferred2 = deferred2.as<int4>();
-    a.deferred2_cap = def_cap / 4 + 1024;
+    a.deferred2_cap = def2_cap();
     a.pdesc = pdesc.as<PieceDesc>();
     a.psite = psite.as<int>();
     a.pout = pout.as<PieceOut>();
@@ -439,12 +446,12 @@ void DeviceState::totals(unsigned long long* out, hipStream_t s, int* status_out
 static std::mutex g_spec_mu;
 static std::map<std::tuple<int, int, unsigned, unsigned, unsigned>, size_t> g_spec;
 
-// Sorted element lists of the current state, copied to the host and split per shape. Returns false when a table
-// overflowed (the caller retries with larger tables). Live entries are compacted first and the counts read back,
+// Sorted element lists of the current state, copied to the host and split per shape. Returns false when a table or the
+// pass's room overflowed (the caller retries with more; asked: what the pass asked for). Live entries are compacted first and the counts read back,
 // so that only they are sorted and downloaded.
 static bool collect(DeviceState& D, const std::vector<ShapeDesc>& hd, const ShapeDesc* dshapes,
                     const rpd_mesh* const* meshes, hipStream_t s, Timing& tm, std::vector<ShapeOut>& outs,
-                    rpd_stats& st) {
+                    rpd_stats& st, PassRoom& asked) {
   const int nsh = (int)hd.size();
   int ns = 0;
   for (const auto& d : hd) ns = std::max(ns, d.site_off + d.ns);
@@ -481,11 +488,9 @@ static bool collect(DeviceState& D, const std::vector<ShapeDesc>& hd, const Shap
   // the counters, status and live counts: a false return (a table or buffer overflowed) has the caller retry
   auto check_totals = [&]() {
     D.totals(hc, s, &hst);
-    if (hst & ST_TABLE_FULL) return false;
-    if (hc[C_DEFER_ITEMS] > (unsigned long long)D.def_cap ||
-        (D.piece_cap &&
-         (hc[C_PIECES] > (unsigned long long)D.piece_cap || hc[C_TERMS] > (unsigned long long)D.term_cap)))
-      return false;
+    asked = D.asked(hc);
+    // (a call that fails whatever its room is not repeated)
+    if (!(hst & (ST_INVALID | ST_SLOW_CAPACITY)) && (hst & ST_FULL)) return false;
     status_error(hst);
     return true;
   };
@@ -820,7 +825,8 @@ static SiteUpload upload_sites(DeviceState& D, const rpd_sites* sites, const std
 
 // All shapes of one call, one attempt. Returns false if a table ran out of room (caller retries larger).
 static bool run_batch(const rpd_mesh* const* meshes, const rpd_sites* sites, int nsh, const rpd_opts& o,
-                      hipStream_t s, int scale, std::vector<ShapeOut>& outs, rpd_stats& st) {
+                      hipStream_t s, int scale, const PassRoom& room, std::vector<ShapeOut>& outs, rpd_stats& st,
+                      PassRoom& asked) {
   const bool dev = (o.flags & RPD_DEVICE_PTRS) != 0;
   std::vector<int> nsites(nsh);
   for (int k = 0; k < nsh; ++k) nsites[k] = sites[k].n_sites;
@@ -835,7 +841,7 @@ static bool run_batch(const rpd_mesh* const* meshes, const rpd_sites* sites, int
   SiteUpload su;
   const DrainOnExit drain{s};
   // the tables are cleared on the device while the host prepares the launches
-  D.alloc(nsh, (int)ns_tot, nt_tot, scale, (o.flags & RPD_KEEP_PIECES) != 0, false, fast_slots(o));
+  D.alloc(nsh, (int)ns_tot, nt_tot, scale, room, (o.flags & RPD_KEEP_PIECES) != 0, false);
   D.clear(s);
   long long nblk = 0, nitems_all = 0, ngrp = 0, grp_cap = 0, nparts = 0;
   int most = 0;
@@ -891,7 +897,7 @@ static bool run_batch(const rpd_mesh* const* meshes, const rpd_sites* sites, int
   tm.mark(2, s);
   hip_check(launch_emit(a, s), "emission");
   D.build_components(a, s);
-  if (!collect(D, hd, dshapes_p, meshes, s, tm, outs, st)) return false;
+  if (!collect(D, hd, dshapes_p, meshes, s, tm, outs, st, asked)) return false;
   st.n_items = nparts;
   st.ms_clip = tm.ms(0, 1);
   st.ms_deferred = tm.ms(1, 2);
@@ -1022,8 +1028,16 @@ static void apply_tuned(rpd_opts& o, const rpd_mesh* const* meshes, const rpd_si
 static bool run_with_retry(const rpd_mesh* const* meshes, const rpd_sites* sites, int32_t n_shapes, const rpd_opts& o,
                            std::vector<rpd::ShapeOut>& shapes, rpd_stats& st) {
   hipStream_t s = (hipStream_t)o.stream;
-  for (int scale = 1; scale <= 16; scale *= 2)
-    if (rpd::run_batch(meshes, sites, n_shapes, o, s, scale, shapes, st)) return true;
+  long long nt = 0, ns = 0;
+  for (int k = 0; k < n_shapes; ++k) {
+    nt += meshes[k]->nt;
+    ns += sites[k].n_sites;
+  }
+  rpd::PassRoom room = rpd::pass_room(nt, ns, 1, rpd::fast_slots(o) == 12), asked;
+  for (int scale = 1; scale <= 16;) {
+    if (rpd::run_batch(meshes, sites, n_shapes, o, s, scale, room, shapes, st, asked)) return true;
+    if (!rpd::grow(room, asked)) scale *= 2;
+  }
   return false;
 }
 
@@ -1281,7 +1295,7 @@ static void check_status(rpd_session* S) {
   int hst = 0;
   hip_check(hipMemcpyAsync(&hst, S->D.status.p, sizeof(int), hipMemcpyDeviceToHost, S->stream), "download");
   hip_check(hipStreamSynchronize(S->stream), "synchronize");
-  if (hst & ST_TABLE_FULL)
+  if (hst & ST_FULL)
     throw Failure{RPD_E_NOMEM, "session tables are full: create the session with a larger max_sites"};
   status_error(hst);
 }
@@ -1296,14 +1310,15 @@ static void clip_pass(rpd_session* S, const ShapeArgs& a) {
 }
 
 // Allocate at the given table scale, upload, compute the initial state. False if a table overflowed.
-static bool session_init(rpd_session* S, const rpd_sites* sites, const rpd_sites* table, int scale) {
+static bool session_init(rpd_session* S, const rpd_sites* sites, const rpd_sites* table, int scale,
+                         const PassRoom& room, PassRoom& asked) {
   const rpd_mesh* m = S->mesh;
   hipStream_t s = S->stream;
   const bool dev = (S->o.flags & RPD_DEVICE_PTRS) != 0;
   const int nt = m->nt, nblk = m->nblk;
   if (nblk >= (1 << ITEM_PART_SHIFT)) throw Failure{RPD_E_INVALID, "mesh with 2^20 or more workgroup blocks"};
   DeviceState& D = S->D;
-  D.alloc(1, S->max_sites, nt, scale, false, true, fast_slots(S->o));
+  D.alloc(1, S->max_sites, nt, scale, room, false, true);
   D.clear(s);
   std::vector<ShapeDesc> hd{S->hd};
   const SiteUpload su = upload_sites(D, sites, hd, dev, s);
@@ -1370,10 +1385,11 @@ static bool session_init(rpd_session* S, const rpd_sites* sites, const rpd_sites
   ShapeArgs a = D.args(ds + 1, nullptr, nblk * S->hd.parts, S->o.flags, S->kmax);
   clip_pass(S, a);
   D.components(a, s);
-  hip_check(hipStreamSynchronize(s), "synchronize");
+  unsigned long long tot[NCOUNTERS + 8];
   int hst = 0;
-  hip_check(hipMemcpy(&hst, D.status.p, sizeof(int), hipMemcpyDeviceToHost), "download");
-  if (hst & ST_TABLE_FULL) return false;
+  D.totals(tot, s, &hst);
+  asked = D.asked(tot);
+  if (!(hst & (ST_INVALID | ST_SLOW_CAPACITY)) && (hst & ST_FULL)) return false;
   status_error(hst);
   int* ints = S->ints.as<int>();
   RoundState& r = S->r;
@@ -1509,7 +1525,11 @@ rpd_status rpd_session_create(const rpd_mesh* mesh, const rpd_sites* sites, cons
     const rpd_mesh* ms[1] = {mesh};
     S->hd = rpd::shape_table(ms, &n0, 1, &ns_tot, &nt_tot)[0];
     bool done = false;
-    for (int scale = 2; scale <= 16 && !done; scale *= 2) done = rpd::session_init(S, sites, table, scale);
+    rpd::PassRoom room = rpd::pass_room(mesh->nt, S->max_sites, 2, rpd::fast_slots(o) == 12), asked;
+    for (int scale = 2; scale <= 16 && !done;) {
+      done = rpd::session_init(S, sites, table, scale, room, asked);
+      if (!done && !rpd::grow(room, asked)) scale *= 2;
+    }
     if (!done) throw Failure{RPD_E_NOMEM, "session tables kept overflowing"};
     rpd::session_capture(S);
   } catch (...) {
@@ -1601,7 +1621,8 @@ rpd_status rpd_session_result(rpd_session* S, rpd_result** out) {
     r->shapes.resize(1);
     rpd::Timing tm(false);
     const rpd_mesh* ms[1] = {S->mesh};
-    if (!rpd::collect(S->D, hd, S->dshapes.as<rpd::ShapeDesc>() + 1, ms, S->stream, tm, r->shapes, r->stats))
+    rpd::PassRoom asked;
+    if (!rpd::collect(S->D, hd, S->dshapes.as<rpd::ShapeDesc>() + 1, ms, S->stream, tm, r->shapes, r->stats, asked))
       throw Failure{RPD_E_NOMEM, "session tables are full"};
   } catch (...) {
     delete r;

@@ -327,7 +327,7 @@ __device__ inline int pool_records(const ShapeArgs& a, int n) {
   if (n == 0) return 0;
   const unsigned long long q = atomicAdd(&a.counters[C_REC_POOL], (unsigned long long)n);
   if (q + n > (unsigned long long)a.pool_cap) {
-    atomicOr(a.status, ST_TABLE_FULL);
+    atomicOr(a.status, ST_POOL_FULL);
     return -1;
   }
   return chunk_cap(a.pcap) * REC_CHUNK + (int)q;
@@ -347,7 +347,7 @@ __device__ __forceinline__ void emit_alone(CL& c, const ShapeDesc& sd, int tl, i
 __device__ inline void defer_item(const ShapeArgs& a, int shape, int t, int p, int first) {
   const unsigned long long idx = atomicAdd(&a.counters[C_DEFER_ITEMS], 1ull);
   if (idx < (unsigned long long)a.deferred_cap) a.deferred[idx] = make_int4(shape, t, p, first);
-  else atomicOr(a.status, ST_TABLE_FULL);
+  else atomicOr(a.status, ST_PASS_FULL);
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -998,7 +998,7 @@ __global__ __launch_bounds__(64, 3) void k_candidates(ShapeArgs a) {
     at = (long long)atomicAdd(&a.counters[lane == 0 ? C_PIECE_SLOTS : C_CLASS + lane - 1], (unsigned long long)(c1 - c0));
   const long long base_l = __shfl(at, 0);
   if (base_l + npairs > (long long)a.pcap) {
-    if (lane == 0) atomicOr(a.status, ST_TABLE_FULL);
+    if (lane == 0) atomicOr(a.status, ST_PASS_FULL);
   } else {
     const int base = (int)base_l;
     for (int p0 = 0; p0 < npairs; p0 += 64) {
@@ -1029,7 +1029,7 @@ __global__ __launch_bounds__(64, 3) void k_candidates(ShapeArgs a) {
           // (items that found no slots have advanced the class cursors too, maybe before this one)
           const long long o = cl_at + (p - cl_c0);
           if (o < (long long)a.pcap) a.order[(size_t)cl * a.pcap + o] = base + p;
-          else atomicOr(a.status, ST_TABLE_FULL);
+          else atomicOr(a.status, ST_PASS_FULL);
           ++n_cand;
         }
       }
@@ -1060,7 +1060,7 @@ __global__ __launch_bounds__(64) void k_clip_pieces(ShapeArgs a) {
   __shared__ int s_csid[WIN];
   __shared__ int s_over[CHUNK];  // this chunk's pieces that ran out of vertex slots
   __shared__ int s_nover;
-  if (*a.status & ST_TABLE_FULL) return;  // some slots were never filled; the call is redone with larger buffers
+  if (*a.status & ST_PASS_FULL) return;  // some slots were never filled; the pass is redone with larger buffers
   const int lane = threadIdx.x;
   // the chunks of the classes, the most candidates first (their chunks take longest)
   int nc[NCLASS], nchunks = 0;
@@ -1183,9 +1183,10 @@ __global__ __launch_bounds__(64) void k_clip_pieces(ShapeArgs a) {
         constexpr size_t REC = (CB + 8 * BIG_VCAP + 64 + 15) / 16 * 16;
         constexpr int NLDS = (int)(sizeof(s_poly) / REC);
         static_assert(CB + 8 * BIG_VCAP + 32 <= BIG_BYTES, "large-capacity polytope record");
-        const unsigned long long slot = atomicAdd(&a.counters[C_BIG], 1ull);
+        atomicAdd(&a.counters[C_BIG], 1ull);
+        const unsigned long long slot = lane < NLDS ? 0ull : atomicAdd(&a.counters[C_BIG_POOL], 1ull);
         if (lane >= NLDS && slot >= (unsigned long long)a.big_cap) {
-          atomicOr(a.status, ST_TABLE_FULL);
+          atomicOr(a.status, ST_PASS_FULL);
         } else {
           unsigned char* b = lane < NLDS ? s_poly + (size_t)lane * REC : a.big + slot * BIG_BYTES;
           Clipper<T, Topo64, unsigned long long, BIG_VCAP, false, MemTab> cb;
@@ -1273,7 +1274,7 @@ struct SlowCfg<false> {
 __device__ inline void push_overflow(const ShapeArgs& a, int4 item) {
   const unsigned long long idx = atomicAdd(&a.counters[C_DEFER2], 1ull);
   if (idx < (unsigned long long)a.deferred2_cap) a.deferred2[idx] = item;
-  else atomicOr(a.status, ST_TABLE_FULL);
+  else atomicOr(a.status, ST_PASS_FULL);
 }
 
 // One wavefront per deferred item: the lanes split the scan over all of the shape's sites (candidates are
@@ -1296,7 +1297,7 @@ __global__ __launch_bounds__(64, LDS ? 1 : 2) void k_clip_slow(ShapeArgs a, unsi
   __shared__ float4 s_csite[SC];
   constexpr int NDOM = 6;
   __shared__ double s_dom[NDOM][4];
-  if (*a.status & ST_TABLE_FULL) return;  // the call is redone with larger buffers
+  if (*a.status & ST_PASS_FULL) return;
   const int n_main = (int)min(min(a.counters[C_DEFER_ITEMS], (unsigned long long)a.deferred_cap),
                               (unsigned long long)item_end);
   const int n_over = LDS ? 0 : (int)min(a.counters[C_DEFER2], (unsigned long long)a.deferred2_cap);
@@ -1497,7 +1498,7 @@ __global__ __launch_bounds__(64, LDS ? 1 : 2) void k_clip_slow(ShapeArgs a, unsi
       if (lane == 0) {
         const unsigned long long at = atomicAdd(&a.counters[C_PIECE_SLOTS], (unsigned long long)m);
         if (at + m <= (unsigned long long)a.pcap) q = (int)at;
-        else atomicOr(a.status, ST_TABLE_FULL);
+        else atomicOr(a.status, ST_PASS_FULL);
       }
       first = __builtin_amdgcn_readfirstlane(q);
       if (first < 0) continue;

@@ -35,10 +35,15 @@ constexpr size_t BIG_BYTES = 32 * BIG_VCAP + 8 * BIG_VCAP + 64;
 
 // status bits raised by kernels (ShapeArgs::status)
 constexpr int ST_DEGENERATE = 1;     // an exact predicate evaluated to zero / duplicate site
-constexpr int ST_TABLE_FULL = 2;     // a hash table or record buffer ran out of room (host retries larger)
+constexpr int ST_TABLE_FULL = 2;     // a hash table or an output buffer ran out of room (host retries larger)
 constexpr int ST_INTERNAL = 4;       // gluing asymmetry or another broken invariant
 constexpr int ST_SLOW_CAPACITY = 8;  // the deferred path ran out of candidate or vertex capacity
 constexpr int ST_INVALID = 16;       // invalid site value (off grid, out of range, not finite)
+// A clipping pass ran out of room (workspace.h): of slots or list entries, some of which then stay unfilled, or of pool
+// records, which the rest of the pass goes on counting.
+constexpr int ST_PASS_FULL = 32;
+constexpr int ST_POOL_FULL = 64;
+constexpr int ST_FULL = ST_TABLE_FULL | ST_PASS_FULL | ST_POOL_FULL;
 
 // counters (ShapeArgs::counters)
 enum {
@@ -60,6 +65,7 @@ enum {
   C_DEFER_ITEMS,  // items for the large-capacity kernel
   C_DEFER2,       // items handed on by the LDS variant of the large-capacity kernel
   C_BIG,          // pieces redone with a 64-slot polytope after running out of vertex slots
+  C_BIG_POOL,     // those of them with a polytope in global memory
   NCOUNTERS
 };
 constexpr int PASS_CURSORS = NCOUNTERS - C_PIECE_SLOTS;

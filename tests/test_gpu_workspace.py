@@ -32,3 +32,15 @@ def test_slots_run_out_in_one_class(copies):
     g = run_gpu(prob)
     assert g["stats"]["n_candidates"] == copies * prob.n_tets
     assert_parity(g, oracle.rpd(prob, assemble=False), label=f"{copies} copies")
+
+
+@pytest.mark.parametrize("N,n", [(8, 600), (8, 1660)])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_dense_sites_of_equal_radius(N, n, precision):
+    """Most chunks of pieces have several times the records of their own range."""
+    import oracle
+
+    prob = synth.cube_random(N=N, n_sites=n, seed=3, weights=False)
+    log(f"case: {prob.n_tets} tets, {n} sites, precision {precision}")
+    g = run_gpu(prob, precision=precision)
+    assert_parity(g, oracle.rpd(prob, assemble=False), vol_rtol=1e-9 if precision else 1e-5, label=f"N{N} n{n}")
