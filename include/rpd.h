@@ -341,7 +341,8 @@ rpd_status rpd_session_create(const rpd_mesh* mesh, const rpd_sites* sites, cons
                               const rpd_session_opts* opts, rpd_session** out);
 
 /* Run `rounds` rounds (graph replays), then synchronise and check the device status (ties with an inserted sphere
- * are broken like every other tie, see the preconditions above). Errors: RPD_E_NOMEM (the session's tables filled
+ * are broken like every other tie, see the preconditions above). A round whose clipping needs more room than the session
+ * has changes no element; the session gets more (device memory), and the round is repeated. Errors: RPD_E_NOMEM (the session's tables filled
  * up: create it with a larger max_sites), RPD_E_DEVICE. After an error the session can only be freed. */
 rpd_status rpd_session_run(rpd_session* s, int32_t rounds);
 

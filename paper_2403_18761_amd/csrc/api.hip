@@ -1273,6 +1273,7 @@ struct rpd_session {
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   hipEvent_t ev[2] = {nullptr, nullptr};
+  rpd::PassRoom room;
   int rounds = 0;
   double ms_last = 0;
 
@@ -1289,12 +1290,16 @@ struct rpd_session {
 namespace rpd {
 
 // int slots of rpd_session::ints
-enum { SI_NSEL = 0, SI_NITEMS, SI_ROUND, SI_NS, SI_INS, SI_DIRTY, SI_COUNT };
+enum { SI_NSEL = 0, SI_NITEMS, SI_ROUND, SI_NS, SI_INS, SI_DIRTY, SI_STALLED, SI_COUNT };
 
-static void check_status(rpd_session* S) {
-  int hst = 0;
-  hip_check(hipMemcpyAsync(&hst, S->D.status.p, sizeof(int), hipMemcpyDeviceToHost, S->stream), "download");
+static int read_int(rpd_session* S, const int* p) {  // after the work queued so far
+  int v = 0;
+  hip_check(hipMemcpyAsync(&v, p, sizeof(int), hipMemcpyDeviceToHost, S->stream), "download");
   hip_check(hipStreamSynchronize(S->stream), "synchronize");
+  return v;
+}
+
+static void check_status(int hst) {
   if (hst & ST_FULL)
     throw Failure{RPD_E_NOMEM, "session tables are full: create the session with a larger max_sites"};
   status_error(hst);
@@ -1310,15 +1315,14 @@ static void clip_pass(rpd_session* S, const ShapeArgs& a) {
 }
 
 // Allocate at the given table scale, upload, compute the initial state. False if a table overflowed.
-static bool session_init(rpd_session* S, const rpd_sites* sites, const rpd_sites* table, int scale,
-                         const PassRoom& room, PassRoom& asked) {
+static bool session_init(rpd_session* S, const rpd_sites* sites, const rpd_sites* table, int scale, PassRoom& asked) {
   const rpd_mesh* m = S->mesh;
   hipStream_t s = S->stream;
   const bool dev = (S->o.flags & RPD_DEVICE_PTRS) != 0;
   const int nt = m->nt, nblk = m->nblk;
   if (nblk >= (1 << ITEM_PART_SHIFT)) throw Failure{RPD_E_INVALID, "mesh with 2^20 or more workgroup blocks"};
   DeviceState& D = S->D;
-  D.alloc(1, S->max_sites, nt, scale, room, false, true);
+  D.alloc(1, S->max_sites, nt, scale, S->room, false, true);
   D.clear(s);
   std::vector<ShapeDesc> hd{S->hd};
   const SiteUpload su = upload_sites(D, sites, hd, dev, s);
@@ -1414,6 +1418,8 @@ static bool session_init(rpd_session* S, const rpd_sites* sites, const rpd_sites
   r.ns_cur = ints + SI_NS;
   r.ins_total = ints + SI_INS;
   r.dirty_total = ints + SI_DIRTY;
+  r.stalled = ints + SI_STALLED;
+  r.status = D.status.as<int>();
   r.old_desc = ds;
   r.new_desc = ds + 1;
   r.max_sites = S->max_sites;
@@ -1460,6 +1466,24 @@ static void session_capture(rpd_session* S) {
   }
   hip_check(hipStreamEndCapture(S->stream, &S->graph), "end capture");
   hip_check(hipGraphInstantiate(&S->exec, S->graph, nullptr, nullptr, 0), "graph instantiate");
+}
+
+// After rounds that left status hst: whether one of them ran out of room for its pass and nothing else went wrong. The
+// session then gets what the pass asked for and a new graph, and its next round repeats that pass.
+static bool session_make_room(rpd_session* S, int hst) {
+  if (!(hst & (ST_PASS_FULL | ST_POOL_FULL)) || (hst & ~(ST_PASS_FULL | ST_POOL_FULL))) return false;
+  unsigned long long tot[NCOUNTERS + 8];
+  S->D.totals(tot, S->stream);
+  if (!grow(S->room, S->D.asked(tot))) return false;
+  if (S->exec) (void)hipGraphExecDestroy(S->exec);
+  S->exec = nullptr;
+  if (S->graph) (void)hipGraphDestroy(S->graph);
+  S->graph = nullptr;
+  S->D.alloc_pass(S->room, false);
+  hip_check(launch_fill_i32(S->D.status.as<int>(), 0, 1, S->stream), "fill");
+  hip_check(hipStreamSynchronize(S->stream), "synchronize");
+  session_capture(S);
+  return true;
 }
 
 struct DeviceGuard {  // make the session's device current for the call, restore the caller's afterwards
@@ -1525,10 +1549,11 @@ rpd_status rpd_session_create(const rpd_mesh* mesh, const rpd_sites* sites, cons
     const rpd_mesh* ms[1] = {mesh};
     S->hd = rpd::shape_table(ms, &n0, 1, &ns_tot, &nt_tot)[0];
     bool done = false;
-    rpd::PassRoom room = rpd::pass_room(mesh->nt, S->max_sites, 2, rpd::fast_slots(o) == 12), asked;
+    S->room = rpd::pass_room(mesh->nt, S->max_sites, 2, rpd::fast_slots(o) == 12);
+    rpd::PassRoom asked;
     for (int scale = 2; scale <= 16 && !done;) {
-      done = rpd::session_init(S, sites, table, scale, room, asked);
-      if (!done && !rpd::grow(room, asked)) scale *= 2;
+      done = rpd::session_init(S, sites, table, scale, asked);
+      if (!done && !rpd::grow(S->room, asked)) scale *= 2;
     }
     if (!done) throw Failure{RPD_E_NOMEM, "session tables kept overflowing"};
     rpd::session_capture(S);
@@ -1549,9 +1574,15 @@ rpd_status rpd_session_run(rpd_session* S, int32_t rounds) {
   rpd::DeviceGuard g(S->device);
   try {
     rpd::hip_check(hipEventRecord(S->ev[0], S->stream), "hipEventRecord");
-    for (int k = 0; k < rounds; ++k) rpd::hip_check(hipGraphLaunch(S->exec, S->stream), "graph launch");
-    rpd::hip_check(hipEventRecord(S->ev[1], S->stream), "hipEventRecord");
-    rpd::check_status(S);
+    int left = rounds, hst = 0;
+    do {
+      for (int k = 0; k < left; ++k) rpd::hip_check(hipGraphLaunch(S->exec, S->stream), "graph launch");
+      rpd::hip_check(hipEventRecord(S->ev[1], S->stream), "hipEventRecord");
+      hst = rpd::read_int(S, S->D.status.as<int>());
+      if (!rpd::session_make_room(S, hst)) break;
+      left = S->rounds + rounds - rpd::read_int(S, S->ints.as<int>() + rpd::SI_ROUND);
+    } while (left > 0);
+    rpd::check_status(hst);
     float ms = 0;
     rpd::hip_check(hipEventElapsedTime(&ms, S->ev[0], S->ev[1]), "hipEventElapsedTime");
     S->ms_last = ms;

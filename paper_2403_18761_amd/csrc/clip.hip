@@ -599,10 +599,11 @@ __global__ __launch_bounds__(64, 3) void k_candidates(ShapeArgs a) {
   __shared__ short s_order[IT];
   __shared__ int s_nsl;
 
-  // (a shape of NaNs has no site that reaches anything: its lists would be empty)
-  if (*a.status & ST_INVALID) return;
   const int tid = threadIdx.x, lane = tid;
-  const int nitems = a.nitems_dev ? *a.nitems_dev : a.nitems;
+  // (a shape of NaNs has no site that reaches anything: its lists would be empty)
+  const bool invalid = (*a.status & ST_INVALID) != 0;
+  const int nlisted = a.nitems_dev ? *a.nitems_dev : a.nitems;
+  const int nitems = invalid ? 0 : nlisted;
   unsigned long long n_cand = 0;
   // A build's grid covers the items (every block of every shape, in a.parts parts), one item per workgroup. The passes
   // of an incremental round read a list of items whose length is known on the device only and launch a grid sized to
@@ -1072,7 +1073,6 @@ __global__ __launch_bounds__(64) void k_clip_pieces(ShapeArgs a) {
     s_nover = 0;
     if (blockIdx.x == 0) a.counters[C_CHUNKS] = (unsigned long long)nchunks;
   }
-  long long n_pairs = 0;
   unsigned long long n64 = 0;
   for (int chunk = blockIdx.x; chunk < nchunks; chunk += gridDim.x) {
     int cls = NCLASS - 1, k0 = chunk;
@@ -1136,7 +1136,6 @@ __global__ __launch_bounds__(64) void k_clip_pieces(ShapeArgs a) {
       r = clip_piece(cl, d.m);
       n64 += cl.n64;
       if (r == CLIP_OK) {
-        n_pairs += sd.sign;  // live pieces
         emit_scan(cl, e);
       } else {
         a.pref[p].word = 0;
@@ -1216,7 +1215,6 @@ __global__ __launch_bounds__(64) void k_clip_pieces(ShapeArgs a) {
           const int rb = clip_piece(cb, m);
           n64 += cb.n64;
           if (rb == CLIP_OK) {
-            n_pairs += sb.sign;
             emit_alone(cb, sb, db.t, pb, a);
           } else if (rb != CLIP_EMPTY) {  // a predicate undecided in FP64, or over BIG_VCAP vertices
             stat_add(a, C_DEFER_CLIP, 1ull);
@@ -1228,14 +1226,8 @@ __global__ __launch_bounds__(64) void k_clip_pieces(ShapeArgs a) {
       if (lane == 0) s_nover = 0;
     }
   }
-  for (int off = 32; off > 0; off >>= 1) {
-    n_pairs += __shfl_xor(n_pairs, off);
-    n64 += __shfl_xor(n64, off);
-  }
-  if (lane == 0) {
-    if (n_pairs) stat_add(a, C_PAIRS, (unsigned long long)n_pairs);  // in two's complement
-    if (n64) stat_add(a, C_FP64, n64);
-  }
+  for (int off = 32; off > 0; off >>= 1) n64 += __shfl_xor(n64, off);
+  if (lane == 0 && n64) stat_add(a, C_FP64, n64);
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -1317,7 +1309,7 @@ __global__ __launch_bounds__(64, LDS ? 1 : 2) void k_clip_slow(ShapeArgs a, unsi
           : (unsigned long long*)(wbase + SlowScratch::wave_bytes + SlowScratch::xyz_bytes) + cl_lane;
   unsigned char* tab =
       LDS ? s_tab + cl_lane : wbase + SlowScratch::wave_bytes + SlowScratch::xyz_bytes + SlowScratch::topo_bytes + cl_lane;
-  unsigned long long n_pairs = 0, n64 = 0, nex = 0;
+  unsigned long long n64 = 0, nex = 0;
   for (int vi = blockIdx.x; vi < n_items; vi += gridDim.x) {
     const int main_count = max(n_main - item_begin, 0);
     const int4 di = vi < main_count ? a.deferred[item_begin + vi] : a.deferred2[vi - main_count];
@@ -1552,19 +1544,16 @@ __global__ __launch_bounds__(64, LDS ? 1 : 2) void k_clip_slow(ShapeArgs a, unsi
         continue;
       }
       if (r == CLIP_OK) {
-        n_pairs += (unsigned long long)(long long)sd.sign;
         emit_alone(cl, sd, t, first + ci, a);
       }
     }
     __syncthreads();  // the candidate list is rewritten by the next item
   }
   for (int off = 32; off > 0; off >>= 1) {
-    n_pairs += __shfl_xor(n_pairs, off);
     n64 += __shfl_xor(n64, off);
     nex += __shfl_xor(nex, off);
   }
   if (lane == 0) {
-    if (n_pairs) stat_add(a, C_PAIRS, n_pairs);
     if (n64) stat_add(a, C_FP64, n64);
     if (nex) stat_add(a, C_EXACT, nex);
   }

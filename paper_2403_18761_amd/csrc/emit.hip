@@ -112,7 +112,7 @@ __device__ __forceinline__ void emit_cells(const ShapeArgs& a) {
   __shared__ CellSums S;
   const int tid = threadIdx.x;
   const int np_all = (int)min(a.counters[C_PIECE_SLOTS], (unsigned long long)a.pcap);
-  unsigned long long nodes = 0;
+  long long pairs = 0;  // nonempty pieces added less those taken back
   const int per = ((np_all + DIES - 1) / DIES + EMIT_PIECES - 1) / EMIT_PIECES * EMIT_PIECES;
   const int end = min(np_all, (int)(blockIdx.x % DIES + 1) * per);
   for (int base = (int)(blockIdx.x % DIES) * per + (int)(blockIdx.x / DIES) * EMIT_PIECES; base < end;
@@ -154,7 +154,7 @@ __device__ __forceinline__ void emit_cells(const ShapeArgs& a) {
       }
       if (!HASH) a.pparent[p] = p;
       node_emit<HASH>(a, sign, node_key(1, i, t), glue);
-      ++nodes;
+      pairs += sign;
       keep_term(a, 1, t, i, -1, -1, -1, glue, o.chi);
       if (a.flags & RPD_KEEP_PIECES) {
         const unsigned long long idx = atomicAdd(&a.counters[C_PIECES], 1ull);
@@ -184,9 +184,10 @@ __device__ __forceinline__ void emit_cells(const ShapeArgs& a) {
     }
     __syncthreads();
   }
-  if (HASH) return;
-  for (int off = 32; off > 0; off >>= 1) nodes += __shfl_xor(nodes, off);
-  if ((tid & 63) == 0 && nodes) stat_add(a, C_NODES, nodes);
+  for (int off = 32; off > 0; off >>= 1) pairs += __shfl_xor(pairs, off);
+  if ((tid & 63) || !pairs) return;
+  stat_add(a, C_PAIRS, (unsigned long long)pairs);  // in two's complement
+  if (!HASH) stat_add(a, C_NODES, (unsigned long long)pairs);
 }
 
 // one element record

@@ -47,7 +47,7 @@ constexpr int ST_FULL = ST_TABLE_FULL | ST_PASS_FULL | ST_POOL_FULL;
 
 // counters (ShapeArgs::counters)
 enum {
-  C_PAIRS = 0, C_CAND, C_FP64, C_EXACT, C_GLUE, C_RPV, C_PIECES, C_NODES,
+  C_PAIRS = 0, C_CAND, C_FP64, C_EXACT, C_RPV, C_PIECES, C_NODES,
   C_DEFER_BLOCK,  // tets deferred because their own candidates overflow the workgroup's site list
   C_DEFER_KMAX,   // tets deferred because they kept more than the candidate budget
   C_DEFER_CLIP,   // pieces deferred because a predicate stayed undecided or the polytope outgrew 64 vertex slots
@@ -358,6 +358,9 @@ struct RoundState {
   int* ns_cur;                // sites in use
   int* ins_total;             // spheres inserted over all rounds
   int* dirty_total;           // dirty blocks over all rounds
+  int* stalled;               // set by a round whose clipping pass ran out of room: nothing was emitted, its insertions
+                              // stay, and the next round repeats its pass instead of selecting again
+  const int* status;
   ShapeDesc* old_desc;        // the shape with the sites before this round's insertions
   ShapeDesc* new_desc;        // ... and after them
   int max_sites;

@@ -21,16 +21,17 @@
 namespace rpd {
 
 
+// A round whose pass ran out of room (k_round_end) is repeated: selection and insertion leave what they did, and the
+// scans between them change nothing that is read. The dirty tets come out the same, though the U_t may be the new
+// state's already: a new sphere that lowered a tet's U_t reaches it, since its own maximum is the new U_t.
 __global__ void k_round_begin(RoundState r) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    *r.nsel = 0;
-    *r.nitems = 0;
-  }
+  if (threadIdx.x == 0 && blockIdx.x == 0) *r.nitems = 0;
 }
 
 // first M violating cells in ascending order (one workgroup, chunked ballot compaction)
 __global__ __launch_bounds__(256) void k_select(RoundState r, const long long* cell_chi, const int* cell_np,
                                                 const int* cell_b0) {
+  if (*r.stalled) return;
   __shared__ int s_count;
   __shared__ int s_warp[4];
   const int n = *r.ns_cur;
@@ -163,6 +164,7 @@ __global__ __launch_bounds__(256) void k_pick_tet(NodeTab N, const int* cell_b0,
 // Insertion in selection order (deterministic site ids): cell k inserts its tet's sphere unless a cell earlier in
 // the order chose the same tet, the tet's sphere is in already, or the site capacity is reached. One workgroup.
 __global__ __launch_bounds__(1024) void k_insert(RoundState r, float4* site) {
+  if (*r.stalled) return;
   __shared__ unsigned long long s_b[MAX_INSERT];
   __shared__ int s_wave[16];
   __shared__ int s_total;
@@ -306,6 +308,8 @@ __global__ void k_dirty_items(RoundState r, int nblk) {
 
 __global__ void k_round_end(RoundState r) {
   if (threadIdx.x != 0 || blockIdx.x != 0) return;
+  *r.stalled = (*r.status & (ST_PASS_FULL | ST_POOL_FULL)) ? 1 : 0;
+  if (*r.stalled) return;
   const int nsel = *r.nsel;
   for (int k = 0; k < nsel; ++k) r.selpos[r.sel[k]] = -1;
   *r.ns_cur = r.new_desc->ns;
