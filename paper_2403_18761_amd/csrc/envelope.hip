@@ -62,13 +62,14 @@ __device__ inline float4 f4(double3 v, double w) { return make_float4((float)v.x
 __device__ inline float4 bound_of(const float4* v, int n, bool value, double cond) {
   double3 m = make_double3(0, 0, 0);
   for (int k = 0; k < n; ++k) m = make_double3(m.x + v[k].x / (double)n, m.y + v[k].y / (double)n, m.z + v[k].z / (double)n);
+  const float4 b = f4(m, value ? INFINITY : -INFINITY);
+  if (!value || !(cond < ENV_COND)) return b;
   double R = -INFINITY;
-  for (int k = 0; k < n; ++k) {
-    const double3 d = sub3(c3(v[k]), m);
+  for (int k = 0; k < n; ++k) {  // from the rounded centre: far from the origin it is as far off as a small element is long
+    const double3 d = sub3(c3(v[k]), c3(b));
     R = fmax(R, sqrt(dot3(d, d)) + v[k].w);
   }
-  const float4 b = f4(m, value ? R + 1e-6 * fabs(R) : -INFINITY);
-  return value && !(cond < ENV_COND) ? make_float4(b.x, b.y, b.z, INFINITY) : b;
+  return make_float4(b.x, b.y, b.z, (float)(R + 1e-6 * fabs(R)));
 }
 
 __global__ void k_env_prep(const float4* sph, int ns, const int* edges, int ne, const int* tris, int nf,
