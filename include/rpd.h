@@ -70,6 +70,8 @@ typedef int32_t rpd_status;
 #define RPD_SHUFFLE_QUEUE (1u << 7)     /* test-only: process the work items in a shuffled order (same results) */
 #define RPD_ESTIMATED_ORDER (1u << 8)   /* no effect (the work is no longer ordered by measured times) */
 #define RPD_NO_SPLIT (1u << 9)          /* take every workgroup block whole in the candidate search (same results, for timing) */
+#define RPD_FORCE_CULLING (1u << 10)    /* test-only: rpd_envelope_distance and rpd_shrink_spheres sort and cull wherever
+                                           the sizes allow it, also where that is expected to be slower (same results) */
 
 /*
  * A prepared tet mesh (device resident): vertex/tet arrays, face adjacency, the multiplicity k(sigma) of every

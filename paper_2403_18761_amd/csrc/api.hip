@@ -80,8 +80,6 @@ static unsigned pow2_cap(size_t n) {
 // region of slow_scratch_bytes(1) (about 240 KB), allocated with the call's other buffers.
 static int slow_waves(long long nt) { return (int)std::max<long long>(64, std::min<long long>(2048, nt / 16)); }
 
-struct HostPinned;
-
 // A result array: its own storage, or a view into the call's downloaded (pinned) buffer that the result keeps.
 template <typename T>
 struct Arr {
@@ -401,31 +399,25 @@ static rpd_status status_error(int hst) {
 static std::mutex g_pin_mu;
 static std::map<size_t, std::vector<void*>> g_pin_pool;
 
-struct HostPinned {
-  void* p = nullptr;
-  size_t bytes = 0;
-  explicit HostPinned(size_t n) {
-    size_t c = 4096;
-    while (c < n) c <<= 1;
-    bytes = c;
-    {
-      std::lock_guard<std::mutex> g(g_pin_mu);
-      auto& v = g_pin_pool[c];
-      if (!v.empty()) {
-        p = v.back();
-        v.pop_back();
-        return;
-      }
-    }
-    hip_check(hipHostMalloc(&p, c, hipHostMallocDefault), "hipHostMalloc");
-  }
-  ~HostPinned() {
+HostPinned::HostPinned(size_t n) {
+  size_t c = 4096;
+  while (c < n) c <<= 1;
+  bytes = c;
+  {
     std::lock_guard<std::mutex> g(g_pin_mu);
-    g_pin_pool[bytes].push_back(p);
+    auto& v = g_pin_pool[c];
+    if (!v.empty()) {
+      p = v.back();
+      v.pop_back();
+      return;
+    }
   }
-  HostPinned(const HostPinned&) = delete;
-  HostPinned& operator=(const HostPinned&) = delete;
-};
+  hip_check(hipHostMalloc(&p, c, hipHostMallocDefault), "hipHostMalloc");
+}
+HostPinned::~HostPinned() {
+  std::lock_guard<std::mutex> g(g_pin_mu);
+  g_pin_pool[bytes].push_back(p);
+}
 
 void DeviceState::totals(unsigned long long* out, hipStream_t s, int* status_out) const {
   const size_t n = NCOUNTERS + 8 + (size_t)NSPREAD * NCOUNTERS;

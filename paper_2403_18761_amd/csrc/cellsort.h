@@ -31,7 +31,27 @@ struct CellSort {
 size_t cell_sort_runs(long long n, int len);
 size_t cell_sort_bytes(long long n, int len);
 CellSort cell_sort_layout(void* memory, long long n, int len);  // memory 8-byte aligned
-// point k is the mean of npt vectors (3 floats each) at pts + stride k; dirs: null, or 3 floats per point
+// The sum of cnt over a kernel's workgroups (below 2^20, 64 of them, every thread of each calls this), from the last one to
+// arrive, in out and, if not null, in host (pinned memory). total must be zero before.
+__device__ inline void probe_total(int cnt, int* total, int* out, int* host) {
+  __shared__ int s_sum;
+  if (threadIdx.x == 0) s_sum = 0;
+  __syncthreads();
+  for (int off = 32; off > 0; off >>= 1) cnt += __shfl_xor(cnt, off);
+  if ((threadIdx.x & 63) == 0 && cnt) atomicAdd(&s_sum, cnt);
+  __syncthreads();
+  if (threadIdx.x) return;
+  const int old = atomicAdd(total, (1 << 20) + s_sum);
+  if (old >> 20 != (int)gridDim.x - 1) return;
+  const int sum = (old & ((1 << 20) - 1)) + s_sum;
+  *out = sum;
+  if (host) *host = sum;
+}
+
+// Two halves: the points' box (and the cleared counts, and zero cleared too if not null), then the sort. Point k is the mean of npt vectors (3 floats each)
+// at pts + stride k; dirs: null, or 3 floats per point.
+hipError_t launch_cell_box(const float* pts, int stride, int npt, int n, const CellSort& S, int* zero,
+                           hipStream_t s);
 hipError_t launch_cell_sort(const float* pts, int stride, int npt, const float* dirs, int n, int len,
                             const CellSort& S, hipStream_t s);
 

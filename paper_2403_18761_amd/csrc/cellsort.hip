@@ -172,16 +172,23 @@ CellSort cell_sort_layout(void* memory, long long n, int len) {
   S.rank = S.order + n;
   return S;
 }
-hipError_t launch_cell_sort(const float* pts, int stride, int npt, const float* dirs, int n, int len,
-                            const CellSort& S, hipStream_t s) {
+static unsigned point_grid(int n) { return (unsigned)std::min((n + 255) / 256, 2048); }
+hipError_t launch_cell_box(const float* pts, int stride, int npt, int n, const CellSort& S, int* zero,
+                           hipStream_t s) {
   FillList L{};
   L.add(S.box, ~0ull, 6, 4);
   L.add(S.cells, 0, CELLS, 4);
-  hipError_t e = launch_fill_multi(L, s);
+  if (zero) L.add(zero, 0, 1, 4);
+  const hipError_t e = launch_fill_multi(L, s);
   if (e != hipSuccess) return e;
+  const Points P{pts, stride, npt, nullptr, n};
+  hipLaunchKernelGGL(k_cell_box, dim3(std::min(point_grid(n), 512u)), dim3(256), 0, s, P, S);
+  return hipGetLastError();
+}
+hipError_t launch_cell_sort(const float* pts, int stride, int npt, const float* dirs, int n, int len,
+                            const CellSort& S, hipStream_t s) {
   const Points P{pts, stride, npt, dirs, n};
-  const unsigned g = (unsigned)std::min((n + 255) / 256, 2048);
-  hipLaunchKernelGGL(k_cell_box, dim3(std::min(g, 512u)), dim3(256), 0, s, P, S);
+  const unsigned g = point_grid(n);
   hipLaunchKernelGGL(k_cell_count, dim3(g), dim3(256), 0, s, P, S);
   hipLaunchKernelGGL(k_cell_scan, dim3(TILES), dim3(TILE), 0, s, S);
   hipLaunchKernelGGL(k_cell_runs, dim3(1), dim3(1024), 0, s, S, len);

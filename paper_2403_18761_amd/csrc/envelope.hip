@@ -23,12 +23,14 @@
 // that the launch fills the chip; per-sample minima meet in one 64-bit atomicMin of (order-preserving float bits,
 // element id), which also breaks exact ties towards the lower element id. Many samples: the samples are sorted into the
 // cells of a grid, and the wavefronts of 64 neighbouring samples evaluate only the elements whose bounding sphere
-// reaches as near as the minimum can be (k_env_near). Both evaluate an element with the same expressions.
+// reaches as near as the minimum can be (k_env_near), where a few probes say that this leaves out enough of them. Both
+// evaluate an element with the same expressions.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cmath>
 #include <mutex>
+#include <optional>
 #include <type_traits>
 
 #include "rpd.h"
@@ -247,7 +249,7 @@ __global__ __launch_bounds__(ENV_THREADS) void k_env_dist(const float* __restric
 // c, and a sample's minimum is at most what it has seen so far. Per ENV_SEG elements the workgroup keeps those that
 // reach the bound from its own ball, each wavefront those that reach it from the wavefront's, and evaluates them. The
 // margin covers the rounding of the bounds and of the values (about ten FP32 roundings, and those of the record of an
-// element of condition up to ENV_COND). 1M samples against 9,841 elements: 0.44 ms, the whole call 0.64 ms (5.86 ms by
+// element of condition up to ENV_COND). 1M samples against 9,841 elements: 0.41 ms, the whole call 0.60 ms (5.8 ms by
 // brute force); bound by the culling tests and FP32 evaluations that remain.
 constexpr int ENV_SEG = 1024;
 template <bool ID>
@@ -400,6 +402,46 @@ __global__ __launch_bounds__(256) void k_env_near(const float* __restrict__ xyz,
   }
 }
 
+// How much the culling will leave: per probe, a sample, its distance to the nearest sphere and the number of elements whose
+// bounding sphere comes as near as that plus twice the reach of a wavefront's samples, summed over the probes; of many
+// spheres and elements, every few. The reach is the distance to the nearest other probe, scaled to the spacing of 64 of
+// the n samples as in three dimensions (on a surface it is less). 10 us, a chain of a few loads.
+constexpr int ENV_PROBES = 64, PROBE_NT = 1024, PROBE_SPHERES = 8192, PROBE_ELEMENTS = 4096;
+__global__ __launch_bounds__(PROBE_NT) void k_env_probe(const float* __restrict__ xyz, int n,
+                                                        const float4* __restrict__ bound, int ns, int ne, int sphere_step,
+                                                        int step, int* reached, int* host) {
+  __shared__ float s_min[PROBE_NT / 64], s_reach;
+  const int tid = threadIdx.x, lane = tid & 63;
+  auto probe = [&](int p, float* q) {
+    const long long s = (2ll * p + 1) * n / (2 * ENV_PROBES);
+    for (int k = 0; k < 3; ++k) q[k] = xyz[3 * s + k];
+  };
+  float q[3];
+  probe(blockIdx.x, q);
+  auto nearest = [&](int e) {  // (a sphere's bound is the sphere)
+    const float4 b = bound[e];
+    return value_sphere(b, q[0], q[1], q[2]);
+  };
+  float best = INFINITY;
+  for (int e = tid * sphere_step; e < ns; e += PROBE_NT * sphere_step) best = fminf(best, nearest(e));
+  for (int off = 32; off > 0; off >>= 1) best = fminf(best, __shfl_xor(best, off));
+  if (lane == 0) s_min[tid >> 6] = best;
+  if (tid < 64) {
+    float o[3], d2 = INFINITY;
+    probe(tid, o);
+    if (tid != (int)blockIdx.x)
+      d2 = (q[0] - o[0]) * (q[0] - o[0]) + (q[1] - o[1]) * (q[1] - o[1]) + (q[2] - o[2]) * (q[2] - o[2]);
+    for (int off = 32; off > 0; off >>= 1) d2 = fminf(d2, __shfl_xor(d2, off));
+    if (tid == 0) s_reach = 2.f * sqrtf(d2) * cbrtf(64.f * ENV_PROBES / (float)n);
+  }
+  __syncthreads();
+  for (int k = 0; k < PROBE_NT / 64; ++k) best = fminf(best, s_min[k]);
+  const float ub = best + s_reach;
+  int cnt = 0;
+  for (long long e = (long long)tid * step; e < ne; e += PROBE_NT * step) cnt += !(nearest((int)e) > ub) ? 1 : 0;
+  probe_total(cnt, reached, reached + 1, host);
+}
+
 __global__ void k_env_finish(const unsigned long long* key, long long n, float* dist, int* nearest) {
   for (long long s = blockIdx.x * (long long)blockDim.x + threadIdx.x; s < n; s += (long long)gridDim.x * blockDim.x) {
     const unsigned long long k = key[s];
@@ -410,37 +452,70 @@ __global__ void k_env_finish(const unsigned long long* key, long long n, float* 
 }
 
 // Working memory of one call: the element records (CONE_F4 float4 per edge, SLAB_F4 per triangle), the per-sample
-// minima (one 64-bit key per sample) and a status word.
+// minima (one 64-bit key per sample), and a status word with the probes' counts behind it.
+constexpr int STATUS_INTS = 3;
 size_t record_bytes(long long ne, long long nf) { return 16 * ((size_t)CONE_F4 * ne + (size_t)SLAB_F4 * nf); }
 
-// Whether the samples are sorted and the elements culled (k_env_near), and the working memory of that.
+// Whether the samples may be sorted and the elements culled (k_env_near), and the working memory of that.
 bool sorted_path(long long n, long long elements) {
   // More launches and a sort of the samples, against fewer evaluations: at 2,398
   // elements 100k samples take 180 us sorted and 213 us not, 30k samples 153 and 107 us; at 451 elements 1M samples
   // 265 and 327 us, 300k samples 162 and 138 us; at 9,841 elements 30k samples 305 and 262 us, 100k 337 and 733 us.
   return n >= 50000 && n < (1ll << 30) && elements < (1ll << 30) && n * elements >= 200000000ll;
 }
+// ... and whether they are, by the share of the elements that the probes reached. A wavefront's samples are those of a
+// coarse cell, which fill few lanes where the cells are many for the samples, and it costs the share of the elements and
+// the tests of all; brute force fills the lanes and costs all elements. Times sorted and by brute force, and the rule's
+// value: surface samples and a medial mesh 0.61 and 5.8 ms (0.16) at 1M x 9,828, 337 and 425 us (0.93) at 60k x 9,445;
+// elements as long as the model and samples in its volume 1.03 and 1.37 ms (0.84) at 1M x 2,400, 2.16 and 1.64 ms (1.23)
+// at 300k x 9,000, 642 and 193 us (2.7) at 100k x 2,400; elements close together, far from the samples 1.93 and 1.37 ms
+// (1.43) at 1M x 2,400. The probes cost the one path 14 us, the other 40 us.
+bool culling_pays(long long n, double reached) {
+  const double waves = (double)n / 64;
+  return (4096 + waves) / waves * (1.8 * reached + 0.1) < 1.0;
+}
 size_t sorted_bytes(long long n, long long elements) {
   return 16 * (size_t)elements + cell_sort_bytes(n, 256);
 }
 
 // The launches of one call on device-resident inputs and outputs, given its working memory; ev0/ev1 (optional)
-// bracket the distance kernel. No allocation and no exception: returns the first HIP error.
+// bracket the distance kernels; early (optional) reads the probes' count, else the call waits for it; force: cull
+// whatever the probes say, where the sizes allow it. No allocation and no exception: returns the first HIP error.
 // work (work_bytes of it): the per-sample minima, or what the sorted path keeps instead.
 hipError_t envelope_launch(const float4* sph, int ns, const int* edg, long long ne, const int* tri, long long nf,
                            const float* xyz, long long n, hipStream_t st, float4* rec, void* work, size_t work_bytes,
-                           int* status, float* dist, int* nearest, hipEvent_t ev0, hipEvent_t ev1) {
+                           int* status, float* dist, int* nearest, hipEvent_t ev0, hipEvent_t ev1, EarlyInt* early, bool force) {
   float4* cone = rec;
   float4* slab = rec + (size_t)CONE_F4 * ne;
-  if (sorted_path(n, ns + ne + nf) && sorted_bytes(n, ns + ne + nf) <= work_bytes) {
-    unsigned char* b = (unsigned char*)work;
-    float4* bound = (float4*)b;
-    const CellSort S = cell_sort_layout(b + 16 * (size_t)(ns + ne + nf), n, 256);
-    hipError_t e = launch_fill_i32(status, 0, 1, st);
+  const long long total = ns + ne + nf;
+  bool sorted = sorted_path(n, total) && sorted_bytes(n, total) <= work_bytes;
+  float4* bound = sorted ? (float4*)work : nullptr;
+  const CellSort S = cell_sort_layout((unsigned char*)work + 16 * (size_t)total, n, 256);
+  hipError_t e = launch_fill_i32(status, 0, STATUS_INTS, st);
+  if (e != hipSuccess) return e;
+  if (sorted || ne + nf > 0) {
+    const int g = (int)std::min<long long>((std::max<long long>(ne + nf, sorted ? ns : 0) + 255) / 256, 4096);
+    hipLaunchKernelGGL(k_env_prep, dim3(g), dim3(256), 0, st, sph, ns, edg, (int)ne, tri, (int)nf, cone, slab, status,
+                       bound);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  if (sorted) {
+    const int step = (int)((total + PROBE_ELEMENTS - 1) / PROBE_ELEMENTS), seen = (int)((total + step - 1) / step);
+    hipLaunchKernelGGL(k_env_probe, dim3(ENV_PROBES), dim3(PROBE_NT), 0, st, xyz, (int)n, bound, ns, (int)total,
+                       (ns + PROBE_SPHERES - 1) / PROBE_SPHERES, step, status + 1, early ? early->p() : nullptr);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    // (read while the samples' box is found, where there is pinned memory to read from)
+    int reached = 0;
+    e = early ? early->mark(st) : hipMemcpyAsync(&reached, status + 2, sizeof(int), hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess && ev0) e = hipEventRecord(ev0, st);
+    if (e == hipSuccess) e = launch_cell_box(xyz, 3, 1, (int)n, S, nullptr, st);
+    if (e == hipSuccess) e = early ? early->wait(&reached) : hipStreamSynchronize(st);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_env_prep, dim3((unsigned)std::min<long long>((std::max<long long>(ne + nf, ns) + 255) / 256, 4096)),
-                       dim3(256), 0, st, sph, ns, edg, (int)ne, tri, (int)nf, cone, slab, status, bound);
-    if (ev0 && (e = hipEventRecord(ev0, st)) != hipSuccess) return e;
+    sorted = force || culling_pays(n, (double)reached / ((double)ENV_PROBES * (double)seen));
+  } else if (ev0 && (e = hipEventRecord(ev0, st)) != hipSuccess) {
+    return e;
+  }
+  if (sorted) {
     if ((e = launch_cell_sort(xyz, 3, 1, nullptr, (int)n, 256, S, st)) != hipSuccess) return e;
     const dim3 grid((unsigned)cell_sort_runs(n, 256));
     if (nearest)
@@ -452,22 +527,12 @@ hipError_t envelope_launch(const float4* sph, int ns, const int* edg, long long 
     if (ev1 && (e = hipEventRecord(ev1, st)) != hipSuccess) return e;
     return hipGetLastError();
   }
-  unsigned long long* key = (unsigned long long*)work;
-  hipError_t e = launch_fill_i32(status, 0, 1, st);
-  if (e == hipSuccess) e = launch_fill_u64(key, ~0ull, (size_t)n, st);
-  if (e != hipSuccess) return e;
-  if (ne + nf > 0) {
-    const int g = (int)std::min<long long>((ne + nf + 255) / 256, 4096);
-    hipLaunchKernelGGL(k_env_prep, dim3(g), dim3(256), 0, st, sph, ns, edg, (int)ne, tri, (int)nf, cone, slab,
-                       status, nullptr);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
+  unsigned long long* key = (unsigned long long*)work;  // (over the bounds)
+  if ((e = launch_fill_u64(key, ~0ull, (size_t)n, st)) != hipSuccess) return e;
   // grid: sample blocks x element chunks, about 2048 workgroups in all, each chunk at least 64 elements
   const long long sblocks = (n + ENV_SAMPLES_PER_BLOCK - 1) / ENV_SAMPLES_PER_BLOCK;
-  const long long total = ns + ne + nf;
   long long chunks = std::max<long long>(1, std::min<long long>((2048 + sblocks - 1) / sblocks, total / 64));
   chunks = std::min<long long>(chunks, 65535);
-  if (ev0 && (e = hipEventRecord(ev0, st)) != hipSuccess) return e;
   if (total > 0) {
     if (nearest)
       hipLaunchKernelGGL(k_env_dist<true>, dim3((unsigned)sblocks, (unsigned)chunks), dim3(ENV_THREADS), 0, st, xyz,
@@ -506,6 +571,8 @@ void envelope_distance(const float* spheres, int ns, const int* edges, long long
   if (hipGetDeviceCount(&ndev) != hipSuccess || ndev <= 0) throw Failure{RPD_E_DEVICE, "no HIP device"};
 
   DBuf d_sph, d_edge, d_tri, d_xyz, d_out, d_near, rec, work, status;
+  std::optional<EarlyInt> early;
+  if (sorted_path(n, ns + ne + nf)) early.emplace();
   const DrainOnExit drain{st};
   const float4* sph = (const float4*)spheres;
   const int* edg = edges;
@@ -528,7 +595,7 @@ void envelope_distance(const float* spheres, int ns, const int* edges, long long
   const size_t work_bytes = std::max(8 * (size_t)n, sorted_path(n, ns + ne + nf) ? sorted_bytes(n, ns + ne + nf) : 0);
   rec.alloc(record_bytes(ne, nf));
   work.alloc(work_bytes);
-  status.alloc(sizeof(int));
+  status.alloc(sizeof(int) * STATUS_INTS);
   hipEvent_t ev[2] = {nullptr, nullptr};
   struct EventGuard {
     hipEvent_t* e;
@@ -549,7 +616,8 @@ void envelope_distance(const float* spheres, int ns, const int* edges, long long
     out_d = d_out.as<float>();
     out_n = nearest ? d_near.as<int>() : nullptr;
   }
-  hip_check(envelope_launch(sph, ns, edg, ne, tri, nf, xyz, n, st, rec.as<float4>(), work.p, work_bytes, status.as<int>(), out_d, out_n, ev[0], ev[1]),
+  hip_check(envelope_launch(sph, ns, edg, ne, tri, nf, xyz, n, st, rec.as<float4>(), work.p, work_bytes, status.as<int>(), out_d, out_n, ev[0],
+                            ev[1], early ? &*early : nullptr, (flags & RPD_FORCE_CULLING) != 0),
             "envelope distance");
   int hst = 0;
   hip_check(hipMemcpyAsync(&hst, status.p, sizeof(int), hipMemcpyDeviceToHost, st), "download");
@@ -627,7 +695,7 @@ extern "C" rpd_status rpd_envelope_distance_noalloc(const float* spheres, int32_
   hipStream_t st = (hipStream_t)stream;
   hipError_t e = envelope_launch((const float4*)spheres, n_spheres, edges, n_edges, tris, n_tris, samples, n_samples,
                                  st, rec, b + at, (size_t)RPD_NOALLOC_SCRATCH_BYTES - at, status, dist, nearest,
-                                 nullptr, nullptr);
+                                 nullptr, nullptr, nullptr, false);
   int hst = 0;
   if (e == hipSuccess) e = hipMemcpyAsync(&hst, status, sizeof(int), hipMemcpyDeviceToHost, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);

@@ -73,6 +73,38 @@ struct DBuf {
   }
 };
 
+// pinned host memory, pooled like device memory
+struct HostPinned {
+  void* p = nullptr;
+  size_t bytes = 0;
+  explicit HostPinned(size_t n);
+  ~HostPinned();
+  HostPinned(const HostPinned&) = delete;
+  HostPinned& operator=(const HostPinned&) = delete;
+};
+
+// An int that a kernel writes to pinned memory and the host reads while the work queued behind that kernel runs.
+struct EarlyInt {
+  HostPinned mem{sizeof(int)};
+  hipEvent_t ev = nullptr;
+  EarlyInt() = default;
+  EarlyInt(const EarlyInt&) = delete;
+  EarlyInt& operator=(const EarlyInt&) = delete;
+  ~EarlyInt() {
+    if (ev) (void)hipEventDestroy(ev);
+  }
+  int* p() const { return (int*)mem.p; }
+  hipError_t mark(hipStream_t s) {  // behind the kernel
+    const hipError_t e = ev ? hipSuccess : hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+    return e == hipSuccess ? hipEventRecord(ev, s) : e;
+  }
+  hipError_t wait(int* v) {
+    const hipError_t e = hipEventSynchronize(ev);
+    *v = *(const volatile int*)mem.p;
+    return e;
+  }
+};
+
 // Waits for a stream on leaving a scope. Device buffers go back to a pool that every thread and stream draws from, so
 // none may be released while queued work still uses it: declared after them, this runs before their destructors, also
 // when an exception leaves the scope.

@@ -121,8 +121,9 @@ hipError_t launch_surface_faces(const float4* tp, const int* tn, int nt, float* 
                                 int* count, hipStream_t s);
 hipError_t launch_iota(int* p, int n, hipStream_t s);
 hipError_t launch_scatter_spheres(const float4* sph, const int* slot, int n, float4* table, int* used, hipStream_t s);
+// (force: cull triangles whatever it is expected to cost, where the sizes allow it)
 void shrink_spheres(const float* tri, long long nt, const float* pins, const float* normals, const int* own,
-                    long long n, hipStream_t st, float4* out);
+                    long long n, hipStream_t st, float4* out, bool force = false);
 // selection, insertion and dirty marking of one round; a supplies the element tables and sites of the new shape
 hipError_t launch_round_front(const RoundState& r, const ShapeArgs& a, const int* cell_b0,
                               const float4* tp, const float* blkbox, int nblk, hipStream_t s);

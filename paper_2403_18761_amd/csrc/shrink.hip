@@ -10,7 +10,8 @@
 // lies in the triangle). So no iteration and no nearest-point search is needed: the result is that minimum over every
 // surface triangle. Few (pin, triangle) pairs: brute force. Many: pins and triangles are sorted into grid cells, and
 // 64 neighbouring pins with about the same normal evaluate only the triangles whose bounding sphere a ball smaller
-// than the least radius so far can touch (k_shrink_near). Both evaluate a triangle with the same expressions.
+// than the least radius so far can touch (k_shrink_near), where a few probes say that this leaves out enough of them.
+// Both evaluate a triangle with the same expressions.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -60,6 +61,19 @@ __device__ inline float edge_rho(float wx, float wy, float wz, float ex, float e
   return best;
 }
 
+// a triangle's bounding sphere (not finite, or too large for its squares: NaN, never passed over)
+__device__ inline float4 triangle_bound(const float* v) {
+  const float c[3] = {(v[0] + v[3] + v[6]) * (1.f / 3.f), (v[1] + v[4] + v[7]) * (1.f / 3.f),
+                      (v[2] + v[5] + v[8]) * (1.f / 3.f)};
+  float d2 = 0.f;
+  for (int k = 0; k < 3; ++k) {
+    const float x = v[3 * k] - c[0], y = v[3 * k + 1] - c[1], z = v[3 * k + 2] - c[2];
+    d2 = fmaxf(d2, x * x + y * y + z * z);
+  }
+  return isfinite(d2) && isfinite(c[0] + c[1] + c[2]) ? make_float4(c[0], c[1], c[2], sqrtf(d2) * 1.0001f)
+                                                      : make_float4(NAN, NAN, NAN, NAN);
+}
+
 // triangle records: (a, 0) (e1 = b - a, 0) (e2 = c - a, 0) (unit normal m, 0) (dual basis u1 of e1, e2) (u2), as six
 // float4, in FP64 then rounded; u1.e1 = 1, u1.e2 = 0 and u2 the other way round give barycentric coordinates
 // (SORTED: record k is of triangle order[k], and bound[k] its bounding sphere; else of triangle k)
@@ -67,19 +81,7 @@ template <bool SORTED>
 __global__ void k_shrink_prep(const float* tri, long long nt, const int* order, float4* rec, float4* bound) {
   for (long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x; t < nt; t += (long long)gridDim.x * blockDim.x) {
     const float* v = tri + 9 * (SORTED ? (long long)order[t] : t);
-    if (SORTED) {
-      const float c[3] = {(v[0] + v[3] + v[6]) * (1.f / 3.f), (v[1] + v[4] + v[7]) * (1.f / 3.f),
-                          (v[2] + v[5] + v[8]) * (1.f / 3.f)};
-      float d2 = 0.f;
-      for (int k = 0; k < 3; ++k) {
-        const float x = v[3 * k] - c[0], y = v[3 * k + 1] - c[1], z = v[3 * k + 2] - c[2];
-        d2 = fmaxf(d2, x * x + y * y + z * z);
-      }
-      // (not finite, or too large for its squares: never passed over)
-      bound[t] = isfinite(d2) && isfinite(c[0] + c[1] + c[2])
-                     ? make_float4(c[0], c[1], c[2], sqrtf(d2) * 1.0001f)
-                     : make_float4(NAN, NAN, NAN, NAN);
-    }
+    if (SORTED) bound[t] = triangle_bound(v);
     const double ax = v[0], ay = v[1], az = v[2];
     const double e1x = v[3] - ax, e1y = v[4] - ay, e1z = v[5] - az;
     const double e2x = v[6] - ax, e2y = v[7] - ay, e2z = v[8] - az;
@@ -270,6 +272,38 @@ __global__ __launch_bounds__(SHR_NEAR) void k_shrink_near(const float4* __restri
   }
 }
 
+// How much the culling will leave: per probe, a pin, the least rho of the triangles' vertices and the number of triangles
+// whose bounding sphere a ball of that radius meets, summed over the probes, each over every stride-th triangle.
+constexpr int SHR_PROBES = 64, PROBE_NT = 1024, PROBE_TRIANGLES = 4096;
+__global__ __launch_bounds__(PROBE_NT) void k_shrink_probe(const float* __restrict__ tri, int nt, int stride,
+                                                           const float* __restrict__ pin, const float* __restrict__ nrm,
+                                                           const int* __restrict__ own, int n, int* reached, int* host) {
+  __shared__ float s_min[PROBE_NT / 64];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const long long s = (2ll * blockIdx.x + 1) * n / (2 * SHR_PROBES);
+  const float px = pin[3 * s], py = pin[3 * s + 1], pz = pin[3 * s + 2];
+  const float nx = nrm[3 * s], ny = nrm[3 * s + 1], nz = nrm[3 * s + 2];
+  const int skip = own ? own[s] : -1;
+  float best = INFINITY;
+  for (int t = tid * stride; t < nt; t += PROBE_NT * stride) {
+    if (t == skip) continue;
+    const float* v = tri + 9 * (size_t)t;
+    for (int k = 0; k < 3; ++k)
+      best = fminf(best, rho_of(v[3 * k] - px, v[3 * k + 1] - py, v[3 * k + 2] - pz, nx, ny, nz));
+  }
+  for (int off = 32; off > 0; off >>= 1) best = fminf(best, __shfl_xor(best, off));
+  if (lane == 0) s_min[tid >> 6] = best;
+  __syncthreads();
+  for (int k = 0; k < PROBE_NT / 64; ++k) best = fminf(best, s_min[k]);
+  int cnt = 0;
+  for (int t = tid * stride; t < nt; t += PROBE_NT * stride) {
+    const float4 b = triangle_bound(tri + 9 * (size_t)t);
+    const float x = b.x - px - best * nx, y = b.y - py - best * ny, z = b.z - pz - best * nz;
+    cnt += !(sqrtf(x * x + y * y + z * z) > best + b.w) ? 1 : 0;
+  }
+  probe_total(cnt, reached, reached + 1, host);
+}
+
 __global__ void k_shrink_finish(const unsigned* bits, const float* pin, const float* nrm, long long n, float4* out) {
   for (long long s = blockIdx.x * (long long)blockDim.x + threadIdx.x; s < n; s += (long long)gridDim.x * blockDim.x) {
     const float r = bits[s] == 0xffffffffu ? INFINITY : __uint_as_float(bits[s]);
@@ -282,21 +316,46 @@ __global__ void k_shrink_finish(const unsigned* bits, const float* pin, const fl
 
 // Returns when the spheres are there: the workspaces, whose sorted orders the kernels index with, go back to the pool.
 void shrink_spheres(const float* tri, long long nt, const float* pins, const float* normals, const int* own,
-                    long long n, hipStream_t st, float4* out) {
+                    long long n, hipStream_t st, float4* out, bool force) {
   if (n == 0) return;
   DBuf rec(16 * 6 * (size_t)std::max<long long>(nt, 1)), bits(4 * (size_t)n), bound, cluster, ts, ps;
+  EarlyInt early;
   const DrainOnExit drain{st};
+  CellSort T{}, P{};
   // The sorts and the starting radii are a fixed cost that brute force passes at about 40M pairs: of the 15,384 triangles
-  // of a 64^3 torus, 2,000 pins take 320 us by brute force, 4,000 take 564 us and 364 us sorted, all 2,108 and 398 us.
+  // of a 64^3 torus, 2,000 pins take 320 us by brute force, 4,000 take 581 us and 321 us sorted, 15,000 2,163 and 360 us.
   // Few pins on many triangles fill the chip badly (1,000 on 65k triangles: 555 us by brute force, 595 us sorted).
-  if (n >= 2048 && n < (1ll << 30) && nt < (1ll << 28) && n * nt >= 40000000ll) {
+  bool sorted = n >= 2048 && n < (1ll << 30) && nt < (1ll << 28) && n * nt >= 40000000ll;
+  if (sorted) {
+    const int stride = (int)((nt + PROBE_TRIANGLES - 1) / PROBE_TRIANGLES);
+    int reached = 0;
+    ts.alloc(cell_sort_bytes(nt, 64));
+    ps.alloc(cell_sort_bytes(n, 64));
+    T = cell_sort_layout(ts.p, nt, 64);
+    P = cell_sort_layout(ps.p, n, 64);
+    hip_check(launch_cell_box(tri, 9, 3, (int)nt, T, bits.as<int>(), st), "sort triangles");
+    hipLaunchKernelGGL(k_shrink_probe, dim3(SHR_PROBES), dim3(PROBE_NT), 0, st, tri, (int)nt, stride, pins, normals, own,
+                       (int)n, bits.as<int>(), early.p());
+    hip_check(hipGetLastError(), "probe");
+    // (read while the triangles are sorted)
+    hip_check(early.mark(st), "probe");
+    hip_check(launch_cell_sort(tri, 9, 3, nullptr, (int)nt, 64, T, st), "sort triangles");
+    hip_check(early.wait(&reached), "probe");
+    // The share of the triangles that the probes' balls met, and runs of a few pins where their cells are many for them
+    // (about 1,300 on a surface), against brute force's full lanes and all triangles. Times sorted and by brute force,
+    // and the rule's value: 64^3 torus 0.34 and 2.16 ms (0.19) for 15,000 pins, 297 and 581 us (0.62) for 4,000, 296 and
+    // 485 us (0.90) for 2,700; a cylinder of strips as long as itself 1.49 and 0.79 ms (5.3) for 20,000 pins on 5,000
+    // triangles, 3.9 and 0.76 ms (18) for 5,000 on 20,000; random triangles as large as the model 7.5 and 0.68 ms (7.2).
+    // The probes cost the one path 12 us, the other 45 us.
+    const double met = (double)reached / ((double)SHR_PROBES * (double)((nt + stride - 1) / stride));
+    const double waves = (double)n / 64;
+    sorted = force || (1300 + waves) / waves * (met + 0.027) < 1.0;
+  }
+  if (sorted) {
     const size_t nc = (size_t)(nt + SHR_CLUSTER - 1) / SHR_CLUSTER;
     bound.alloc(16 * (size_t)nt);
     cluster.alloc(16 * nc);
-    ts.alloc(cell_sort_bytes(nt, 64));
-    ps.alloc(cell_sort_bytes(n, 64));
-    const CellSort T = cell_sort_layout(ts.p, nt, 64), P = cell_sort_layout(ps.p, n, 64);
-    hip_check(launch_cell_sort(tri, 9, 3, nullptr, (int)nt, 64, T, st), "sort triangles");
+    hip_check(launch_cell_box(pins, 3, 1, (int)n, P, nullptr, st), "sort pins");
     hip_check(launch_cell_sort(pins, 3, 1, normals, (int)n, 64, P, st), "sort pins");
     const unsigned g = (unsigned)std::min<long long>((nt + 255) / 256, 4096);
     hipLaunchKernelGGL(k_shrink_prep<true>, dim3(g), dim3(256), 0, st, tri, nt, T.order, rec.as<float4>(),
@@ -342,7 +401,8 @@ extern "C" rpd_status rpd_shrink_spheres(const float* tris, int64_t n_tris, cons
     hipStream_t st = (hipStream_t)stream;
     const bool dev = (flags & RPD_DEVICE_PTRS) != 0;
     if (dev) {
-      rpd::shrink_spheres(tris, n_tris, pins, normals, own_tri, n_pins, st, (float4*)spheres);
+      rpd::shrink_spheres(tris, n_tris, pins, normals, own_tri, n_pins, st, (float4*)spheres,
+                          (flags & RPD_FORCE_CULLING) != 0);
     } else {
       rpd::DBuf t(36 * (size_t)n_tris), p(12 * (size_t)n_pins), q(12 * (size_t)n_pins), o(4 * (size_t)n_pins),
           out(16 * (size_t)n_pins);
@@ -353,7 +413,7 @@ extern "C" rpd_status rpd_shrink_spheres(const float* tris, int64_t n_tris, cons
       if (own_tri)
         rpd::hip_check(hipMemcpyAsync(o.p, own_tri, 4 * (size_t)n_pins, hipMemcpyHostToDevice, st), "upload");
       rpd::shrink_spheres(t.as<float>(), n_tris, p.as<float>(), q.as<float>(), own_tri ? o.as<int>() : nullptr, n_pins,
-                          st, out.as<float4>());
+                          st, out.as<float4>(), (flags & RPD_FORCE_CULLING) != 0);
       rpd::hip_check(hipMemcpyAsync(spheres, out.p, 16 * (size_t)n_pins, hipMemcpyDeviceToHost, st), "download");
       rpd::hip_check(hipStreamSynchronize(st), "synchronize");
     }

@@ -30,6 +30,7 @@ RPD_OWNER_WEIGHTS = 1 << 6
 RPD_SHUFFLE_QUEUE = 1 << 7
 RPD_ESTIMATED_ORDER = 1 << 8
 RPD_NO_SPLIT = 1 << 9
+RPD_FORCE_CULLING = 1 << 10  # test-only
 RPD_NOALLOC_SCRATCH_BYTES = 64 << 20  # the no-allocation entry point's working memory per device
 
 _f32p = C.POINTER(C.c_float)
@@ -378,7 +379,8 @@ def thin(n_vertices: int, edges, tris, alpha, tets, sigma: float):
     return ke[:e.shape[0]].astype(bool), kf[:f.shape[0]].astype(bool), kt[:t.shape[0]].astype(bool)
 
 
-def envelope_distance(spheres, edges, tris, samples, stream=None, timing: bool = False, nearest: bool = True):
+def envelope_distance(spheres, edges, tris, samples, stream=None, timing: bool = False, nearest: bool = True,
+                      flags: int = 0):
     """rpd_envelope_distance: distance from each sample to the enveloping volume of a medial mesh.
 
     spheres (n, 4) float32 (x, y, z, r); edges (m, 2) and tris (k, 3) int32 sphere ids; samples (s, 3) float32.
@@ -401,7 +403,7 @@ def envelope_distance(spheres, edges, tris, samples, stream=None, timing: bool =
         ptr = lambda t: C.c_void_p(t.data_ptr() if t is not None and t.numel() else 0)
         st = _stream_ptr(stream) if stream is not None else C.c_void_p(torch.cuda.current_stream(dev).cuda_stream)
         _check(lib.rpd_envelope_distance(ptr(sp), sp.shape[0], ptr(ed), ed.shape[0], ptr(tr), tr.shape[0], ptr(q),
-                                         q.shape[0], RPD_DEVICE_PTRS, st, ptr(dist), ptr(near), kptr))
+                                         q.shape[0], RPD_DEVICE_PTRS | flags, st, ptr(dist), ptr(near), kptr))
         return (dist, near, kms.value) if timing else (dist, near)
     sp = np.ascontiguousarray(np.asarray(spheres, np.float32).reshape(-1, 4))
     ed = np.ascontiguousarray(np.asarray(edges, np.int32).reshape(-1, 2))
@@ -411,7 +413,7 @@ def envelope_distance(spheres, edges, tris, samples, stream=None, timing: bool =
     near = np.empty(q.shape[0], np.int32) if nearest else None
     ptr = lambda a: C.c_void_p(a.ctypes.data if a is not None and a.size else 0)
     _check(lib.rpd_envelope_distance(ptr(sp), sp.shape[0], ptr(ed), ed.shape[0], ptr(tr), tr.shape[0], ptr(q),
-                                     q.shape[0], 0, _stream_ptr(stream), ptr(dist), ptr(near), kptr))
+                                     q.shape[0], flags, _stream_ptr(stream), ptr(dist), ptr(near), kptr))
     return (dist, near, kms.value) if timing else (dist, near)
 
 
@@ -437,7 +439,7 @@ def envelope_distance_noalloc(spheres, edges, tris, samples, dist, nearest=None,
                                              ptr(dist), ptr(nearest)))
 
 
-def shrink_spheres(tris, pins, normals, own_tri=None, stream=None):
+def shrink_spheres(tris, pins, normals, own_tri=None, stream=None, flags: int = 0):
     """rpd_shrink_spheres: maximal empty balls tangent to the surface (triangles (m, 3, 3)) at the pins (s, 3) with
     inward unit normals (s, 3); own_tri (s,) the pin's triangle or None. CUDA tensors run on the device (output a
     tensor), numpy arrays through host memory. Returns (s, 4) float32 (centre, radius)."""
@@ -453,8 +455,8 @@ def shrink_spheres(tris, pins, normals, own_tri=None, stream=None):
         out = torch.empty((p.shape[0], 4), dtype=torch.float32, device=dev)
         ptr = lambda x: C.c_void_p(x.data_ptr() if x is not None and x.numel() else 0)
         st = _stream_ptr(stream) if stream is not None else C.c_void_p(torch.cuda.current_stream(dev).cuda_stream)
-        _check(lib.rpd_shrink_spheres(ptr(t), t.shape[0], ptr(p), ptr(n), ptr(o), p.shape[0], RPD_DEVICE_PTRS, st,
-                                      ptr(out)))
+        _check(lib.rpd_shrink_spheres(ptr(t), t.shape[0], ptr(p), ptr(n), ptr(o), p.shape[0], RPD_DEVICE_PTRS | flags,
+                                      st, ptr(out)))
         return out
     t = np.ascontiguousarray(np.asarray(tris, np.float32).reshape(-1, 9))
     p = np.ascontiguousarray(np.asarray(pins, np.float32).reshape(-1, 3))
@@ -462,7 +464,7 @@ def shrink_spheres(tris, pins, normals, own_tri=None, stream=None):
     o = np.ascontiguousarray(np.asarray(own_tri, np.int32)) if own_tri is not None else None
     out = np.empty((p.shape[0], 4), np.float32)
     ptr = lambda x: C.c_void_p(x.ctypes.data if x is not None and x.size else 0)
-    _check(lib.rpd_shrink_spheres(ptr(t), t.shape[0], ptr(p), ptr(n), ptr(o), p.shape[0], 0, _stream_ptr(stream),
+    _check(lib.rpd_shrink_spheres(ptr(t), t.shape[0], ptr(p), ptr(n), ptr(o), p.shape[0], flags, _stream_ptr(stream),
                                   ptr(out)))
     return out
 
