@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include "rpd_common.h"
+#include "rpd_launch.h"
 
 namespace rpd {
 
@@ -48,10 +49,10 @@ __device__ inline void probe_total(int cnt, int* total, int* out, int* host) {
   if (host) *host = sum;
 }
 
-// Two halves: the points' box (and the cleared counts, and zero cleared too if not null), then the sort. Point k is the mean of npt vectors (3 floats each)
-// at pts + stride k; dirs: null, or 3 floats per point.
-hipError_t launch_cell_box(const float* pts, int stride, int npt, int n, const CellSort& S, int* zero,
-                           hipStream_t s);
+// In three steps, with the caller's other work between them: the jobs that clear what a sort counts in, the points' box,
+// and the rest. Point k is the mean of npt vectors (3 floats each) at pts + stride k; dirs: null, or 3 floats per point.
+void cell_sort_clear(FillList& L, const CellSort& S);
+hipError_t launch_cell_box(const float* pts, int stride, int npt, int n, const CellSort& S, hipStream_t s);
 hipError_t launch_cell_sort(const float* pts, int stride, int npt, const float* dirs, int n, int len,
                             const CellSort& S, hipStream_t s);
 

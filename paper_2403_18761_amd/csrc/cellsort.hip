@@ -173,14 +173,11 @@ CellSort cell_sort_layout(void* memory, long long n, int len) {
   return S;
 }
 static unsigned point_grid(int n) { return (unsigned)std::min((n + 255) / 256, 2048); }
-hipError_t launch_cell_box(const float* pts, int stride, int npt, int n, const CellSort& S, int* zero,
-                           hipStream_t s) {
-  FillList L{};
+void cell_sort_clear(FillList& L, const CellSort& S) {
   L.add(S.box, ~0ull, 6, 4);
   L.add(S.cells, 0, CELLS, 4);
-  if (zero) L.add(zero, 0, 1, 4);
-  const hipError_t e = launch_fill_multi(L, s);
-  if (e != hipSuccess) return e;
+}
+hipError_t launch_cell_box(const float* pts, int stride, int npt, int n, const CellSort& S, hipStream_t s) {
   const Points P{pts, stride, npt, nullptr, n};
   hipLaunchKernelGGL(k_cell_box, dim3(std::min(point_grid(n), 512u)), dim3(256), 0, s, P, S);
   return hipGetLastError();

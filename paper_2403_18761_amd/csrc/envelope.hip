@@ -469,7 +469,7 @@ bool sorted_path(long long n, long long elements) {
 // value: surface samples and a medial mesh 0.61 and 5.8 ms (0.16) at 1M x 9,828, 337 and 425 us (0.93) at 60k x 9,445;
 // elements as long as the model and samples in its volume 1.03 and 1.37 ms (0.84) at 1M x 2,400, 2.16 and 1.64 ms (1.23)
 // at 300k x 9,000, 642 and 193 us (2.7) at 100k x 2,400; elements close together, far from the samples 1.93 and 1.37 ms
-// (1.43) at 1M x 2,400. The probes cost the one path 14 us, the other 40 us.
+// (1.43) at 1M x 2,400. The probes cost the one path about 5 us, the other 40 us.
 bool culling_pays(long long n, double reached) {
   const double waves = (double)n / 64;
   return (4096 + waves) / waves * (1.8 * reached + 0.1) < 1.0;
@@ -491,7 +491,10 @@ hipError_t envelope_launch(const float4* sph, int ns, const int* edg, long long 
   bool sorted = sorted_path(n, total) && sorted_bytes(n, total) <= work_bytes;
   float4* bound = sorted ? (float4*)work : nullptr;
   const CellSort S = cell_sort_layout((unsigned char*)work + 16 * (size_t)total, n, 256);
-  hipError_t e = launch_fill_i32(status, 0, STATUS_INTS, st);
+  FillList L{};
+  L.add(status, 0, STATUS_INTS, 4);
+  if (sorted) cell_sort_clear(L, S);
+  hipError_t e = launch_fill_multi(L, st);
   if (e != hipSuccess) return e;
   if (sorted || ne + nf > 0) {
     const int g = (int)std::min<long long>((std::max<long long>(ne + nf, sorted ? ns : 0) + 255) / 256, 4096);
@@ -508,7 +511,7 @@ hipError_t envelope_launch(const float4* sph, int ns, const int* edg, long long 
     int reached = 0;
     e = early ? early->mark(st) : hipMemcpyAsync(&reached, status + 2, sizeof(int), hipMemcpyDeviceToHost, st);
     if (e == hipSuccess && ev0) e = hipEventRecord(ev0, st);
-    if (e == hipSuccess) e = launch_cell_box(xyz, 3, 1, (int)n, S, nullptr, st);
+    if (e == hipSuccess) e = launch_cell_box(xyz, 3, 1, (int)n, S, st);
     if (e == hipSuccess) e = early ? early->wait(&reached) : hipStreamSynchronize(st);
     if (e != hipSuccess) return e;
     sorted = force || culling_pays(n, (double)reached / ((double)ENV_PROBES * (double)seen));

@@ -333,12 +333,17 @@ void shrink_spheres(const float* tri, long long nt, const float* pins, const flo
     ps.alloc(cell_sort_bytes(n, 64));
     T = cell_sort_layout(ts.p, nt, 64);
     P = cell_sort_layout(ps.p, n, 64);
-    hip_check(launch_cell_box(tri, 9, 3, (int)nt, T, bits.as<int>(), st), "sort triangles");
+    FillList L{};
+    L.add(bits.p, 0, 2, 4);
+    cell_sort_clear(L, T);
+    cell_sort_clear(L, P);
+    hip_check(launch_fill_multi(L, st), "fill");
     hipLaunchKernelGGL(k_shrink_probe, dim3(SHR_PROBES), dim3(PROBE_NT), 0, st, tri, (int)nt, stride, pins, normals, own,
                        (int)n, bits.as<int>(), early.p());
     hip_check(hipGetLastError(), "probe");
     // (read while the triangles are sorted)
     hip_check(early.mark(st), "probe");
+    hip_check(launch_cell_box(tri, 9, 3, (int)nt, T, st), "sort triangles");
     hip_check(launch_cell_sort(tri, 9, 3, nullptr, (int)nt, 64, T, st), "sort triangles");
     hip_check(early.wait(&reached), "probe");
     // The share of the triangles that the probes' balls met, and runs of a few pins where their cells are many for them
@@ -355,7 +360,7 @@ void shrink_spheres(const float* tri, long long nt, const float* pins, const flo
     const size_t nc = (size_t)(nt + SHR_CLUSTER - 1) / SHR_CLUSTER;
     bound.alloc(16 * (size_t)nt);
     cluster.alloc(16 * nc);
-    hip_check(launch_cell_box(pins, 3, 1, (int)n, P, nullptr, st), "sort pins");
+    hip_check(launch_cell_box(pins, 3, 1, (int)n, P, st), "sort pins");
     hip_check(launch_cell_sort(pins, 3, 1, normals, (int)n, 64, P, st), "sort pins");
     const unsigned g = (unsigned)std::min<long long>((nt + 255) / 256, 4096);
     hipLaunchKernelGGL(k_shrink_prep<true>, dim3(g), dim3(256), 0, st, tri, nt, T.order, rec.as<float4>(),
