@@ -131,8 +131,8 @@ typedef struct rpd_stats {
   double ms_deferred;     /* deferred kernel */
   double ms_reduce;       /* gluing, union-find, compaction and sorting */
   double ms_total;        /* whole rpd_build on the stream */
-  int64_t n_defer_block;  /* tets deferred because their own candidates overflow the fast path's site list */
-  int64_t n_defer_kmax;   /* tets deferred because more candidates than the clip budget remained */
+  int64_t n_defer_block;  /* tets deferred by RPD_FORCE_SLOW_PATH */
+  int64_t n_defer_kmax;   /* tets deferred because more candidates than the clip budget remained, or than fit their list */
   int64_t n_defer_clip;   /* pieces deferred by the fast path: a predicate undecided in FP64, or over 64 vertices */
   int64_t n_split;        /* workgroup blocks redone in smaller chunks because their site list overflowed */
   int64_t n_items;        /* work items of the candidate kernel (parts of blocks; whole blocks with RPD_NO_SPLIT) */
@@ -278,8 +278,8 @@ void rpd_free(rpd_result* r);
 
 /* Autotuner for the batched FP32 path: runs rpd_build on these inputs once per launch shape (clip budget 8, 16 or 28
  * with 16 vertex slots, and 16 or 28 with 12 slots, all with block 64), each timed by HIP events over the clipping
- * kernels, best of two after a warm-up, writes the fastest into *best (a copy of *opts with block, clip_budget and slots set; the default 64 x 28 x 16 is kept unless another shape is more than
- * 2% faster) and caches it for the process under the bucket (floor log2 of the mean sites per shape, floor log2 of
+ * kernels, best of two after a warm-up, writes the fastest into *best (a copy of *opts with block, clip_budget and
+ * slots set; the default 64 x 28 x 16 is kept unless another shape is more than 2% faster) and caches it for the process under the bucket (floor log2 of the mean sites per shape, floor log2 of
  * the mean tets per shape). Later rpd_build calls take the cached value of their bucket for each of block,
  * clip_budget and slots that is 0 (else 64, 28 and 16), and so does a session. Every launch shape gives the same
  * elements (keys, chi, beta0); a piece that one shape defers to the large-capacity kernel and another does not has

@@ -439,8 +439,8 @@ static std::mutex g_spec_mu;
 static std::map<std::tuple<int, int, unsigned, unsigned, unsigned>, size_t> g_spec;
 
 // Sorted element lists of the current state, copied to the host and split per shape. Returns false when a table or the
-// pass's room overflowed (the caller retries with more; asked: what the pass asked for). Live entries are compacted first and the counts read back,
-// so that only they are sorted and downloaded.
+// pass's room overflowed (the caller retries with more; asked: what the pass asked for). Live entries are compacted
+// first and the counts read back, so that only they are sorted and downloaded.
 static bool collect(DeviceState& D, const std::vector<ShapeDesc>& hd, const ShapeDesc* dshapes,
                     const rpd_mesh* const* meshes, hipStream_t s, Timing& tm, std::vector<ShapeOut>& outs,
                     rpd_stats& st, PassRoom& asked) {

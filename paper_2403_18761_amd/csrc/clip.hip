@@ -1248,8 +1248,9 @@ constexpr int SLOW_LDS_ITEMS = 512;  // the first deferred items go to the LDS v
 // The LDS variant (few items: latency) keeps the candidate lists and 32 lanes' polytopes (32 vertices) in LDS; an item
 // with more than 256 candidates, or a piece with more vertices, is handed to the global variant through the overflow
 // list, and so are the candidates past an item's first 32: one wave that took them round after round was the launch's
-// tail (1.23 -> 0.77 ms on a batch of 48 shapes). The global variant (many items: throughput) keeps the lists and all 64 lanes' polytopes (64 vertices) in its
-// scratch and takes the items past the LDS variant's share, then the overflow list.
+// tail (1.23 -> 0.77 ms on a batch of 48 shapes). The global variant (many items: throughput) keeps the lists and all 64
+// lanes' polytopes (64 vertices) in its scratch and takes the items past the LDS variant's share, then the overflow
+// list.
 template <bool LDS>
 struct SlowCfg;
 template <>

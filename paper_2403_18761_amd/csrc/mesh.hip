@@ -216,6 +216,8 @@ __global__ __launch_bounds__(256) void k_presence(const int* kcount, int n, int*
   __syncthreads();
   if (threadIdx.x == 0 && s_used) atomicAdd(used, s_used);
 }
+
+// owner of every vertex, edge and face: the lowest caller tet index among the tets containing it
 __global__ void k_owners(const int* itv, const int* tedge, const int* tface, const int* perm, int nt, int* ov,
                          int* oe, int* of) {
   for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < nt; k += gridDim.x * blockDim.x) {

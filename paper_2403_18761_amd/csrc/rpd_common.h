@@ -48,8 +48,8 @@ constexpr int ST_FULL = ST_TABLE_FULL | ST_PASS_FULL | ST_POOL_FULL;
 // counters (ShapeArgs::counters)
 enum {
   C_PAIRS = 0, C_CAND, C_FP64, C_EXACT, C_RPV, C_PIECES, C_NODES,
-  C_DEFER_BLOCK,  // tets deferred because their own candidates overflow the workgroup's site list
-  C_DEFER_KMAX,   // tets deferred because they kept more than the candidate budget
+  C_DEFER_BLOCK,  // tets deferred by RPD_FORCE_SLOW_PATH
+  C_DEFER_KMAX,   // tets deferred because they kept more candidates than the budget, or than their list holds
   C_DEFER_CLIP,   // pieces deferred because a predicate stayed undecided or the polytope outgrew 64 vertex slots
   C_SPLIT,        // workgroup blocks redone in chunks because their site list overflowed
   C_GLUE_BITS,    // gluing bits of the pieces whose components are (re)computed
