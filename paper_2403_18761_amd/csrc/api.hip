@@ -723,13 +723,13 @@ static std::vector<ShapeDesc> shape_table(const rpd_mesh* const* meshes, const i
     d.tet_off = *nt_tot;
     d.sign = +1;
     d.pad = 0;
-    d.blkbox = m->grpbox[0].as<float>();
+    d.blkbox = m->grpbox(0);
     // Groups whose site lists the blocks share: a list is worth its scan of all sites when it serves many blocks, and
     // is short when the group is small. Dense sites (over two per block) make the lists of larger groups as long as the
     // shape's site list; with very many sites the scans for small groups cost more than they save.
     const int level = d.ns > 2 * m->nblk ? 0 : d.ns > 8192 ? 2 : 1;
-    d.grp = level ? m->grp[level].as<int>() : nullptr;
-    d.grpbox = m->grpbox[level].as<float>();
+    d.grp = m->grp(level);
+    d.grpbox = m->grpbox(level);
     d.ngrp = m->ngrp[level];
     d.grp_off = d.item_off = 0;
     d.parts = TB / SPLIT_TETS;
@@ -1438,7 +1438,7 @@ static void session_round(rpd_session* S) {
   D.set_touch(a);
   D.set_touch(a_new);
   hip_check(launch_round_front(S->r, a_new, D.cell_b0.as<int>(), m->tp.as<float4>(),
-                               m->grpbox[0].as<float>(), m->nblk, s),
+                               m->grpbox(0), m->nblk, s),
             "round selection");
   clip_pass(S, a);
   hip_check(launch_touch_removed(a_new, s), "changed pieces");

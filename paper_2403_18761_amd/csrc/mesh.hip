@@ -312,9 +312,11 @@ __global__ void k_tet_roots(int* par, int nt, int* roots) {
 
 // A block starts at tet k of the sorted keys when k is a multiple of TB past the first tet of its octree cell (the
 // first key with the same bits above shift). Counted per tile of CUT_TILE tets, then written in order with their keys.
-// (The host made the cuts, from a download of all keys and a loop over them: a new model of
-// the 64^3 torus took 1.53 ms that way, 1.47 ms this way.)
+// Meshes of up to CUT_HOST tets are cut by the host, from a download of all keys: it saves three launches and a wait
+// (preparation at 762 tets 278 us, 326 on the device; at 11,244 340 and 392; at 24,576 400 and 440). A new model of the
+// 114,408-tet torus took 1.53 ms with the host's cuts, 1.47 ms with the device's.
 constexpr int CUT_TILE = 1024;
+constexpr int CUT_HOST = 32768;
 __device__ inline bool block_start(const unsigned long long* keys, int k, int shift) {
   const unsigned long long first = keys[k] >> shift << shift;
   int lo = 0, hi = k;  // the first key that is at least first
@@ -416,12 +418,14 @@ __global__ __launch_bounds__(64) void k_block_boxes(const float4* tp, const int*
   }
   if (threadIdx.x == 0) box[7 * (size_t)b + 6] = dd * 1.000001f;
 }
-// box of the blocks [first[g], first[g + 1]) of every group g, with the largest squared diagonal among them
-__global__ void k_group_boxes(const float* blkbox, const int* first, int ng, float* box) {
+// box of the blocks [first[g], first[g + 1]) of every group g, with the largest squared diagonal among them; the n1 groups
+// of one level, then (first: their n1 + 1 entries before) those of the next
+__global__ void k_group_boxes(const float* blkbox, const int* first, int n1, int ng, float* box) {
   for (int g = blockIdx.x * blockDim.x + threadIdx.x; g < ng; g += gridDim.x * blockDim.x) {
+    const int b0 = first[g + (g >= n1)], b1 = first[g + (g >= n1) + 1];
     float v[7];
-    for (int k = 0; k < 7; ++k) v[k] = blkbox[7 * (size_t)first[g] + k];
-    for (int b = first[g] + 1; b < first[g + 1]; ++b)
+    for (int k = 0; k < 7; ++k) v[k] = blkbox[7 * (size_t)b0 + k];
+    for (int b = b0 + 1; b < b1; ++b)
       for (int k = 0; k < 7; ++k) {
         const float x = blkbox[7 * (size_t)b + k];
         v[k] = k < 3 ? fminf(v[k], x) : fmaxf(v[k], x);
@@ -602,57 +606,70 @@ void mesh_prepare(rpd_mesh* m, const rpd_mesh_desc* d, uint32_t flags, hipStream
     int level = 0;
     while (level < 20 && (double)(1ll << (level + 1)) <= 2.0 * edge) ++level;
     const int shift = 3 * (level + 1);
-    const int ntile = (nt + CUT_TILE - 1) / CUT_TILE;
-    DBuf tiles(sizeof(int) * (size_t)(ntile + 1));
-    const unsigned long long* dkeys = mkey2.as<unsigned long long>();
-    hipLaunchKernelGGL(k_cut_count, dim3(ntile), dim3(256), 0, s, dkeys, nt, shift, tiles.as<int>());
-    hipLaunchKernelGGL(k_cut_scan, dim3(1), dim3(1024), 0, s, tiles.as<int>(), ntile);
-    hip_check(hipGetLastError(), "block cuts");
-    hip_check(hipMemcpyAsync(&m->nblk, tiles.as<int>() + ntile, sizeof(int), hipMemcpyDeviceToHost, s), "download");
-    hip_check(hipStreamSynchronize(s), "sync");
-    m->blk.alloc(sizeof(int) * (size_t)(m->nblk + 1));
-    DBuf dstart(sizeof(unsigned long long) * (size_t)m->nblk);
-    hipLaunchKernelGGL(k_cut_write, dim3(ntile), dim3(256), 0, s, dkeys, nt, shift, tiles.as<int>(), m->blk.as<int>(),
-                       dstart.as<unsigned long long>());
-    hip_check(hipGetLastError(), "block cuts");
-    std::vector<int> starts(m->nblk + 1);
-    std::vector<unsigned long long> keys(m->nblk);  // of the blocks' first tets
-    hip_check(hipMemcpyAsync(starts.data(), m->blk.p, sizeof(int) * starts.size(), hipMemcpyDeviceToHost, s),
-              "download");
-    hip_check(hipMemcpyAsync(keys.data(), dstart.p, sizeof(unsigned long long) * keys.size(), hipMemcpyDeviceToHost, s),
-              "download");
-    hip_check(hipStreamSynchronize(s), "sync");
+    std::vector<int> starts;                // of the blocks
+    std::vector<unsigned long long> keys;   // of their first tets
+    if (nt <= CUT_HOST) {  // small: the keys come down and the host cuts
+      std::vector<unsigned long long> all(nt);
+      hip_check(hipMemcpyAsync(all.data(), mkey2.p, sizeof(unsigned long long) * nt, hipMemcpyDeviceToHost, s),
+                "download");
+      hip_check(hipStreamSynchronize(s), "sync");
+      for (int k = 0; k < nt; ++k)
+        if (k == 0 || (all[k] >> shift) != (all[k - 1] >> shift) || k - starts.back() >= TB) {
+          starts.push_back(k);
+          keys.push_back(all[k]);
+        }
+      m->nblk = (int)starts.size();
+      starts.push_back(nt);
+    } else {
+      const int ntile = (nt + CUT_TILE - 1) / CUT_TILE;
+      DBuf tiles(sizeof(int) * (size_t)(ntile + 1));
+      const unsigned long long* dkeys = mkey2.as<unsigned long long>();
+      hipLaunchKernelGGL(k_cut_count, dim3(ntile), dim3(256), 0, s, dkeys, nt, shift, tiles.as<int>());
+      hipLaunchKernelGGL(k_cut_scan, dim3(1), dim3(1024), 0, s, tiles.as<int>(), ntile);
+      hip_check(hipGetLastError(), "block cuts");
+      hip_check(hipMemcpyAsync(&m->nblk, tiles.as<int>() + ntile, sizeof(int), hipMemcpyDeviceToHost, s), "download");
+      hip_check(hipStreamSynchronize(s), "sync");
+      DBuf dblk(sizeof(int) * (size_t)(m->nblk + 1)), dstart(sizeof(unsigned long long) * (size_t)m->nblk);
+      hipLaunchKernelGGL(k_cut_write, dim3(ntile), dim3(256), 0, s, dkeys, nt, shift, tiles.as<int>(), dblk.as<int>(),
+                         dstart.as<unsigned long long>());
+      hip_check(hipGetLastError(), "block cuts");
+      starts.resize(m->nblk + 1);
+      keys.resize(m->nblk);
+      hip_check(hipMemcpyAsync(starts.data(), dblk.p, sizeof(int) * starts.size(), hipMemcpyDeviceToHost, s), "download");
+      hip_check(hipMemcpyAsync(keys.data(), dstart.p, sizeof(unsigned long long) * keys.size(), hipMemcpyDeviceToHost, s),
+                "download");
+      hip_check(hipStreamSynchronize(s), "sync");
+    }
     for (int q = 0; q < 4; ++q) {
       const int pt = TB >> q;
       for (int b = 0; b < m->nblk; ++b) m->nparts[q] += (starts[b + 1] - starts[b] + pt - 1) / pt;
     }
-    m->ngrp[0] = m->nblk;
-    m->grpbox[0].alloc(sizeof(float) * 7 * (size_t)m->nblk);
-    hipLaunchKernelGGL(k_block_boxes, dim3(m->nblk), dim3(64), 0, s, m->tp.as<float4>(), m->blk.as<int>(),
-                       m->grpbox[0].as<float>());
-    std::vector<int> grp[3], first[3];
-    DBuf dfirst[3];
-    // the runs of blocks inside one octree cell of about four and of about eight times the mean tet size
+    // the runs of blocks inside one octree cell of about four and of about eight times the mean tet size: the group of
+    // every block, and (only for their boxes) the first block of every group, go up with the blocks in one copy
+    std::vector<int> up(starts), first;
     const int lv = std::max(0, (int)std::lround(std::log2(std::max(1.0, edge))));
+    m->ngrp[0] = m->nblk;
     for (int q = 1; q < 3; ++q) {
       const int sh = std::min(63, std::max(shift, 3 * (lv + 1 + q)));
-      grp[q].resize(m->nblk);
+      int n = 0;
       for (int b = 0; b < m->nblk; ++b) {
-        if (b == 0 || (keys[b] >> sh) != (keys[b - 1] >> sh)) first[q].push_back(b);
-        grp[q][b] = (int)first[q].size() - 1;
+        if (b == 0 || (keys[b] >> sh) != (keys[b - 1] >> sh)) {
+          first.push_back(b);
+          ++n;
+        }
+        up.push_back(n - 1);
       }
-      m->ngrp[q] = (int)first[q].size();
-      first[q].push_back(m->nblk);
-      m->grp[q].alloc(sizeof(int) * (size_t)m->nblk);
-      m->grpbox[q].alloc(sizeof(float) * 7 * (size_t)m->ngrp[q]);
-      dfirst[q].alloc(sizeof(int) * first[q].size());
-      hip_check(hipMemcpyAsync(m->grp[q].p, grp[q].data(), sizeof(int) * grp[q].size(), hipMemcpyHostToDevice, s),
-                "upload");
-      hip_check(hipMemcpyAsync(dfirst[q].p, first[q].data(), sizeof(int) * first[q].size(), hipMemcpyHostToDevice, s),
-                "upload");
-      hipLaunchKernelGGL(k_group_boxes, dim3(gsz(m->ngrp[q])), dim3(256), 0, s, m->grpbox[0].as<float>(),
-                         dfirst[q].as<int>(), m->ngrp[q], m->grpbox[q].as<float>());
+      m->ngrp[q] = n;
+      first.push_back(m->nblk);
     }
+    up.insert(up.end(), first.begin(), first.end());
+    m->blk.alloc(sizeof(int) * up.size());
+    m->boxes.alloc(sizeof(float) * 7 * ((size_t)m->nblk + m->ngrp[1] + m->ngrp[2]));
+    hip_check(hipMemcpyAsync(m->blk.p, up.data(), sizeof(int) * up.size(), hipMemcpyHostToDevice, s), "upload");
+    hipLaunchKernelGGL(k_block_boxes, dim3(m->nblk), dim3(64), 0, s, m->tp.as<float4>(), m->blk.as<int>(), m->grpbox(0));
+    const int ng = m->ngrp[1] + m->ngrp[2];
+    hipLaunchKernelGGL(k_group_boxes, dim3(gsz(ng)), dim3(256), 0, s, m->grpbox(0),
+                       m->blk.as<int>() + (up.size() - first.size()), m->ngrp[1], ng, m->grpbox(1));
     hip_check(hipGetLastError(), "block groups");
     hip_check(hipStreamSynchronize(s), "sync");
   }

@@ -128,12 +128,16 @@ struct rpd_mesh {
   rpd::DBuf tn;    // int [4 nt]: neighbour internal tet across local face f
   rpd::DBuf nu;    // unsigned [14 nt]: weight numerators
   rpd::DBuf perm;  // int [nt]: internal -> caller tet index
-  rpd::DBuf blk;   // int [nblk + 1]: workgroup blocks over the internal order
+  rpd::DBuf blk;   // int [nblk + 1]: workgroup blocks over the internal order; behind them the groups (below)
   int32_t nblk = 0;
   // Groups of blocks that share a site list: level 0: every block is one; levels 1 and 2: the blocks in an octree cell
   // of about four and eight times the mean tet size. The group of every block, and the groups' boxes with the largest
   // squared diagonal of a block in them.
-  rpd::DBuf grp[3], grpbox[3];  // int [nblk] (level 0: none); float [7 ngrp]
+  rpd::DBuf boxes;  // float [7 ngrp] of levels 0, 1 and 2
+  const int* grp(int level) const { return level ? blk.as<int>() + nblk + 1 + (size_t)(level - 1) * nblk : nullptr; }
+  float* grpbox(int level) const {
+    return boxes.as<float>() + 7 * (level > 0 ? (size_t)nblk + (level > 1 ? ngrp[1] : 0) : 0);
+  }
   int32_t ngrp[3] = {0, 0, 0};
   int32_t nparts[4] = {0, 0, 0, 0};  // nonempty parts when every block is taken in 1, 2, 4 or 8 parts
 };
