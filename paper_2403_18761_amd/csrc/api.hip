@@ -1028,6 +1028,8 @@ static bool run_with_retry(const rpd_mesh* const* meshes, const rpd_sites* sites
   rpd::PassRoom room = rpd::pass_room(nt, ns, 1, rpd::fast_slots(o) == 12), asked;
   for (int scale = 1; scale <= 16;) {
     if (rpd::run_batch(meshes, sites, n_shapes, o, s, scale, room, shapes, st, asked)) return true;
+    if (asked.slots > rpd::MAX_SLOTS)
+      throw Failure{RPD_E_NOMEM, "the tets of the call have more than 800 million candidate sites together"};
     if (!rpd::grow(room, asked)) scale *= 2;
   }
   return false;
